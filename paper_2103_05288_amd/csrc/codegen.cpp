@@ -331,7 +331,7 @@ struct Gen {
           // the first element of the tensor opens the first run; in[1] is the same operand read one
           // element earlier
           const RegKind kc = g.an.nodes[n.in[0]].rk;
-          return "((disc::i64)col + e == 0) || (" + as(n.in[0], kc) + " != " + as(n.in[1], kc) + ")";
+          return "(!__is_same(SP, disc::InnerSpan) && (disc::i64)col + e == 0) || (" + as(n.in[0], kc) + " != " + as(n.in[1], kc) + ")";
         }
         case DISC_SELECT: return as(n.in[0], RK_BOOL) + " ? " + a(1) + " : " + a(2);
         case DISC_CAST:
@@ -455,7 +455,7 @@ struct Gen {
   // load of a slot of an operand; a padded one takes the padding value wherever the operand is not
   std::string load_call(const Access& a, size_t i, const std::string& dst, const std::string& ld_tmpl, const std::string& extra) {
     const std::string ptr = elem_ptr(a, fmt("A.p%d", a.slot));
-    if (a.prev) return "disc::ld_prev(" + dst + ", " + ptr + ", (disc::i64)" + elem_base(a, i) + ", sp);";
+    if (a.prev) return "disc::ld_prev(" + dst + ", " + ptr + ", " + elem_base(a, i) + ", sp, rc.sb + (disc::i64)" + elem_base(a, i) + " > 0);";
     if (!a.padded) return "disc::ld" + ld_tmpl + "(" + dst + ", " + ptr + ", " + elem_base(a, i) + ", sp" + extra + ");";
     std::string lo = "0", hi = "0x7fffffffffffffffLL";
     for (size_t t = 0; t < a.groups.size(); ++t)
@@ -1076,21 +1076,26 @@ struct Gen {
 
   // compaction pattern: where the kept values, the slots and the count go
   void emit_compact_fns() {
-    os << "  template <int V> static DISC_DEV void compact_store(const Args& A, const OutSlot<V>& o, int e, disc::i64 pos) {\n";
+    // the kept values of one slot of a wavefront, one output after the other through the same LDS
+    int bytes = 0;
+    os << "  template <int V, bool NT> static DISC_DEV void compact_put(const Args& A, const OutSlot<V>& o, disc::u32 kb, int before, int kept, disc::i64 pos, char* stage) {\n";
     for (const auto& out : an.outputs) {
       const Access& a = an.accesses[out.access];
-      if (a.compact) os << "    A.o" << a.slot << "[pos] = o.o" << a.slot << ".get(e);\n";
+      if (!a.compact) continue;
+      bytes = std::max(bytes, dtype_bytes(a.dtype));
+      os << "    disc::compact_put_elems<V, NT>(A.o" << a.slot << ", pos, kb, before, kept, stage, [&](int e) { return o.o" << a.slot << ".get(e); });\n";
     }
-    os << "    (void)A; (void)o; (void)e; (void)pos;\n  }\n";
+    os << "    (void)A; (void)o; (void)kb; (void)before; (void)kept; (void)pos; (void)stage;\n  }\n";
+    os << "  static constexpr int COMPACT_BYTES = " << bytes << ";\n";
     // the slots of the V elements of one slot of the tile, stored as one vector
-    os << "  template <int V> static DISC_DEV void rank_store(const Args& A, disc::i64 col, const disc::i64 (&rank)[V], disc::Span sp) {\n";
+    os << "  template <int V, bool NT, class SP> static DISC_DEV void rank_store(const Args& A, disc::i64 base, unsigned col, const disc::i64 (&rank)[V], SP sp) {\n";
     for (const auto& out : an.outputs) {
       const Access& a = an.accesses[out.access];
       if (!a.compact_rank) continue;
       os << "    {\n      disc::Vec<" << dtype_ctype(a.dtype) << ", V> t;\n#pragma unroll\n      for (int e = 0; e < V; ++e) t.v[e] = ("
-         << dtype_ctype(a.dtype) << ")rank[e];\n      disc::st(A.o" << a.slot << ", col, t, sp);\n    }\n";
+         << dtype_ctype(a.dtype) << ")rank[e];\n      disc::st<NT>(A.o" << a.slot << " + base, col, t, sp);\n    }\n";
     }
-    os << "    (void)A; (void)col; (void)rank; (void)sp;\n  }\n";
+    os << "    (void)A; (void)base; (void)col; (void)rank; (void)sp;\n  }\n";
     bool has_rank = false;
     for (const auto& out : an.outputs) has_rank = has_rank || an.accesses[out.access].compact_rank;
     os << "  static constexpr bool HAS_RANK = " << (has_rank ? "true" : "false") << ";\n";
@@ -1167,6 +1172,7 @@ struct Gen {
       k("k_compact_count_vec", fmt("disc::compact_count_body<Pat, %d>(A);", V), nullptr);
       k("k_compact_count_scalar", "disc::compact_count_body<Pat, 1>(A);", nullptr);
       k("k_compact_scatter_vec", fmt("disc::compact_scatter_body<Pat, %d>(A);", V), nullptr);
+      k("k_compact_scatter_vec_nt", fmt("disc::compact_scatter_body<Pat, %d, true>(A);", V), nullptr);
       k("k_compact_scatter_scalar", "disc::compact_scatter_body<Pat, 1>(A);", nullptr);
       max_threads = 1024;
       k("k_compact_scan", "disc::compact_scan_body<Pat>(A);", nullptr);

@@ -115,6 +115,16 @@ struct EvenSpan {
   DISC_DEV bool any() const { return n > 0; }
 };
 
+// The same of a slot that is not the first of its tensor (compaction tiles): an operand read one
+// element earlier has that element too.
+struct InnerSpan : EvenSpan {
+  static DISC_DEV InnerSpan upto(int n) {
+    InnerSpan s;
+    s.n = n;
+    return s;
+  }
+};
+
 // Element offset of a slot relative to the base row of the access.  A caller that passes the
 // column as `unsigned` promises that lane_base + col, scaled to bytes, fits 32 bits (the
 // register-resident row kernels: a wavefront's rows span at most 3 * 1024 slots); the access can
@@ -234,17 +244,17 @@ DISC_DEV void ld_win(Vec<T, N>& d, const T* __restrict__ p, I off, SP sp, i64 co
 }
 
 // Slot of an operand read one element earlier: d[e] = p[off + e - 1].  The very first slot of the
-// tensor (off == 0) has no element in front of it: its element 0 stays zero (the caller never looks
+// tensor (!has_prev) has no element in front of it: its element 0 stays zero (the caller never looks
 // at it) and the rest is read one by one.
-template <class T, int N, class SP>
-DISC_DEV void ld_prev(Vec<T, N>& d, const T* __restrict__ p, i64 off, SP sp) {
-  if (off > 0) {
-    ld(d, p, off - 1, sp);
+template <class T, int N, class I, class SP>
+DISC_DEV void ld_prev(Vec<T, N>& d, const T* __restrict__ p, I off, SP sp, bool has_prev) {
+  if (__is_same(SP, InnerSpan) || has_prev) {
+    ld(d, p - 1, off, sp);
   } else {
     d.clear();
 #pragma unroll
     for (int e = 1; e < N; ++e)
-      if (sp.has(e)) d.set(e, p[e - 1]);
+      if (sp.has(e)) d.set(e, at(p, off)[e - 1]);
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
 }
@@ -1475,67 +1485,174 @@ DISC_DEV void col_epi2_body(const typename Pat::Args& A, const ColPlan& cp) {
 // =======================================================================================
 // Outputs whose size depends on the data (compaction by a predicate computed in the pattern; Unique
 // of a sorted tensor is the case keep[i] = x[i] != x[i-1]).  Rank-1 values of length N = A.inner.
-// Three launches, no atomics, nothing read back by the host:
-//   1. compact_count:   a block owns a tile of 256 * kCompactSlots * V consecutive elements (a lane
-//                       owns kCompactSlots consecutive slots), evaluates the fused chain and counts
-//                       what is kept; one count per block to the workspace.
-//   2. compact_scan:    one block turns the counts into exclusive offsets, in a fixed order, and
-//                       stores the total -- the data-dependent size -- in the COMPACT_COUNT outputs.
-//   3. compact_scatter: the blocks evaluate their tiles again (the inputs are read twice; nothing
-//                       but the counts is kept between the launches), rank what they keep with a
-//                       scan over the lanes, and store the kept values at offset + rank, in order;
-//                       COMPACT_RANK outputs get the slot of every element.
+// A tile is 4 wavefronts x kCompactSlots slots x 64 lanes x V elements; a wavefront's part of it is
+// contiguous and its slots are striped over the lanes, so every load and every rank store is one
+// contiguous stretch per wavefront.  Kept elements are counted and ranked with lane masks (ballot,
+// mbcnt, popcount: two or three instructions per element, no scan over the lanes) and meet in LDS,
+// slot by slot, so that they leave as contiguous stores whatever the share that is kept.
+// No atomics, nothing read back by the host, no block waits for another:
+//   1. compact_count:   a block owns a chunk of consecutive tiles, evaluates the fused chain and
+//                       counts what is kept; one count per chunk to the workspace.
+//   2. compact_scan:    (short inputs only: chunks of one tile) one block turns the counts into
+//                       exclusive offsets, in a fixed order, and stores the total -- the
+//                       data-dependent size -- in the COMPACT_COUNT outputs.
+//   3. compact_scatter: the blocks evaluate their chunks again (the inputs are read twice; nothing
+//                       but the counts is kept between the launches) and store the kept values and
+//                       the ranks.  Without the scan launch every block adds up the counts in
+//                       front of its own (at most a couple of thousand), and the last one stores
+//                       the total.
 // =======================================================================================
-constexpr int kCompactSlots = 4;
-
-// inclusive scan over the 64 lanes of a wavefront
-DISC_DEV int wave_inclusive_scan(int x) {
-  const int lane = (int)threadIdx.x & 63;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int t = __builtin_amdgcn_ds_bpermute(((lane - d) & 63) << 2, x);
-    if (lane >= d) x += t;
-  }
-  return x;
+constexpr int kCompactWaves = 4;          // wavefronts per block
+constexpr int kCompactSlots = 4;          // slots per lane
+// The lane's number, not known to be the same from tile to tile: what is derived from it is cheap to
+// derive again, and carried through the loop over the tiles it doubled the registers of the kernels.
+DISC_DEV int opaque_lane() {
+  int lane = (int)threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  return lane;
 }
 
-// evaluates the tile of the calling lane: kept flags and values of its kCompactSlots slots
-template <class Pat, int V>
-DISC_DEV int compact_eval(const typename Pat::Args& A, i64 first, typename Pat::template OutSlot<V> (&o)[kCompactSlots],
-                          int (&nvalid)[kCompactSlots]) {
-  int cnt = 0;
+// Evaluates the calling lane's slots of a wavefront's part of a tile: values, and one word of kept
+// flags per slot (bit e = element e).  `w0` = first element of the part (a scalar: the lanes add
+// 32-bit offsets).  Returns what the WAVEFRONT keeps.  WHOLE: the part lies inside the tensor, so
+// no slot is ragged and every load is one wide access; only slot 0 can be the tensor's first one.
+template <bool WHOLE, class Pat, int V, int U>
+DISC_DEV int compact_eval(const typename Pat::Args& A, i64 w0, typename Pat::template OutSlot<V> (&o)[U], u32 (&kb)[U]) {
+  const int lane = opaque_lane();
   typename Pat::RowCtx rc;
-  Pat::row_begin(A, 0, rc);
+  Pat::row_begin3(A, 0, 0, w0, rc);
+  typename Pat::template Slot<V> slot[U];
 #pragma unroll
-  for (int u = 0; u < kCompactSlots; ++u) {
-    const i64 col = first + (i64)u * V;
-    const i64 rem = A.inner - col;
-    nvalid[u] = rem <= 0 ? 0 : (rem < (i64)V ? (int)rem : V);
-    if (nvalid[u] > 0) {
-      typename Pat::template Slot<V> slot;
-      typename Pat::template Keep<V> kp;
-      Pat::template load<V>(A, rc, col, Span::upto(nvalid[u]), slot);
-      Pat::template epilogue<V, false>(A, rc, slot, kp, col, Span::upto(nvalid[u]), o[u]);
-#pragma unroll
-      for (int e = 0; e < V; ++e) cnt += (e < nvalid[u] && o[u].keep[e]) ? 1 : 0;
+  for (int u = 0; u < U; ++u) {             // all loads first
+    const unsigned at = (unsigned)((u * 64 + lane) * V);
+    if constexpr (WHOLE) {
+      if (u == 0) Pat::template load<V>(A, rc, at, EvenSpan::upto(V), slot[u]);
+      else Pat::template load<V>(A, rc, at, InnerSpan::upto(V), slot[u]);
+    } else {
+      const i64 rem = A.inner - (w0 + at);
+      if (rem > 0) Pat::template load<V>(A, rc, at, Span::upto(rem < (i64)V ? (int)rem : V), slot[u]);
     }
+  }
+  int cnt = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const i64 col = w0 + (u * 64 + lane) * V, rem = A.inner - col;
+    const int n = WHOLE ? V : rem <= 0 ? 0 : (rem < (i64)V ? (int)rem : V);
+    u32 bits = 0;
+    if (n > 0) {
+      typename Pat::template Keep<V> kp;
+      if constexpr (!WHOLE) Pat::template epilogue<V, false>(A, rc, slot[u], kp, col, Span::upto(n), o[u]);
+      else if (u == 0) Pat::template epilogue<V, false>(A, rc, slot[u], kp, col, EvenSpan::upto(n), o[u]);
+      else Pat::template epilogue<V, false>(A, rc, slot[u], kp, col, InnerSpan::upto(n), o[u]);
+#pragma unroll
+      for (int e = 0; e < V; ++e) bits |= (e < n && o[u].keep[e]) ? 1u << e : 0u;
+    }
+    // one register of flags per slot from here on: as lane masks, U * V of them would not fit the
+    // scalar registers
+    asm volatile("" : "+v"(bits));
+    kb[u] = bits;
+#pragma unroll
+    for (int e = 0; e < V; ++e) cnt += __builtin_popcountll(__builtin_amdgcn_ballot_w64((bits >> e) & 1));
   }
   return cnt;
 }
 
+// Stores the kept values and the ranks of a wavefront's part of a tile; `pos` = number of elements
+// kept in front of it.  `stage`: 64 * V * COMPACT_BYTES bytes of LDS of the wavefront's own.
+template <bool WHOLE, bool NT, class Pat, int V, int U>
+DISC_DEV void compact_emit(const typename Pat::Args& A, i64 w0, const typename Pat::template OutSlot<V> (&o)[U],
+                           const u32 (&kb)[U], i64 pos, char* stage) {
+  const int lane = opaque_lane();
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    int before = 0, kept = 0;               // kept in front of the lane / by the wavefront, in this slot
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const u64 m = __builtin_amdgcn_ballot_w64((kb[u] >> e) & 1);
+      before = (int)__builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, (u32)before));
+      kept += __builtin_popcountll(m);
+    }
+    Pat::template compact_put<V, NT>(A, o[u], kb[u], before, kept, pos, stage);
+    if constexpr (Pat::HAS_RANK) {
+      const unsigned at = (unsigned)((u * 64 + lane) * V);
+      i64 rank[V];
+      int r = before - 1;
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        r += (int)((kb[u] >> e) & 1);
+        rank[e] = pos + r;
+      }
+      const i64 rem = A.inner - (w0 + at);
+      if constexpr (WHOLE) Pat::template rank_store<V, NT>(A, w0, at, rank, EvenSpan::upto(V));
+      else if (rem > 0) Pat::template rank_store<V, NT>(A, w0, at, rank, Span::upto(rem < (i64)V ? (int)rem : V));
+    }
+    pos += kept;
+  }
+}
+
+// A wavefront's part of a tile, first the count and later the stores.
+template <bool NT, class Pat, int V, int U>
+struct CompactPart {
+  typename Pat::template OutSlot<V> o[U];
+  u32 kb[U];
+  i64 w0;
+  bool whole;
+  DISC_DEV int count(const typename Pat::Args& A, i64 tile) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    w0 = (tile * kCompactWaves + wave) * (64 * U * V);
+    whole = w0 + 64 * U * V <= A.inner;
+    return whole ? compact_eval<true, Pat, V, U>(A, w0, o, kb) : compact_eval<false, Pat, V, U>(A, w0, o, kb);
+  }
+  DISC_DEV void store(const typename Pat::Args& A, i64 pos, char* stage) {
+    if (whole) compact_emit<true, NT, Pat, V, U>(A, w0, o, kb, pos, stage);
+    else compact_emit<false, NT, Pat, V, U>(A, w0, o, kb, pos, stage);
+  }
+};
+DISC_DEV i64 wave_scalar(i64 x) {
+  return ((i64)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) | (u32)__builtin_amdgcn_readfirstlane((int)x);
+}
+
+// LDS written by lanes of a wavefront and read by other lanes of the same one: the accesses stay in
+// program order (one wavefront's LDS operations complete in order)
+DISC_DEV void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The kept elements of one slot of a wavefront (at most 64 * V), collected in LDS and stored as one
+// contiguous stretch at dst + pos.  (Stored straight from the lanes, a kept element here and there,
+// every store instruction covers the same few cache lines once more.)
+template <int V, bool NT, class T, class GET>
+DISC_DEV void compact_put_elems(T* __restrict__ dst, i64 pos, u32 kb, int before, int kept, char* stage, GET get) {
+  T* q = reinterpret_cast<T*>(stage);
+  const int lane = (int)threadIdx.x & 63;
+  wave_lds_sync();
+  int r = before;
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    if ((kb >> e) & 1) q[r++] = get(e);
+  }
+  wave_lds_sync();
+  for (int i = lane; i < kept; i += 64) {
+    if constexpr (NT) __builtin_nontemporal_store(q[i], dst + pos + i);
+    else dst[pos + i] = q[i];
+  }
+}
+
+// A.aux0 = number of chunks, A.aux1 = tiles per chunk
 template <class Pat, int V>
 DISC_DEV void compact_count_body(const typename Pat::Args& A) {
-  __shared__ int wsum[4];
-  const i64 tile = (i64)blockDim.x * kCompactSlots * V;
-  i64* counts = reinterpret_cast<i64*>(A.ws0);
-  for (i64 b = blockIdx.x; b < A.aux0; b += gridDim.x) {
-    typename Pat::template OutSlot<V> o[kCompactSlots];
-    int nvalid[kCompactSlots];
-    const int cnt = compact_eval<Pat, V>(A, b * tile + (i64)threadIdx.x * kCompactSlots * V, o, nvalid);
-    const int incl = wave_inclusive_scan(cnt);
-    if (((int)threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = incl;
+  __shared__ i64 wsum[kCompactWaves];
+  const int wave = (int)threadIdx.x >> 6;
+  for (i64 c = blockIdx.x; c < A.aux0; c += gridDim.x) {
+    i64 cnt = 0;
+    for (i64 t = c * A.aux1; t < (c + 1) * A.aux1; ++t) {
+      CompactPart<false, Pat, V, kCompactSlots> part;
+      cnt += part.count(A, t);
+    }
+    if (((int)threadIdx.x & 63) == 0) wsum[wave] = cnt;
     __syncthreads();
-    if (threadIdx.x == 0) counts[b] = (i64)wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    if (threadIdx.x == 0) reinterpret_cast<i64*>(A.ws0)[c] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
     __syncthreads();
   }
 }
@@ -1568,37 +1685,62 @@ DISC_DEV void compact_scan_body(const typename Pat::Args& A) {
   if (tid == nt - 1) Pat::count_store(A, part[nt - 1]);
 }
 
-template <class Pat, int V>
+// sum of x over the 256 threads of a block, in every thread
+DISC_DEV i64 compact_block_sum(i64 x, i64 (&cell)[kCompactWaves]) {
+  x += lane_xchg<1>(x);
+  x += lane_xchg<2>(x);
+  x += lane_xchg<4>(x);
+  x += lane_xchg<8>(x);
+  x += lane_xchg<16>(x);
+  x += lane_xchg<32>(x);
+  if (((int)threadIdx.x & 63) == 0) cell[threadIdx.x >> 6] = x;
+  __syncthreads();
+  x = cell[0] + cell[1] + cell[2] + cell[3];
+  __syncthreads();
+  return x;
+}
+
+// A.aux2: the workspace holds counts (no scan launch), not offsets.  NT: non-temporal stores, for
+// launches whose results do not fit the memory-side cache anyway.  With plain stores the results of
+// one call sit there dirty, and the count launch of the next call, which only reads, first has to
+// push them out to memory: 2^25 i32 keys, a quarter of them distinct: count 44 us (3.0 TB/s), scatter
+// 60 us with plain stores, 27 us (5.0 TB/s) and 54 us (5.6 TB/s, all traffic) with these.  What is
+// left is the second read of the inputs.  (With slots that lie next to each other in a lane, one
+// kept element per store and a scan launch of its own it was 48 + 12 + 89 us.  A single pass that
+// chains the tiles' counts by look-back was built as well: 72 us + 5 us to clear its status words;
+// its tile counter alone costs 25 us at 4096 tiles, 12 ns an increment.)
+template <class Pat, int V, bool NT = false>
 DISC_DEV void compact_scatter_body(const typename Pat::Args& A) {
-  __shared__ int wsum[4];
-  const i64 tile = (i64)blockDim.x * kCompactSlots * V;
-  const i64* offsets = reinterpret_cast<const i64*>(A.ws0);
-  for (i64 b = blockIdx.x; b < A.aux0; b += gridDim.x) {
-    typename Pat::template OutSlot<V> o[kCompactSlots];
-    int nvalid[kCompactSlots];
-    const i64 first = b * tile + (i64)threadIdx.x * kCompactSlots * V;
-    const int cnt = compact_eval<Pat, V>(A, first, o, nvalid);
-    const int incl = wave_inclusive_scan(cnt);
-    const int wave = (int)threadIdx.x >> 6;
-    if (((int)threadIdx.x & 63) == 63) wsum[wave] = incl;
-    __syncthreads();
-    i64 pos = offsets[b] + (incl - cnt);
-    for (int w = 0; w < wave; ++w) pos += wsum[w];
-#pragma unroll
-    for (int u = 0; u < kCompactSlots; ++u) {
-      i64 rank[V];
-#pragma unroll
-      for (int e = 0; e < V; ++e) {
-        if (e < nvalid[u] && o[u].keep[e]) {
-          Pat::template compact_store<V>(A, o[u], e, pos);
-          ++pos;
-        }
-        rank[e] = pos - 1;
-      }
-      if constexpr (Pat::HAS_RANK) {
-        if (nvalid[u] > 0) Pat::template rank_store<V>(A, first + (i64)u * V, rank, Span::upto(nvalid[u]));
-      }
+  __shared__ i64 cell[kCompactWaves];
+  __shared__ int wsum[2][kCompactWaves];
+  __shared__ __attribute__((aligned(16))) char stage[kCompactWaves][64 * V * Pat::COMPACT_BYTES + 16];
+  const int wave = (int)threadIdx.x >> 6;
+  const i64* counts = reinterpret_cast<const i64*>(A.ws0);
+  for (i64 c = blockIdx.x; c < A.aux0; c += gridDim.x) {
+    i64 pos;
+    if (A.aux2) {
+      i64 x = 0;
+      for (i64 i = threadIdx.x; i < c; i += 256) x += counts[i];
+      pos = wave_scalar(compact_block_sum(x, cell));
+    } else {
+      pos = wave_scalar(counts[c]);
     }
+    int buf = 0;
+    for (i64 t = c * A.aux1; t < (c + 1) * A.aux1; ++t, buf ^= 1) {
+      CompactPart<NT, Pat, V, kCompactSlots> part;
+      const int cnt = part.count(A, t);
+      if (((int)threadIdx.x & 63) == 0) wsum[buf][wave] = cnt;
+      __syncthreads();
+      int before = 0, all = 0;
+#pragma unroll
+      for (int w = 0; w < kCompactWaves; ++w) {
+        before += w < wave ? wsum[buf][w] : 0;
+        all += wsum[buf][w];
+      }
+      part.store(A, pos + __builtin_amdgcn_readfirstlane(before), stage[wave]);
+      pos += __builtin_amdgcn_readfirstlane(all);
+    }
+    if (A.aux2 && c == A.aux0 - 1 && threadIdx.x == 0) Pat::count_store(A, pos);
     __syncthreads();
   }
 }

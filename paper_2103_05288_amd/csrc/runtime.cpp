@@ -310,6 +310,12 @@ struct FullPlan {
 // whatever kernel consumes the result; the non-temporal versions are kept for larger ones, which
 // stream through the caches anyway.
 constexpr int64_t kNonTemporalMinBytes = 64ll << 20;
+// Compaction: from this many tiles on (2^17 i32 elements), two launches instead of three: the blocks of
+// the scatter launch add up the counts in front of them by themselves (14 us a call against 15-16 at
+// 2^17 .. 2^20 elements, where the launches are what is paid for).  Most chunks of a
+// launch: 1024 .. 4096 measured alike at 2^25 elements (103, 105, 100 us), and every block reads up
+// to that many counts.
+constexpr int64_t kCompactTwoLaunchTiles = 32, kCompactMaxChunks = 2048;
 
 // nt_name: the non-temporal sibling of names[0] (vector width, 32-bit index), taken for large
 // launches (`big`) whose rows start on 16-byte boundaries (`aligned`: the full-size operands are;
@@ -406,9 +412,6 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     pub.vec_width = 1;
     pub.index_bits = 64;
   } else if (an.tmpl == DISC_TEMPLATE_COMPACT) {
-    // count -> scan -> scatter over tiles of 256 lanes x kCompactSlots slots; the workspace holds one
-    // 8-byte count / offset per tile.  An empty input still runs the scan launch: it stores the
-    // count (zero) that the caller reads from device memory.
     if (force >= 0 && force != DISC_V_COMPACT_VEC && force != DISC_V_COMPACT_SCALAR)
       return set_err(c, DISC_ERR_INVALID_ARG, "forced version does not belong to a compaction pattern");
     constexpr int kCompactSlots = 4;   // (mirrors the device header)
@@ -417,26 +420,36 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     const int v = vec ? V : 1;
     const int64_t tile = 256ll * kCompactSlots * v;
     const int64_t nb = (sv.inner + tile - 1) / tile;
-    fp->aux[0] = nb;
+    // From kCompactTwoLaunchTiles tiles on, chunks of consecutive tiles whose counts every block of
+    // the scatter launch adds up by itself, and no scan launch; below, a chunk is a tile.
+    const bool two = nb >= kCompactTwoLaunchTiles;
+    const int64_t per_chunk = two ? (nb + kCompactMaxChunks - 1) / kCompactMaxChunks : 1;
+    const int64_t chunks = (nb + per_chunk - 1) / per_chunk;
+    fp->aux[0] = chunks;
+    fp->aux[1] = per_chunk;
+    fp->aux[2] = two;
     fp->ws_off[0] = 0;
     pub.workspace_bytes = (size_t)std::max<int64_t>(nb, 1) * 8;
     pub.variant = vec ? DISC_V_COMPACT_VEC : DISC_V_COMPACT_SCALAR;
     pub.vec_width = v;
     pub.index_bits = 64;
     pub.slots_per_lane = kCompactSlots;
-    const uint32_t grid = (uint32_t)std::min<int64_t>(nb, max_grid * 4);
+    const uint32_t grid = (uint32_t)std::min<int64_t>(chunks, max_grid * 4);
     int l = 0;
     if (nb > 0) {
       fp->launches[l].kid = vec ? K_COMPACT_COUNT_VEC : K_COMPACT_COUNT_SCALAR;
       fp->launches[l].grid[0] = grid;
       ++l;
     }
-    fp->launches[l].kid = K_COMPACT_SCAN;
-    fp->launches[l].block = 1024;
-    fp->launches[l].grid[0] = 1;
-    ++l;
+    if (!two) {   // (an empty input still runs the scan launch: it stores the count, zero)
+      fp->launches[l].kid = K_COMPACT_SCAN;
+      fp->launches[l].block = 1024;
+      fp->launches[l].grid[0] = 1;
+      ++l;
+    }
     if (nb > 0) {
-      fp->launches[l].kid = vec ? K_COMPACT_SCATTER_VEC : K_COMPACT_SCATTER_SCALAR;
+      const bool nt = vec && two && c->row_nt != 0 && (c->row_nt > 0 || sv.alg_bytes >= kNonTemporalMinBytes);
+      fp->launches[l].kid = nt ? K_COMPACT_SCATTER_VEC_NT : vec ? K_COMPACT_SCATTER_VEC : K_COMPACT_SCATTER_SCALAR;
       fp->launches[l].grid[0] = grid;
       ++l;
     }

@@ -124,3 +124,38 @@ def test_empty_input_still_delivers_the_count(ctx):
     a = run_gpu(h, pat, [50000], [x])
     b = run_gpu(h, pat, [50000], [x])
     assert all(torch.equal(p, q) for p, q in zip(a, b))
+
+
+@pytest.mark.parametrize("what", ["unique i32", "unique i64", "filter", "filter scalar"])
+def test_two_launch_version(ctx, what):
+    """Large inputs: chunks of tiles whose counts the scatter launch adds up by itself (no scan launch).
+    Sizes on both sides of the line and of the step from one tile to two tiles per chunk, a last tile
+    of one element, parts of a tile that end inside a slot; everything, nothing and some kept.
+    Index, integer and bf16 results against the oracle (whole numbers exactly; x + 1 in bf16 is
+    rounded once on both sides)."""
+    unique = what.startswith("unique")
+    pat = unique_sorted(what.split()[1]) if unique else filtered()
+    h = ctx.register(pat)
+    scalar = what.endswith("scalar")
+    vec = 1 if scalar else {"unique i32": 4, "unique i64": 2, "filter": 8}[what]
+    tile = 256 * 4 * vec
+    from paper_2103_05288_amd import VARIANTS
+    force = VARIANTS.index("compact_scalar") if scalar else -1
+    kernels = lambda n: [k.split("k_compact_")[1].split("_")[0] for k in h.plan([n], force)["kernels"]]
+    assert kernels(31 * tile) == ["count", "scan", "scatter"] and kernels(31 * tile + 1) == ["count", "scatter"]
+    g = torch.Generator().manual_seed(13)
+    for n in (31 * tile, 31 * tile + 1, 45 * tile + tile // 2 + 3 * vec + 1, 2049 * tile - 1):
+        if n > 1 << 22 and not unique:
+            continue
+        if unique:
+            for spread in (2, 3 * n):
+                x = torch.sort(torch.randint(-spread, spread + 1, (n,), generator=g, dtype=torch.int64)).values
+                x = x * 3000000007 if what == "unique i64" else x.to(torch.int32)
+                print(f"[two launches] {what} n={n} spread={spread}", flush=True)
+                check(ctx, pat, [n], [x], what)
+        else:
+            x = (torch.randn(n, generator=g) * 2).to(torch.bfloat16)
+            w = torch.round(torch.randn(n, generator=g) * 4)
+            for thr in (1e9, -1e9, 0.0, 3.3):
+                print(f"[two launches] {what} n={n} thr={thr}", flush=True)
+                check(ctx, pat, [n], [x, w, torch.tensor(thr)], what, force="compact_scalar" if scalar else None)
