@@ -77,6 +77,11 @@ struct Gen {
         for (int k = 0; k < operand_count(op.opcode); ++k) read_on.insert(op.in[k]);
   }
 
+  // no reduction along the rows, sums over the rows only: a row need not stay in one block (one outer
+  // group at most, so that an operand that does not span it is the same in every row)
+  bool row_cols_ok() const {
+    return row_tmpl() && an.n_phases == 0 && an.n_col_sums > 0 && an.n_row_reds == 0 && an.inner_group <= 1;
+  }
   static bool is_reduce(int oc) { return oc >= DISC_REDUCE_SUM && oc <= DISC_REDUCE_ARGMAX; }
   bool col_tmpl() const { return an.tmpl == DISC_TEMPLATE_COL_REDUCE; }
   bool row_tmpl() const { return an.tmpl == DISC_TEMPLATE_ROW_REDUCE; }
@@ -784,10 +789,24 @@ struct Gen {
     os << "    (void)A; (void)lds; (void)tid; (void)nthreads;\n  }\n";
   }
 
+  // version by column tiles: a lane's columns are the same in every row, so the operands that do not
+  // depend on the row are loaded once, into a struct of the lane's own that rc.sl points to
+  void emit_late_struct() {
+    os << "  template <int V> struct Late {\n";
+    for (size_t i = 0; i < an.accesses.size(); ++i)
+      if (late(an.accesses[i])) os << "    disc::Vec<" << dtype_ctype(an.accesses[i].dtype) << ", V> l" << i << ";\n";
+    os << "    int unused_;\n  };\n";
+    os << "  template <int V, class C, class SP> static DISC_DEV void load_late(const Args& A, const RowCtx& rc, C col, SP sp, Late<V>& h) {\n";
+    for (size_t i = 0; i < an.accesses.size(); ++i)
+      if (late(an.accesses[i])) os << "    " << load_call(an.accesses[i], i, fmt("h.l%zu", i), "", "") << "\n";
+    os << "    (void)A; (void)rc; (void)col; (void)sp; (void)h;\n  }\n";
+  }
+
   void emit_late_loads(std::ostream& o, const Fn& fn, const char* ind) {
     for (int ai : fn.late_used) {
       const Access& a = an.accesses[ai];
       o << ind << "disc::Vec<" << dtype_ctype(a.dtype) << ", V> l" << ai << ";\n";
+      if (row_cols_ok()) o << ind << "if constexpr (HOISTED) l" << ai << " = reinterpret_cast<const Late<V>*>(rc.sl)->l" << ai << "; else\n";
       const int st = staged_index(ai);
       if (st >= 0) {
         // a compile-time choice: behind a run-time branch the wait for the operand would cover both
@@ -1137,13 +1156,14 @@ struct Gen {
     // the row-vector operands from their LDS copy
     const bool staged = !staged_accesses().empty();
     auto krow = [&](const std::string& name, int v, int nv) {
+      if (v > 1 && row_cols_ok()) return;   // the version by column tiles takes every such launch
       // the two-slot version for blocks above 256 threads runs without the software pipeline: the
       // registers it saves let a CU hold three 8-wavefront blocks instead of two (+10 % measured);
       // with three slots the residency is the same either way and the pipeline wins
       const char* pipe = max_threads > 256 && nv == 2 ? "false" : "true";
       k(name, fmt("disc::row_reg_body<Pat, %d, %d, %s>(A, rp);", v, nv, pipe), "RowPlan");
       if (staged && v > 1)
-        k(name + "_s", fmt("disc::row_reg_body<PatT<true>, %d, %d, %s>(A, rp);", v, nv, pipe), "RowPlan", "PatT<true>");
+        k(name + "_s", fmt("disc::row_reg_body<PatT<1>, %d, %d, %s>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
       // blocks of one wavefront quad, vector width: versions whose vector slots are all whole (no
       // ragged-tail path anywhere in them).  _e: rows that are a whole number of slots; _nt: the
       // same with non-temporal accesses of the full-size operands, for large launches of rows that
@@ -1156,16 +1176,16 @@ struct Gen {
         if (tail) k(name + "_t", fmt("disc::row_reg_body<Pat, %d, %d, %s, 0, true, true>(A, rp);", v, nv, pipe), "RowPlan");
         k(name + "_nt", fmt("disc::row_reg_body<Pat, %d, %d, %s, 3, true>(A, rp);", v, nv, pipe), "RowPlan");
         if (staged) {
-          k(name + "_s_e", fmt("disc::row_reg_body<PatT<true>, %d, %d, %s, 0, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<true>");
-          if (tail) k(name + "_s_t", fmt("disc::row_reg_body<PatT<true>, %d, %d, %s, 0, true, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<true>");
-          k(name + "_s_nt", fmt("disc::row_reg_body<PatT<true>, %d, %d, %s, 3, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<true>");
+          k(name + "_s_e", fmt("disc::row_reg_body<PatT<1>, %d, %d, %s, 0, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
+          if (tail) k(name + "_s_t", fmt("disc::row_reg_body<PatT<1>, %d, %d, %s, 0, true, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
+          k(name + "_s_nt", fmt("disc::row_reg_body<PatT<1>, %d, %d, %s, 3, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
         }
       }
       // blocks above 256 threads: the _t version of the two-slot kernel only (the three-slot one
       // has no registers to spare under its 128-register cap)
       if (v > 1 && max_threads > 256 && nv == 2 && tail) {
         k(name + "_t", fmt("disc::row_reg_body<Pat, %d, %d, %s, 0, true, true>(A, rp);", v, nv, pipe), "RowPlan");
-        if (staged) k(name + "_s_t", fmt("disc::row_reg_body<PatT<true>, %d, %d, %s, 0, true, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<true>");
+        if (staged) k(name + "_s_t", fmt("disc::row_reg_body<PatT<1>, %d, %d, %s, 0, true, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
       }
     };
     if (an.tmpl == DISC_TEMPLATE_COMPACT) {
@@ -1197,6 +1217,10 @@ struct Gen {
       krow("k_row_vec_nv3w", V, 3);
       krow("k_row_scalar_nv2w", 1, 2);
       max_threads = 256;
+      if (row_cols_ok()) {
+        k("k_row_cols_vec", fmt("disc::row_cols_body<PatT<2>, %d, 2, 0, disc::Span>(A);", V), nullptr, "PatT<2>");
+        if (V > 1) k("k_row_cols_vec_nt", fmt("disc::row_cols_body<PatT<2>, %d, 2, 3, disc::EvenSpan>(A);", V), nullptr, "PatT<2>");
+      }
       k("k_row_stream_vec", fmt("disc::row_stream_body<Pat, %d>(A);", V), nullptr);
       k("k_row_stream_scalar", "disc::row_stream_body<Pat, 1>(A);", nullptr);
       if (an.n_col_sums > 0) k("k_colsum_finish", "disc::colsum_finish_body<Pat>(A);", nullptr);
@@ -1257,8 +1281,8 @@ struct Gen {
     os << "// generated: one fused pattern, every kernel version\n";
     emit_acc_types();
     std::vector<char> all(an.accesses.size(), 1);
-    const bool staged_versions = !staged_accesses().empty();
-    if (staged_versions) os << "template <bool ST> struct PatT {\n  static constexpr bool STAGED = ST;\n";
+    const bool staged_versions = row_cols_ok() || !staged_accesses().empty();
+    if (staged_versions) os << "template <int ST> struct PatT {\n  static constexpr bool STAGED = ST == 1, HOISTED = ST == 2;\n";
     else os << "struct Pat {\n  static constexpr bool STAGED = false;\n";
     os << "  static constexpr int NPHASE = " << an.n_phases << ";\n";
     os << "  static constexpr int MAX_ACC_BYTES = " << acc_bytes << ";\n";
@@ -1272,6 +1296,7 @@ struct Gen {
       emit_acc_basic();
       if (row_tmpl()) {
         emit_stage_fns();
+        if (row_cols_ok()) emit_late_struct();
         emit_row_phase_fns();
       }
       emit_epilogue(M_ELEM);
@@ -1279,7 +1304,7 @@ struct Gen {
       emit_row_reds();
       if (compact_tmpl()) emit_compact_fns();
       os << "};\n";
-      if (staged_versions) os << "typedef PatT<false> Pat;\n";
+      if (staged_versions) os << "typedef PatT<0> Pat;\n";
     } else {
       // stage 1 + 2: operands that feed the reductions
       std::vector<int> roots;
@@ -1326,6 +1351,7 @@ struct Gen {
     out->n_row_reds = row_tmpl() ? an.n_row_reds : 0;
     out->row_tail_ok = an.n_col_sums == 0;
     out->row_shift_ok = row_shift_ok();
+    out->row_cols_ok = row_cols_ok();
     out->staged_elem_bytes.clear();
     for (int ai : staged_accesses()) out->staged_elem_bytes.push_back(dtype_bytes(an.accesses[ai].dtype));
     return DISC_OK;

@@ -974,6 +974,93 @@ DISC_DEV void row_stream_body(const typename Pat::Args& A) {
   }
 }
 
+// An element-wise pattern with sums over the rows (no reduction along the rows: NPHASE = 0) does not need
+// a row in one block.  A block of 256 threads is TX = A.aux1 lanes along the columns (a power of two;
+// 256 for long rows, which then take gridDim.y blocks) times TY = 256 / TX rows; a lane keeps its
+// columns, U rows in flight, and its sums in registers.  Nothing is exchanged between the lanes until
+// the end, where the TY lanes of a column meet in LDS and the block writes its part of one row of
+// partial sums.  Rows are dealt out one by one, so that the blocks of a launch stream through the
+// tensor side by side.  kRun batches are added up before they meet the sums of the whole block (short
+// chains of additions: 16 + rows of a lane / 16).
+template <class Pat, int V, int U, int NT, class SP>
+DISC_DEV void row_cols_body(const typename Pat::Args& A) {
+  constexpr int kRun = 16 / U;
+  __shared__ typename Vec<float, V>::vec_t cbuf[256];
+  const int TX = (int)A.aux1, TY = 256 / TX;
+  const int tx = (int)threadIdx.x & (TX - 1);
+  // (whole wavefronts along a row: the row number is a scalar)
+  int ty = (int)threadIdx.x / TX;
+  const int col = ((int)blockIdx.y * TX + tx) * V;
+  const i64 rem = A.inner - col;
+  const bool mine = rem > 0;
+  const SP sp = SP::upto(rem < (i64)V ? (int)rem : V);
+  typename Pat::template ColAcc<V> acc{};
+  auto walk = [&](i64 row) {
+    typename Pat::template Late<V> same;          // operands that are the same in every row
+    {
+      typename Pat::RowCtx rc;
+      Pat::row_begin(A, 0, rc);
+      Pat::template load_late<V>(A, rc, col, sp, same);
+    }
+    const char* held = reinterpret_cast<const char*>(&same);
+    const i64 step = (i64)gridDim.x * TY;
+    while (row + (U - 1) * step < A.rows) {
+      typename Pat::template ColAcc<V> part{};
+      const i64 stop = row + kRun * U * step < A.rows ? row + kRun * U * step : A.rows;
+      for (; row + (U - 1) * step < stop; row += U * step) {
+        typename Pat::RowCtx rc[U];
+        typename Pat::template Slot<V> slot[U];
+        typename Pat::template Keep<V> keep;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          Pat::row_begin(A, row + u * step, rc[u]);
+          rc[u].sl = held;
+          Pat::template load<V, NT>(A, rc[u], col, sp, slot[u]);
+        }
+        asm volatile("" ::: "memory");     // all loads of the batch before its first row
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          typename Pat::template OutSlot<V> o;
+          Pat::template epilogue<V, false>(A, rc[u], slot[u], keep, col, sp, o);
+          Pat::template store<V, NT>(A, rc[u], col, sp, o);
+          Pat::template col_sums<V, false>(A, rc[u], slot[u], keep, col, sp, part);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < Pat::NCOLSUM; ++q) acc.c[q] += part.c[q];
+    }
+    for (; row < A.rows; row += step) {
+      typename Pat::RowCtx rc;
+      typename Pat::template Slot<V> slot;
+      typename Pat::template Keep<V> keep;
+      Pat::row_begin(A, row, rc);
+      rc.sl = held;
+      Pat::template load<V, NT>(A, rc, col, sp, slot);
+      typename Pat::template OutSlot<V> o;
+      Pat::template epilogue<V, false>(A, rc, slot, keep, col, sp, o);
+      Pat::template store<V, NT>(A, rc, col, sp, o);
+      Pat::template col_sums<V, false>(A, rc, slot, keep, col, sp, acc);
+    }
+  };
+  if (mine) {
+    if (TX >= 64) walk((i64)blockIdx.x * TY + __builtin_amdgcn_readfirstlane(ty));
+    else walk((i64)blockIdx.x * TY + ty);
+  }
+#pragma unroll
+  for (int q = 0; q < Pat::NCOLSUM; ++q) {
+    Vec<float, V> t;
+    t.v = acc.c[q];
+    if (TY > 1) {
+      if (q > 0) __syncthreads();
+      cbuf[threadIdx.x] = t.v;
+      __syncthreads();
+      if (ty == 0)
+        for (int k = 1; k < TY; ++k) t.v += cbuf[tx + k * TX];
+    }
+    if (mine && ty == 0) st(reinterpret_cast<float*>(A.ws0) + ((i64)q * A.aux0 + blockIdx.x) * A.inner, (i64)col, t, sp);
+  }
+}
+
 // Last launch of a row reduce with reductions of per-row values over the rows: one block of 1024
 // threads folds the per-block partial results of every reduction in a fixed order (sums in fp64)
 // and stores them.  All reductions advance together and two strides are in flight per lane, so a

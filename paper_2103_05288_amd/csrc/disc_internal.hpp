@@ -218,6 +218,7 @@ struct Generated {
   int n_row_reds = 0;                 // row reduce: per-row values reduced over the rows to one number (last launch)
   std::vector<int> staged_elem_bytes; // row reduce: element size of each row vector that can be staged in LDS
   bool row_tail_ok = false;           // row reduce: there are versions that take a ragged end of a row as single elements (_t)
+  bool row_cols_ok = false;           // row reduce without reductions along the rows: the version by column tiles exists
   bool row_shift_ok = false;          // ... and their vector slots may be shifted to the 16-byte boundaries of the tensor
   std::vector<std::string> field_names;   // member name of each args.fields entry in Pat::Args
 };
@@ -233,7 +234,7 @@ enum KernelId {
   K_TRANSPOSE_TILE,
   K_COL_EPI2_VEC, K_COL_EPI2_VEC_NT, K_COL_EPI2_SCALAR,
   K_COMPACT_COUNT_VEC, K_COMPACT_COUNT_SCALAR, K_COMPACT_SCAN, K_COMPACT_SCATTER_VEC, K_COMPACT_SCATTER_SCALAR,
-  K_COMPACT_SCATTER_VEC_NT,
+  K_COMPACT_SCATTER_VEC_NT, K_ROW_COLS_VEC, K_ROW_COLS_VEC_NT,
   K_ROW_BASE,
   K_COUNT = K_ROW_BASE + 96
 };

@@ -497,7 +497,33 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     fp->nslots = 0;
     LaunchRec& L = fp->launches[0];
     L.block = 256;
-    if (stream) {
+    int TX = 8;                                      // lanes along the columns, version by column tiles
+    while (TX < 256 && TX < spr) TX *= 2;
+    const int64_t col_tiles = (spr + TX - 1) / TX;
+    if (p.gen.row_cols_ok && vec && (force < 0 || force == DISC_V_ROW_REG_VEC) && col_tiles <= 65535) {
+      const bool nt = v > 1 && sv.inner % v == 0 && c->row_nt != 0 &&
+                      (c->row_nt > 0 || (sv.alg_bytes >= kNonTemporalMinBytes && full_aligned()));
+      pub.variant = DISC_V_ROW_REG_VEC;
+      L.kid = nt ? K_ROW_COLS_VEC_NT : K_ROW_COLS_VEC;
+      // Two blocks per CU with non-temporal accesses, three with plain ones: the chip holds seven, but
+      // with more streams in flight the memory delivers less.  Measured (bf16, 2^26 elements; 2 / 3 /
+      // 4 / 7 blocks per CU): 4096 columns 71.0 / 73.9 / 77.5 / 79.9 us, 1024 columns 71.1 / 74.3 /
+      // 79.9 / 84.4; plain accesses, 1100 columns 104 / 90 / 95 / 108, 5001 columns 102 / 100 / 112 /
+      // 104.  Rows of partial sums, one per block of a column tile, then follow: four rows to a lane
+      // where that leaves enough blocks, and no more than fit the fixed scratch array.
+      const int64_t held = (int64_t)c->n_cus * std::min(nt ? 2 : 3, resident_blocks(c, p, L.kid, L.block, 0));
+      const int64_t row_groups = (sv.rows + 256 / TX - 1) / (256 / TX);
+      const int64_t per_tile = (held + col_tiles - 1) / col_tiles, least = ((int64_t)c->n_cus * 2 + col_tiles - 1) / col_tiles;
+      int64_t grid = std::min<int64_t>(row_groups, std::min<int64_t>(per_tile, std::max<int64_t>(least, (row_groups + 3) / 4)));
+      grid = std::max<int64_t>(1, std::min<int64_t>(grid, DISC_STATIC_SCRATCH_BYTES / (4ll * n_col_sums * sv.inner)));
+      L.grid[0] = (uint32_t)grid;
+      L.grid[1] = (uint32_t)col_tiles;
+      fp->aux[0] = grid;        // rows of partial sums
+      fp->aux[1] = TX;
+      pub.lanes_per_row = TX;
+      pub.slots_per_lane = 2;   // rows in flight
+      pub.reg_slots = 2;
+    } else if (stream) {
       pub.variant = vec ? DISC_V_ROW_STREAM_VEC : DISC_V_ROW_STREAM_SCALAR;
       L.kid = vec ? K_ROW_STREAM_VEC : K_ROW_STREAM_SCALAR;
       // (sums over the rows: a row of partial sums per block in the workspace, so fewer blocks)
@@ -1207,7 +1233,7 @@ static int register_impl(disc_ctx* ctx, const disc_op* ops, int n_ops, const dis
       // non-temporal version for launches whose operands turn out not to be 16-byte aligned
       // (for a row kernel that sibling is the version for rows of whole slots, _e)
       if (k.size() > 3 && k.compare(k.size() - 3, 3, "_nt") == 0)
-        opt.only_kernels.push_back(k.substr(0, k.size() - 3) + (k.compare(0, 6, "k_row_") == 0 ? "_e" : ""));
+        opt.only_kernels.push_back(k.substr(0, k.size() - 3) + (k.compare(0, 9, "k_row_vec") == 0 ? "_e" : ""));
     }
     if (opt.only_kernels.empty()) return set_err(ctx, DISC_ERR_SHAPE, "a single-shape pattern needs a shape that launches something");
     const std::string macros = static_macros(*p, fp, static_dims);

@@ -381,3 +381,69 @@ def test_column_sums_and_scalar_reductions_together():
                 assert_close(g, w, f"dims={dims} out{k}")
     finally:
         ctx.close()
+
+
+def scaled_squares_with_sums():
+    """No reduction along the rows: y = x * s[t] + b[h] with x a window of a wider input padded on the left, and
+    two sums over the rows (non-negative terms)."""
+    pb = PatternBuilder("scaled_squares")
+    t, h, wide, low = pb.dims(4)
+    x = pb.cast(pb.pad(pb.param("bf16", [t, wide]), [pb.static_start(0), low], [t, h], 0.5), "f32")
+    s = pb.param("f32", [t])
+    b = pb.param("f32", [h])
+    y = pb.op("add", pb.op("mul", x, pb.broadcast(s, [t, h], [0])), pb.broadcast(b, [t, h], [1]))
+    pb.output(pb.cast(y, "bf16"))
+    pb.output(pb.reduce("sum", pb.op("mul", y, y), 0))
+    pb.output(pb.reduce("sum", pb.op("abs", y), 0))
+    return pb.build()
+
+
+def test_single_shape_build_by_column_tiles(hctx):
+    """The single-shape module of a non-temporal launch also holds the plain version for misaligned operands."""
+    h = hctx.register_static(gelu_backward_bias_gradient(), [16384, 1024])
+    assert h.info["n_variants"] == 3
+    assert h.plan([16384, 1024])["kernels"][0].endswith("k_row_cols_vec_nt")
+    q = h.plan([16384, 1024], inputs=[4096, 4098, 4096], outputs=[4096, 4096])
+    assert q["kernels"][0].endswith("k_row_cols_vec") and q["workspace_bytes"] <= 16 << 20
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nt", [0, 1])
+def test_version_by_column_tiles(nt):
+    """Element-wise patterns with sums over the rows run in k_row_cols: every number of lanes along the columns
+    (8 .. 256) at its edges, several column tiles, fewer rows than a batch, and more than a block sums up in
+    one go; plain accesses, and the version for rows of whole slots with non-temporal ones."""
+    from oracle import run as oracle_run
+    from paper_2103_05288_amd import Context
+    from tests.util import assert_close, run_gpu, to_oracle_input
+    ctx = Context(0)
+    ctx.test_option("non_temporal", nt)
+    try:
+        gen = torch.Generator().manual_seed(41)
+        plain, padded = gelu_backward_bias_gradient(), scaled_squares_with_sums()
+        hp, hq = ctx.register(plain), ctx.register(padded)
+        assert (hp.info["template"], hp.info["n_phases"]) == (hq.info["template"], hq.info["n_phases"]) == ("row_reduce", 0)
+        lanes = set()
+        for i, h in enumerate((4, 8, 9, 64, 65, 128, 129, 255, 256, 504, 513, 1024, 1032, 2041, 2048, 2049, 4104)):
+            for t in ((1, 3 + i, 200 + 7 * i) if h > 64 else (1, 5000 + i)):
+                pl = hp.plan([t, h])
+                lanes.add(pl["lanes_per_row"])
+                assert pl["kernels"][0].endswith("k_row_cols_vec_nt" if nt and h % 8 == 0 else "k_row_cols_vec"), pl["kernels"]
+                assert pl["workspace_bytes"] == pl["grid"][0][0] * h * 4
+                ins = _inputs(plain, [t, h], gen)
+                got = run_gpu(hp, plain, [t, h], ins)
+                want = oracle_run(plain, [t, h], [to_oracle_input(x) for x in ins])[0]
+                assert_close(got[0], want[0], f"dx {t}x{h} nt={nt}")
+                dy, x, b = (v.double().numpy() for v in ins)
+                a = 1.702 * (x + b)
+                s = 1.0 / (1.0 + np.exp(-a))
+                _check_sum(got[1], want[1], np.abs(dy * s * (1.0 + a * (1.0 - s))), -(-t // pl["grid"][0][0]), f"db {t}x{h} nt={nt}")
+                dims = [t, h, max(1, h - 3), min(2, h - 1)] if i % 2 else [t, h, h, 0]
+                ins = [torch.randn(t, dims[2], generator=gen).bfloat16(), torch.randn(t, generator=gen), torch.randn(h, generator=gen)]
+                got = run_gpu(hq, padded, dims, ins)
+                want = oracle_run(padded, dims, [to_oracle_input(v) for v in ins])[0]
+                for k, (g, w) in enumerate(zip(got, want)):
+                    assert_close(g, w, f"padded {dims} out{k} nt={nt}")
+        assert lanes == {8, 16, 32, 64, 128, 256}
+    finally:
+        ctx.close()
