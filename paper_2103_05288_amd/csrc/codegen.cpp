@@ -1221,8 +1221,10 @@ struct Gen {
         k("k_row_cols_vec", fmt("disc::row_cols_body<PatT<2>, %d, 2, 0, disc::Span>(A);", V), nullptr, "PatT<2>");
         if (V > 1) k("k_row_cols_vec_nt", fmt("disc::row_cols_body<PatT<2>, %d, 2, 3, disc::EvenSpan>(A);", V), nullptr, "PatT<2>");
       }
-      k("k_row_stream_vec", fmt("disc::row_stream_body<Pat, %d>(A);", V), nullptr);
-      k("k_row_stream_scalar", "disc::row_stream_body<Pat, 1>(A);", nullptr);
+      k("k_row_stream_scalar", "disc::row_stream_body<Pat, 1, 0>(A);", nullptr);
+      max_threads = 1024;
+      k("k_row_stream_vec", fmt("disc::row_stream_body<Pat, %d, 4>(A);", V), nullptr);
+      max_threads = 256;
       if (an.n_col_sums > 0) k("k_colsum_finish", "disc::colsum_finish_body<Pat>(A);", nullptr);
       if (an.n_row_reds > 0) {
         max_threads = 1024;
@@ -1299,6 +1301,7 @@ struct Gen {
         if (row_cols_ok()) emit_late_struct();
         emit_row_phase_fns();
       }
+      os << "  static constexpr bool HAS_ELEM_OUT = " << (has_elem_outputs() ? "true" : "false") << ";\n";
       emit_epilogue(M_ELEM);
       emit_col_sums();
       emit_row_reds();
@@ -1352,6 +1355,7 @@ struct Gen {
     out->row_tail_ok = an.n_col_sums == 0;
     out->row_shift_ok = row_shift_ok();
     out->row_cols_ok = row_cols_ok();
+    out->row_elem_out = row_tmpl() && has_elem_outputs();
     out->staged_elem_bytes.clear();
     for (int ai : staged_accesses()) out->staged_elem_bytes.push_back(dtype_bytes(an.accesses[ai].dtype));
     return DISC_OK;

@@ -51,6 +51,11 @@ typedef unsigned long long u64;
 
 #define DISC_DEV __device__ __forceinline__
 
+template <int N>
+struct IntC {
+  static constexpr int value = N;
+};
+
 // ---------------------------------------------------------------------------------------
 // Vectors of N storage elements, loaded and stored with ELEMENT alignment only.  gfx950
 // runs with unaligned global access enabled, so the compiler still emits one wide access
@@ -883,23 +888,55 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
   }
 }
 
-// Streaming version for rows that do not fit the register budget: one block per row, the
-// row is re-read (from L2 / Infinity Cache when it fits) once per reduction phase and once
-// for the epilogue.  Any row length below 2^31 works.
-template <class Pat, int P, int V>
-DISC_DEV void row_stream_phases(const typename Pat::Args& A, typename Pat::RowCtx& rc, int inner,
-                                char* lds, int& parity) {
+// Streaming version for rows that do not fit the register-resident versions: one block per row.  The
+// first NR slots of every lane stay in registers, as loaded (no values carried between the phases, no
+// second register set for the next row: with blocks of 1024 threads two of them can share a CU, and
+// one loads while the other computes); what lies behind them is read again, from L2 / Infinity Cache
+// when it fits, once per reduction phase and once for the epilogue.  The elements behind the last
+// whole slot of a row go one each to the first lanes, as slots of one element.  Any row length below
+// 2^31 works.
+//
+// as_loaded: the slot's registers with their contents unknown to the compiler.  It would otherwise
+// convert a slot to fp32 once and keep that, twice the registers, through all phases.
+template <class S>
+DISC_DEV S as_loaded(const S& s) {
+  constexpr int W = (int)(sizeof(S) - sizeof(int)) / 4;      // (the last member is a placeholder)
+  u32 w[W > 0 ? W : 1];
+  __builtin_memcpy(w, &s, W * 4);
+#pragma unroll
+  for (int i = 0; i < W; ++i) asm volatile("" : "+v"(w[i]));
+  S r;
+  __builtin_memcpy(&r, w, W * 4);
+  return r;
+}
+template <class Pat, int V, int NR>
+struct StreamRow {
+  typename Pat::template Slot<V> held[NR > 0 ? NR : 1];
+  typename Pat::template Slot<1> end;
+  int end_col;            // column of this lane's single element, -1: none
+};
+template <class Pat, int P, int V, int NR>
+DISC_DEV void row_stream_phases(const typename Pat::Args& A, typename Pat::RowCtx& rc, int whole,
+                                const StreamRow<Pat, V, NR>& r, char* lds, int& parity) {
   if constexpr (P < Pat::NPHASE) {
     typedef typename Pat::template Acc<P> AccT;
     AccT acc;
     Pat::template acc_init<P>(acc);
-    for (int col = threadIdx.x * V; col < inner; col += blockDim.x * V) {
-      int n = inner - col;
-      n = n > V ? V : n;
-      typename Pat::template Slot<V> slot;
-      Pat::template load<V>(A, rc, col, Span::upto(n), slot);
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+      const int col = (int)(j * blockDim.x + threadIdx.x) * V;
       typename Pat::template Keep<V> kp;
-      Pat::template phase<P, V, false>(A, acc, slot, kp, Span::upto(n), col, rc);
+      if (col < whole) Pat::template phase<P, V, false>(A, acc, as_loaded(r.held[j]), kp, TailSpan::upto(V), col, rc);
+    }
+    for (int col = (int)(NR * blockDim.x + threadIdx.x) * V; col < whole; col += blockDim.x * V) {
+      typename Pat::template Slot<V> slot;
+      Pat::template load<V>(A, rc, col, TailSpan::upto(V), slot);
+      typename Pat::template Keep<V> kp;
+      Pat::template phase<P, V, false>(A, acc, slot, kp, TailSpan::upto(V), col, rc);
+    }
+    if (r.end_col >= 0) {
+      typename Pat::template Keep<1> kp;
+      Pat::template phase<P, 1, false>(A, acc, r.end, kp, TailSpan::upto(1), r.end_col, rc);
     }
     group_allreduce<Pat, P>(acc, 64);
     AccT* ex = reinterpret_cast<AccT*>(lds + parity * 16 * Pat::MAX_ACC_BYTES);
@@ -907,21 +944,18 @@ DISC_DEV void row_stream_phases(const typename Pat::Args& A, typename Pat::RowCt
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) ex[wave] = acc;
     __syncthreads();
-    const int nw = blockDim.x >> 6;
-    acc = ex[0];
-    for (int w = 1; w < nw; ++w) {
-      AccT o = ex[w];
-      Pat::template acc_merge<P>(acc, o);
-    }
+    const int nw = __builtin_amdgcn_readfirstlane((int)(blockDim.x >> 6));         // a power of two
+    acc = ex[(int)threadIdx.x & (nw - 1)];
+    group_allreduce<Pat, P>(acc, nw);
     Pat::template row_after<P>(A, rc, acc);
-    row_stream_phases<Pat, P + 1, V>(A, rc, inner, lds, parity);
+    row_stream_phases<Pat, P + 1, V, NR>(A, rc, whole, r, lds, parity);
   }
 }
 
-template <class Pat, int V>
+template <class Pat, int V, int NR>
 DISC_DEV void row_stream_body(const typename Pat::Args& A) {
   __shared__ __attribute__((aligned(16))) char lds[2 * 16 * Pat::MAX_ACC_BYTES];
-  const int inner = (int)A.inner;
+  const int inner = (int)A.inner, whole = inner / V * V;
   int parity = 0;
   bool first = true;
   float racc[Pat::NROWRED > 0 ? Pat::NROWRED : 1];
@@ -933,35 +967,54 @@ DISC_DEV void row_stream_body(const typename Pat::Args& A) {
     typename Pat::RowCtx rc;
     Pat::row_begin(A, row, rc);
     rc.sl = nullptr;
-    row_stream_phases<Pat, 0, V>(A, rc, inner, lds, parity);
+    StreamRow<Pat, V, NR> r;
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+      const int col = (int)(j * blockDim.x + threadIdx.x) * V;
+      if (col < whole) Pat::template load<V>(A, rc, col, TailSpan::upto(V), r.held[j]);
+    }
+    r.end_col = whole + (int)threadIdx.x < inner ? whole + (int)threadIdx.x : -1;
+    if (r.end_col >= 0) Pat::template load<1>(A, rc, r.end_col, TailSpan::upto(1), r.end);
+    if constexpr (NR > 0) asm volatile("" ::: "memory");     // all of these loads before the first phase
+    row_stream_phases<Pat, 0, V, NR>(A, rc, whole, r, lds, parity);
     if constexpr (Pat::NROWRED > 0) Pat::row_reds(A, rc, racc);   // (every lane holds the row's values)
-    for (int col = threadIdx.x * V; col < inner; col += blockDim.x * V) {
-      int n = inner - col;
-      n = n > V ? V : n;
-      typename Pat::template Slot<V> slot;
-      Pat::template load<V>(A, rc, col, Span::upto(n), slot);
-      typename Pat::template OutSlot<V> o;
-      typename Pat::template Keep<V> kp;
-      Pat::template epilogue<V, false>(A, rc, slot, kp, col, Span::upto(n), o);
-      Pat::template store<V>(A, rc, col, Span::upto(n), o);
+    auto finish = [&](auto slot, auto width, int col) {
+      constexpr int W = decltype(width)::value;
+      typename Pat::template OutSlot<W> o;
+      typename Pat::template Keep<W> kp;
+      Pat::template epilogue<W, false>(A, rc, slot, kp, col, TailSpan::upto(W), o);
+      Pat::template store<W>(A, rc, col, TailSpan::upto(W), o);
       if constexpr (Pat::NCOLSUM > 0) {
         // sums over the rows: the block's row of partial sums lives in the workspace (the rows are
         // too long for registers); every lane owns its columns there, so no other lane touches them
-        typename Pat::template ColAcc<V> ca{};
-        Pat::template col_sums<V, false>(A, rc, slot, kp, col, Span::upto(n), ca);
+        typename Pat::template ColAcc<W> ca{};
+        Pat::template col_sums<W, false>(A, rc, slot, kp, col, TailSpan::upto(W), ca);
 #pragma unroll
         for (int q = 0; q < Pat::NCOLSUM; ++q) {
           float* dst = reinterpret_cast<float*>(A.ws0) + ((i64)q * A.aux0 + blockIdx.x) * A.inner;
-          Vec<float, V> t;
+          Vec<float, W> t;
           t.v = ca.c[q];
           if (!first) {
-            Vec<float, V> old;
-            ld(old, dst, (i64)col, Span::upto(n));
+            Vec<float, W> old;
+            ld(old, dst, (i64)col, TailSpan::upto(W));
             t.v += old.v;
           }
-          st(dst, (i64)col, t, Span::upto(n));
+          st(dst, (i64)col, t, TailSpan::upto(W));
         }
       }
+    };
+    if constexpr (Pat::HAS_ELEM_OUT || Pat::NCOLSUM > 0) {
+#pragma unroll
+      for (int j = 0; j < NR; ++j) {
+        const int col = (int)(j * blockDim.x + threadIdx.x) * V;
+        if (col < whole) finish(as_loaded(r.held[j]), IntC<V>{}, col);
+      }
+      for (int col = (int)(NR * blockDim.x + threadIdx.x) * V; col < whole; col += blockDim.x * V) {
+        typename Pat::template Slot<V> slot;
+        Pat::template load<V>(A, rc, col, TailSpan::upto(V), slot);
+        finish(slot, IntC<V>{}, col);
+      }
+      if (r.end_col >= 0) finish(r.end, IntC<1>{}, r.end_col);
     }
     if (threadIdx.x == 0) Pat::row_store(A, row, rc);
     first = false;

@@ -218,6 +218,7 @@ struct Generated {
   int n_row_reds = 0;                 // row reduce: per-row values reduced over the rows to one number (last launch)
   std::vector<int> staged_elem_bytes; // row reduce: element size of each row vector that can be staged in LDS
   bool row_tail_ok = false;           // row reduce: there are versions that take a ragged end of a row as single elements (_t)
+  bool row_elem_out = false;          // row reduce: some output has an element per element of the iteration space
   bool row_cols_ok = false;           // row reduce without reductions along the rows: the version by column tiles exists
   bool row_shift_ok = false;          // ... and their vector slots may be shifted to the 16-byte boundaries of the tensor
   std::vector<std::string> field_names;   // member name of each args.fields entry in Pat::Args

@@ -489,6 +489,17 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     const int v = vec ? V : 1;
     int64_t spr = (sv.inner + v - 1) / v;
     stream = spr > 1024 * (vec ? 3 : 2);
+    if (force < 0 && vec) {
+      // Rows of blocks above 256 threads that write nothing per element: there is no store for the
+      // register-resident versions to overlap with the next row's loads, and the streaming version
+      // keeps as much of the row (bf16 log-sum-exp, 2^27 elements: 8192 columns 53.5 us against 82.0,
+      // 12288: 56.7 / 61.4, 16000: 55.5 / 99.1, 24000: 62.0 / 71.7; 4096 columns, blocks of 256: 57.8 /
+      // 55.6).
+      if (!p.gen.row_elem_out && n_col_sums == 0 && spr > 3 * 256) stream = true;
+      // Sums over the rows and three slots per lane do not fit the registers of a wide block
+      // (LayerNorm backward of 24000 columns: 1007 us, 514 in the streaming version)
+      if (n_col_sums > 0 && spr > 2 * 1024) stream = true;
+    }
     if (force == DISC_V_ROW_STREAM_VEC || force == DISC_V_ROW_STREAM_SCALAR) stream = true;
     else if (force >= 0 && stream) return set_err(c, DISC_ERR_INVALID_ARG, "row too long for the forced register-resident version");
     pub.vec_width = v;
@@ -497,6 +508,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     fp->nslots = 0;
     LaunchRec& L = fp->launches[0];
     L.block = 256;
+    int64_t partial_rows = 0;                        // rows of partial sums the workspace holds
     int TX = 8;                                      // lanes along the columns, version by column tiles
     while (TX < 256 && TX < spr) TX *= 2;
     const int64_t col_tiles = (spr + TX - 1) / TX;
@@ -511,11 +523,17 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // 79.9 / 84.4; plain accesses, 1100 columns 104 / 90 / 95 / 108, 5001 columns 102 / 100 / 112 /
       // 104.  Rows of partial sums, one per block of a column tile, then follow: four rows to a lane
       // where that leaves enough blocks, and no more than fit the fixed scratch array.
-      const int64_t held = (int64_t)c->n_cus * std::min(nt ? 2 : 3, resident_blocks(c, p, L.kid, L.block, 0));
+      // The workspace is that of the plain version either way: a caller asks for it without saying how
+      // its operands will be aligned.
       const int64_t row_groups = (sv.rows + 256 / TX - 1) / (256 / TX);
-      const int64_t per_tile = (held + col_tiles - 1) / col_tiles, least = ((int64_t)c->n_cus * 2 + col_tiles - 1) / col_tiles;
-      int64_t grid = std::min<int64_t>(row_groups, std::min<int64_t>(per_tile, std::max<int64_t>(least, (row_groups + 3) / 4)));
-      grid = std::max<int64_t>(1, std::min<int64_t>(grid, DISC_STATIC_SCRATCH_BYTES / (4ll * n_col_sums * sv.inner)));
+      const int64_t least = ((int64_t)c->n_cus * 2 + col_tiles - 1) / col_tiles;
+      auto blocks_per_tile = [&](int per_cu) {
+        const int64_t per_tile = ((int64_t)c->n_cus * per_cu + col_tiles - 1) / col_tiles;
+        int64_t g = std::min<int64_t>(row_groups, std::min<int64_t>(per_tile, std::max<int64_t>(least, (row_groups + 3) / 4)));
+        return std::max<int64_t>(1, std::min<int64_t>(g, DISC_STATIC_SCRATCH_BYTES / (4ll * n_col_sums * sv.inner)));
+      };
+      const int64_t grid = blocks_per_tile(nt ? 2 : 3);
+      partial_rows = blocks_per_tile(3);
       L.grid[0] = (uint32_t)grid;
       L.grid[1] = (uint32_t)col_tiles;
       fp->aux[0] = grid;        // rows of partial sums
@@ -526,12 +544,20 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     } else if (stream) {
       pub.variant = vec ? DISC_V_ROW_STREAM_VEC : DISC_V_ROW_STREAM_SCALAR;
       L.kid = vec ? K_ROW_STREAM_VEC : K_ROW_STREAM_SCALAR;
-      // (sums over the rows: a row of partial sums per block in the workspace, so fewer blocks)
-      L.grid[0] = (uint32_t)std::min<int64_t>(sv.rows, n_col_sums > 0 ? (int64_t)c->n_cus * 2 : max_grid * 2);
+      // the least block whose registers hold the row; rows up to twice of what the largest one holds
+      // still run in it, longer ones (which are read again in every phase anyway) in blocks of 256
+      constexpr int64_t kHeld = 4;   // (mirrors the instantiation)
+      if (vec && spr <= 2 * 1024 * kHeld)
+        while (L.block < 1024 && L.block * kHeld < spr) L.block *= 2;
+      // (sums over the rows: a row of partial sums per block in the workspace, so fewer blocks, and for
+      // rows that a register-resident version could hold no more than that would need)
+      const int64_t most = n_col_sums > 0 ? (spr <= 3 * 1024 ? (int64_t)c->n_cus - 1 : (int64_t)c->n_cus * 2)
+                           : L.block > 256 ? (int64_t)c->n_cus * resident_blocks(c, p, L.kid, L.block, 0) : max_grid * 2;
+      L.grid[0] = (uint32_t)std::min<int64_t>(sv.rows, most);
       fp->aux[0] = L.grid[0];   // rows of partial sums: one per block
-      pub.lanes_per_row = 256;
-      pub.slots_per_lane = (int)((spr + 255) / 256);
-      pub.reg_slots = 1;
+      pub.lanes_per_row = (int)L.block;
+      pub.slots_per_lane = (int)((spr + L.block - 1) / L.block);
+      pub.reg_slots = vec ? (int)kHeld : 1;
     } else {
       // Lanes per row G and slots per lane nv (<= 2): the pair with the least capacity G * nv that
       // holds the row, two slots per lane on a tie.  G is a power of two.  The kernels accept any
@@ -548,6 +574,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         int64_t best_cap = -1;
         for (const Shape& s : shapes)
           for (int k = max_nv; k >= 1; --k) {
+            if (k == 3 && s.block > 256 && n_col_sums > 0 && force < 0) continue;   // (see above: 12288 columns 986 us)
             const int64_t cap = (int64_t)s.G * k;
             if (cap >= slots && (best_cap < 0 || cap < best_cap)) { best_cap = cap; G = s.G; nv = k; block = s.block; }
           }
@@ -569,6 +596,14 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         choose(spr);
         tail = tail_ok && tail_fits(sv.inner / v);   // (the whole slots alone would have fitted fewer lanes than a slot has elements)
       }
+      // Blocks of 1024 threads that walk several rows: the two-slot version for wide blocks has no
+      // software pipeline, and with one or two such blocks on a CU nothing else covers the loads of
+      // the next row.  The three-slot version (which has one) runs the same rows, from eight of them per
+      // CU on (2^27 elements in rows of 16000: mixed chain 190 us / 151 with it, LayerNorm 172 / 149;
+      // 13000: 209 / 172 and 192 / 164).  Not where the two-slot version takes the ragged ends as
+      // single elements with shifted slots (12289: mixed chain 162 / 184; LayerNorm, unshifted, 224 / 200).
+      const bool piped_wide = vec && block == 1024 && n_col_sums == 0 && sv.rows >= 8ll * c->n_cus && !(tail && p.gen.row_shift_ok);
+      if (piped_wide) tail = false;
       if (tail) spr = sv.inner / v;
       nv = (int)((spr + G - 1) / G);
       // Vector slots on the 16-byte boundaries of the tensor (the elements of a row in front of the
@@ -591,7 +626,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         }
         shift = shift && off_dword;
       }
-      int inst = std::max(nv, 2);   // instantiated slots per lane: 2 or 3
+      int inst = piped_wide ? 3 : std::max(nv, 2);   // instantiated slots per lane: 2 or 3
       pub.variant = vec ? DISC_V_ROW_REG_VEC : DISC_V_ROW_REG_SCALAR;
       L.block = (uint32_t)block;
       L.plan_kind = 1;
@@ -671,10 +706,11 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       pub.reg_slots = inst;
     }
     pub.n_launches = 1;
+    if (partial_rows < fp->aux[0]) partial_rows = fp->aux[0];
     if (n_col_sums > 0) {
       // workspace: n_col_sums planes of [partial rows, inner] fp32; the second launch adds the rows up
       int64_t cells, bytes;
-      if (mul_ovf(fp->aux[0], sv.inner, &cells) || mul_ovf(cells, 4ll * n_col_sums, &bytes))
+      if (mul_ovf(partial_rows, sv.inner, &cells) || mul_ovf(cells, 4ll * n_col_sums, &bytes))
         return set_err(c, DISC_ERR_SHAPE, "workspace size overflows int64");
       pub.workspace_bytes = (size_t)bytes;
       fp->ws_off[0] = 0;

@@ -405,6 +405,8 @@ def test_single_shape_build_by_column_tiles(hctx):
     assert h.plan([16384, 1024])["kernels"][0].endswith("k_row_cols_vec_nt")
     q = h.plan([16384, 1024], inputs=[4096, 4098, 4096], outputs=[4096, 4096])
     assert q["kernels"][0].endswith("k_row_cols_vec") and q["workspace_bytes"] <= 16 << 20
+    # the workspace a caller asked for without showing its operands is enough for any alignment
+    assert q["workspace_bytes"] == hctx.workspace_bytes(h.id, [16384, 1024]) == h.plan([16384, 1024])["workspace_bytes"]
 
 
 @pytest.mark.gpu
@@ -429,7 +431,7 @@ def test_version_by_column_tiles(nt):
                 pl = hp.plan([t, h])
                 lanes.add(pl["lanes_per_row"])
                 assert pl["kernels"][0].endswith("k_row_cols_vec_nt" if nt and h % 8 == 0 else "k_row_cols_vec"), pl["kernels"]
-                assert pl["workspace_bytes"] == pl["grid"][0][0] * h * 4
+                assert pl["workspace_bytes"] >= pl["grid"][0][0] * h * 4 and pl["workspace_bytes"] == ctx.workspace_bytes(hp.id, [t, h])
                 ins = _inputs(plain, [t, h], gen)
                 got = run_gpu(hp, plain, [t, h], ins)
                 want = oracle_run(plain, [t, h], [to_oracle_input(x) for x in ins])[0]
@@ -445,5 +447,48 @@ def test_version_by_column_tiles(nt):
                 for k, (g, w) in enumerate(zip(got, want)):
                     assert_close(g, w, f"padded {dims} out{k} nt={nt}")
         assert lanes == {8, 16, 32, 64, 128, 256}
+    finally:
+        ctx.close()
+
+
+@pytest.mark.gpu
+def test_wide_rows_of_patterns_with_and_without_element_outputs():
+    """Rows beyond blocks of 256 threads: LayerNorm backward never takes three slots per lane there (two on twice the
+    lanes, else the streaming version); a pattern without per-element outputs takes the streaming version."""
+    from oracle import run as oracle_run
+    from paper_2103_05288_amd import Context
+    from tests.util import assert_close, run_gpu, to_oracle_input
+    ctx = Context(0)
+    try:
+        gen = torch.Generator().manual_seed(43)
+        pat = layernorm_backward_graph()
+        h = ctx.register(pat)
+        for dims, want_kernel in (([300, 8201], "nv2w_s"), ([270, 12289], "nv2w"), ([40, 16385], "stream_vec"), ([261, 24576], "stream_vec"),
+                                  ([5, 33000], "stream_vec")):
+            ins = _inputs(pat, dims, gen)
+            pl = h.plan(dims)
+            assert pl["kernels"][0].endswith(want_kernel), (dims, pl["kernels"])
+            got = run_gpu(h, pat, dims, ins)
+            want = oracle_run(pat, dims, [to_oracle_input(t) for t in ins])[0]
+            assert_close(got[0], want[0], f"dx {dims}")
+            x64, dy64 = ins[0].double().numpy(), ins[1].double().numpy()
+            xc = x64 - x64.mean(1, keepdims=True)
+            xhat = xc / np.sqrt((xc * xc).mean(1, keepdims=True) + 1e-5)
+            rpb = -(-dims[0] // pl["grid"][0][0])
+            _check_sum(got[1], want[1], np.abs(dy64 * xhat), rpb, f"dgamma {dims}")
+            _check_sum(got[2], want[2], np.abs(dy64), rpb, f"dbeta {dims}")
+        pat = logsumexp_with_total_and_amax()
+        h = ctx.register(pat)
+        assert h.plan([50, 6144])["variant_name"] == "row_reg_vec"
+        for dims in ([50, 6145], [600, 8191], [9, 8193], [9, 16384], [9, 16391], [513, 32768], [7, 32769], [3, 65543]):
+            ins = [(3 * torch.randn(*dims, generator=gen)).bfloat16()]
+            pl = h.plan(dims)
+            assert pl["variant_name"] == "row_stream_vec"
+            got = run_gpu(h, pat, dims, ins)
+            want = oracle_run(pat, dims, [to_oracle_input(t) for t in ins])[0]
+            assert_close(got[0], want[0], f"lse {dims}")
+            lim = (16 + -(-dims[0] // pl["grid"][0][0])) * 2.0 ** -24 * np.abs(np.asarray(want[0])).sum() + 1e-6
+            assert abs(float(got[1]) - float(want[1])) <= lim
+            assert float(got[2]) == float(want[2])
     finally:
         ctx.close()

@@ -316,3 +316,25 @@ def test_single_element_ends_in_fp32_and_f16_patterns(ctx):
             for k, (g, w) in enumerate(zip(got, want)):
                 assert_close(g, w, f"softmax {dt} dims={dims} out{k} kernel={plan['kernels'][0]}")
         assert seen_t >= 5
+
+
+@pytest.mark.parametrize("cfg_name", ["C2", "C4"])
+def test_streaming_rows_and_piped_wide_rows(ctx, cfg_name):
+    """The streaming version at the edges of what its blocks hold in registers (4 slots of 8 elements per lane,
+    blocks of up to 1024 threads; longer rows are read again; far longer ones in blocks of 256), ragged ends of
+    every kind, and blocks of 1024 threads that walk several rows."""
+    h = ctx.register(CONFIGS[cfg_name].pattern())
+    blocks = set()
+    for i, H in enumerate((24577, 24584, 24583, 32760, 32767, 32768, 32769, 32777, 40004, 65535, 65536, 65537, 70003)):
+        plan = check(ctx, cfg_name, [2 + i % 3, H], seed=300 + i, handle=h)
+        assert plan["variant_name"] == "row_stream_vec"
+        blocks.add((H > 65536, plan["block"][0][0]))
+    assert blocks == {(False, 1024), (True, 256)}
+    for H in (8, 100, 8191, 8192, 8200, 16385):      # forced: blocks of 256 to 1024 threads
+        ctx.force_variant(VARIANTS.index("row_stream_vec"))
+        try:
+            check(ctx, cfg_name, [7, H], seed=H, handle=h)
+        finally:
+            ctx.force_variant(-1)
+    plan = check(ctx, cfg_name, [2060, 12296], seed=5, handle=h)
+    assert plan["kernels"][0].endswith("k_row_vec_nv3w") and plan["lanes_per_row"] == 1024 and plan["slots_per_lane"] == 2
