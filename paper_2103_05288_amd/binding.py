@@ -87,6 +87,19 @@ EXPORTS = ("disc_create", "disc_destroy", "disc_last_error", "disc_register_patt
            "disc_graph_workspace_bytes", "disc_graph_launch")
 
 _lib = None
+_pylaunch = None        # the per-call part in C (csrc/pylaunch.cpp), loaded with the library
+_torch = None
+
+
+def _current_stream() -> int:
+    """The hipStream_t of torch's current stream on torch's current device."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    if not _torch.cuda.is_initialized():
+        return _torch.cuda.current_stream().cuda_stream
+    return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
 
 
 def lib_path() -> str:
@@ -102,6 +115,11 @@ def load_library():
     if not os.path.exists(path):
         raise ImportError(f"{path} is missing: build it with `python -m paper_2103_05288_amd.build` "
                           "(or __graft_entry__.build()); there is no CPU fallback")
+    global _pylaunch
+    try:
+        from . import _pylaunch
+    except ImportError as e:
+        raise ImportError(f"{e}: build it with `python -m paper_2103_05288_amd.build` (or __graft_entry__.build())") from None
     lib = C.CDLL(path)
     vp, i32p, i64p = C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int64)
     lib.disc_create.argtypes = [C.POINTER(vp), C.c_int]
@@ -224,17 +242,11 @@ class GraphHandle:
 
     def launch(self, dims, inputs: Sequence, outputs: Sequence, workspace=None, workspace_bytes: int = 0,
                stream: Optional[int] = None):
-        arr, n = self.ctx._dims(dims)
-        ins = (C.c_void_p * max(1, len(inputs)))(*[_ptr(t) for t in inputs])
-        outs = (C.c_void_p * max(1, len(outputs)))(*[_ptr(t) for t in outputs])
-        ws = C.c_void_p(_ptr(workspace)) if workspace is not None else C.c_void_p()
-        if workspace is not None and not workspace_bytes and hasattr(workspace, "numel"):
-            workspace_bytes = workspace.numel() * workspace.element_size()
-        if stream is None:
-            import torch
-            stream = torch.cuda.current_stream().cuda_stream
-        self.ctx._check(self.ctx.lib.disc_graph_launch(self.ctx.h, self.id, arr, n, ins, len(inputs), outs, len(outputs),
-                                                       ws, C.c_size_t(workspace_bytes), C.c_void_p(stream)))
+        ctx = self.ctx
+        rc = _pylaunch.launch(ctx._graph_launch, ctx.h.value or 0, self.id, dims, inputs, outputs, workspace, workspace_bytes,
+                              _current_stream() if stream is None else stream)
+        if rc != 0:
+            ctx._check(rc)
 
 
 def _ptr(t) -> int:
@@ -247,6 +259,8 @@ class Context:
     def __init__(self, device: int = 0):
         self.lib = load_library()
         self.h = C.c_void_p()
+        self._launch = C.cast(self.lib.disc_launch, C.c_void_p).value
+        self._graph_launch = C.cast(self.lib.disc_graph_launch, C.c_void_p).value
         rc = self.lib.disc_create(C.byref(self.h), int(device))
         if rc != 0:
             raise DiscError(rc, "disc_create failed (no such HIP device?)")
@@ -337,17 +351,10 @@ class Context:
     def launch(self, pid: int, dims, inputs: Sequence, outputs: Sequence, workspace=None,
                workspace_bytes: int = 0, stream: Optional[int] = None):
         """inputs / outputs: torch tensors (their data_ptr is passed) or raw device addresses."""
-        arr, n = self._dims(dims)
-        ins = (C.c_void_p * max(1, len(inputs)))(*[_ptr(t) for t in inputs])
-        outs = (C.c_void_p * max(1, len(outputs)))(*[_ptr(t) for t in outputs])
-        ws = C.c_void_p(_ptr(workspace)) if workspace is not None else C.c_void_p()
-        if workspace is not None and not workspace_bytes and hasattr(workspace, "numel"):
-            workspace_bytes = workspace.numel() * workspace.element_size()
-        if stream is None:
-            import torch
-            stream = torch.cuda.current_stream().cuda_stream
-        self._check(self.lib.disc_launch(self.h, pid, arr, n, ins, len(inputs), outs, len(outputs), ws,
-                                         C.c_size_t(workspace_bytes), C.c_void_p(stream)))
+        rc = _pylaunch.launch(self._launch, self.h.value or 0, pid, dims, inputs, outputs, workspace, workspace_bytes,
+                              _current_stream() if stream is None else stream)
+        if rc != 0:
+            self._check(rc)
 
     def launch_static_scratch(self, pid: int, dims, inputs: Sequence, outputs: Sequence, stream: Optional[int] = None):
         """disc_launch_static_scratch: no workspace argument, nothing allocated (the library's own

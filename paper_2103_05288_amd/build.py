@@ -9,11 +9,13 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdisc.so")
+PYLAUNCH = os.path.join(HERE, "_pylaunch" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 SOURCES = ["checker.cpp", "codegen.cpp", "runtime.cpp"]
 
 
@@ -63,6 +65,15 @@ def build_library(verbose: bool = False) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("host compile failed:\n" + r.stdout + r.stderr)
+    # the per-call argument marshalling of the Python binding (links nothing: it gets the addresses of
+    # the library's functions from the binding)
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fno-exceptions", "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(ROOT, "include"), "-o", PYLAUNCH, os.path.join(CSRC, "pylaunch.cpp")]
+    if verbose:
+        print(" ".join(cmd))
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("compile of the Python launch module failed:\n" + r.stdout + r.stderr)
     return LIB
 
 

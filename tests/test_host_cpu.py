@@ -563,3 +563,38 @@ def test_compaction_patterns_checker_and_plan(ctx):
     xx = pb.param("f32", [t])
     pb.output(pb.compact(xx, pb.op("gt", xx, pb.const(0.0), dims=[t])))
     expect("UNFUSIBLE", ctx.register, pb.build())
+
+
+# ------------------------------------------------------------------ argument marshalling of the Python launches
+def test_launch_arguments_reach_the_library_unchanged():
+    """The C marshalling of launch() against a recording function of disc_launch's type: numbers of any kind
+    as dims, tensors and raw addresses, more operands than fit its inline storage, the workspace's size taken from
+    the tensor, and errors raised by an operand."""
+    import ctypes as C
+    import numpy as np
+    import torch
+    import paper_2103_05288_amd  # noqa: F401
+    from paper_2103_05288_amd import binding
+    binding.load_library()
+    seen = {}
+    F = C.CFUNCTYPE(C.c_int, C.c_void_p, C.c_int32, C.POINTER(C.c_int64), C.c_int, C.POINTER(C.c_void_p), C.c_int,
+                    C.POINTER(C.c_void_p), C.c_int, C.c_void_p, C.c_size_t, C.c_void_p)
+
+    def record(ctx, pid, dims, n, ins, n_in, outs, n_out, ws, nbytes, stream):
+        seen.update(ctx=ctx, pid=pid, dims=dims[:n], ins=ins[:n_in], outs=outs[:n_out], ws=ws, bytes=nbytes, stream=stream)
+        return -5
+
+    fn = F(record)
+    call = lambda *a: binding._pylaunch.launch(C.cast(fn, C.c_void_p).value, *a)
+    ts = [torch.zeros(3) for _ in range(40)]
+    ws = torch.zeros(10, dtype=torch.float64)
+    assert call(4096, 7, [5, np.int64(768), 3.9, -1, 1 << 70], ts, (ts[0], 123456789), ws, 0, 99) == -5
+    assert seen["ctx"] == 4096 and seen["pid"] == 7 and seen["dims"] == [5, 768, 3, -1, 0] and seen["stream"] == 99
+    assert seen["ins"] == [t.data_ptr() for t in ts] and seen["outs"] == [ts[0].data_ptr(), 123456789]
+    assert seen["ws"] == ws.data_ptr() and seen["bytes"] == 80
+    assert call(0, 7, (), (), (), None, 0, 0) == -5 and (seen["ws"], seen["bytes"], seen["dims"], seen["ins"]) == (None, 0, [], [])
+    assert call(0, 7, (), (), (), ws, 16, 0) == -5 and seen["bytes"] == 16
+    assert call(0, 7, (), (), (), 4096, 32, 0) == -5 and (seen["ws"], seen["bytes"]) == (4096, 32)
+    for bad in ((0, 7, ["x"], (), (), None, 0, 0), (0, 7, (), [object()], (), None, 0, 0), (0, 7, 3, (), (), None, 0, 0)):
+        with pytest.raises((TypeError, ValueError)):
+            call(*bad)
