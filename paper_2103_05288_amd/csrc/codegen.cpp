@@ -1173,19 +1173,19 @@ struct Gen {
       const bool tail = an.n_col_sums == 0;
       if (v > 1 && max_threads <= 256) {
         k(name + "_e", fmt("disc::row_reg_body<Pat, %d, %d, %s, 0, true>(A, rp);", v, nv, pipe), "RowPlan");
-        if (tail) k(name + "_t", fmt("disc::row_reg_body<Pat, %d, %d, %s, 0, true, true>(A, rp);", v, nv, pipe), "RowPlan");
+        if (tail) k(name + "_t", fmt("disc::row_tail_body<Pat, %d, %d, %s>(A, rp);", v, nv, pipe), "RowPlan");
         k(name + "_nt", fmt("disc::row_reg_body<Pat, %d, %d, %s, 3, true>(A, rp);", v, nv, pipe), "RowPlan");
         if (staged) {
           k(name + "_s_e", fmt("disc::row_reg_body<PatT<1>, %d, %d, %s, 0, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
-          if (tail) k(name + "_s_t", fmt("disc::row_reg_body<PatT<1>, %d, %d, %s, 0, true, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
+          if (tail) k(name + "_s_t", fmt("disc::row_tail_body<PatT<1>, %d, %d, %s>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
           k(name + "_s_nt", fmt("disc::row_reg_body<PatT<1>, %d, %d, %s, 3, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
         }
       }
       // blocks above 256 threads: the _t version of the two-slot kernel only (the three-slot one
       // has no registers to spare under its 128-register cap)
       if (v > 1 && max_threads > 256 && nv == 2 && tail) {
-        k(name + "_t", fmt("disc::row_reg_body<Pat, %d, %d, %s, 0, true, true>(A, rp);", v, nv, pipe), "RowPlan");
-        if (staged) k(name + "_s_t", fmt("disc::row_reg_body<PatT<1>, %d, %d, %s, 0, true, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
+        k(name + "_t", fmt("disc::row_tail_body<Pat, %d, %d, %s>(A, rp);", v, nv, pipe), "RowPlan");
+        if (staged) k(name + "_s_t", fmt("disc::row_tail_body<PatT<1>, %d, %d, %s>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
       }
     };
     if (an.tmpl == DISC_TEMPLATE_COMPACT) {

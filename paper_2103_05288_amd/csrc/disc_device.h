@@ -482,7 +482,8 @@ struct RowPlan {
   int nv;       // slots per lane actually needed at this shape (<= NV of the instantiation)
   int flags;    // bit 0: the launched kernel is the version that stages row-vector operands in LDS
                 // bit 1: the slot grid is not turned from row to row
-                // bit 2: (_t versions) vector slots on the V-element boundaries of the tensor
+                // bit 2: (_t versions) vector slots on boundaries of the tensor, every (flags >> 8) elements
+                // bit 3: (_t versions) non-temporal accesses of the vector slots
   int rpb;      // rows per block = blockDim.x / G
 };
 
@@ -637,19 +638,21 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
   const i64 sbstep = rstep * A.inner;
   i64 rw = (i64)blockIdx.x * rpb + grp_w;
   i64 sbw = rw * A.inner;
-  // TAIL versions, flags bit 2: the vector slots of a row are shifted to the V-element boundaries
-  // of the TENSOR (row * inner + column a multiple of V), so that every wide access of a full-size
-  // operand whose base is aligned is aligned itself, whatever the row length: the `head` elements
-  // in front of the first boundary are single elements like those behind the last whole slot.
+  // TAIL versions, flags bit 2: the vector slots of a row are shifted to the boundaries of
+  // al = flags >> 8 elements (a power of two, V at least) of the TENSOR (row * inner + column a
+  // multiple of al), so that every wide access of a full-size operand whose base is aligned is aligned
+  // itself, whatever the row length: the `head` elements in front of the first boundary are single
+  // elements like those behind the last whole slot, one per lane (head + V - 1 lanes at most).
   // The host launches a grid that puts rows of equal alignment on a lane group (the distance
-  // between its rows times the row length is a multiple of V), so `head` is worked out once.  It is
-  // an alignment matter only: any value 0 .. V-1 addresses the row correctly.
+  // between its rows times the row length is a multiple of al), so `head` is worked out once.  It is
+  // an alignment matter only: any value 0 .. al-1 addresses the row correctly.
   int head = 0;
   if constexpr (TAIL) {
     if (rp.flags & 4) {
       const i64 r = rw + dgrp < rows ? rw + dgrp : rows - 1;
-      const int e0 = (int)(((r & (V - 1)) * (i64)(inner & (V - 1))) & (V - 1));   // (row * inner) mod V
-      head = (V - e0) & (V - 1);
+      const int al = rp.flags >> 8;
+      const int e0 = ((int)(r & (al - 1)) * (inner & (al - 1))) & (al - 1);   // (row * inner) mod al
+      head = (al - e0) & (al - 1);
     }
   }
   int col0 = lane * V;
@@ -886,6 +889,14 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
       }
     }
   }
+}
+
+// _t versions: one entry point, both kinds of access (behind a branch inside the body the compiler would
+// merge them into one plain access).
+template <class Pat, int V, int NV, bool PIPE>
+DISC_DEV void row_tail_body(const typename Pat::Args& A, const RowPlan& rp) {
+  if (rp.flags & 8) row_reg_body<Pat, V, NV, PIPE, 3, true, true>(A, rp);
+  else row_reg_body<Pat, V, NV, PIPE, 0, true, true>(A, rp);
 }
 
 // Streaming version for rows that do not fit the register-resident versions: one block per row.  The

@@ -310,6 +310,8 @@ struct FullPlan {
 // whatever kernel consumes the result; the non-temporal versions are kept for larger ones, which
 // stream through the caches anyway.
 constexpr int64_t kNonTemporalMinBytes = 64ll << 20;
+// Ragged rows with the non-temporal hint: fewest lanes per row, rows off dword boundaries / others.
+constexpr int kMinLinesG = 64, kMinLinesEvenG = 128;
 // Compaction: from this many tiles on (2^17 i32 elements), two launches instead of three: the blocks of
 // the scatter launch add up the counts in front of them by themselves (14 us a call against 15-16 at
 // 2^17 .. 2^20 elements, where the launches are what is paid for).  Most chunks of a
@@ -615,16 +617,28 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // TB/s) and lose 1-6 % when shifted (more single elements); rows that start off a dword
       // boundary (odd lengths of 2-byte elements) run at 4.90 unshifted and 4.95-5.01 shifted.
       // So the shift is for rows that start off dword boundaries only.
+      // Large launches, 64 lanes per row and more (128 for rows on dword boundaries): non-temporal accesses,
+      // with the slots on boundaries of whole 128-byte lines of the tensor -- of its one-byte operands too,
+      // with 256 lanes; of 64 bytes with 64 -- which leaves more single elements, one to a lane.  On
+      // 16-byte boundaries alone the hint loses (the lines between two wavefronts' accesses are written
+      // in two parts), on whole lines it gains what it gains on aligned rows.  Mixed chain, 2^28 elements,
+      // without and with: rows of 5739 272 / 253 us, 2047 272 / 249, 4095 272 / 248, 8191 250 / 237,
+      // 1501 261 / 254, 1023 261 / 258, 4098 260 / 251, 5740 263 / 245; with 32 lanes (515) 269 / 289.
       bool shift = tail && p.gen.row_shift_ok && G >= 2 * v - 2 && c->row_shift != 0;
+      int align = v;                        // elements
+      bool lines = shift && G >= kMinLinesG && c->row_nt != 0 && (c->row_nt > 0 || sv.alg_bytes >= kNonTemporalMinBytes);
       if (shift) {
         bool off_dword = false;
         for (const Access& a : an.accesses) {
           if (a.kind != ACC_FULL || a.src_value >= 0) continue;
           const void* ptr = a.is_output ? (outputs ? outputs[a.slot] : nullptr) : (inputs ? inputs[a.slot] : nullptr);
           if (reinterpret_cast<uintptr_t>(ptr) % (uintptr_t)(v * dtype_bytes(a.dtype)) != 0) shift = false;
+          if (reinterpret_cast<uintptr_t>(ptr) % 128 != 0) lines = false;
           if (dtype_bytes(a.dtype) >= 2 && (sv.inner * dtype_bytes(a.dtype)) % 4 != 0) off_dword = true;
         }
-        shift = shift && off_dword;
+        lines = lines && shift && (off_dword || G >= kMinLinesEvenG);
+        shift = shift && (off_dword || lines);
+        if (lines) align = std::min(128, G / 2);
       }
       int inst = piped_wide ? 3 : std::max(nv, 2);   // instantiated slots per lane: 2 or 3
       pub.variant = vec ? DISC_V_ROW_REG_VEC : DISC_V_ROW_REG_SCALAR;
@@ -691,12 +705,12 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       if (shift) {
         // rows of one alignment per lane group: (distance between its rows) x (row length) must be a
         // multiple of the vector width
-        int64_t m = v / std::gcd<int64_t>(sv.inner % v, v);
+        int64_t m = align / std::gcd<int64_t>(sv.inner % align, align);
         m /= std::gcd<int64_t>(m, rpb);
         if (grid >= m) grid -= grid % m;
         else shift = false;
       }
-      if (shift) L.rp.flags |= 4;
+      if (shift) L.rp.flags |= 4 | align << 8 | (lines ? 8 : 0);
       else if (grid > 2 && grid % 2 == 0 && grid < ngroups) grid -= 1;
       L.grid[0] = (uint32_t)grid;
       // rows of partial sums: one per block of 256 threads, one per lane group of a wider block

@@ -338,3 +338,38 @@ def test_streaming_rows_and_piped_wide_rows(ctx, cfg_name):
             ctx.force_variant(-1)
     plan = check(ctx, cfg_name, [2060, 12296], seed=5, handle=h)
     assert plan["kernels"][0].endswith("k_row_vec_nv3w") and plan["lanes_per_row"] == 1024 and plan["slots_per_lane"] == 2
+
+
+def test_ragged_rows_on_whole_lines():
+    """Ragged rows with non-temporal accesses: vector slots on boundaries of 32, 64 or 128 elements of the tensor, up to
+    127 + 7 single elements per row.  Odd and even lengths, a last slot that ends exactly at the row's end, the least
+    and the most single elements, two rows per block; bases off a line fall back to 16-byte boundaries; too few rows
+    for a grid of one alignment per lane group leave the slots where they are."""
+    from paper_2103_05288_amd import Context
+    c = Context(0)
+    c.test_option("non_temporal", 1)
+    try:
+        h = c.register(CONFIGS["C4"].pattern())
+        for H, T, al in ((777, 1100, 32), (1023, 700, 32), (1537, 400, 32), (1601, 600, 64), (2046, 515, 64), (2047, 515, 64), (3001, 390, 64),
+                         (3073, 300, 128), (4095, 300, 128), (4097, 390, 128), (5739, 260, 128), (6150, 257, 128), (8185, 259, 128)):
+            plan = check(c, "C4", [T, H], seed=H, handle=h)
+            rpb = plan["block"][0][0] // plan["lanes_per_row"]
+            assert plan["kernels"][0].endswith("_t") and plan["grid"][0][0] * rpb * H % al == 0, (H, plan["grid"])
+        check(c, "C4", [20, 4095], seed=6, handle=h)
+        cfg = CONFIGS["C4"]
+        pat, dims = cfg.pattern(), [260, 4095]
+        ins = cfg.inputs(dims, seed=8)
+        for shift in (8, 1):                       # 16 bytes (bf16) or one element past a line
+            dev = [torch.cat([torch.zeros(shift, dtype=t.dtype), t.reshape(-1)]).cuda()[shift:] for t in ins]
+            out = torch.full((dims[0] * dims[1] + 64,), float("nan"), dtype=torch.bfloat16, device="cuda")
+            h.launch(dims, dev, [out[32:]])
+            torch.cuda.synchronize()
+            want = oracle_run(pat, dims, [to_oracle_input(t) for t in ins])[0][0]
+            assert_close(out[32:-32].reshape(dims).cpu(), want, f"base shifted by {shift}")
+            assert bool(torch.isnan(out[:32]).all()) and bool(torch.isnan(out[-32:]).all())
+        h1 = c.register(CONFIGS["C1"].pattern())   # a row-group operand read at the shifted columns
+        for S in (777, 1023):
+            plan = check(c, "C1", [1, 2, S], seed=S, handle=h1)
+            assert plan["lanes_per_row"] == 64 and plan["kernels"][0].endswith("_t")
+    finally:
+        c.close()
