@@ -373,3 +373,17 @@ def test_ragged_rows_on_whole_lines():
             assert plan["lanes_per_row"] == 64 and plan["kernels"][0].endswith("_t")
     finally:
         c.close()
+
+
+def test_short_ragged_rows_on_eight_lanes(ctx):
+    """Ragged rows of 10 to 12 slots: four lanes and a ragged last slot when there are few of them, eight lanes and single
+    elements (up to seven, one to a lane) from 1024 rows on."""
+    h = ctx.register(CONFIGS["C4"].pattern())
+    for H in (73, 78, 79, 85, 93, 95):
+        few, many = h.plan([1023, H]), h.plan([1024, H])
+        assert few["lanes_per_row"] == 4 and not few["kernels"][0].endswith("_t")
+        assert many["lanes_per_row"] == 8 and many["kernels"][0].endswith("_t")
+        check(ctx, "C4", [1031, H], seed=H, handle=h)
+    h1 = ctx.register(CONFIGS["C1"].pattern())
+    for S in (73, 77, 93):
+        assert check(ctx, "C1", [4, 4, S], seed=S, handle=h1)["lanes_per_row"] == 8
