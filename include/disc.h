@@ -178,9 +178,10 @@ typedef enum {
                                    transpose (what an op graph falls back to for such an op)    */
   DISC_TEMPLATE_COMPACT = 4     /* loop fusion over rank-1 values whose outputs are compacted by a
                                    predicate computed in the same pattern (DISC_COMPACT and
-                                   friends): per-block counts, a fixed-order scan of the counts, a
-                                   scatter -- three launches, no atomics, the element count written
-                                   to device memory                                              */
+                                   friends): per-block counts, a fixed-order scan of the counts (short
+                                   inputs; the blocks of the scatter add up the counts themselves
+                                   otherwise), a scatter -- two or three launches, no atomics, the
+                                   element count written to device memory                         */
 } disc_template;
 
 typedef struct {
@@ -214,7 +215,7 @@ typedef enum {
   DISC_V_TRANSPOSE_TILE,    /* batched 2-D transpose through a 64 x 64 tile in LDS              */
   DISC_V_COL_2STAGE_VEC,    /* column reduce: partial -> finish + epilogue in one kernel (2 launches) */
   DISC_V_COL_2STAGE_SCALAR,
-  DISC_V_COMPACT_VEC,       /* compaction: count -> scan -> scatter, vector loads               */
+  DISC_V_COMPACT_VEC,       /* compaction: count (-> scan) -> scatter, vector loads             */
   DISC_V_COMPACT_SCALAR,
   DISC_V_COUNT
 } disc_variant;
