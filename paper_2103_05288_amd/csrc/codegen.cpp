@@ -1155,6 +1155,11 @@ struct Gen {
     // the wide register-resident row kernels come in a second version (suffix _s) that reads
     // the row-vector operands from their LDS copy
     const bool staged = !staged_accesses().empty();
+    // (slots that cannot be shifted never take the non-temporal body)
+    auto tail_body = [&](const char* pat, int v, int nv, const char* pipe) {
+      return row_shift_ok() ? fmt("disc::row_tail_body<%s, %d, %d, %s>(A, rp);", pat, v, nv, pipe)
+                            : fmt("disc::row_reg_body<%s, %d, %d, %s, 0, true, true>(A, rp);", pat, v, nv, pipe);
+    };
     auto krow = [&](const std::string& name, int v, int nv) {
       if (v > 1 && row_cols_ok()) return;   // the version by column tiles takes every such launch
       // the two-slot version for blocks above 256 threads runs without the software pipeline: the
@@ -1173,19 +1178,19 @@ struct Gen {
       const bool tail = an.n_col_sums == 0;
       if (v > 1 && max_threads <= 256) {
         k(name + "_e", fmt("disc::row_reg_body<Pat, %d, %d, %s, 0, true>(A, rp);", v, nv, pipe), "RowPlan");
-        if (tail) k(name + "_t", fmt("disc::row_tail_body<Pat, %d, %d, %s>(A, rp);", v, nv, pipe), "RowPlan");
+        if (tail) k(name + "_t", tail_body("Pat", v, nv, pipe), "RowPlan");
         k(name + "_nt", fmt("disc::row_reg_body<Pat, %d, %d, %s, 3, true>(A, rp);", v, nv, pipe), "RowPlan");
         if (staged) {
           k(name + "_s_e", fmt("disc::row_reg_body<PatT<1>, %d, %d, %s, 0, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
-          if (tail) k(name + "_s_t", fmt("disc::row_tail_body<PatT<1>, %d, %d, %s>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
+          if (tail) k(name + "_s_t", tail_body("PatT<1>", v, nv, pipe), "RowPlan", "PatT<1>");
           k(name + "_s_nt", fmt("disc::row_reg_body<PatT<1>, %d, %d, %s, 3, true>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
         }
       }
       // blocks above 256 threads: the _t version of the two-slot kernel only (the three-slot one
       // has no registers to spare under its 128-register cap)
       if (v > 1 && max_threads > 256 && nv == 2 && tail) {
-        k(name + "_t", fmt("disc::row_tail_body<Pat, %d, %d, %s>(A, rp);", v, nv, pipe), "RowPlan");
-        if (staged) k(name + "_s_t", fmt("disc::row_tail_body<PatT<1>, %d, %d, %s>(A, rp);", v, nv, pipe), "RowPlan", "PatT<1>");
+        k(name + "_t", tail_body("Pat", v, nv, pipe), "RowPlan");
+        if (staged) k(name + "_s_t", tail_body("PatT<1>", v, nv, pipe), "RowPlan", "PatT<1>");
       }
     };
     if (an.tmpl == DISC_TEMPLATE_COMPACT) {
