@@ -602,7 +602,8 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // enough of them, eight lanes that take the ragged ends as single elements are faster although a
       // third of them is idle (mixed chain, 300007 rows of 77 / 85 / 93 / 95: 36.8 / 39.8 / 42.7 / 44.2 us on
       // four lanes, 35.3 / 36.7 / 38.6 / 39.1 on eight; 20000 rows of 93: 6.0 / 5.0).  Rows of fewer slots
-      // would gain as well (65: 29.1 / 23.7), but a caller may count on one version per row length up to there.
+      // would gain as well (65: 29.1 / 23.7); their schedule is one that tests/test_host_cpu.py fixes whatever
+      // the number of rows, so they keep it.
       if (tail_ok && !tail && G == 4 && v == 8 && sv.inner / v > 8 && sv.rows >= 4ll * c->n_cus) {
         G = 8;
         tail = true;
