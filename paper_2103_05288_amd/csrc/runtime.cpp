@@ -302,6 +302,7 @@ struct FullPlan {
   int64_t nslots = 0, spr = 0;
   int64_t aux[4] = {0, 0, 0, 0};
   size_t ws_off[2] = {0, 0};
+  size_t ws_need = 0;        // what this launch uses; pub.workspace_bytes covers every alignment of the operands
 };
 
 // Loop-fusion launch geometry for an iteration space [rows, inner]; shared by loop patterns and
@@ -510,7 +511,9 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     fp->nslots = 0;
     LaunchRec& L = fp->launches[0];
     L.block = 256;
-    int64_t partial_rows = 0;                        // rows of partial sums the workspace holds
+    // Workspace that covers the launch whatever the alignment of the operands, which a caller does not show
+    // when it asks for the size: rows of partial sums, and blocks of the row kernel.
+    int64_t most_rows = 0, most_blocks = 0;
     int TX = 8;                                      // lanes along the columns, version by column tiles
     while (TX < 256 && TX < spr) TX *= 2;
     const int64_t col_tiles = (spr + TX - 1) / TX;
@@ -535,7 +538,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         return std::max<int64_t>(1, std::min<int64_t>(g, DISC_STATIC_SCRATCH_BYTES / (4ll * n_col_sums * sv.inner)));
       };
       const int64_t grid = blocks_per_tile(nt ? 2 : 3);
-      partial_rows = blocks_per_tile(3);
+      most_rows = blocks_per_tile(3);
       L.grid[0] = (uint32_t)grid;
       L.grid[1] = (uint32_t)col_tiles;
       fp->aux[0] = grid;        // rows of partial sums
@@ -635,6 +638,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // without and with: rows of 5739 272 / 253 us, 2047 272 / 249, 4095 272 / 248, 8191 250 / 237,
       // 1501 261 / 254, 1023 261 / 258, 4098 260 / 251, 5740 263 / 245; with 32 lanes (515) 269 / 289.
       bool shift = tail && p.gen.row_shift_ok && G >= 2 * v - 2 && c->row_shift != 0;
+      const bool may_shift = shift;         // with operands of the right alignment
       int align = v;                        // elements
       bool lines = shift && G >= kMinLinesG && c->row_nt != 0 && (c->row_nt > 0 || sv.alg_bytes >= kNonTemporalMinBytes);
       if (shift) {
@@ -651,6 +655,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         if (lines) align = std::min(128, G / 2);
       }
       int inst = piped_wide ? 3 : std::max(nv, 2);   // instantiated slots per lane: 2 or 3
+      int kid_aligned = 0, kid_any = 0;     // kernel for aligned operands, and for others
       pub.variant = vec ? DISC_V_ROW_REG_VEC : DISC_V_ROW_REG_SCALAR;
       L.block = (uint32_t)block;
       L.plan_kind = 1;
@@ -681,18 +686,18 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         if (even && !tail && c->row_nt != 0) {
           nt = c->row_nt > 0;
           if (c->row_nt < 0 && sv.inner >= 128 && sv.alg_bytes >= kNonTemporalMinBytes) {
-            nt = true;
             bool whole_lines = true;
-            for (const Access& a : an.accesses) {
-              if (a.kind != ACC_FULL) continue;
-              const void* ptr = a.is_output ? (outputs ? outputs[a.slot] : nullptr) : (inputs ? inputs[a.slot] : nullptr);
-              if (reinterpret_cast<uintptr_t>(ptr) % 16 != 0) nt = false;
-              if ((sv.inner * dtype_bytes(a.dtype)) % 128 != 0) whole_lines = false;
-            }
-            if (!whole_lines && sv.inner < 512) nt = false;
+            for (const Access& a : an.accesses)
+              if (a.kind == ACC_FULL && (sv.inner * dtype_bytes(a.dtype)) % 128 != 0) whole_lines = false;
+            nt = whole_lines || sv.inner >= 512;
           }
         }
-        L.kid = K_ROW_BASE + row_kernel_index(!vec, inst, wide_version, stage, nt ? 1 : tail ? 3 : even ? 2 : 0);
+        auto version = [&](bool hint) {
+          return K_ROW_BASE + row_kernel_index(!vec, inst, wide_version, stage, hint ? 1 : tail ? 3 : even ? 2 : 0);
+        };
+        kid_aligned = version(nt);
+        L.kid = nt && c->row_nt < 0 && !full_aligned() ? version(false) : kid_aligned;
+        kid_any = nt && c->row_nt < 0 ? version(false) : kid_aligned;
       }
       // grid-stride over row groups: a small whole number of rounds of the blocks the chip holds
       // at once.  Measured: with plenty of rows, blocks of one wavefront-quad do best with three
@@ -702,11 +707,17 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // the staging of the row vectors)
       const int rpb = (int)L.block / G;
       const int64_t ngroups = (sv.rows + rpb - 1) / rpb;
-      const int64_t held = (int64_t)c->n_cus * resident_blocks(c, p, L.kid, L.block, L.dyn_lds);
-      // (with sums over the rows every block writes a row of partial sums per wavefront: one round)
-      const int rounds = c->row_rounds > 0 ? c->row_rounds
-                         : (L.block > 256 || n_col_sums > 0 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(3, ngroups / (held * 4))));
-      int64_t grid = std::min<int64_t>(ngroups, held * rounds);
+      auto blocks_of = [&](int kid) {
+        const int64_t held = (int64_t)c->n_cus * resident_blocks(c, p, kid, L.block, L.dyn_lds);
+        // (with sums over the rows every block writes a row of partial sums per wavefront: one round)
+        const int rounds = c->row_rounds > 0 ? c->row_rounds
+                           : (L.block > 256 || n_col_sums > 0 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(3, ngroups / (held * 4))));
+        return std::min<int64_t>(ngroups, held * rounds);
+      };
+      auto odd = [&](int64_t g) { return g > 2 && g % 2 == 0 && g < ngroups ? g - 1 : g; };
+      int64_t grid = blocks_of(L.kid);
+      for (const int kid : {kid_aligned, kid_any})
+        if (n_col_sums + n_row_reds > 0) most_blocks = std::max(most_blocks, may_shift ? blocks_of(kid) : odd(blocks_of(kid)));
       // An odd grid: with an even one a block of one row per iteration would only ever see even or
       // only odd rows, and when the row length is odd every other row starts two bytes off a
       // dword -- half of the blocks would run ~20 % slower all the time and set the kernel's time
@@ -721,37 +732,42 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         else shift = false;
       }
       if (shift) L.rp.flags |= 4 | align << 8 | (lines ? 8 : 0);
-      else if (grid > 2 && grid % 2 == 0 && grid < ngroups) grid -= 1;
+      else grid = odd(grid);
       L.grid[0] = (uint32_t)grid;
       // rows of partial sums: one per block of 256 threads, one per lane group of a wider block
-      fp->aux[0] = grid * (L.block <= 256 ? 1 : (int64_t)L.block / std::max(G, 64));
+      const int64_t per_block = L.block <= 256 ? 1 : (int64_t)L.block / std::max(G, 64);
+      fp->aux[0] = grid * per_block;
+      most_rows = most_blocks * per_block;
       pub.lanes_per_row = G;
       pub.slots_per_lane = nv;
       pub.reg_slots = inst;
     }
     pub.n_launches = 1;
-    if (partial_rows < fp->aux[0]) partial_rows = fp->aux[0];
+    if (n_col_sums == 0) fp->aux[0] = 0;
+    if (n_row_reds > 0) fp->aux[1] = L.grid[0];
+    most_rows = std::max(most_rows, fp->aux[0]);
+    most_blocks = std::max<int64_t>(most_blocks, L.grid[0]);
+    // workspace: n_col_sums planes of [partial rows, inner] fp32, which the second launch adds up; behind
+    // them one partial result per block and reduction of per-row values, folded by a last launch of one block
+    auto layout = [&](int64_t partial_rows, int64_t blocks, size_t* reds_at, size_t* total) {
+      int64_t cells, bytes = 0;
+      if (n_col_sums > 0 && (mul_ovf(partial_rows, sv.inner, &cells) || mul_ovf(cells, 4ll * n_col_sums, &bytes))) return false;
+      *reds_at = ((size_t)bytes + 255) / 256 * 256;
+      *total = n_row_reds > 0 ? *reds_at + (size_t)n_row_reds * (size_t)blocks * 4 : (size_t)bytes;
+      return true;
+    };
+    size_t unused;
+    if (!layout(fp->aux[0], L.grid[0], &fp->ws_off[1], &fp->ws_need) || !layout(most_rows, most_blocks, &unused, &pub.workspace_bytes))
+      return set_err(c, DISC_ERR_SHAPE, "workspace size overflows int64");
     if (n_col_sums > 0) {
-      // workspace: n_col_sums planes of [partial rows, inner] fp32; the second launch adds the rows up
-      int64_t cells, bytes;
-      if (mul_ovf(partial_rows, sv.inner, &cells) || mul_ovf(cells, 4ll * n_col_sums, &bytes))
-        return set_err(c, DISC_ERR_SHAPE, "workspace size overflows int64");
-      pub.workspace_bytes = (size_t)bytes;
       fp->ws_off[0] = 0;
       LaunchRec& L1 = fp->launches[1];
       L1.kid = K_COLSUM_FINISH;
       L1.block = 256;
       L1.grid[0] = (uint32_t)std::min<int64_t>((sv.inner + 15) / 16, max_grid * 4);   // 16 columns per block
       pub.n_launches = 2;
-    } else {
-      fp->aux[0] = 0;
     }
     if (n_row_reds > 0) {
-      // one partial result per block and reduction behind the column-sum planes; a last launch of
-      // one block folds them
-      fp->aux[1] = L.grid[0];
-      fp->ws_off[1] = (pub.workspace_bytes + 255) / 256 * 256;
-      pub.workspace_bytes = fp->ws_off[1] + (size_t)n_row_reds * (size_t)L.grid[0] * 4;
       LaunchRec& Lr = fp->launches[pub.n_launches++];
       Lr.kid = K_ROWRED_FINISH;
       Lr.block = 1024;
@@ -1418,9 +1434,10 @@ int disc_test_option(disc_ctx* ctx, int option, int value) {
   DISC_CATCH(ctx)
 }
 
-int disc_launch(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, const void* const* inputs, int n_in,
-                void* const* outputs, int n_out, void* workspace, size_t workspace_bytes, void* hip_stream) {
-  DISC_TRY
+// own_need: the workspace has to hold what this launch uses (the static scratch array), not what
+// disc_workspace_bytes gives for operands of any alignment (a caller's workspace).
+static int launch_impl(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, const void* const* inputs, int n_in,
+                       void* const* outputs, int n_out, void* workspace, size_t workspace_bytes, void* hip_stream, bool own_need) {
   const int64_t t0 = now_ns();
   Pattern* p = get_pattern(ctx, id);
   if (!p) return set_err(ctx, DISC_ERR_INVALID_ARG, "bad pattern id");
@@ -1445,7 +1462,8 @@ int disc_launch(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, cons
     if (!inputs[i]) return set_err(ctx, DISC_ERR_INVALID_ARG, "null input pointer");
   for (int i = 0; i < n_out; ++i)
     if (!outputs[i]) return set_err(ctx, DISC_ERR_INVALID_ARG, "null output pointer");
-  if (fp.pub.workspace_bytes > 0 && (!workspace || workspace_bytes < fp.pub.workspace_bytes))
+  const size_t need = own_need && fp.ws_need > 0 ? fp.ws_need : fp.pub.workspace_bytes;
+  if (need > 0 && (!workspace || workspace_bytes < need))
     return set_err(ctx, DISC_ERR_WORKSPACE, "workspace missing or too small");
 
   alignas(16) unsigned char buf[kArgBufBytes];
@@ -1473,8 +1491,40 @@ int disc_launch(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, cons
   if (fp.pub.variant >= 0 && fp.pub.variant < DISC_V_COUNT) ctx->stats.variant_count[fp.pub.variant]++;
   ctx->stats.host_launch_ns += now_ns() - t0;
   return DISC_OK;
+}
+
+int disc_launch(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, const void* const* inputs, int n_in,
+                void* const* outputs, int n_out, void* workspace, size_t workspace_bytes, void* hip_stream) {
+  DISC_TRY
+  return launch_impl(ctx, id, dims, n_dims, inputs, n_in, outputs, n_out, workspace, workspace_bytes, hip_stream, false);
   DISC_CATCH(ctx)
 }
+
+}  // extern "C"
+namespace disc {
+// scratch.hip: what a launch with these operands uses, and the launch itself, with the static array
+int launch_need(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, const void* const* inputs, int n_in,
+                void* const* outputs, int n_out, size_t* need) {
+  DISC_TRY
+  Pattern* p = get_pattern(ctx, id);
+  if (!p) return set_err(ctx, DISC_ERR_INVALID_ARG, "bad pattern id or null output");
+  // (the launch itself refuses operands that do not match the pattern)
+  const bool match = n_in == p->an.n_inputs && n_out == p->an.n_outputs;
+  FullPlan fp;
+  int rc = make_plan(ctx, *p, dims, n_dims, ctx->force_variant, match ? inputs : nullptr, match ? outputs : nullptr, &fp);
+  if (rc) return rc;
+  *need = fp.ws_need > 0 ? fp.ws_need : fp.pub.workspace_bytes;
+  return DISC_OK;
+  DISC_CATCH(ctx)
+}
+int launch_scratch(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, const void* const* inputs, int n_in,
+                   void* const* outputs, int n_out, void* scratch, size_t bytes, void* hip_stream) {
+  DISC_TRY
+  return launch_impl(ctx, id, dims, n_dims, inputs, n_in, outputs, n_out, scratch, bytes, hip_stream, true);
+  DISC_CATCH(ctx)
+}
+}  // namespace disc
+extern "C" {
 
 int disc_get_stats(disc_ctx* ctx, disc_stats_t* out) {
   DISC_TRY

@@ -18,6 +18,10 @@ namespace disc {
 // runtime.cpp
 int context_device(const disc_ctx* ctx);
 int context_fail(disc_ctx* ctx, int code, const char* msg);
+int launch_need(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, const void* const* inputs, int n_in,
+                void* const* outputs, int n_out, size_t* need);
+int launch_scratch(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, const void* const* inputs, int n_in,
+                   void* const* outputs, int n_out, void* scratch, size_t bytes, void* hip_stream);
 }  // namespace disc
 
 namespace {
@@ -66,9 +70,9 @@ extern "C" int disc_launch_static_scratch(disc_ctx* ctx, int32_t id, const int64
   if (!ctx) return DISC_ERR_INVALID_ARG;
   const int device = disc::context_device(ctx);
   if (device < 0) return disc::context_fail(ctx, DISC_ERR_INVALID_ARG, "host-only context cannot launch");
-  // what the call needs, from the same host planning disc_launch does (no allocation in there)
+  // what this very call needs, from the same host planning disc_launch does (no allocation in there)
   size_t need = 0;
-  int rc = disc_workspace_bytes(ctx, id, dims, n_dims, &need);
+  int rc = disc::launch_need(ctx, id, dims, n_dims, inputs, n_in, outputs, n_out, &need);
   if (rc != DISC_OK) return rc;
   if (need > (size_t)DISC_STATIC_SCRATCH_BYTES)
     return disc::context_fail(ctx, DISC_ERR_WORKSPACE,
@@ -83,6 +87,6 @@ extern "C" int disc_launch_static_scratch(disc_ctx* ctx, int32_t id, const int64
   // The kernels take `ptr` as their workspace argument.  Nothing in the array has to start at zero:
   // every cell a kernel reads was written earlier in the same call (no atomics, no counters), so
   // what an earlier call left behind is never seen.
-  return disc_launch(ctx, id, dims, n_dims, inputs, n_in, outputs, n_out, ptr, need > 0 ? (size_t)DISC_STATIC_SCRATCH_BYTES : 0,
-                     hip_stream);
+  return disc::launch_scratch(ctx, id, dims, n_dims, inputs, n_in, outputs, n_out, ptr,
+                              need > 0 ? (size_t)DISC_STATIC_SCRATCH_BYTES : 0, hip_stream);
 }

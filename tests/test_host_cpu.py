@@ -598,3 +598,36 @@ def test_launch_arguments_reach_the_library_unchanged():
     for bad in ((0, 7, ["x"], (), (), None, 0, 0), (0, 7, (), [object()], (), None, 0, 0), (0, 7, 3, (), (), None, 0, 0)):
         with pytest.raises((TypeError, ValueError)):
             call(*bad)
+
+
+# ------------------------------------------------------------------ workspace size and operand alignment
+def test_workspace_size_covers_every_alignment(ctx):
+    """The workspace size is asked for without showing the operands, and launches with operands on any
+    boundary then run in it: what a plan needs must not depend on the pointers (the grid, and with it the partial
+    results, does).  Element outputs with a sum of per-row values, log-sum-exp, sums over the rows."""
+    from workloads.extras import layernorm_backward_graph, logsumexp_with_total_and_amax
+    pb = PatternBuilder("centred_with_total")
+    t, h = pb.dims(2)
+    v = pb.cast(pb.param("bf16", [t, h]), "f32")
+    for _ in range(6):
+        v = pb.op("add", v, pb.cast(pb.param("bf16", [t, h]), "f32"))
+    m = pb.reduce("max", v, 1)
+    pb.output(pb.cast(pb.op("sub", v, pb.broadcast(m, [t, h], [0])), "bf16"))
+    pb.output(pb.reduce("sum", m, 0))
+    rng = __import__("random").Random(5)
+    shapes = [[1020, 5740], [1023, 5739], [110, 4183], [16384, 1024], [3000, 300], [700, 511]]
+    shapes += [[rng.randint(1, 6000), rng.randint(1, 12300)] for _ in range(250)]
+    grids = set()
+    for pat in (pb.build(), logsumexp_with_total_and_amax(), layernorm_backward_graph()):
+        hd = ctx.register(pat)
+        for dims in shapes:
+            asked = ctx.workspace_bytes(hd.id, dims)
+            for off in (0, 2, 16):
+                at = lambda n: [4096 * (i + 1) + off for i in range(n)]
+                p = hd.plan(dims, inputs=at(hd.info["n_inputs"]), outputs=at(hd.info["n_outputs"]))
+                assert p["workspace_bytes"] == asked, (dims, off)
+                n_reds = 1 if pat.name == "centred_with_total" else 2
+                if pat.name != "ln_bwd":                     # one partial result per block and reduction
+                    assert asked >= 4 * n_reds * p["grid"][0][0]
+                grids.add((tuple(dims), off, p["grid"][0][0]))
+    assert len({g[0] for g in grids}) < len({(g[0], g[2]) for g in grids})     # (the pointers do change grids)

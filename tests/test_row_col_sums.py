@@ -492,3 +492,37 @@ def test_wide_rows_of_patterns_with_and_without_element_outputs():
             assert float(got[2]) == float(want[2])
     finally:
         ctx.close()
+
+
+@pytest.mark.gpu
+def test_misaligned_operands_fit_the_workspace_asked_for():
+    """A launch whose operands lie off the boundaries that the plan without pointers assumes runs another grid; the
+    workspace asked for beforehand is enough for it."""
+    from oracle import run as oracle_run
+    from paper_2103_05288_amd import Context
+    from tests.util import assert_close, to_oracle_input
+    ctx = Context(0)
+    try:
+        pat = logsumexp_with_total_and_amax()
+        h = ctx.register(pat)
+        gen = torch.Generator().manual_seed(3)
+        for dims in ([110, 4183], [1020, 5740]):
+            x = torch.randn(*dims, generator=gen).bfloat16()
+            want = oracle_run(pat, dims, [to_oracle_input(x)])[0]
+            n = dims[0] * dims[1]
+            for off in (0, 1, 8):                       # elements past a 256-byte boundary
+                dev = torch.zeros(n + 64, dtype=torch.bfloat16, device="cuda")
+                dev[off : off + n] = x.reshape(-1).cuda()
+                outs = [torch.full((dims[0],), float("nan"), device="cuda")] + [torch.full((), float("nan"), device="cuda") for _ in range(2)]
+                ws = torch.empty(ctx.workspace_bytes(h.id, dims), dtype=torch.uint8, device="cuda")
+                h.launch(dims, [dev[off:]], outs, workspace=ws)
+                torch.cuda.synchronize()
+                assert_close(outs[0].cpu(), want[0], f"lse {dims} off={off}")
+                lim = 2.0 ** -20 * np.abs(np.asarray(want[0])).sum()
+                assert abs(float(outs[1]) - float(want[1])) <= lim and float(outs[2]) == float(want[2])
+                outs2 = [torch.full_like(o, float("nan")) for o in outs]
+                ctx.launch_static_scratch(h.id, dims, [dev[off:]], outs2)
+                torch.cuda.synchronize()
+                assert all(torch.equal(a, b) for a, b in zip(outs, outs2))
+    finally:
+        ctx.close()
