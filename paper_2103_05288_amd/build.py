@@ -66,7 +66,12 @@ def build_library(verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError("host compile failed:\n" + r.stdout + r.stderr)
     # the per-call argument marshalling of the Python binding (links nothing: it gets the addresses of
-    # the library's functions from the binding)
+    # the library's functions from the binding); without the interpreter's headers the binding does it
+    if os.path.exists(PYLAUNCH):
+        os.remove(PYLAUNCH)
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        print("no Python.h: launches from Python go through ctypes (5 us a call more)")
+        return LIB
     cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fno-exceptions", "-I", sysconfig.get_paths()["include"],
            "-I", os.path.join(ROOT, "include"), "-o", PYLAUNCH, os.path.join(CSRC, "pylaunch.cpp")]
     if verbose:

@@ -35,13 +35,26 @@ bool call_u64(PyObject* x, PyObject* method, uint64_t* out) {
   return ok;
 }
 
+// after a failed call_u64: the object has no such method (the error is cleared), or the method failed
+bool lacks(PyObject* x, PyObject* method) {
+  if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return false;
+  PyObject *type, *value, *trace;
+  PyErr_Fetch(&type, &value, &trace);
+  if (PyObject_HasAttr(x, method)) {
+    PyErr_Restore(type, value, trace);
+    return false;
+  }
+  Py_XDECREF(type);
+  Py_XDECREF(value);
+  Py_XDECREF(trace);
+  return true;
+}
+
 // the device address of a tensor (anything with data_ptr()), or a raw address
 bool as_address(PyObject* x, uint64_t* out) {
   if (PyLong_CheckExact(x)) return as_u64(x, out);
   if (call_u64(x, s_data_ptr, out)) return true;
-  if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return false;
-  PyErr_Clear();
-  return as_u64(x, out);
+  return lacks(x, s_data_ptr) && as_u64(x, out);
 }
 
 // A Python sequence as an array of 8-byte words; up to kInline of them need no allocation.
@@ -82,16 +95,17 @@ struct Words {
 typedef int (*launch_fn)(void*, int32_t, const int64_t*, int, const void* const*, int, void* const*, int, void*, size_t, void*);
 
 // launch(function address, ctx address, id, dims, inputs, outputs, workspace or None, workspace
-// bytes (0: the size of the workspace tensor), stream) -> status.  The GIL is released during the call.
+// bytes (0 or None: the size of the workspace tensor), stream) -> status.  The GIL is released during the call.
 PyObject* launch(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   if (n_args != 9) {
     PyErr_SetString(PyExc_TypeError, "launch takes 9 arguments");
     return nullptr;
   }
-  uint64_t fn, ctx, id, ws = 0, bytes, stream;
+  uint64_t fn, ctx, id, ws = 0, bytes = 0, stream;
+  bool no_bytes = a[7] == Py_None;
   Words dims, ins, outs;
   if (!as_u64(a[0], &fn) || !as_u64(a[1], &ctx) || !as_u64(a[2], &id) || !dims.fill(a[3], false) || !ins.fill(a[4], true) ||
-      !outs.fill(a[5], true) || !as_u64(a[7], &bytes) || !as_u64(a[8], &stream))
+      !outs.fill(a[5], true) || (!no_bytes && !as_u64(a[7], &bytes)) || !as_u64(a[8], &stream))
     return nullptr;
   if (a[6] != Py_None) {
     if (!as_address(a[6], &ws)) return nullptr;
@@ -100,12 +114,15 @@ PyObject* launch(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
       if (call_u64(a[6], s_numel, &n)) {
         if (!call_u64(a[6], s_element_size, &size)) return nullptr;
         bytes = n * size;
-      } else if (PyErr_ExceptionMatches(PyExc_AttributeError)) {
-        PyErr_Clear();
-      } else {
+        no_bytes = false;
+      } else if (!lacks(a[6], s_numel)) {
         return nullptr;
       }
     }
+  }
+  if (no_bytes) {
+    PyErr_SetString(PyExc_TypeError, "workspace_bytes=None needs a workspace tensor to take the size from");
+    return nullptr;
   }
   int rc;
   Py_BEGIN_ALLOW_THREADS

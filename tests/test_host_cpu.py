@@ -631,3 +631,51 @@ def test_workspace_size_covers_every_alignment(ctx):
                     assert asked >= 4 * n_reds * p["grid"][0][0]
                 grids.add((tuple(dims), off, p["grid"][0][0]))
     assert len({g[0] for g in grids}) < len({(g[0], g[2]) for g in grids})     # (the pointers do change grids)
+
+
+@pytest.mark.parametrize("how", ["C", "ctypes"])
+def test_launch_argument_forms(how):
+    """Both marshallings (the C module, and ctypes where it could not be built): no workspace size, an operand
+    whose data_ptr() fails (its error, not its value taken for an address), a library that loads without the module."""
+    import ctypes as C
+    import torch
+    from paper_2103_05288_amd import binding
+    binding.load_library()
+    assert binding._pylaunch is not binding._CtypesLaunch and os.path.exists(binding._pylaunch_path())
+    launch = binding._pylaunch.launch if how == "C" else binding._CtypesLaunch.launch
+    seen = []
+    F = C.CFUNCTYPE(C.c_int, C.c_void_p, C.c_int32, C.POINTER(C.c_int64), C.c_int, C.POINTER(C.c_void_p), C.c_int,
+                    C.POINTER(C.c_void_p), C.c_int, C.c_void_p, C.c_size_t, C.c_void_p)
+    fn = F(lambda c, i, d, n, ins, ni, outs, no, ws, nb, st: seen.append((d[:n], ins[:ni], outs[:no], ws, nb, st)) or -5)
+    addr = C.cast(fn, C.c_void_p).value
+    t, ws = torch.zeros(3), torch.zeros(10, dtype=torch.float64)
+    for size in (0, None):
+        assert launch(addr, 0, 7, [5], [t], [t, 64], ws, size, 9) == -5
+        assert seen.pop() == ([5], [t.data_ptr()], [t.data_ptr(), 64], ws.data_ptr(), 80, 9)
+    assert launch(addr, 0, 7, torch.Size([5, 6]), [t], [t], 4096, 32, 9) == -5 and seen.pop()[3:5] == (4096, 32)
+    for workspace in (None, 4096):
+        with pytest.raises((TypeError, C.ArgumentError)):
+            launch(addr, 0, 7, [5], [t], [t], workspace, None, 9)
+
+    class Broken(int):
+        def data_ptr(self):
+            return self.storage_that_is_not_there
+
+    with pytest.raises(AttributeError, match="storage_that_is_not_there"):
+        launch(addr, 0, 7, [5], [Broken(3)], [t], None, 0, 9)
+    assert not seen
+
+
+def test_current_stream_without_torch_private_accessors(monkeypatch):
+    import torch
+    from paper_2103_05288_amd import binding
+
+    class S:
+        cuda_stream = 77
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: S)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(binding, "_torch", None)
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert binding._current_stream() == 77
