@@ -1308,6 +1308,7 @@ struct Gen {
         if (row_cols_ok()) emit_late_struct();
         emit_row_phase_fns();
       }
+      os << "  static constexpr bool ROW_COLS = " << (row_cols_ok() ? "true" : "false") << ";\n";
       os << "  static constexpr bool HAS_ELEM_OUT = " << (has_elem_outputs() ? "true" : "false") << ";\n";
       emit_epilogue(M_ELEM);
       emit_col_sums();

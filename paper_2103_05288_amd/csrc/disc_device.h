@@ -1044,12 +1044,15 @@ DISC_DEV void row_stream_body(const typename Pat::Args& A) {
 // columns, U rows in flight, and its sums in registers.  Nothing is exchanged between the lanes until
 // the end, where the TY lanes of a column meet in LDS and the block writes its part of one row of
 // partial sums.  Rows are dealt out one by one, so that the blocks of a launch stream through the
-// tensor side by side.  kRun batches are added up before they meet the sums of the whole block (short
-// chains of additions: 16 + rows of a lane / 16).
+// tensor side by side.  Few blocks mean that a lane adds up many rows (hundreds, in wide tensors), so
+// all of it is in fp64, and a few partial rows, or those of few rows, go to the workspace in fp64 too
+// (A.aux2): a sum is then rounded once, however the rows were split.  Relative rms error of the sums
+// of normally distributed values (half an ulp of the result alone is 2.5e-8), fp32 rows of partial sums of
+// fp32 chains in runs of 16 / as it is here: 4000 x 200000 1.5e-7 / 2.5e-8, 700 x 8192 4.8e-8 / 2.5e-8, 32768 x 512
+// 9.1e-8 / 3.5e-8.  GELU backward, the same: 8192 x 16384 136.9 us / 135.6, 32768 x 512 22.2 / 22.9.
 template <class Pat, int V, int U, int NT, class SP>
 DISC_DEV void row_cols_body(const typename Pat::Args& A) {
-  constexpr int kRun = 16 / U;
-  __shared__ typename Vec<float, V>::vec_t cbuf[256];
+  __shared__ double cbuf[V][256 + 8];                          // (pitch: the V columns of a slot on other banks)
   const int TX = (int)A.aux1, TY = 256 / TX;
   const int tx = (int)threadIdx.x & (TX - 1);
   // (whole wavefronts along a row: the row number is a scalar)
@@ -1058,7 +1061,11 @@ DISC_DEV void row_cols_body(const typename Pat::Args& A) {
   const i64 rem = A.inner - col;
   const bool mine = rem > 0;
   const SP sp = SP::upto(rem < (i64)V ? (int)rem : V);
-  typename Pat::template ColAcc<V> acc{};
+  double acc[Pat::NCOLSUM][V];
+#pragma unroll
+  for (int q = 0; q < Pat::NCOLSUM; ++q)
+#pragma unroll
+    for (int e = 0; e < V; ++e) acc[q][e] = 0.0;
   auto walk = [&](i64 row) {
     typename Pat::template Late<V> same;          // operands that are the same in every row
     {
@@ -1067,61 +1074,68 @@ DISC_DEV void row_cols_body(const typename Pat::Args& A) {
       Pat::template load_late<V>(A, rc, col, sp, same);
     }
     const char* held = reinterpret_cast<const char*>(&same);
+    auto begin = [&](i64 r, typename Pat::RowCtx& rc, typename Pat::template Slot<V>& slot) {
+      Pat::row_begin(A, r, rc);
+      rc.sl = held;
+      Pat::template load<V, NT>(A, rc, col, sp, slot);
+    };
+    auto finish = [&](const typename Pat::RowCtx& rc, const typename Pat::template Slot<V>& slot) {
+      typename Pat::template OutSlot<V> o;
+      typename Pat::template Keep<V> keep;
+      Pat::template epilogue<V, false>(A, rc, slot, keep, col, sp, o);
+      Pat::template store<V, NT>(A, rc, col, sp, o);
+      typename Pat::template ColAcc<V> one;        // (-0 + x is x, which the compiler knows)
+#pragma unroll
+      for (int q = 0; q < Pat::NCOLSUM; ++q) one.c[q] = -0.0f;
+      Pat::template col_sums<V, false>(A, rc, slot, keep, col, sp, one);
+#pragma unroll
+      for (int q = 0; q < Pat::NCOLSUM; ++q)
+#pragma unroll
+        for (int e = 0; e < V; ++e) acc[q][e] += (double)one.c[q][e];
+    };
     const i64 step = (i64)gridDim.x * TY;
-    while (row + (U - 1) * step < A.rows) {
-      typename Pat::template ColAcc<V> part{};
-      const i64 stop = row + kRun * U * step < A.rows ? row + kRun * U * step : A.rows;
-      for (; row + (U - 1) * step < stop; row += U * step) {
-        typename Pat::RowCtx rc[U];
-        typename Pat::template Slot<V> slot[U];
-        typename Pat::template Keep<V> keep;
+    for (; row + (U - 1) * step < A.rows; row += U * step) {
+      typename Pat::RowCtx rc[U];
+      typename Pat::template Slot<V> slot[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          Pat::row_begin(A, row + u * step, rc[u]);
-          rc[u].sl = held;
-          Pat::template load<V, NT>(A, rc[u], col, sp, slot[u]);
-        }
-        asm volatile("" ::: "memory");     // all loads of the batch before its first row
+      for (int u = 0; u < U; ++u) begin(row + u * step, rc[u], slot[u]);
+      asm volatile("" ::: "memory");     // all loads of the batch before its first row
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          typename Pat::template OutSlot<V> o;
-          Pat::template epilogue<V, false>(A, rc[u], slot[u], keep, col, sp, o);
-          Pat::template store<V, NT>(A, rc[u], col, sp, o);
-          Pat::template col_sums<V, false>(A, rc[u], slot[u], keep, col, sp, part);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < Pat::NCOLSUM; ++q) acc.c[q] += part.c[q];
+      for (int u = 0; u < U; ++u) finish(rc[u], slot[u]);
     }
     for (; row < A.rows; row += step) {
       typename Pat::RowCtx rc;
       typename Pat::template Slot<V> slot;
-      typename Pat::template Keep<V> keep;
-      Pat::row_begin(A, row, rc);
-      rc.sl = held;
-      Pat::template load<V, NT>(A, rc, col, sp, slot);
-      typename Pat::template OutSlot<V> o;
-      Pat::template epilogue<V, false>(A, rc, slot, keep, col, sp, o);
-      Pat::template store<V, NT>(A, rc, col, sp, o);
-      Pat::template col_sums<V, false>(A, rc, slot, keep, col, sp, acc);
+      begin(row, rc, slot);
+      finish(rc, slot);
     }
   };
   if (mine) {
     if (TX >= 64) walk((i64)blockIdx.x * TY + __builtin_amdgcn_readfirstlane(ty));
     else walk((i64)blockIdx.x * TY + ty);
   }
+  const i64 tile = (i64)blockIdx.y * TX * V;                 // first column of the block
+  const int cols = A.inner - tile < (i64)TX * V ? (int)(A.inner - tile) : TX * V;
 #pragma unroll
   for (int q = 0; q < Pat::NCOLSUM; ++q) {
-    Vec<float, V> t;
-    t.v = acc.c[q];
-    if (TY > 1) {
-      if (q > 0) __syncthreads();
-      cbuf[threadIdx.x] = t.v;
+#pragma unroll
+    for (int e = 0; e < V; ++e) cbuf[e][threadIdx.x] = acc[q][e];
+    // halves of the rows fold onto each other: every step a lane adds what lies s rows behind it
+    for (int s = TY >> 1; s > 0; s >>= 1) {
       __syncthreads();
-      if (ty == 0)
-        for (int k = 1; k < TY; ++k) t.v += cbuf[tx + k * TX];
+      if (ty < s) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) cbuf[e][threadIdx.x] += cbuf[e][(int)threadIdx.x + s * TX];
+      }
     }
-    if (mine && ty == 0) st(reinterpret_cast<float*>(A.ws0) + ((i64)q * A.aux0 + blockIdx.x) * A.inner, (i64)col, t, sp);
+    __syncthreads();
+    const i64 at = ((i64)q * A.aux0 + blockIdx.x) * A.inner + tile;
+    for (int c = (int)threadIdx.x; c < cols; c += 256) {
+      const double t = cbuf[c % V][c / V];
+      if (A.aux2) reinterpret_cast<double*>(A.ws0)[at + c] = t;
+      else reinterpret_cast<float*>(A.ws0)[at + c] = (float)t;
+    }
+    if (q + 1 < Pat::NCOLSUM) __syncthreads();
   }
 }
 
@@ -1172,20 +1186,20 @@ DISC_DEV void rowred_finish_body(const typename Pat::Args& A) {
 }
 
 // Second launch of a row reduce with sums over the rows: adds up the P rows of partial sums of
-// every summed output, in a fixed order (the result does not depend on timing) and in fp64 (the
-// fp32 partial sums each cover the rows of one block only).  A block takes 16 columns; its 256
+// every summed output, in a fixed order (the result does not depend on timing) and in fp64
+// (partial sums in fp32 each cover the rows of one block only).  A block takes 16 columns; its 256
 // lanes are 16 columns x 16 lanes that each walk every 16th partial row of all sums together,
 // eight loads in flight; the 16 lane totals of a column meet in LDS.  (Measured at 1023 partial
 // rows x 1024 columns x 2 sums: 8.7 us, 12.6 with one sum after the other; 8 columns x 32 lanes,
 // and blocks of 1024 threads covering whole 128-byte lines, both took 19 us.)
 constexpr int kColsumCols = 16, kColsumLanes = 16;
-template <class Pat>
-DISC_DEV void colsum_finish_body(const typename Pat::Args& A) {
+template <class Pat, class PART>
+DISC_DEV void colsum_add_up(const typename Pat::Args& A) {
   constexpr int NQ = Pat::NCOLSUM, CL = kColsumCols, PL = kColsumLanes;
   __shared__ double red[NQ][PL][CL + 1];
   const int cl = (int)threadIdx.x % CL, pl = (int)threadIdx.x / CL;
   const i64 inner = A.inner, P = A.aux0;
-  const float* ws = reinterpret_cast<const float*>(A.ws0);
+  const PART* ws = reinterpret_cast<const PART*>(A.ws0);
   for (i64 c0 = (i64)blockIdx.x * CL; c0 < inner; c0 += (i64)gridDim.x * CL) {
     const i64 col = c0 + cl;
     constexpr int U = NQ >= 2 ? 4 : 8;            // partial rows in flight per lane and sum
@@ -1195,11 +1209,11 @@ DISC_DEV void colsum_finish_body(const typename Pat::Args& A) {
 #pragma unroll
       for (int u = 0; u < U; ++u) acc[q][u] = 0.0;
     if (col < inner) {
-      const float* src = ws + col;
+      const PART* src = ws + col;
       const i64 plane = P * inner;
       i64 p = pl;
       for (; p + (U - 1) * PL < P; p += U * PL) {
-        float x[NQ][U];
+        PART x[NQ][U];
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
@@ -1235,6 +1249,14 @@ DISC_DEV void colsum_finish_body(const typename Pat::Args& A) {
     }
     __syncthreads();
   }
+}
+// A.aux2: the partial rows are fp64 (row_cols_body)
+template <class Pat>
+DISC_DEV void colsum_finish_body(const typename Pat::Args& A) {
+  if constexpr (Pat::ROW_COLS) {
+    if (A.aux2) return colsum_add_up<Pat, double>(A);
+  }
+  colsum_add_up<Pat, float>(A);
 }
 
 // =======================================================================================

@@ -513,9 +513,16 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     L.block = 256;
     // Workspace that covers the launch whatever the alignment of the operands, which a caller does not show
     // when it asks for the size: rows of partial sums, and blocks of the row kernel.
-    int64_t most_rows = 0, most_blocks = 0;
-    int TX = 8;                                      // lanes along the columns, version by column tiles
-    while (TX < 256 && TX < spr) TX *= 2;
+    // (Rows are counted in fp32; own_rows: those of this launch.)
+    int64_t most_rows = 0, most_blocks = 0, own_rows = 0;
+    // Lanes along the columns, version by column tiles: 64, so that four rows of a block meet in LDS and
+    // leave one row of partial sums (GELU backward, 64 / 128 / 256 lanes: 3000 x 2048 12.1 / 12.5 / 13.8 us, 900 x
+    // 12000 18.2 / 18.4 / 19.5, 8192 x 16384 136 / 140 / 138).  Large launches of ragged rows run faster with
+    // 256 (60000 x 1100 94.7 / 99.3 / 91.2, 12000 x 5001 96.8 / 95.3 / 92.0).
+    // (so do rows of more tiles than a grid is high)
+    const int most_tx = (sv.inner % v == 0 || sv.alg_bytes < kNonTemporalMinBytes) && spr <= 64 * 65535ll ? 64 : 256;
+    int TX = 8;
+    while (TX < most_tx && TX < spr) TX *= 2;
     const int64_t col_tiles = (spr + TX - 1) / TX;
     if (p.gen.row_cols_ok && vec && (force < 0 || force == DISC_V_ROW_REG_VEC) && col_tiles <= 65535) {
       const bool nt = v > 1 && sv.inner % v == 0 && c->row_nt != 0 &&
@@ -526,23 +533,39 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // with more streams in flight the memory delivers less.  Measured (bf16, 2^26 elements; 2 / 3 /
       // 4 / 7 blocks per CU): 4096 columns 71.0 / 73.9 / 77.5 / 79.9 us, 1024 columns 71.1 / 74.3 /
       // 79.9 / 84.4; plain accesses, 1100 columns 104 / 90 / 95 / 108, 5001 columns 102 / 100 / 112 /
-      // 104.  Rows of partial sums, one per block of a column tile, then follow: four rows to a lane
-      // where that leaves enough blocks, and no more than fit the fixed scratch array.
+      // 104.  Every block writes (and the second launch reads) a row of partial sums: three per
+      // CU need eight rows a lane (3000 x 2048, 2.9 / 2 per CU: 16.5 / 13.9 us), and a lane has two rows where
+      // that leaves a block per CU (256 x 4096, one / two rows a lane: 9.2 / 8.3).  Numbers in between load the
+      // CUs unevenly (2000 x 3072, 3 / 2.6 / 2 per CU: 14.2 / 15.4 / 13.3).  No more rows of partial sums
+      // than fit the fixed scratch array.
       // The workspace is that of the plain version either way: a caller asks for it without saying how
       // its operands will be aligned.
       const int64_t row_groups = (sv.rows + 256 / TX - 1) / (256 / TX);
-      const int64_t least = ((int64_t)c->n_cus * 2 + col_tiles - 1) / col_tiles;
       auto blocks_per_tile = [&](int per_cu) {
-        const int64_t per_tile = ((int64_t)c->n_cus * per_cu + col_tiles - 1) / col_tiles;
-        int64_t g = std::min<int64_t>(row_groups, std::min<int64_t>(per_tile, std::max<int64_t>(least, (row_groups + 3) / 4)));
-        return std::max<int64_t>(1, std::min<int64_t>(g, DISC_STATIC_SCRATCH_BYTES / (4ll * n_col_sums * sv.inner)));
+        auto at = [&](int n) {
+          const int64_t q = (int64_t)c->n_cus * n / col_tiles;
+          return q >= 8 ? q : ((int64_t)c->n_cus * n + col_tiles - 1) / col_tiles;
+        };
+        const int64_t fill = per_cu == 3 && row_groups < 8 * at(3) ? at(2) : at(per_cu);
+        int64_t g = std::min(row_groups, std::min(fill, std::max(at(1), (row_groups + 1) / 2)));
+        // Rows of partial sums in fp64 where fp32 ones would show: every one of them rounded once is as much
+        // again as the rounding of the result when the terms have both signs, and 1 / number of rows of it
+        // when they have one sign.  256 of them for 4096 rows and more are no worse than chains of a
+        // few fp32 additions each; a single one is the sum itself.
+        const int64_t fit = DISC_STATIC_SCRATCH_BYTES / (4ll * n_col_sums * sv.inner);
+        const bool wide = sv.rows < 4096 || std::min(g, fit) < 256;
+        g = std::max<int64_t>(1, std::min(g, wide ? fit / 2 : fit));
+        return std::make_pair(g, wide && g > 1);
       };
-      const int64_t grid = blocks_per_tile(nt ? 2 : 3);
-      most_rows = blocks_per_tile(3);
+      const auto [grid, fp64_rows] = blocks_per_tile(nt ? 2 : 3);
+      const auto plain = blocks_per_tile(3);
+      most_rows = plain.first * (plain.second ? 2 : 1);
       L.grid[0] = (uint32_t)grid;
       L.grid[1] = (uint32_t)col_tiles;
       fp->aux[0] = grid;        // rows of partial sums
       fp->aux[1] = TX;
+      fp->aux[2] = fp64_rows;
+      own_rows = grid * (fp64_rows ? 2 : 1);
       pub.lanes_per_row = TX;
       pub.slots_per_lane = 2;   // rows in flight
       pub.reg_slots = 2;
@@ -745,10 +768,11 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     pub.n_launches = 1;
     if (n_col_sums == 0) fp->aux[0] = 0;
     if (n_row_reds > 0) fp->aux[1] = L.grid[0];
-    most_rows = std::max(most_rows, fp->aux[0]);
+    own_rows = std::max(own_rows, fp->aux[0]);
+    most_rows = std::max(most_rows, own_rows);
     most_blocks = std::max<int64_t>(most_blocks, L.grid[0]);
-    // workspace: n_col_sums planes of [partial rows, inner] fp32, which the second launch adds up; behind
-    // them one partial result per block and reduction of per-row values, folded by a last launch of one block
+    // workspace: n_col_sums planes of [partial rows, inner] (fp32, or fp64 from the version by column
+    // tiles), which the second launch adds up; behind them one partial result per block and reduction of per-row values, folded by a last launch of one block
     auto layout = [&](int64_t partial_rows, int64_t blocks, size_t* reds_at, size_t* total) {
       int64_t cells, bytes = 0;
       if (n_col_sums > 0 && (mul_ovf(partial_rows, sv.inner, &cells) || mul_ovf(cells, 4ll * n_col_sums, &bytes))) return false;
@@ -757,7 +781,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       return true;
     };
     size_t unused;
-    if (!layout(fp->aux[0], L.grid[0], &fp->ws_off[1], &fp->ws_need) || !layout(most_rows, most_blocks, &unused, &pub.workspace_bytes))
+    if (!layout(own_rows, L.grid[0], &fp->ws_off[1], &fp->ws_need) || !layout(most_rows, most_blocks, &unused, &pub.workspace_bytes))
       return set_err(c, DISC_ERR_SHAPE, "workspace size overflows int64");
     if (n_col_sums > 0) {
       fp->ws_off[0] = 0;

@@ -446,7 +446,74 @@ def test_version_by_column_tiles(nt):
                 want = oracle_run(padded, dims, [to_oracle_input(v) for v in ins])[0]
                 for k, (g, w) in enumerate(zip(got, want)):
                     assert_close(g, w, f"padded {dims} out{k} nt={nt}")
-        assert lanes == {8, 16, 32, 64, 128, 256}
+        assert lanes == {8, 16, 32, 64}          # (more of them for large ragged rows only, see the next test)
+    finally:
+        ctx.close()
+
+
+def plain_sums(second):
+    """Sums over the rows of the values as they are stored: nothing is rounded before it is added."""
+    pb = PatternBuilder("plain_sums2" if second else "plain_sums")
+    t, h = pb.dims(2)
+    x = pb.param("f32", [t, h])
+    pb.output(pb.cast(x, "bf16"))
+    pb.output(pb.reduce("sum", x, 0))
+    if second:
+        pb.output(pb.reduce("sum", pb.op("neg", x), 0))
+    return pb.build()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("second", [False, True])
+def test_sums_by_column_tiles_are_rounded_once(second):
+    """k_row_cols adds up in fp64.  With partial rows in fp64 (fewer than 256 of them, or fewer than 4096 rows) a sum is
+    the exact one rounded to fp32: half an ulp, against 64 bits in plain torch, on values of both signs (where
+    every earlier rounding shows).  Otherwise every partial row is rounded once as well.  From one row per lane to
+    more than a hundred, whole and odd batches, lanes without a row, one partial row, 8 to 256 lanes along
+    the columns, plain and non-temporal accesses; a small workspace limit (more columns than 2 MiB of fp64)."""
+    from paper_2103_05288_amd import Context
+    ctx = Context(0)
+    try:
+        pat = plain_sums(second)
+        h = ctx.register(pat)
+        gen = torch.Generator(device="cuda").manual_seed(47)
+        seen, reached, kinds = set(), set(), set()
+        cases = [[1, 36], [2, 36], [700, 4096], [513, 4096], [3, 2200001], [11000, 1101], [25000, 500], [16003, 1001]]
+        for H, big in ((40, 1 << 22), (100, 1 << 22), (250, 1 << 20), (504, 1 << 20), (20001, 1 << 14)):
+            p = h.plan([big, H])
+            rows = p["grid"][0][0] * (256 // p["lanes_per_row"])        # one row per lane
+            for k, r in ((2, 0), (15, 1), (16, 0), (17, rows - 1), (31, 5), (33, 0), (110, 3)):
+                if rows * (k + 1) * H < 1 << 28:
+                    cases.append([rows * k + r, H])
+        for T, H in cases:
+            p = h.plan([T, H])
+            print(f"[rounded once] {T}x{H} {p['kernels'][0]} {p['grid'][0]}", flush=True)
+            seen.add((p["lanes_per_row"], p["kernels"][0].endswith("_nt")))
+            reached.add(-(-T // (p["grid"][0][0] * (256 // p["lanes_per_row"]))))
+            x = torch.empty((T, H), device="cuda").normal_(generator=gen)
+            outs = [torch.full((T, H), float("nan"), device="cuda", dtype=torch.bfloat16)]
+            outs += [torch.full((H,), float("nan"), device="cuda") for _ in range(2 if second else 1)]
+            ws = torch.full((ctx.workspace_bytes(h.id, [T, H]),), 255, dtype=torch.uint8, device="cuda")
+            h.launch([T, H], [x], outs, workspace=ws)
+            torch.cuda.synchronize()
+            P, TY = p["grid"][0][0], 256 // p["lanes_per_row"]
+            part = torch.zeros((P, H), dtype=torch.float64, device="cuda")         # the blocks' shares
+            for i in range(0, T, 1 << 14):
+                rows = torch.arange(i, min(T, i + (1 << 14)), device="cuda")
+                part.index_add_(0, rows // TY % P, x[i : i + (1 << 14)].double())
+            want = part.sum(0)
+            few = P < 256 or T < 4096
+            kinds.add(few)
+            assert torch.equal(outs[0], x.bfloat16())
+            # half an ulp of the result (and of the partial rows), and what the order of the fp64 additions
+            # changes (T * 2^-53 of the terms)
+            lim = (want.abs() + (0 if few else part.abs().sum(0))) * 2.0 ** -24 + T * 2.0 ** -50
+            for sign, o in zip((1, -1), outs[1:]):
+                assert bool(((o.double() - sign * want).abs() <= lim).all()), (T, H, (o.double() - sign * want).abs().max())
+            del x, outs, ws, part
+        assert kinds == {True, False}
+        assert {s[0] for s in seen} == {8, 16, 32, 64, 128, 256} and {s[1] for s in seen} == {False, True}
+        assert {1, 2, 16, 18, 32, 33} <= reached and max(reached) > 100, reached
     finally:
         ctx.close()
 
