@@ -519,9 +519,11 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     // leave one row of partial sums (GELU backward, 64 / 128 / 256 lanes: 3000 x 2048 12.1 / 12.5 / 13.8 us, 900 x
     // 12000 18.2 / 18.4 / 19.5, 8192 x 16384 136 / 140 / 138).  Large launches of ragged rows run faster with
     // 256 (60000 x 1100 94.7 / 99.3 / 91.2, 12000 x 5001 96.8 / 95.3 / 92.0).
-    // (so do rows of more tiles than a grid is high)
+    // (so do rows of more tiles than a grid is high).  Down to one lane for rows of one slot: with eight
+    // lanes at least, seven of them idle there (2^24 rows of 8: 784 us / 139; 2^21 of 16: 84.7 / 39.3, of 24: 86.2 /
+    // 56.7, of 32: 89.1 / 71.7).
     const int most_tx = (sv.inner % v == 0 || sv.alg_bytes < kNonTemporalMinBytes) && spr <= 64 * 65535ll ? 64 : 256;
-    int TX = 8;
+    int TX = 1;
     while (TX < most_tx && TX < spr) TX *= 2;
     const int64_t col_tiles = (spr + TX - 1) / TX;
     if (p.gen.row_cols_ok && vec && (force < 0 || force == DISC_V_ROW_REG_VEC) && col_tiles <= 65535) {

@@ -413,7 +413,7 @@ def test_single_shape_build_by_column_tiles(hctx):
 @pytest.mark.parametrize("nt", [0, 1])
 def test_version_by_column_tiles(nt):
     """Element-wise patterns with sums over the rows run in k_row_cols: every number of lanes along the columns
-    (8 .. 256) at its edges, several column tiles, fewer rows than a batch, and more than a block sums up in
+    (1 .. 64) at its edges, several column tiles, fewer rows than a batch, and more than a block sums up in
     one go; plain accesses, and the version for rows of whole slots with non-temporal ones."""
     from oracle import run as oracle_run
     from paper_2103_05288_amd import Context
@@ -426,7 +426,7 @@ def test_version_by_column_tiles(nt):
         hp, hq = ctx.register(plain), ctx.register(padded)
         assert (hp.info["template"], hp.info["n_phases"]) == (hq.info["template"], hq.info["n_phases"]) == ("row_reduce", 0)
         lanes = set()
-        for i, h in enumerate((4, 8, 9, 64, 65, 128, 129, 255, 256, 504, 513, 1024, 1032, 2041, 2048, 2049, 4104)):
+        for i, h in enumerate((4, 8, 9, 17, 24, 64, 65, 128, 129, 255, 256, 504, 513, 1024, 1032, 2041, 2048, 2049, 4104)):
             for t in ((1, 3 + i, 200 + 7 * i) if h > 64 else (1, 5000 + i)):
                 pl = hp.plan([t, h])
                 lanes.add(pl["lanes_per_row"])
@@ -446,7 +446,7 @@ def test_version_by_column_tiles(nt):
                 want = oracle_run(padded, dims, [to_oracle_input(v) for v in ins])[0]
                 for k, (g, w) in enumerate(zip(got, want)):
                     assert_close(g, w, f"padded {dims} out{k} nt={nt}")
-        assert lanes == {8, 16, 32, 64}          # (more of them for large ragged rows only, see the next test)
+        assert lanes == {1, 2, 4, 8, 16, 32, 64}          # (more of them for large ragged rows only, see the next test)
     finally:
         ctx.close()
 
@@ -469,7 +469,7 @@ def test_sums_by_column_tiles_are_rounded_once(second):
     """k_row_cols adds up in fp64.  With partial rows in fp64 (fewer than 256 of them, or fewer than 4096 rows) a sum is
     the exact one rounded to fp32: half an ulp, against 64 bits in plain torch, on values of both signs (where
     every earlier rounding shows).  Otherwise every partial row is rounded once as well.  From one row per lane to
-    more than a hundred, whole and odd batches, lanes without a row, one partial row, 8 to 256 lanes along
+    more than a hundred, whole and odd batches, lanes without a row, one partial row, 1 to 256 lanes along
     the columns, plain and non-temporal accesses; a small workspace limit (more columns than 2 MiB of fp64)."""
     from paper_2103_05288_amd import Context
     ctx = Context(0)
@@ -479,7 +479,7 @@ def test_sums_by_column_tiles_are_rounded_once(second):
         gen = torch.Generator(device="cuda").manual_seed(47)
         seen, reached, kinds = set(), set(), set()
         cases = [[1, 36], [2, 36], [700, 4096], [513, 4096], [3, 2200001], [11000, 1101], [25000, 500], [16003, 1001]]
-        for H, big in ((40, 1 << 22), (100, 1 << 22), (250, 1 << 20), (504, 1 << 20), (20001, 1 << 14)):
+        for H, big in ((8, 1 << 23), (13, 1 << 22), (24, 1 << 22), (40, 1 << 22), (100, 1 << 22), (250, 1 << 20), (504, 1 << 20), (20001, 1 << 14)):
             p = h.plan([big, H])
             rows = p["grid"][0][0] * (256 // p["lanes_per_row"])        # one row per lane
             for k, r in ((2, 0), (15, 1), (16, 0), (17, rows - 1), (31, 5), (33, 0), (110, 3)):
@@ -512,7 +512,7 @@ def test_sums_by_column_tiles_are_rounded_once(second):
                 assert bool(((o.double() - sign * want).abs() <= lim).all()), (T, H, (o.double() - sign * want).abs().max())
             del x, outs, ws, part
         assert kinds == {True, False}
-        assert {s[0] for s in seen} == {8, 16, 32, 64, 128, 256} and {s[1] for s in seen} == {False, True}
+        assert {s[0] for s in seen} == {1, 2, 4, 8, 16, 32, 64, 128, 256} and {s[1] for s in seen} == {False, True}
         assert {1, 2, 16, 18, 32, 33} <= reached and max(reached) > 100, reached
     finally:
         ctx.close()
@@ -593,3 +593,13 @@ def test_misaligned_operands_fit_the_workspace_asked_for():
                 assert all(torch.equal(a, b) for a, b in zip(outs, outs2))
     finally:
         ctx.close()
+
+
+def test_narrow_rows_keep_every_lane_busy(hctx):
+    """The version by column tiles has the fewest lanes along the columns that hold a row (a power of two), one for a
+    row of one slot: with more of them the rest would idle for the whole kernel."""
+    h = hctx.register(gelu_backward_bias_gradient())
+    for width, lanes in ((4, 1), (8, 1), (9, 2), (16, 2), (24, 4), (32, 4), (40, 8), (64, 8), (128, 16), (512, 64), (4096, 64)):
+        for rows in (100, 1 << 20):
+            p = h.plan([rows, width])
+            assert p["lanes_per_row"] == lanes and "row_cols" in p["kernels"][0], (rows, width)
