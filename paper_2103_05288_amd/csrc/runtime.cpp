@@ -364,8 +364,9 @@ int plan_loop(disc_ctx* c, int64_t rows, int64_t inner, int V, int want_vec, int
 int resident_blocks(const disc_ctx* c, const Pattern& p, int kid, uint32_t block, uint32_t dyn_lds);
 
 // ---- version + launch-dimension selection (host) ---------------------------------------------
+// ws_limit: where a plan can do with less workspace than it would like, what it may use.
 int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, int force, const void* const* inputs,
-              void* const* outputs, FullPlan* fp) {
+              void* const* outputs, FullPlan* fp, size_t ws_limit = SIZE_MAX) {
   // pointer values: wide accesses need element alignment only; the non-temporal row versions are
   // picked for 16-byte aligned full-size operands (null arrays: assumed aligned)
   if (p.is_static) {
@@ -732,11 +733,22 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // the staging of the row vectors)
       const int rpb = (int)L.block / G;
       const int64_t ngroups = (sv.rows + rpb - 1) / rpb;
+      // Sums over the rows of 1025 .. 1536 slots: blocks of 1024 threads, half as many as there would be of 512
+      // (three slots per lane), so two rounds of them: a lane's chain of fp32 additions stays as short (relative
+      // rms error of dgamma, LayerNorm backward 32768 x 9000, one round / two: 2.1e-7 / 1.55e-7; 436
+      // us / 450, most of it the second row of partial sums per CU).  Not where that does not fit ws_limit.
+      bool two_rounds = n_col_sums > 0 && vec && block == 1024 && spr <= 3 * 512;
+      {
+        int64_t cells, bytes;
+        if (mul_ovf(2ll * c->n_cus, sv.inner, &cells) || mul_ovf(cells, 4ll * n_col_sums, &bytes) ||
+            (uint64_t)bytes + 8ull * (uint64_t)n_row_reds * (uint64_t)c->n_cus + 256 > ws_limit)
+          two_rounds = false;
+      }
       auto blocks_of = [&](int kid) {
         const int64_t held = (int64_t)c->n_cus * resident_blocks(c, p, kid, L.block, L.dyn_lds);
-        // (with sums over the rows every block writes a row of partial sums per wavefront: one round)
+        // (with sums over the rows every block writes a row of partial sums: one round, or two)
         const int rounds = c->row_rounds > 0 ? c->row_rounds
-                           : (L.block > 256 || n_col_sums > 0 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(3, ngroups / (held * 4))));
+                           : (L.block > 256 || n_col_sums > 0 ? (two_rounds ? 2 : 1) : (int)std::max<int64_t>(1, std::min<int64_t>(3, ngroups / (held * 4))));
         return std::min<int64_t>(ngroups, held * rounds);
       };
       auto odd = [&](int64_t g) { return g > 2 && g % 2 == 0 && g < ngroups ? g - 1 : g; };
@@ -1475,7 +1487,7 @@ static int launch_impl(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dim
   }
   if ((n_in > 0 && !inputs) || !outputs) return set_err(ctx, DISC_ERR_INVALID_ARG, "null pointer array");
   FullPlan fp;
-  int rc = make_plan(ctx, *p, dims, n_dims, ctx->force_variant, inputs, outputs, &fp);
+  int rc = make_plan(ctx, *p, dims, n_dims, ctx->force_variant, inputs, outputs, &fp, own_need ? workspace_bytes : SIZE_MAX);
   const int64_t t1 = now_ns();
   ctx->stats.host_plan_ns += t1 - t0;
   if (rc) return rc;
@@ -1537,7 +1549,8 @@ int launch_need(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, cons
   // (the launch itself refuses operands that do not match the pattern)
   const bool match = n_in == p->an.n_inputs && n_out == p->an.n_outputs;
   FullPlan fp;
-  int rc = make_plan(ctx, *p, dims, n_dims, ctx->force_variant, match ? inputs : nullptr, match ? outputs : nullptr, &fp);
+  int rc = make_plan(ctx, *p, dims, n_dims, ctx->force_variant, match ? inputs : nullptr, match ? outputs : nullptr, &fp,
+                     DISC_STATIC_SCRATCH_BYTES);
   if (rc) return rc;
   *need = fp.ws_need > 0 ? fp.ws_need : fp.pub.workspace_bytes;
   return DISC_OK;

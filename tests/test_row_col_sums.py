@@ -603,3 +603,55 @@ def test_narrow_rows_keep_every_lane_busy(hctx):
         for rows in (100, 1 << 20):
             p = h.plan([rows, width])
             assert p["lanes_per_row"] == lanes and "row_cols" in p["kernels"][0], (rows, width)
+
+
+def softmax_with_column_sums():
+    """Row softmax of bf16 scores and the sum over the rows of the probabilities: one reduction over the rows."""
+    pb = PatternBuilder("softmax_col_sums")
+    t, h = pb.dims(2)
+    x = pb.cast(pb.param("bf16", [t, h]), "f32")
+    e = pb.op("exp", pb.op("sub", x, pb.broadcast(pb.reduce("max", x, 1), [t, h], [0])))
+    y = pb.op("div", e, pb.broadcast(pb.reduce("sum", e, 1), [t, h], [0]))
+    pb.output(pb.cast(y, "bf16"))
+    pb.output(pb.reduce("sum", y, 0))
+    return pb.build()
+
+
+def test_partial_rows_of_wide_blocks(hctx):
+    """A row of partial sums holds no more rows of the tensor where the rows need blocks of 1024 threads than where
+    they fit blocks of 512, as long as three slots per lane would have fitted those."""
+    h = hctx.register(layernorm_backward_graph())
+    narrow = h.plan([32768, 8192])
+    assert narrow["block"][0][0] == 512
+    for width in (8193, 9000, 12288):
+        p = h.plan([32768, width])
+        assert p["block"][0][0] == 1024 and p["grid"][0][0] >= narrow["grid"][0][0], width
+        assert p["workspace_bytes"] >= 2 * 4 * width * p["grid"][0][0]
+        assert h.plan([300, width])["grid"][0][0] >= 299
+
+
+@pytest.mark.gpu
+def test_wide_blocks_with_little_scratch():
+    """The static scratch array holds one row of partial sums per CU, not two, of rows of 10000 columns: the call is
+    accepted and runs one round of blocks."""
+    from oracle import run as oracle_run
+    from paper_2103_05288_amd import Context
+    from tests.util import assert_close, run_gpu, to_oracle_input
+    ctx = Context(0)
+    try:
+        pat = softmax_with_column_sums()
+        h = ctx.register(pat)
+        gen = torch.Generator().manual_seed(7)
+        for dims in ([600, 10000], [257, 12283]):
+            x = (2 * torch.randn(*dims, generator=gen)).bfloat16()
+            assert ctx.workspace_bytes(h.id, dims) > 16 << 20 or dims[0] < 400
+            want = oracle_run(pat, dims, [to_oracle_input(x)])[0]
+            terms = np.asarray(want[0], dtype=np.float64)
+            outs = [torch.full(dims, float("nan"), dtype=torch.bfloat16, device="cuda"), torch.full((dims[1],), float("nan"), device="cuda")]
+            ctx.launch_static_scratch(h.id, dims, [x.cuda()], outs)
+            torch.cuda.synchronize()
+            for got, rows in ((run_gpu(h, pat, dims, [x]), 2), ([o.cpu() for o in outs], 3)):
+                assert_close(got[0], want[0], f"softmax {dims}")
+                _check_sum(got[1], want[1], terms, rows, f"column sums {dims}")
+    finally:
+        ctx.close()
