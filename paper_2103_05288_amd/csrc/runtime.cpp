@@ -1234,9 +1234,13 @@ static std::string static_macros(const Pattern& p, const FullPlan& fp, const int
   }
   a << "\n#define DISC_STATIC_PLAN(rp)";
   const LaunchRec& L = fp.launches[0];
+  const std::string kernel = kernel_name(L.kid);
+  const bool tail = kernel.size() > 2 && kernel.compare(kernel.size() - 2, 2, "_t") == 0;
   if (L.plan_kind == 1)
-    a << " rp.G = " << L.rp.G << "; rp.log2G = " << L.rp.log2G << "; rp.nv = " << L.rp.nv << "; rp.flags = " << L.rp.flags
-      << "; rp.rpb = " << L.rp.rpb << ";";
+    // (in a _t version the slot alignment and the kind of access follow the operands of each launch: bits 2 up
+    // of the flags stay a run-time argument)
+    a << " rp.G = " << L.rp.G << "; rp.log2G = " << L.rp.log2G << "; rp.nv = " << L.rp.nv << "; rp.flags = "
+      << (tail ? "(rp.flags & ~3) | " : "") << (tail ? L.rp.flags & 3 : L.rp.flags) << "; rp.rpb = " << L.rp.rpb << ";";
   else if (L.plan_kind == 2)
     a << " rp.GC = " << L.cp.GC << "; rp.log2GC = " << L.cp.log2GC << "; rp.nchunk = " << L.cp.nchunk << "; rp.chunk_rows = "
       << L.cp.chunk_rows << "LL; rp.outer = " << L.cp.outer << "LL; rp.epi_rows = " << L.cp.epi_rows << "LL;";

@@ -679,3 +679,16 @@ def test_current_stream_without_torch_private_accessors(monkeypatch):
     monkeypatch.setattr(binding, "_raw_stream", None)
     monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
     assert binding._current_stream() == 77
+
+
+def test_single_shape_module_takes_the_alignment_of_each_launch(ctx):
+    """Large ragged rows: a launch whose operands lie off a cache line has neither shifted slots nor non-temporal
+    accesses, in the module for one shape as in the generic one; only the launch knows, so these bits stay arguments."""
+    for dims in ([46773, 5739], [46773, 5740], [1000, 5739]):
+        h = ctx.register_static(CONFIGS["C4"].pattern(), dims)
+        plan = re.search(r"#define DISC_STATIC_PLAN\(rp\)(.*)", h.source).group(1)
+        assert h.plan(dims)["kernels"][0].endswith("_t")
+        assert re.search(r"rp\.flags = \(rp\.flags & ~3\) \| [0-3];", plan), plan
+        assert re.search(r"rp\.G = 256;", plan), plan
+    h = ctx.register_static(CONFIGS["C4"].pattern(), [1000, 5736])
+    assert re.search(r"rp\.flags = \d+;", h.source)

@@ -387,3 +387,25 @@ def test_short_ragged_rows_on_eight_lanes(ctx):
     h1 = ctx.register(CONFIGS["C1"].pattern())
     for S in (73, 77, 93):
         assert check(ctx, "C1", [4, 4, S], seed=S, handle=h1)["lanes_per_row"] == 8
+
+
+def test_single_shape_module_with_operands_off_a_line():
+    """Ragged rows on whole lines in a module for one shape: operands on a line, on 16 bytes and off them."""
+    from paper_2103_05288_amd import Context
+    c = Context(0)
+    c.test_option("non_temporal", 1)
+    try:
+        cfg, dims = CONFIGS["C4"], [260, 4095]
+        pat, ins = cfg.pattern(), cfg.inputs([260, 4095], seed=9)
+        h = c.register_static(pat, dims)
+        want = oracle_run(pat, dims, [to_oracle_input(t) for t in ins])[0][0]
+        for shift in (0, 8, 1):
+            dev = [torch.cat([torch.zeros(shift, dtype=t.dtype), t.reshape(-1)]).cuda()[shift:] for t in ins]
+            out = torch.full((dims[0] * dims[1] + 64,), float("nan"), dtype=torch.bfloat16, device="cuda")
+            h.launch(dims, dev, [out[shift:]])
+            torch.cuda.synchronize()
+            n = dims[0] * dims[1]
+            assert_close(out[shift : shift + n].reshape(dims).cpu(), want, f"base shifted by {shift}")
+            assert bool(out[:shift].isnan().all()) and bool(out[shift + n :].isnan().all())
+    finally:
+        c.close()
