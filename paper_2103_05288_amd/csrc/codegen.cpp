@@ -1362,6 +1362,9 @@ struct Gen {
     out->n_row_reds = row_tmpl() ? an.n_row_reds : 0;
     out->row_tail_ok = an.n_col_sums == 0;
     out->row_shift_ok = row_shift_ok();
+    out->row_narrow_late = false;
+    for (const Access& a : an.accesses)
+      if (late(a) && a.kind != ACC_ROWVEC && dtype_bytes(a.dtype) < 4) out->row_narrow_late = true;
     out->row_cols_ok = row_cols_ok();
     out->row_elem_out = row_tmpl() && has_elem_outputs();
     out->staged_elem_bytes.clear();

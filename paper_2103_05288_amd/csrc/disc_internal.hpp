@@ -221,6 +221,7 @@ struct Generated {
   bool row_elem_out = false;          // row reduce: some output has an element per element of the iteration space
   bool row_cols_ok = false;           // row reduce without reductions along the rows: the version by column tiles exists
   bool row_shift_ok = false;          // ... and their vector slots may be shifted to the 16-byte boundaries of the tensor
+  bool row_narrow_late = false;       // row reduce: an operand of less than four bytes an element is the same for many rows, but not staged
   std::vector<std::string> field_names;   // member name of each args.fields entry in Pat::Args
 };
 

@@ -662,7 +662,10 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // 16-byte boundaries alone the hint loses (the lines between two wavefronts' accesses are written
       // in two parts), on whole lines it gains what it gains on aligned rows.  Mixed chain, 2^28 elements,
       // without and with: rows of 5739 272 / 253 us, 2047 272 / 249, 4095 272 / 248, 8191 250 / 237,
-      // 1501 261 / 254, 1023 261 / 258, 4098 260 / 251, 5740 263 / 245; with 32 lanes (515) 269 / 289.
+      // 1501 261 / 254, 1023 261 / 258, 4098 260 / 251, 5740 263 / 245; with 32 lanes (515) 269 / 289.  2^28
+      // elements of other patterns: bf16 softmax 2047 203 / 180, 4100 204 / 177, 777 205 / 202; fp32 softmax 1501 405 / 378,
+      // 8191 403 / 366, 601 405 / 407; log-sum-exp (no element outputs) 1501 99.5 / 91.1, 4095 109 / 108; add + RMS norm 4100
+      // 425 / 387; row amax 3001 94.0 / 90.9, 1023 90.1 / 91.9.
       bool shift = tail && p.gen.row_shift_ok && G >= 2 * v - 2 && c->row_shift != 0;
       const bool may_shift = shift;         // with operands of the right alignment
       int align = v;                        // elements
@@ -676,6 +679,10 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
           if (reinterpret_cast<uintptr_t>(ptr) % 128 != 0) lines = false;
           if (dtype_bytes(a.dtype) >= 2 && (sv.inner * dtype_bytes(a.dtype)) % 4 != 0) off_dword = true;
         }
+        // An operand like the mask [B, 1, 1, S] of a softmax has its own boundaries, which shifted slots miss: then
+        // only where two slots per lane are nearly full, and in wide blocks (f16, without / with lines: S = 777 170 us /
+        // 177, 1501 177 / 180, 1700 159 / 164, 3001 157 / 166, 5742 116 / 123; 2047 143 / 137, 4098 105 / 103, 8191 206 / 194).
+        if (p.gen.row_narrow_late && block <= 256 && !(G >= 128 && nv == 2 && 8 * spr >= 7 * 2 * G)) lines = false;
         lines = lines && shift && (off_dword || G >= kMinLinesEvenG);
         shift = shift && (off_dword || lines);
         if (lines) align = std::min(128, G / 2);

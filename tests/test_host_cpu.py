@@ -692,3 +692,18 @@ def test_single_shape_module_takes_the_alignment_of_each_launch(ctx):
         assert re.search(r"rp\.G = 256;", plan), plan
     h = ctx.register_static(CONFIGS["C4"].pattern(), [1000, 5736])
     assert re.search(r"rp\.flags = \d+;", h.source)
+
+
+def test_slots_on_whole_lines_by_pattern(ctx):
+    """Large ragged rows: the slots move to boundaries of whole lines, which an operand that belongs to many rows but has
+    boundaries of its own (a 16-bit mask per batch) does not follow; with one, only where that was measured to gain.
+    Seen in rows of even length: with lines the grid is cut to a multiple, without them it is odd."""
+    def lines(h, dims):
+        p = h.plan(dims)
+        assert p["kernels"][0].endswith("_t") and p["lanes_per_row"] >= 128, p["kernels"]
+        return p["grid"][0][0] % 2 == 0
+
+    masked, plain = ctx.register(CONFIGS["C1"].pattern()), ctx.register(CONFIGS["C4"].pattern())
+    for s, want in ((1700, False), (3002, False), (4802, False), (5742, False), (2046, True), (4094, True)):
+        assert lines(masked, [max(4, (1 << 27) // (4 * s * s)), 4, s]) == want, s
+        assert lines(plain, [(1 << 28) // s, s]), s
