@@ -1105,7 +1105,7 @@ struct Gen {
       os << "    disc::compact_put_elems<V, NT>(A.o" << a.slot << ", pos, kb, before, kept, stage, [&](int e) { return o.o" << a.slot << ".get(e); });\n";
     }
     os << "    (void)A; (void)o; (void)kb; (void)before; (void)kept; (void)pos; (void)stage;\n  }\n";
-    os << "  static constexpr int COMPACT_BYTES = " << bytes << ";\n";
+    os << "  static constexpr int COMPACT_BYTES = " << bytes << ", COMPACT_SLOTS = " << kCompactLaneSlots << ";\n";
     // the slots of the V elements of one slot of the tile, stored as one vector
     os << "  template <int V, bool NT, class SP> static DISC_DEV void rank_store(const Args& A, disc::i64 base, unsigned col, const disc::i64 (&rank)[V], SP sp) {\n";
     for (const auto& out : an.outputs) {
@@ -1228,7 +1228,7 @@ struct Gen {
       }
       k("k_row_stream_scalar", "disc::row_stream_body<Pat, 1, 0>(A);", nullptr);
       max_threads = 1024;
-      k("k_row_stream_vec", fmt("disc::row_stream_body<Pat, %d, 4>(A);", V), nullptr);
+      k("k_row_stream_vec", fmt("disc::row_stream_body<Pat, %d, %d>(A);", V, kStreamHeldSlots), nullptr);
       max_threads = 256;
       if (an.n_col_sums > 0) k("k_colsum_finish", "disc::colsum_finish_body<Pat>(A);", nullptr);
       if (an.n_row_reds > 0) {

@@ -1658,7 +1658,7 @@ DISC_DEV void col_epi2_body(const typename Pat::Args& A, const ColPlan& cp) {
 // =======================================================================================
 // Outputs whose size depends on the data (compaction by a predicate computed in the pattern; Unique
 // of a sorted tensor is the case keep[i] = x[i] != x[i-1]).  Rank-1 values of length N = A.inner.
-// A tile is 4 wavefronts x kCompactSlots slots x 64 lanes x V elements; a wavefront's part of it is
+// A tile is 4 wavefronts x COMPACT_SLOTS slots x 64 lanes x V elements; a wavefront's part of it is
 // contiguous and its slots are striped over the lanes, so every load and every rank store is one
 // contiguous stretch per wavefront.  Kept elements are counted and ranked with lane masks (ballot,
 // mbcnt, popcount: two or three instructions per element, no scan over the lanes) and meet in LDS,
@@ -1676,7 +1676,7 @@ DISC_DEV void col_epi2_body(const typename Pat::Args& A, const ColPlan& cp) {
 //                       the total.
 // =======================================================================================
 constexpr int kCompactWaves = 4;          // wavefronts per block
-constexpr int kCompactSlots = 4;          // slots per lane
+// (slots per lane: Pat::COMPACT_SLOTS)
 // The lane's number, not known to be the same from tile to tile: what is derived from it is cheap to
 // derive again, and carried through the loop over the tiles it doubled the registers of the kernels.
 DISC_DEV int opaque_lane() {
@@ -1820,7 +1820,7 @@ DISC_DEV void compact_count_body(const typename Pat::Args& A) {
   for (i64 c = blockIdx.x; c < A.aux0; c += gridDim.x) {
     i64 cnt = 0;
     for (i64 t = c * A.aux1; t < (c + 1) * A.aux1; ++t) {
-      CompactPart<false, Pat, V, kCompactSlots> part;
+      CompactPart<false, Pat, V, Pat::COMPACT_SLOTS> part;
       cnt += part.count(A, t);
     }
     if (((int)threadIdx.x & 63) == 0) wsum[wave] = cnt;
@@ -1900,7 +1900,7 @@ DISC_DEV void compact_scatter_body(const typename Pat::Args& A) {
     }
     int buf = 0;
     for (i64 t = c * A.aux1; t < (c + 1) * A.aux1; ++t, buf ^= 1) {
-      CompactPart<NT, Pat, V, kCompactSlots> part;
+      CompactPart<NT, Pat, V, Pat::COMPACT_SLOTS> part;
       const int cnt = part.count(A, t);
       if (((int)threadIdx.x & 63) == 0) wsum[buf][wave] = cnt;
       __syncthreads();

@@ -206,6 +206,10 @@ struct ArgLayout {
   int size = 0;
 };
 
+// What the planner and the generated kernels have to agree on.
+constexpr int kStreamHeldSlots = 4;     // streaming row version: slots of a row that a lane holds in registers
+constexpr int kCompactLaneSlots = 4;    // compaction: slots per lane and tile
+
 struct Generated {
   std::string source;
   ArgLayout args;

@@ -418,11 +418,10 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
   } else if (an.tmpl == DISC_TEMPLATE_COMPACT) {
     if (force >= 0 && force != DISC_V_COMPACT_VEC && force != DISC_V_COMPACT_SCALAR)
       return set_err(c, DISC_ERR_INVALID_ARG, "forced version does not belong to a compaction pattern");
-    constexpr int kCompactSlots = 4;   // (mirrors the device header)
     bool vec = V > 1;
     if (force >= 0) vec = force == DISC_V_COMPACT_VEC;
     const int v = vec ? V : 1;
-    const int64_t tile = 256ll * kCompactSlots * v;
+    const int64_t tile = 256ll * kCompactLaneSlots * v;
     const int64_t nb = (sv.inner + tile - 1) / tile;
     // From kCompactTwoLaunchTiles tiles on, chunks of consecutive tiles whose counts every block of
     // the scatter launch adds up by itself, and no scan launch; below, a chunk is a tile.
@@ -437,7 +436,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     pub.variant = vec ? DISC_V_COMPACT_VEC : DISC_V_COMPACT_SCALAR;
     pub.vec_width = v;
     pub.index_bits = 64;
-    pub.slots_per_lane = kCompactSlots;
+    pub.slots_per_lane = kCompactLaneSlots;
     const uint32_t grid = (uint32_t)std::min<int64_t>(chunks, max_grid * 4);
     int l = 0;
     if (nb > 0) {
@@ -577,7 +576,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       L.kid = vec ? K_ROW_STREAM_VEC : K_ROW_STREAM_SCALAR;
       // the least block whose registers hold the row; rows up to twice of what the largest one holds
       // still run in it, longer ones (which are read again in every phase anyway) in blocks of 256
-      constexpr int64_t kHeld = 4;   // (mirrors the instantiation)
+      constexpr int64_t kHeld = kStreamHeldSlots;
       if (vec && spr <= 2 * 1024 * kHeld)
         while (L.block < 1024 && L.block * kHeld < spr) L.block *= 2;
       // (sums over the rows: a row of partial sums per block in the workspace, so fewer blocks, and for
