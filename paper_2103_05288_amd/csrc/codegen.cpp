@@ -1218,8 +1218,9 @@ struct Gen {
       krow("k_row_scalar_nv2", 1, 2);
       krow("k_row_vec_nv3", V, 3);
       max_threads = 1024;
-      krow("k_row_vec_nv2w", V, 2);
-      krow("k_row_vec_nv3w", V, 3);
+      // (wide blocks: patterns without element outputs stream, three slots beside sums over the rows spill)
+      if (has_elem_outputs() || an.n_col_sums > 0) krow("k_row_vec_nv2w", V, 2);
+      if (has_elem_outputs() && an.n_col_sums == 0) krow("k_row_vec_nv3w", V, 3);
       krow("k_row_scalar_nv2w", 1, 2);
       max_threads = 256;
       if (row_cols_ok()) {

@@ -492,7 +492,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     const int v = vec ? V : 1;
     int64_t spr = (sv.inner + v - 1) / v;
     stream = spr > 1024 * (vec ? 3 : 2);
-    if (force < 0 && vec) {
+    if (vec) {
       // Rows of blocks above 256 threads that write nothing per element: there is no store for the
       // register-resident versions to overlap with the next row's loads, and the streaming version
       // keeps as much of the row (bf16 log-sum-exp, 2^27 elements: 8192 columns 53.5 us against 82.0,
@@ -604,7 +604,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         int64_t best_cap = -1;
         for (const Shape& s : shapes)
           for (int k = max_nv; k >= 1; --k) {
-            if (k == 3 && s.block > 256 && n_col_sums > 0 && force < 0) continue;   // (see above: 12288 columns 986 us)
+            if (k == 3 && s.block > 256 && n_col_sums > 0) continue;   // (see above: 12288 columns 986 us)
             const int64_t cap = (int64_t)s.G * k;
             if (cap >= slots && (best_cap < 0 || cap < best_cap)) { best_cap = cap; G = s.G; nv = k; block = s.block; }
           }

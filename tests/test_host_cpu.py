@@ -707,3 +707,16 @@ def test_slots_on_whole_lines_by_pattern(ctx):
     for s, want in ((1700, False), (3002, False), (4802, False), (5742, False), (2046, True), (4094, True)):
         assert lines(masked, [max(4, (1 << 27) // (4 * s * s)), 4, s]) == want, s
         assert lines(plain, [(1 << 28) // s, s]), s
+
+
+def test_modules_hold_no_row_version_that_no_plan_takes(ctx):
+    """Blocks above 256 threads: patterns without element outputs stream, and three slots per lane beside sums over
+    the rows spill; neither is generated, and the version that would need it is not legal at such a shape."""
+    from workloads.extras import layernorm_backward_graph, logsumexp_with_total_and_amax
+    lse, ln = ctx.register(logsumexp_with_total_and_amax()), ctx.register(layernorm_backward_graph())
+    assert "nv2w" not in lse.source.replace("scalar_nv2w", "") and "nv3w" not in lse.source
+    assert "k_row_vec_nv2w" in ln.source and "nv3w" not in ln.source
+    reg = V["row_reg_vec"]
+    assert lse.plan([9, 6144], reg)["variant_name"] == ln.plan([9, 16384], reg)["variant_name"] == "row_reg_vec"
+    expect("INVALID_ARG", lse.plan, [9, 6145], reg)
+    expect("INVALID_ARG", ln.plan, [9, 16385], reg)
