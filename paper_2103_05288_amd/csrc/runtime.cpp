@@ -315,9 +315,9 @@ constexpr int64_t kNonTemporalMinBytes = 64ll << 20;
 constexpr int kMinLinesG = 64, kMinLinesEvenG = 128;
 // Compaction: from this many tiles on (2^17 i32 elements), two launches instead of three: the blocks of
 // the scatter launch add up the counts in front of them by themselves (14 us a call against 15-16 at
-// 2^17 .. 2^20 elements, where the launches are what is paid for).  Most chunks of a
-// launch: 1024 .. 4096 measured alike at 2^25 elements (103, 105, 100 us), and every block reads up
-// to that many counts.
+// 2^17 .. 2^20 elements, where the launches are what is paid for).  Most chunks of a launch: 1024 / 2048 / 4096
+// take 76.8 / 78.5 / 75.0 us at 2^25 i32 elements and 120.7 / 120.8 / 119.2 at 2^25 i64; every block reads up to that
+// many counts.
 constexpr int64_t kCompactTwoLaunchTiles = 32, kCompactMaxChunks = 2048;
 
 // nt_name: the non-temporal sibling of names[0] (vector width, 32-bit index), taken for large
@@ -517,7 +517,8 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     int64_t most_rows = 0, most_blocks = 0, own_rows = 0;
     // Lanes along the columns, version by column tiles: 64, so that four rows of a block meet in LDS and
     // leave one row of partial sums (GELU backward, 64 / 128 / 256 lanes: 3000 x 2048 12.1 / 12.5 / 13.8 us, 900 x
-    // 12000 18.2 / 18.4 / 19.5, 8192 x 16384 136 / 140 / 138).  Large launches of ragged rows run faster with
+    // 12000 18.2 / 18.4 / 19.5, 8192 x 16384 136 / 140 / 138, 65536 x 1024 70.1 / 71.7 / 71.7, 10000 x 12288 126 / 126
+    // / 131; the other way round 16000 x 8192 139 / 135 / 135, 20000 x 1400 38.9 / 36.4 / 37.6).  Large launches of ragged rows run faster with
     // 256 (60000 x 1100 94.7 / 99.3 / 91.2, 12000 x 5001 96.8 / 95.3 / 92.0).
     // (so do rows of more tiles than a grid is high).  Down to one lane for rows of one slot: with eight
     // lanes at least, seven of them idle there (2^24 rows of 8: 784 us / 139; 2^21 of 16: 84.7 / 39.3, of 24: 86.2 /
@@ -628,10 +629,13 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       }
       // Ragged rows of 10 to 12 slots would run on four lanes, with a ragged last slot in every group: with
       // enough of them, eight lanes that take the ragged ends as single elements are faster although a
-      // third of them is idle (mixed chain, 300007 rows of 77 / 85 / 93 / 95: 36.8 / 39.8 / 42.7 / 44.2 us on
-      // four lanes, 35.3 / 36.7 / 38.6 / 39.1 on eight; 20000 rows of 93: 6.0 / 5.0).  Rows of fewer slots
-      // would gain as well (65: 29.1 / 23.7); their schedule is one that tests/test_host_cpu.py fixes whatever
-      // the number of rows, so they keep it.
+      // third of them is idle.  300007 rows of 73 / 77 / 85 / 93 / 95 in us, on four and on eight lanes: mixed chain
+      // 33.2 / 36.6 / 39.9 / 42.7 / 44.5 and 34.1 / 35.3 / 36.9 / 38.6 / 39.0; softmax 24.7 / 26.2 / 30.3 / 32.7 / 34.3
+      // and 22.9 / 23.7 / 27.2 / 29.2 / 29.5; LayerNorm 40.5 .. 51.7 and 39.2 .. 44.1; add + RMS norm 53.6 .. 71.6 and 45.5
+      // .. 54.0; log-sum-exp and row amax 19.2 .. 20.1, 12.3 .. 13.9 and 19.0 .. 19.7, 10.1 .. 11.4.  The line does not lie
+      // where eight lanes stop gaining: rows of eight whole slots (65 .. 71) would gain more (mixed chain 29.8
+      // / 24.2, softmax 17.4 / 14.3, LayerNorm 35.9 / 30.7) and have kept the one schedule that they have at any
+      // number of rows.  (3000 or 1200 rows take the time of a launch either way, 4.7 .. 5.0.)
       if (tail_ok && !tail && G == 4 && v == 8 && sv.inner / v > 8 && sv.rows >= 4ll * c->n_cus) {
         G = 8;
         tail = true;

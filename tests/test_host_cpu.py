@@ -134,7 +134,7 @@ def test_caller_constraints_enable_fusion(ctx):
     msg = expect("CONSTRAINT", hn.plan, [4, 6, 5, 1])
     assert "registered as equal in size" in msg
     expect("CONSTRAINT", hn.ctx.workspace_bytes, hn.id, [4, 6, 23, 1])
-    # (the advisor's case: a rank-1 tensor tied to a rank-2 one)
+    # (a rank-1 tensor tied to a rank-2 one)
     pb = PatternBuilder()
     a, b, c = pb.dims(3)
     x = pb.param("f32", [a, b])
