@@ -1244,14 +1244,17 @@ static std::string static_macros(const Pattern& p, const FullPlan& fp, const int
   }
   a << "\n#define DISC_STATIC_PLAN(rp)";
   const LaunchRec& L = fp.launches[0];
-  const std::string kernel = kernel_name(L.kid);
-  const bool tail = kernel.size() > 2 && kernel.compare(kernel.size() - 2, 2, "_t") == 0;
-  if (L.plan_kind == 1)
-    // (in a _t version the slot alignment and the kind of access follow the operands of each launch: bits 2 up
-    // of the flags stay a run-time argument)
-    a << " rp.G = " << L.rp.G << "; rp.log2G = " << L.rp.log2G << "; rp.nv = " << L.rp.nv << "; rp.flags = "
-      << (tail ? "(rp.flags & ~3) | " : "") << (tail ? L.rp.flags & 3 : L.rp.flags) << "; rp.rpb = " << L.rp.rpb << ";";
-  else if (L.plan_kind == 2)
+  if (L.plan_kind == 1) {
+    // Planned for aligned operands.  Whether a large launch of ragged rows has non-temporal accesses and slots on
+    // whole lines, on 16-byte boundaries or unshifted follows its own operands (mixed chain 131072 x 2047, 2 bytes off:
+    // 303 us with lines, 274 without; aligned 255 either way).  In a small one the shift alone stays a constant: as an
+    // argument it costs every launch more (9000 x 1023 10.8 us / 11.0) than it gives the misaligned ones.
+    const int low = L.rp.flags & 3, shifted = low | 4 | fp.pub.vec_width << 8;
+    a << " rp.G = " << L.rp.G << "; rp.log2G = " << L.rp.log2G << "; rp.nv = " << L.rp.nv << "; rp.flags = ";
+    if (L.rp.flags & 8) a << "rp.flags & 8 ? " << L.rp.flags << " : rp.flags & 4 ? " << shifted << " : " << low;
+    else a << L.rp.flags;
+    a << "; rp.rpb = " << L.rp.rpb << ";";
+  } else if (L.plan_kind == 2)
     a << " rp.GC = " << L.cp.GC << "; rp.log2GC = " << L.cp.log2GC << "; rp.nchunk = " << L.cp.nchunk << "; rp.chunk_rows = "
       << L.cp.chunk_rows << "LL; rp.outer = " << L.cp.outer << "LL; rp.epi_rows = " << L.cp.epi_rows << "LL;";
   a << "\n";

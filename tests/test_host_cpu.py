@@ -682,16 +682,16 @@ def test_current_stream_without_torch_private_accessors(monkeypatch):
 
 
 def test_single_shape_module_takes_the_alignment_of_each_launch(ctx):
-    """Large ragged rows: a launch whose operands lie off a cache line has neither shifted slots nor non-temporal
-    accesses, in the module for one shape as in the generic one; only the launch knows, so these bits stay arguments."""
-    for dims in ([46773, 5739], [46773, 5740], [1000, 5739]):
+    """Large ragged rows: slots on whole lines and non-temporal accesses follow the operands' boundaries, in the module for
+    one shape as in the generic one; only the launch knows them, so what the plan has of both stays an argument."""
+    for dims in ([46773, 5739], [46773, 5740]):
         h = ctx.register_static(CONFIGS["C4"].pattern(), dims)
         plan = re.search(r"#define DISC_STATIC_PLAN\(rp\)(.*)", h.source).group(1)
         assert h.plan(dims)["kernels"][0].endswith("_t")
-        assert re.search(r"rp\.flags = \(rp\.flags & ~3\) \| [0-3];", plan), plan
+        assert re.search(r"rp\.flags = rp\.flags & 8 \? \d+ : rp\.flags & 4 \? \d+ : [0-3];", plan), plan
         assert re.search(r"rp\.G = 256;", plan), plan
-    h = ctx.register_static(CONFIGS["C4"].pattern(), [1000, 5736])
-    assert re.search(r"rp\.flags = \d+;", h.source)
+    for dims in ([1000, 5736], [1000, 5739], [1000, 5740]):                 # small launches
+        assert re.search(r"rp\.flags = \d+;", ctx.register_static(CONFIGS["C4"].pattern(), dims).source)
 
 
 def test_slots_on_whole_lines_by_pattern(ctx):
