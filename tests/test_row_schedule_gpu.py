@@ -409,3 +409,28 @@ def test_single_shape_module_with_operands_off_a_line():
             assert bool(out[:shift].isnan().all()) and bool(out[shift + n :].isnan().all())
     finally:
         c.close()
+
+
+def test_lines_with_bases_on_sixteen_bytes():
+    """Slots on whole lines of the tensor where its base lies on 16 bytes but off a line: taken from 128 lanes on; the
+    guard elements around the result stay untouched."""
+    from paper_2103_05288_amd import Context
+    c = Context(0)
+    c.test_option("non_temporal", 1)
+    try:
+        cfg = CONFIGS["C4"]
+        pat = cfg.pattern()
+        h = c.register(pat)
+        for dims in ([600, 1023], [300, 2047], [257, 4098], [260, 5739]):
+            ins = cfg.inputs(dims, seed=11)
+            dev = [torch.cat([torch.zeros(24, dtype=t.dtype), t.reshape(-1)]).cuda()[24:] if t.numel() == dims[0] * dims[1] else t.cuda() for t in ins]
+            dev = [torch.cat([torch.zeros(16, dtype=t.dtype), t.reshape(-1)]).cuda()[16:] if t.dtype == torch.bool else d for t, d in zip(ins, dev)]
+            n = dims[0] * dims[1]
+            out = torch.full((n + 64,), float("nan"), dtype=torch.bfloat16, device="cuda")
+            h.launch(dims, dev, [out[8:]])
+            torch.cuda.synchronize()
+            want = oracle_run(pat, dims, [to_oracle_input(t) for t in ins])[0][0]
+            assert_close(out[8 : 8 + n].reshape(dims).cpu(), want, f"{dims}")
+            assert bool(out[:8].isnan().all()) and bool(out[8 + n :].isnan().all())
+    finally:
+        c.close()
