@@ -541,8 +541,8 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // that leaves a block per CU (256 x 4096, one / two rows a lane: 9.2 / 8.3).  Numbers in between load the
       // CUs unevenly (2000 x 3072, 3 / 2.6 / 2 per CU: 14.2 / 15.4 / 13.3).  No more rows of partial sums
       // than fit the fixed scratch array.
-      // The workspace is that of the plain version either way: a caller asks for it without saying how
-      // its operands will be aligned.
+      // The workspace is enough for both versions: a caller asks for it without saying how its operands
+      // will be aligned.
       const int64_t row_groups = (sv.rows + 256 / TX - 1) / (256 / TX);
       auto blocks_per_tile = [&](int per_cu) {
         auto at = [&](int n) {
@@ -798,7 +798,8 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     most_rows = std::max(most_rows, own_rows);
     most_blocks = std::max<int64_t>(most_blocks, L.grid[0]);
     // workspace: n_col_sums planes of [partial rows, inner] (fp32, or fp64 from the version by column
-    // tiles), which the second launch adds up; behind them one partial result per block and reduction of per-row values, folded by a last launch of one block
+    // tiles), which the second launch adds up; behind them one partial result per block and reduction
+    // of per-row values, folded by a last launch of one block
     auto layout = [&](int64_t partial_rows, int64_t blocks, size_t* reds_at, size_t* total) {
       int64_t cells, bytes = 0;
       if (n_col_sums > 0 && (mul_ovf(partial_rows, sv.inner, &cells) || mul_ovf(cells, 4ll * n_col_sums, &bytes))) return false;
