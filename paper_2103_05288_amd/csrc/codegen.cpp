@@ -1250,11 +1250,11 @@ struct Gen {
         k("k_col_epi_vec_i64", fmt("disc::kloop_body<PatE, %d, 1, true>(A);", V), nullptr);
         k("k_col_epi_scalar", "disc::kloop_body<PatE, 1, 4, false>(A);", nullptr);
         k("k_col_epi_scalar_i64", "disc::kloop_body<PatE, 1, 1, true>(A);", nullptr);
-        // two-launch version: finish + epilogue in one kernel (plain; non-temporal accesses: this is the
-        // last read of the operands, and with the hint on the loads as well as on the stores 60000 x
-        // 512 fp32 takes 60.9 us instead of 67.3, 12000 x 1024 27.7 / 29.0, 65536 x 1024 130.6 / 131.8)
+        // two-launch version: finish + epilogue in one kernel (plain; non-temporal accesses; non-temporal
+        // stores only)
         k("k_col_epi2_vec", fmt("disc::col_epi2_body<Pat, PatE, %d, 0>(A, rp);", V), "ColPlan");
         if (V > 1) k("k_col_epi2_vec_nt", fmt("disc::col_epi2_body<Pat, PatE, %d, 3>(A, rp);", V), "ColPlan");
+        if (V > 1) k("k_col_epi2_vec_nts", fmt("disc::col_epi2_body<Pat, PatE, %d, 2>(A, rp);", V), "ColPlan");
         k("k_col_epi2_scalar", "disc::col_epi2_body<Pat, PatE, 1, 0>(A, rp);", "ColPlan");
       }
     }

@@ -958,7 +958,15 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // operand, which the second launch reads again, out of the memory-side cache
       const bool nt = vec && v > 1 && inner % v == 0 && c->row_nt != 0 &&
                       (c->row_nt > 0 || (sv.alg_bytes >= kNonTemporalMinBytes && full_aligned()));
-      L1.kid = vec ? (nt ? K_COL_EPI2_VEC_NT : K_COL_EPI2_VEC) : K_COL_EPI2_SCALAR;
+      // This is the last read of the operands, and the hint on the loads as well gains where the row pieces of
+      // a block are whole 128-byte lines, i.e. nobody else wants the rest of a line (fp32, stores only / both: 60000 x
+      // 512 66.3 / 61.0 us, 40000 x 768 73.6 / 65.4, 20000 x 2016 88.9 / 77.8, 65536 x 1024 130.9 / 128.9); with
+      // pieces of 64 bytes, or rows that end inside a line, it loses (60000 x 256 52.8 / 62.5, 90000 x 384 116 / 130;
+      // 30000 x 1000 80.8 / 91.6, 7857 x 3628 84.3 / 93.2, 276620 x 248 306 / 373).
+      bool lines = true;
+      for (const Access& a : an.accesses)
+        if (a.kind == ACC_FULL && !a.is_output && (inner * dtype_bytes(a.dtype) % 128 != 0 || (int64_t)GC * v * dtype_bytes(a.dtype) < 128)) lines = false;
+      L1.kid = !vec ? K_COL_EPI2_SCALAR : !nt ? K_COL_EPI2_VEC : lines || c->row_nt > 0 ? K_COL_EPI2_VEC_NT : K_COL_EPI2_VEC_NTS;
       L1.grid[0] = (uint32_t)col_tiles;
       L1.grid[1] = (uint32_t)row_blocks;
       L1.grid[2] = (uint32_t)std::min<int64_t>(outer, 65535);
@@ -1366,6 +1374,7 @@ static int register_impl(disc_ctx* ctx, const disc_op* ops, int n_ops, const dis
       // planned without pointers, i.e. for aligned operands: keep the plain sibling of a
       // non-temporal version for launches whose operands turn out not to be 16-byte aligned
       // (for a row kernel that sibling is the version for rows of whole slots, _e)
+      if (k == "k_col_epi2_vec_nts") opt.only_kernels.push_back("k_col_epi2_vec");
       if (k.size() > 3 && k.compare(k.size() - 3, 3, "_nt") == 0)
         opt.only_kernels.push_back(k.substr(0, k.size() - 3) + (k.compare(0, 9, "k_row_vec") == 0 ? "_e" : ""));
     }

@@ -720,3 +720,17 @@ def test_modules_hold_no_row_version_that_no_plan_takes(ctx):
     assert lse.plan([9, 6144], reg)["variant_name"] == ln.plan([9, 16384], reg)["variant_name"] == "row_reg_vec"
     expect("INVALID_ARG", lse.plan, [9, 6145], reg)
     expect("INVALID_ARG", ln.plan, [9, 16385], reg)
+
+
+def test_column_epilogue_loads_with_the_hint_on_whole_lines_only(ctx, handles):
+    """Second launch of a column reduce, large tensors: non-temporal loads where a block's row pieces are whole 128-byte
+    lines, non-temporal stores alone elsewhere; the single-shape module keeps the plain version beside either."""
+    h = handles["C3"]
+    for dims, want in (([60000, 512], "nt"), ([40000, 768], "nt"), ([20000, 2016], "nt"), ([60000, 256], "nts"), ([90000, 384], "nts"),
+                       ([30000, 1000], "nts"), ([7857, 3628], "nts"), ([3000, 1024], "vec"), ([30000, 1001], "vec")):
+        p = h.plan(dims)
+        assert p["kernels"][1].endswith("k_col_epi2_" + ("vec" if want == "vec" else "vec_" + want)), (dims, p["kernels"])
+        q = h.plan(dims, inputs=[4100], outputs=[4096] * h.info["n_outputs"])
+        assert q["kernels"][1].endswith("k_col_epi2_vec")
+    s = ctx.register_static(CONFIGS["C3"].pattern(), [60000, 256])
+    assert s.info["n_variants"] == 3 and s.plan([60000, 256], inputs=[4100], outputs=[4096] * s.info["n_outputs"])["kernels"][1].endswith("k_col_epi2_vec")

@@ -434,3 +434,11 @@ def test_lines_with_bases_on_sixteen_bytes():
             assert bool(out[:8].isnan().all()) and bool(out[8 + n :].isnan().all())
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("dims,kernel", [([34001, 248], "vec_nts"), ([9001, 1000], "vec_nts"), ([33001, 256], "vec_nts"), ([16501, 512], "vec_nt")])
+def test_column_epilogue_versions_of_large_tensors(ctx, dims, kernel):
+    """Large column reduces: non-temporal stores alone (row pieces of 64 bytes, rows that end inside a line), and with the
+    loads (whole lines)."""
+    plan = check(ctx, "C3", dims, seed=21)
+    assert plan["kernels"][-1].endswith("k_col_epi2_" + kernel), plan["kernels"]
