@@ -1114,15 +1114,19 @@ DISC_DEV void row_cols_body(const typename Pat::Args& A) {
     if (TX >= 64) walk((i64)blockIdx.x * TY + __builtin_amdgcn_readfirstlane(ty));
     else walk((i64)blockIdx.x * TY + ty);
   }
+  int filled = TY;                                           // (a power of two) lanes of a column that may have had a row
+  while (filled > 1 && filled / 2 >= A.rows) filled >>= 1;
   const i64 tile = (i64)blockIdx.y * TX * V;                 // first column of the block
   const int cols = A.inner - tile < (i64)TX * V ? (int)(A.inner - tile) : TX * V;
 #pragma unroll
   for (int q = 0; q < Pat::NCOLSUM; ++q) {
 #pragma unroll
     for (int e = 0; e < V; ++e) cbuf[e][threadIdx.x] = acc[q][e];
-    // halves of the rows fold onto each other: every step a lane adds what lies s rows behind it
-    for (int s = TY >> 1; s > 0; s >>= 1) {
+    // more than 16 rows: halves fold onto each other, every step a lane adds what lies s rows behind it
+    int left = filled;
+    for (; left > 16; left >>= 1) {
       __syncthreads();
+      const int s = left >> 1;
       if (ty < s) {
 #pragma unroll
         for (int e = 0; e < V; ++e) cbuf[e][threadIdx.x] += cbuf[e][(int)threadIdx.x + s * TX];
@@ -1131,7 +1135,8 @@ DISC_DEV void row_cols_body(const typename Pat::Args& A) {
     __syncthreads();
     const i64 at = ((i64)q * A.aux0 + blockIdx.x) * A.inner + tile;
     for (int c = (int)threadIdx.x; c < cols; c += 256) {
-      const double t = cbuf[c % V][c / V];
+      double t = cbuf[c % V][c / V];
+      for (int k = 1; k < left; ++k) t += cbuf[c % V][c / V + k * TX];
       if (A.aux2) reinterpret_cast<double*>(A.ws0)[at + c] = t;
       else reinterpret_cast<float*>(A.ws0)[at + c] = (float)t;
     }
