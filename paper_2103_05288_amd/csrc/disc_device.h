@@ -1049,7 +1049,7 @@ DISC_DEV void row_stream_body(const typename Pat::Args& A) {
 // (A.aux2): a sum is then rounded once, however the rows were split.  Relative rms error of the sums
 // of normally distributed values (half an ulp of the result alone is 2.5e-8), fp32 rows of partial sums of
 // fp32 chains in runs of 16 / as it is here: 4000 x 200000 1.5e-7 / 2.5e-8, 700 x 8192 4.8e-8 / 2.5e-8, 32768 x 512
-// 9.1e-8 / 3.5e-8.  GELU backward, the same: 8192 x 16384 136.9 us / 135.6, 32768 x 512 22.2 / 22.9.
+// 9.1e-8 / 3.5e-8.  GELU backward, the same: 8192 x 16384 137.2 us / 135.3, 32768 x 512 22.4 / 22.4.
 template <class Pat, int V, int U, int NT, class SP>
 DISC_DEV void row_cols_body(const typename Pat::Args& A) {
   __shared__ double cbuf[V][256 + 8];                          // (pitch: the V columns of a slot on other banks)

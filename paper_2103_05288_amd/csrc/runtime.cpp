@@ -517,12 +517,12 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     int64_t most_rows = 0, most_blocks = 0, own_rows = 0;
     // Lanes along the columns, version by column tiles: 64, so that four rows of a block meet in LDS and
     // leave one row of partial sums (GELU backward, 64 / 128 / 256 lanes: 3000 x 2048 12.1 / 12.5 / 13.8 us, 900 x
-    // 12000 18.2 / 18.4 / 19.5, 8192 x 16384 136 / 140 / 138, 65536 x 1024 70.1 / 71.7 / 71.7, 10000 x 12288 126 / 126
+    // 12000 18.2 / 18.4 / 19.5, 8192 x 16384 136 / 140 / 138, 65536 x 1024 70.1 / 71.7 / 71.7 (two more barriers a block than now), 10000 x 12288 126 / 126
     // / 131; the other way round 16000 x 8192 139 / 135 / 135, 20000 x 1400 38.9 / 36.4 / 37.6).  Large launches of ragged rows run faster with
     // 256 (60000 x 1100 94.7 / 99.3 / 91.2, 12000 x 5001 96.8 / 95.3 / 92.0).
     // (so do rows of more tiles than a grid is high).  Down to one lane for rows of one slot: with eight
-    // lanes at least, seven of them idle there (2^24 rows of 8: 784 us / 139; 2^21 of 16: 84.7 / 39.3, of 24: 86.2 /
-    // 56.7, of 32: 89.1 / 71.7).
+    // lanes at least, seven of them idle there (2^24 rows of 8: 786 us / 139; 2^21 of 16: 84.6 / 38.4, of 24: 86.3 /
+    // 55.7, of 32: 88.8 / 70.5).
     const int most_tx = (sv.inner % v == 0 || sv.alg_bytes < kNonTemporalMinBytes) && spr <= 64 * 65535ll ? 64 : 256;
     int TX = 1;
     while (TX < most_tx && TX < spr) TX *= 2;
