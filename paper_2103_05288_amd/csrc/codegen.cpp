@@ -609,6 +609,14 @@ struct Gen {
     return fmt("rc.b%zu + col", i);
   }
 
+  void emit_opaque() {
+    os << "  template <int V> static DISC_DEV void opaque(Slot<V>& s) {\n";
+    for (size_t i = 0; i < an.accesses.size(); ++i) {
+      const Access& a = an.accesses[i];
+      if (!a.is_output && a.has_inner && !late(a)) os << "    disc::opaque(s.a" << i << ");\n";
+    }
+    os << "    (void)s;\n  }\n";
+  }
   void emit_load_store(const std::vector<char>& need, bool with_red) {
     if (with_red) emit_load(need, false, "load_x");   // operands only: the caller holds the reduce results
     emit_load(need, with_red, "load");
@@ -1138,6 +1146,16 @@ struct Gen {
     return false;
   }
 
+  // Streaming row version of patterns that write nothing per element
+  bool row_held() const { return row_tmpl() && !has_elem_outputs() && an.n_col_sums == 0; }
+  int stream_held() const { return row_held() && stream_slot_bytes() <= 16 ? 2 * kStreamHeldSlots : kStreamHeldSlots; }
+  int stream_slot_bytes() const {   // registers of one slot, operands as they are loaded
+    int bytes = 0;
+    for (const Access& a : an.accesses)
+      if (!a.is_output && a.has_inner && !late(a)) bytes += std::max(4, an.vec_width * dtype_bytes(a.dtype));
+    return bytes;
+  }
+
   void emit_kernels(Generated* out) {
     const int V = an.vec_width;
     int max_threads = 256;   // largest block the entry point may be launched with
@@ -1228,8 +1246,15 @@ struct Gen {
         if (V > 1) k("k_row_cols_vec_nt", fmt("disc::row_cols_body<PatT<2>, %d, 2, 3, disc::EvenSpan>(A);", V), nullptr, "PatT<2>");
       }
       k("k_row_stream_scalar", "disc::row_stream_body<Pat, 1, 0>(A);", nullptr);
-      max_threads = 1024;
-      k("k_row_stream_vec", fmt("disc::row_stream_body<Pat, %d, %d>(A);", V, kStreamHeldSlots), nullptr);
+      if (row_held()) {
+        max_threads = 512;
+        k("k_row_stream_vec", fmt("disc::row_held_body<Pat, %d, %d>(A);", V, stream_held()), nullptr);
+        max_threads = 1024;
+        k("k_row_stream_vecw", fmt("disc::row_held_body<Pat, %d, %d>(A);", V, kStreamHeldSlots), nullptr);
+      } else {
+        max_threads = 1024;
+        k("k_row_stream_vec", fmt("disc::row_stream_body<Pat, %d, %d>(A);", V, kStreamHeldSlots), nullptr);
+      }
       max_threads = 256;
       if (an.n_col_sums > 0) k("k_colsum_finish", "disc::colsum_finish_body<Pat>(A);", nullptr);
       if (an.n_row_reds > 0) {
@@ -1306,6 +1331,7 @@ struct Gen {
       emit_acc_basic();
       if (row_tmpl()) {
         emit_stage_fns();
+        emit_opaque();
         if (row_cols_ok()) emit_late_struct();
         emit_row_phase_fns();
       }
@@ -1368,6 +1394,8 @@ struct Gen {
       if (late(a) && a.kind != ACC_ROWVEC && dtype_bytes(a.dtype) < 4) out->row_narrow_late = true;
     out->row_cols_ok = row_cols_ok();
     out->row_elem_out = row_tmpl() && has_elem_outputs();
+    out->row_held = row_held();
+    out->stream_held = stream_held();
     out->staged_elem_bytes.clear();
     for (int ai : staged_accesses()) out->staged_elem_bytes.push_back(dtype_bytes(an.accesses[ai].dtype));
     return DISC_OK;

@@ -907,18 +907,25 @@ DISC_DEV void row_tail_body(const typename Pat::Args& A, const RowPlan& rp) {
 // whole slot of a row go one each to the first lanes, as slots of one element.  Any row length below
 // 2^31 works.
 //
-// as_loaded: the slot's registers with their contents unknown to the compiler.  It would otherwise
-// convert a slot to fp32 once and keep that, twice the registers, through all phases.
-template <class S>
-DISC_DEV S as_loaded(const S& s) {
-  constexpr int W = (int)(sizeof(S) - sizeof(int)) / 4;      // (the last member is a placeholder)
-  u32 w[W > 0 ? W : 1];
-  __builtin_memcpy(w, &s, W * 4);
+// as_loaded: a slot's registers with their contents unknown to the compiler, in place (a copy would cost a move
+// per register and phase).  It would otherwise convert a slot to fp32 once and keep that, twice the
+// registers, through all phases.  Operand by operand: a slot as a whole has words that are only padding, and
+// each of those would take a register too (log-sum-exp, eight slots a lane: 99 registers, 75 without them).
+template <class T, int N>
+DISC_DEV void opaque(Vec<T, N>& x) {
+  constexpr int W = (int)sizeof(x.v) / 4;
+  if constexpr (W > 0) {
+    u32 w[W];
+    __builtin_memcpy(w, &x.v, W * 4);
 #pragma unroll
-  for (int i = 0; i < W; ++i) asm volatile("" : "+v"(w[i]));
-  S r;
-  __builtin_memcpy(&r, w, W * 4);
-  return r;
+    for (int i = 0; i < W; ++i) asm volatile("" : "+v"(w[i]));
+    __builtin_memcpy(&x.v, w, W * 4);
+  }
+}
+template <class Pat, int V>
+DISC_DEV typename Pat::template Slot<V>& as_loaded(typename Pat::template Slot<V>& s) {
+  Pat::template opaque<V>(s);
+  return s;
 }
 template <class Pat, int V, int NR>
 struct StreamRow {
@@ -926,9 +933,32 @@ struct StreamRow {
   typename Pat::template Slot<1> end;
   int end_col;            // column of this lane's single element, -1: none
 };
+// Row `row` into the held slots, and the elements behind the last whole slot one each to the first lanes
+template <class Pat, int V, int NR, int NT>
+DISC_DEV void stream_load(const typename Pat::Args& A, i64 row, int inner, int whole, typename Pat::RowCtx& rc, StreamRow<Pat, V, NR>& r) {
+  Pat::row_begin(A, row, rc);
+  rc.sl = nullptr;
+#pragma unroll
+  for (int j = 0; j < NR; ++j) {
+    const int col = (int)(j * blockDim.x + threadIdx.x) * V;
+    if (col < whole) Pat::template load<V, NT>(A, rc, col, TailSpan::upto(V), r.held[j]);
+  }
+  r.end_col = whole + (int)threadIdx.x < inner ? whole + (int)threadIdx.x : -1;
+  if (r.end_col >= 0) Pat::template load<1>(A, rc, r.end_col, TailSpan::upto(1), r.end);
+  if constexpr (NR > 0) asm volatile("" ::: "memory");     // all of these loads before the first phase
+}
+// The block's partial results of reductions of per-row values over the rows
+template <class Pat>
+DISC_DEV void stream_row_reds(const typename Pat::Args& A, const float (&racc)[Pat::NROWRED]) {
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int q = 0; q < Pat::NROWRED; ++q) reinterpret_cast<float*>(A.ws1)[(i64)q * A.aux1 + blockIdx.x] = racc[q];
+  }
+}
+
 template <class Pat, int P, int V, int NR>
 DISC_DEV void row_stream_phases(const typename Pat::Args& A, typename Pat::RowCtx& rc, int whole,
-                                const StreamRow<Pat, V, NR>& r, char* lds, int& parity) {
+                                StreamRow<Pat, V, NR>& r, char* lds, int& parity) {
   if constexpr (P < Pat::NPHASE) {
     typedef typename Pat::template Acc<P> AccT;
     AccT acc;
@@ -937,7 +967,7 @@ DISC_DEV void row_stream_phases(const typename Pat::Args& A, typename Pat::RowCt
     for (int j = 0; j < NR; ++j) {
       const int col = (int)(j * blockDim.x + threadIdx.x) * V;
       typename Pat::template Keep<V> kp;
-      if (col < whole) Pat::template phase<P, V, false>(A, acc, as_loaded(r.held[j]), kp, TailSpan::upto(V), col, rc);
+      if (col < whole) Pat::template phase<P, V, false>(A, acc, as_loaded<Pat, V>(r.held[j]), kp, TailSpan::upto(V), col, rc);
     }
     for (int col = (int)(NR * blockDim.x + threadIdx.x) * V; col < whole; col += blockDim.x * V) {
       typename Pat::template Slot<V> slot;
@@ -963,6 +993,42 @@ DISC_DEV void row_stream_phases(const typename Pat::Args& A, typename Pat::RowCt
   }
 }
 
+// The same for patterns that write nothing per element and sum nothing over the rows.  Bound by the reads.
+// There is no store for a block's loads to hide behind, so what counts is how many rows a CU holds in
+// different phases: the least block that holds the row, down to one wavefront, with NR = 8 slots a lane
+// in place of the four of row_stream_body (blocks of 512 threads at most: at 1024 only one would fit a CU).
+// bf16 log-sum-exp, four slots / eight: 8000 x 16000 54 us / 45 (5.7 TB/s), 4096 x 32000 57 / 50,
+// 16384 x 8000 54 / 48, 16384 x 4096 34 / 28.5.  Loading the next row while one is worked on took 44.4, 51.2, 50.4
+// and, in blocks of 1024, 61.8 us where four slots take 62 (2096 x 64000); 16 slots on half the threads 53 and
+// 51.6; 80 registers (28 of them spilled) 70 and 63.
+template <class Pat, int V, int NR, int NT>
+DISC_DEV void row_held_run(const typename Pat::Args& A) {
+  __shared__ __attribute__((aligned(16))) char lds[2 * 16 * Pat::MAX_ACC_BYTES];
+  const int inner = (int)A.inner, whole = inner / V * V;
+  int parity = 0;
+  float racc[Pat::NROWRED > 0 ? Pat::NROWRED : 1];
+  if constexpr (Pat::NROWRED > 0) {
+#pragma unroll
+    for (int q = 0; q < Pat::NROWRED; ++q) racc[q] = Pat::rr_identity(q);
+  }
+  for (i64 row = blockIdx.x; row < A.rows; row += gridDim.x) {
+    typename Pat::RowCtx rc;
+    StreamRow<Pat, V, NR> r;
+    stream_load<Pat, V, NR, NT>(A, row, inner, whole, rc, r);
+    row_stream_phases<Pat, 0, V, NR>(A, rc, whole, r, lds, parity);
+    if constexpr (Pat::NROWRED > 0) Pat::row_reds(A, rc, racc);   // (every lane holds the row's values)
+    if (threadIdx.x == 0) Pat::row_store(A, row, rc);
+  }
+  if constexpr (Pat::NROWRED > 0) stream_row_reds<Pat>(A, racc);
+}
+// A.aux2: non-temporal loads of the held slots (behind a branch inside the body the compiler would merge the
+// two kinds of access into a plain one)
+template <class Pat, int V, int NR>
+DISC_DEV void row_held_body(const typename Pat::Args& A) {
+  if (A.aux2) row_held_run<Pat, V, NR, 1>(A);
+  else row_held_run<Pat, V, NR, 0>(A);
+}
+
 template <class Pat, int V, int NR>
 DISC_DEV void row_stream_body(const typename Pat::Args& A) {
   __shared__ __attribute__((aligned(16))) char lds[2 * 16 * Pat::MAX_ACC_BYTES];
@@ -976,20 +1042,11 @@ DISC_DEV void row_stream_body(const typename Pat::Args& A) {
   }
   for (i64 row = blockIdx.x; row < A.rows; row += gridDim.x) {
     typename Pat::RowCtx rc;
-    Pat::row_begin(A, row, rc);
-    rc.sl = nullptr;
     StreamRow<Pat, V, NR> r;
-#pragma unroll
-    for (int j = 0; j < NR; ++j) {
-      const int col = (int)(j * blockDim.x + threadIdx.x) * V;
-      if (col < whole) Pat::template load<V>(A, rc, col, TailSpan::upto(V), r.held[j]);
-    }
-    r.end_col = whole + (int)threadIdx.x < inner ? whole + (int)threadIdx.x : -1;
-    if (r.end_col >= 0) Pat::template load<1>(A, rc, r.end_col, TailSpan::upto(1), r.end);
-    if constexpr (NR > 0) asm volatile("" ::: "memory");     // all of these loads before the first phase
+    stream_load<Pat, V, NR, 0>(A, row, inner, whole, rc, r);
     row_stream_phases<Pat, 0, V, NR>(A, rc, whole, r, lds, parity);
     if constexpr (Pat::NROWRED > 0) Pat::row_reds(A, rc, racc);   // (every lane holds the row's values)
-    auto finish = [&](auto slot, auto width, int col) {
+    auto finish = [&](const auto& slot, auto width, int col) {
       constexpr int W = decltype(width)::value;
       typename Pat::template OutSlot<W> o;
       typename Pat::template Keep<W> kp;
@@ -1018,7 +1075,7 @@ DISC_DEV void row_stream_body(const typename Pat::Args& A) {
 #pragma unroll
       for (int j = 0; j < NR; ++j) {
         const int col = (int)(j * blockDim.x + threadIdx.x) * V;
-        if (col < whole) finish(as_loaded(r.held[j]), IntC<V>{}, col);
+        if (col < whole) finish(as_loaded<Pat, V>(r.held[j]), IntC<V>{}, col);
       }
       for (int col = (int)(NR * blockDim.x + threadIdx.x) * V; col < whole; col += blockDim.x * V) {
         typename Pat::template Slot<V> slot;
@@ -1030,12 +1087,7 @@ DISC_DEV void row_stream_body(const typename Pat::Args& A) {
     if (threadIdx.x == 0) Pat::row_store(A, row, rc);
     first = false;
   }
-  if constexpr (Pat::NROWRED > 0) {
-    if (threadIdx.x == 0) {
-#pragma unroll
-      for (int q = 0; q < Pat::NROWRED; ++q) reinterpret_cast<float*>(A.ws1)[(i64)q * A.aux1 + blockIdx.x] = racc[q];
-    }
-  }
+  if constexpr (Pat::NROWRED > 0) stream_row_reds<Pat>(A, racc);
 }
 
 // An element-wise pattern with sums over the rows (no reduction along the rows: NPHASE = 0) does not need

@@ -207,7 +207,7 @@ struct ArgLayout {
 };
 
 // What the planner and the generated kernels have to agree on.
-constexpr int kStreamHeldSlots = 4;     // streaming row version: slots of a row that a lane holds in registers
+constexpr int kStreamHeldSlots = 4;     // streaming row version: slots of a row that a lane holds in registers ...
 constexpr int kCompactLaneSlots = 4;    // compaction: slots per lane and tile
 
 struct Generated {
@@ -223,6 +223,8 @@ struct Generated {
   std::vector<int> staged_elem_bytes; // row reduce: element size of each row vector that can be staged in LDS
   bool row_tail_ok = false;           // row reduce: there are versions that take a ragged end of a row as single elements (_t)
   bool row_elem_out = false;          // row reduce: some output has an element per element of the iteration space
+  bool row_held = false;              // row reduce, nothing written per element or summed over the rows
+  int stream_held = kStreamHeldSlots; // ... and in its blocks of up to 512 threads of row_held patterns
   bool row_cols_ok = false;           // row reduce without reductions along the rows: the version by column tiles exists
   bool row_shift_ok = false;          // ... and their vector slots may be shifted to the 16-byte boundaries of the tensor
   bool row_narrow_late = false;       // row reduce: an operand of less than four bytes an element is the same for many rows, but not staged
@@ -240,7 +242,7 @@ enum KernelId {
   K_TRANSPOSE_TILE,
   K_COL_EPI2_VEC, K_COL_EPI2_VEC_NT, K_COL_EPI2_SCALAR,
   K_COMPACT_COUNT_VEC, K_COMPACT_COUNT_SCALAR, K_COMPACT_SCAN, K_COMPACT_SCATTER_VEC, K_COMPACT_SCATTER_SCALAR,
-  K_COMPACT_SCATTER_VEC_NT, K_ROW_COLS_VEC, K_ROW_COLS_VEC_NT, K_COL_EPI2_VEC_NTS,
+  K_COMPACT_SCATTER_VEC_NT, K_ROW_COLS_VEC, K_ROW_COLS_VEC_NT, K_COL_EPI2_VEC_NTS, K_ROW_STREAM_VECW,
   K_ROW_BASE,
   K_COUNT = K_ROW_BASE + 96
 };
@@ -258,6 +260,7 @@ int kernel_id(const std::string& name);      // -1 when unknown (registration ti
 struct GenOptions {
   std::vector<std::string> only_kernels;
 };
+
 
 // checker.cpp: validate, close constraints, decide fusion, resolve contexts, collapse.
 // number of operands (`in[]` entries that mean something) of an opcode

@@ -493,12 +493,23 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     int64_t spr = (sv.inner + v - 1) / v;
     stream = spr > 1024 * (vec ? 3 : 2);
     if (vec) {
-      // Rows of blocks above 256 threads that write nothing per element: there is no store for the
-      // register-resident versions to overlap with the next row's loads, and the streaming version
-      // keeps as much of the row (bf16 log-sum-exp, 2^27 elements: 8192 columns 53.5 us against 82.0,
-      // 12288: 56.7 / 61.4, 16000: 55.5 / 99.1, 24000: 62.0 / 71.7; 4096 columns, blocks of 256: 57.8 /
-      // 55.6).
-      if (!p.gen.row_elem_out && n_col_sums == 0 && spr > 3 * 256) stream = true;
+      // Rows that write nothing per element: there is no store for the register-resident versions to
+      // overlap with the next row's loads, and the streaming version keeps more rows on a CU.  bf16 log-sum-exp,
+      // register-resident / streaming, 2^27 elements: 8192 columns 82.0 us / 48.8, 12288 61.4 / 55, 16000 99.1 / 45.
+      // Rows of up to 768 slots (blocks of at most 256 threads in the register-resident versions): with enough of
+      // them and more than three slots for every lane of a wavefront, where they start on dword boundaries and one
+      // operand of 16 bytes a slot is all there is (two of them, or a row vector beside: 16384 rows of 2000, 22.6
+      // / 24.9; 2500, 27.3 / 34.6).
+      // 16384 rows of 6000 columns 41.1 / 39.7, 4096 33.9 / 28.5, 3000 26.4 / 23.2, 2500 22.2 / 20.4, 2000 20.8 / 17.7;
+      // but 1501 15.3 / 16.7, 1024 13.3 / 13.9; odd rows, whose slots the others shift: 4095 34.3 / 35.9, 2049 21.8 /
+      // 21.8; 8192 rows of 2500 14.8 / 13.9, 6000 of 4096 17.4 / 14.8, 5000 of 3000 12.2 / 11.7, 4000 of 2500 10.1 / 10.4.
+      if (p.gen.row_held) {
+        bool dwords = true;
+        for (const Access& a : an.accesses)
+          if (a.kind == ACC_FULL && (sv.inner * dtype_bytes(a.dtype)) % 4 != 0) dwords = false;
+        const bool one = p.gen.stream_held > kStreamHeldSlots && p.gen.staged_elem_bytes.empty();
+        if (spr > 3 * 256 || (force < 0 && one && spr > 3 * 64 && dwords && sv.rows > 16ll * c->n_cus)) stream = true;
+      }
       // Sums over the rows and three slots per lane do not fit the registers of a wide block
       // (LayerNorm backward of 24000 columns: 1007 us, 514 in the streaming version)
       if (n_col_sums > 0 && spr > 2 * 1024) stream = true;
@@ -577,9 +588,22 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       L.kid = vec ? K_ROW_STREAM_VEC : K_ROW_STREAM_SCALAR;
       // the least block whose registers hold the row; rows up to twice of what the largest one holds
       // still run in it, longer ones (which are read again in every phase anyway) in blocks of 256
-      constexpr int64_t kHeld = kStreamHeldSlots;
-      if (vec && spr <= 2 * 1024 * kHeld)
-        while (L.block < 1024 && L.block * kHeld < spr) L.block *= 2;
+      const bool held = vec && p.gen.row_held;
+      // (a few rows per CU: more threads to a row instead, 1000 x 8000 bf16 9.4 us / 9.1)
+      const int64_t per_lane = held && sv.rows > 4ll * c->n_cus ? p.gen.stream_held : kStreamHeldSlots;
+      if (vec && spr <= 2 * 1024 * kStreamHeldSlots) {
+        if (held && per_lane > kStreamHeldSlots) L.block = 64;
+        while (L.block < 512 && L.block * per_lane < spr) L.block *= 2;
+        if (L.block * per_lane < spr) L.block = 1024;
+      }
+      if (held) {
+        if (L.block > 512) L.kid = K_ROW_STREAM_VECW;
+        // Held slots are read once.  (The line lies above that of the other non-temporal versions: nothing is
+        // written, and inputs of up to 85 MB are still found in the memory-side cache when three of them take turns: 700 x
+        // 50257 bf16, 70 MB, 21.1 us / 23.4 with the hint; 16384 x 2000 f32, 131 MB, 23.9 / 21.6; larger ones gain 3-10 %,
+        // rows off 16-byte boundaries too.)
+        fp->aux[2] = c->row_nt != 0 && (c->row_nt > 0 || sv.alg_bytes >= kNonTemporalMinBytes * 3 / 2);
+      }
       // (sums over the rows: a row of partial sums per block in the workspace, so fewer blocks, and for
       // rows that a register-resident version could hold no more than that would need)
       const int64_t most = n_col_sums > 0 ? (spr <= 3 * 1024 ? (int64_t)c->n_cus - 1 : (int64_t)c->n_cus * 2)
@@ -588,7 +612,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       fp->aux[0] = L.grid[0];   // rows of partial sums: one per block
       pub.lanes_per_row = (int)L.block;
       pub.slots_per_lane = (int)((spr + L.block - 1) / L.block);
-      pub.reg_slots = vec ? (int)kHeld : 1;
+      pub.reg_slots = !vec ? 1 : (int)(L.kid == K_ROW_STREAM_VECW ? kStreamHeldSlots : per_lane);
     } else {
       // Lanes per row G and slots per lane nv (<= 2): the pair with the least capacity G * nv that
       // holds the row, two slots per lane on a tie.  G is a power of two.  The kernels accept any
