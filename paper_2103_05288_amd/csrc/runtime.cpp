@@ -590,7 +590,8 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // still run in it, longer ones (which are read again in every phase anyway) in blocks of 256
       const bool held = vec && p.gen.row_held;
       // (a few rows per CU: more threads to a row instead, 1000 x 8000 bf16 9.4 us / 9.1)
-      const int64_t per_lane = held && sv.rows > 4ll * c->n_cus ? p.gen.stream_held : kStreamHeldSlots;
+      const bool few = sv.rows <= 4ll * c->n_cus && spr <= 512 * kStreamHeldSlots;
+      const int64_t per_lane = held && !few ? p.gen.stream_held : kStreamHeldSlots;
       if (vec && spr <= 2 * 1024 * kStreamHeldSlots) {
         if (held && per_lane > kStreamHeldSlots) L.block = 64;
         while (L.block < 512 && L.block * per_lane < spr) L.block *= 2;
