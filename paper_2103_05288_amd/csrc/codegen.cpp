@@ -1140,6 +1140,7 @@ struct Gen {
     os << "  };\n";
   }
 
+  bool col_held = false;     // column reduce: the epilogue reads no per-element operand that the reduction does not
   bool has_elem_outputs() const {
     for (const auto& out : an.outputs)
       if (elem_output(an.accesses[out.access])) return true;
@@ -1267,8 +1268,10 @@ struct Gen {
       k("k_col_partial_scalar", "disc::col_partial_body<Pat, 1>(A, rp);", "ColPlan");
       k("k_col_finish", "disc::col_finish_body<Pat>(A, rp);", "ColPlan");
       const char* epi = has_elem_outputs() ? "PatE" : "void";
-      k("k_col_strip_vec", fmt("disc::col_strip_body<Pat, %s, %d>(A, rp);", epi, V), "ColPlan");
-      k("k_col_strip_scalar", fmt("disc::col_strip_body<Pat, %s, 1>(A, rp);", epi), "ColPlan");
+      if (col_held) max_threads = 1024;
+      k("k_col_strip_vec", fmt("disc::col_strip_body<Pat, %s, %d, %d>(A, rp);", epi, V, col_held ? kColHeldRows : 0), "ColPlan");
+      max_threads = 256;
+      k("k_col_strip_scalar", fmt("disc::col_strip_body<Pat, %s, 1, 0>(A, rp);", epi), "ColPlan");
       if (has_elem_outputs()) {
         k("k_col_epi_vec", fmt("disc::kloop_body<PatE, %d, 4, false>(A);", V), nullptr);
         if (V > 1) k("k_col_epi_vec_nt", fmt("disc::kloop_body<PatE, %d, 4, false, 3>(A);", V), nullptr);
@@ -1371,6 +1374,16 @@ struct Gen {
         emit_load_store(need3, true);
         emit_epilogue(M_COL_EPI);
         emit_finish_elem();
+        // the epilogue's operands out of a slot of the reduction's, where it reads no others
+        col_held = true;
+        for (size_t i = 0; i < an.accesses.size(); ++i)
+          if (!an.accesses[i].is_output && an.accesses[i].has_inner && need3[i] && !need1[i]) col_held = false;
+        if (col_held) {
+          os << "  template <int V> static DISC_DEV void take(Slot<V>& d, const Pat::Slot<V>& s) {\n";
+          for (size_t i = 0; i < an.accesses.size(); ++i)
+            if (!an.accesses[i].is_output && an.accesses[i].has_inner && need3[i]) os << "    d.a" << i << " = s.a" << i << ";\n";
+          os << "    (void)d; (void)s;\n  }\n";
+        }
         os << "};\n";
       }
     }
@@ -1396,6 +1409,7 @@ struct Gen {
     out->row_elem_out = row_tmpl() && has_elem_outputs();
     out->row_held = row_held();
     out->stream_held = stream_held();
+    out->col_held = col_held;
     out->staged_elem_bytes.clear();
     for (int ai : staged_accesses()) out->staged_elem_bytes.push_back(dtype_bytes(an.accesses[ai].dtype));
     return DISC_OK;

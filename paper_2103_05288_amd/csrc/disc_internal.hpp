@@ -208,6 +208,7 @@ struct ArgLayout {
 
 // What the planner and the generated kernels have to agree on.
 constexpr int kStreamHeldSlots = 4;     // streaming row version: slots of a row that a lane holds in registers ...
+constexpr int kColHeldRows = 8;         // column reduce, strips held in registers: most rows per lane
 constexpr int kCompactLaneSlots = 4;    // compaction: slots per lane and tile
 
 struct Generated {
@@ -225,6 +226,7 @@ struct Generated {
   bool row_elem_out = false;          // row reduce: some output has an element per element of the iteration space
   bool row_held = false;              // row reduce, nothing written per element or summed over the rows
   int stream_held = kStreamHeldSlots; // ... and in its blocks of up to 512 threads of row_held patterns
+  bool col_held = false;              // column reduce: strips may stay in registers between the reduction and the epilogue
   bool row_cols_ok = false;           // row reduce without reductions along the rows: the version by column tiles exists
   bool row_shift_ok = false;          // ... and their vector slots may be shifted to the 16-byte boundaries of the tensor
   bool row_narrow_late = false;       // row reduce: an operand of less than four bytes an element is the same for many rows, but not staged

@@ -858,6 +858,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     if (mid >= (1ll << 31) - 1) return set_err(c, DISC_ERR_SHAPE, "reduced axis longer than 2^31");
     // the column tiles are the x dimension of the grids (no grid stride across columns)
     if (inner >= (1ll << 31) - 4096) return set_err(c, DISC_ERR_SHAPE, "column reduce: more than 2^31 columns");
+    constexpr int64_t kTwoLaunchChunks = 32;
     int want_vec = -1, want_strip = -1, want_two = -1;
     if (force >= 0) {
       const bool two = force == DISC_V_COL_2STAGE_VEC || force == DISC_V_COL_2STAGE_SCALAR;
@@ -878,18 +879,40 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     const int v = vec ? V : 1;
     const int64_t spr = (inner + v - 1) / v;
     // Small problems: one launch, a block per strip of columns (reduce, finish and epilogue in the
-    // same kernel).  A launch that makes a round trip to memory costs 5-6 us whatever it moves; up
-    // to about a million elements one such launch (4.5-10 us measured on 1024 fp32 columns) beats
-    // two (12 us).  Measured alternatives: the strip version up to two million elements (17 us at
-    // 1500 rows: too few blocks) and 128 narrower strips instead of 64 (no gain).
+    // same kernel), up to about a million elements.  A strip that the block can hold in registers is read once
+    // (col_held).  Long reduced axes leave too few strips and too many rows to a lane: two launches then, if
+    // the caller's workspace allows them.  fp32, one launch / two, us: 1000 x 1024 7.3 / 8.5, 500 x 2000 6.5 / 8.0, 2000 x
+    // 256 7.7 / 8.6, 2000 x 128 7.1 / 8.6; 2000 x 512 10.7 / 8.8, 3000 x 100 9.4 / 8.4, 4096 x 256 16.4 / 7.5, 5000 x 200 22.3 / 12.0, 16384
+    // x 64 46.4 / 9.2.  (1300 x 777 9.3 / 10.4 is on the wrong side of the line.)
     int64_t total;
-    const bool small = !mul_ovf(outer * mid, inner, &total) && total <= (1ll << 20);
+    const bool held = vec && p.gen.col_held;
+    const bool million = !mul_ovf(outer * mid, inner, &total) && total <= (1ll << 20);
+    const bool long_axis = p.gen.has_epilogue && mid > (held && million && total <= (1ll << 19) ? 2048 : 1024);
+    const bool small = million && !long_axis;
     const bool strip = want_strip >= 0 ? want_strip != 0 : small;
     if (strip) {
       // strips of >= 32 bytes per row keep the accesses coalesced; narrower strips = more blocks
       int GC = 1;
       while (GC < 64 && (GC * (vec ? 16 : 4) < 32 || spr / (GC * 2) >= 64)) GC *= 2;
       GC = std::min<int>(GC, 1 << ilog2_ceil(std::min<int64_t>(spr, 64)));
+      // Held strips: few rows leave room for more and narrower strips, many rows take more threads, four to
+      // eight rows to a lane (64 strips / 256: 256 x 4096 7.7 us / 5.4, 100 x 4096 5.3 / 4.8; 700 x 1024 6.0 / 6.8, 500
+      // x 2000 6.4 / 7.5; 256 / 512 / 1024 threads: 300 x 1024 5.0 / 4.8 / 5.7, 700 x 1024 - / 6.0 / 6.4, 1000 x 1024
+      // - / 7.6 / 7.3).  Before, in 256 threads that read the strip twice: 700 x 1024 7.2, 256 x 4096 7.7.
+      uint32_t block = 256;
+      if (held) {
+        const int64_t strips = mid <= 256 ? 256 : 64;
+        int g = 1;
+        while (g < 16 && (g * 16 < 32 || spr / (g * 2) >= strips)) g *= 2;
+        g = std::min<int>(g, 1 << ilog2_ceil(std::min<int64_t>(spr, 16)));
+        uint32_t b = 256;
+        if (mid > 4 * (256 / g)) b = 512;
+        if (mid > 6 * (512 / g)) b = 1024;
+        if (mid <= (int64_t)kColHeldRows * (b / g)) {
+          GC = g;
+          block = b;
+        }
+      }
       const int64_t col_tiles = (spr + GC - 1) / GC;
       DeviceColPlan cp{GC, ilog2_ceil(GC), 1, 0, mid, outer, 0};
       fp->aux[0] = 0;
@@ -904,6 +927,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       pub.index_bits = 64;
       LaunchRec& L0 = fp->launches[0];
       L0.kid = vec ? K_COL_STRIP_VEC : K_COL_STRIP_SCALAR;
+      L0.block = block;
       L0.grid[0] = (uint32_t)col_tiles;
       L0.grid[1] = (uint32_t)std::min<int64_t>(outer, 65535);
       L0.plan_kind = 2;
@@ -920,7 +944,6 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     // whole cache lines) unless the rows are narrower; the other lanes of the block run down the
     // rows.  Narrow column tiles give the grid its width: with 64 lanes across, 1024 fp32 columns
     // are only 4 tiles, and the chunks of the reduced axis would have to supply all the parallelism.
-    constexpr int64_t kTwoLaunchChunks = 32;
     // (narrow tensors: 8 or 4 lanes across when that yields more blocks, down to 64-byte row pieces)
     int GC = 1 << ilog2_ceil(std::min<int64_t>(spr, 16));
     {
@@ -945,7 +968,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     const int64_t max_chunks = std::max<int64_t>(1, mid / (4ll * TY));
     int64_t nchunk = ((int64_t)c->n_cus * 2 + tiles - 1) / tiles;
     nchunk = std::max<int64_t>(1, std::min<int64_t>(nchunk, max_chunks));
-    bool two = p.gen.has_epilogue && nchunk <= kTwoLaunchChunks;
+    bool two = p.gen.has_epilogue && (nchunk <= kTwoLaunchChunks || million);
     if (want_two >= 0) two = want_two != 0;
     if (two) nchunk = std::min<int64_t>(nchunk, kTwoLaunchChunks);
     else nchunk = std::min<int64_t>(std::max<int64_t>(1, std::min<int64_t>(((int64_t)c->n_cus * 4 + tiles - 1) / tiles, max_chunks)), 1024);
@@ -955,6 +978,9 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     int64_t cells, red_bytes;
     if (mul_ovf(outer * nchunk, inner, &cells) || mul_ovf(cells, (int64_t)p.gen.n_acc_cells * 8, &red_bytes))
       return set_err(c, DISC_ERR_SHAPE, "workspace size overflows int64");
+    // (no workspace for a problem that fits one launch: one launch)
+    if (million && long_axis && force < 0 && !p.is_static && (uint64_t)red_bytes > ws_limit)
+      return make_plan(c, p, dims, n_dims, vec ? DISC_V_COL_STRIP_VEC : DISC_V_COL_STRIP_SCALAR, inputs, outputs, fp, ws_limit);
     fp->aux[0] = cells;                 // cells per accumulator-field plane
     fp->aux[1] = outer * inner * 8;     // bytes per reduce-result plane
     fp->ws_off[0] = 0;
@@ -1541,7 +1567,9 @@ static int launch_impl(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dim
   }
   if ((n_in > 0 && !inputs) || !outputs) return set_err(ctx, DISC_ERR_INVALID_ARG, "null pointer array");
   FullPlan fp;
-  int rc = make_plan(ctx, *p, dims, n_dims, ctx->force_variant, inputs, outputs, &fp, own_need ? workspace_bytes : SIZE_MAX);
+  // (a column reduce that could do without a workspace does, if there is none)
+  const size_t limit = own_need ? workspace_bytes : p->an.tmpl == DISC_TEMPLATE_COL_REDUCE ? (workspace ? workspace_bytes : 0) : SIZE_MAX;
+  int rc = make_plan(ctx, *p, dims, n_dims, ctx->force_variant, inputs, outputs, &fp, limit);
   const int64_t t1 = now_ns();
   ctx->stats.host_plan_ns += t1 - t0;
   if (rc) return rc;

@@ -173,6 +173,46 @@ def test_column_argmax_and_minmax(ctx):
             compare(ctx, pat, [T, C], [torch.from_numpy(x)], "col argmax", force=v, handle=hd)
 
 
+@pytest.mark.parametrize("kind", ["center", "max_bf16", "other_operand"])
+def test_strips_held_in_registers(ctx, kind):
+    """Single-launch column reduces at the edges of what a block's lanes hold (eight rows a lane in 256, 512 and 1024
+    threads), ragged rows, a batch dimension, an epilogue that reads more than the reduction (never held), and long
+    axes, which take two launches only where the caller has a workspace for them."""
+    if kind == "center":
+        pat, dt = CONFIGS["C3"].pattern(), torch.float32
+        shapes = [[1, 1024], [255, 1024], [256, 1024], [257, 1024], [769, 1024], [1023, 1000], [1024, 1024], [768, 516], [256, 4092], [257, 4093],
+                  [1025, 64], [2048, 256], [2049, 256], [8000, 64], [5001, 200], [700, 39], [16384, 5]]
+    else:
+        pb = PatternBuilder()
+        a, t, c = pb.dims(3)
+        dt = torch.bfloat16
+        x = pb.cast(pb.param("bf16", [a, t, c]), "f32")
+        m = pb.broadcast(pb.reduce("max", x, 1), [a, t, c], [0, 2])
+        y = pb.op("sub", x, m)
+        if kind == "other_operand":
+            y = pb.op("mul", y, pb.cast(pb.param("bf16", [a, t, c]), "f32"))
+        pb.output(pb.cast(y, "bf16"))
+        pat = pb.build()
+        shapes = [[1, 7, 8], [3, 256, 520], [2, 511, 1000], [5, 1024, 64], [2, 1030, 72], [1, 2048, 250], [1, 4000, 77]]
+    h = ctx.register(pat)
+    g = torch.Generator().manual_seed(6)
+    for dims in shapes:
+        ins = [torch.randn(pat.shape_of(i, dims), generator=g).to(dt) for i in pat.params]
+        if len(dims) == 3:
+            ins[0][-1, -1, -1] = 9.0                  # the last row decides a column
+        compare(ctx, pat, dims, ins, "strip " + kind, handle=h)
+    dims = shapes[-4] if kind == "center" else shapes[-1]
+    assert h.plan(dims)["n_launches"] == 2 and ctx.workspace_bytes(h.id, dims) > 0
+    ins = [torch.randn(pat.shape_of(i, dims), generator=g).to(dt) for i in pat.params]
+    outs, before = alloc_outputs(pat, dims, "cuda"), ctx.stats()["device_launches"]
+    h.launch(dims, [t.cuda() for t in ins], outs, workspace=None)
+    torch.cuda.synchronize()
+    assert ctx.stats()["device_launches"] == before + 1
+    want = oracle_run(pat, dims, [to_oracle_input(t) for t in ins])[0]
+    for k, (o, w) in enumerate(zip(outs, want)):
+        assert_close(o.cpu(), w, f"strip without workspace {dims} out{k}")
+
+
 # ---------------------------------------------------------------- generic patterns
 def test_elementwise_op_zoo_fp32(ctx):
     pb = PatternBuilder()
