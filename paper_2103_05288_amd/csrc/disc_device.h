@@ -1245,52 +1245,55 @@ DISC_DEV void rowred_finish_body(const typename Pat::Args& A) {
 // Second launch of a row reduce with sums over the rows: adds up the P rows of partial sums of
 // every summed output, in a fixed order (the result does not depend on timing) and in fp64
 // (partial sums in fp32 each cover the rows of one block only).  A block takes 16 columns; its 256
-// lanes are 16 columns x 16 lanes that each walk every 16th partial row of all sums together,
-// eight loads in flight; the 16 lane totals of a column meet in LDS.  (Measured at 1023 partial
-// rows x 1024 columns x 2 sums: 8.7 us, 12.6 with one sum after the other; 8 columns x 32 lanes,
-// and blocks of 1024 threads covering whole 128-byte lines, both took 19 us.)
-constexpr int kColsumCols = 16, kColsumLanes = 16;
+// or (from 128 partial rows on) 512 lanes are 16 columns x 16 or 32 lanes that each walk every 16th or 32nd partial
+// row of all sums together, eight loads in flight, the ones past the last row from that row instead (a tail
+// of single loads is a chain of trips to memory); the lanes of a column meet by lane exchanges, then in LDS.
+// Bound by those trips.  Whole calls, 256 lanes with such a tail / 256 / 512 / 1024: LayerNorm backward 32768 x 1024 (767 partial
+// rows, two sums) 47.0 us / 47.1 / 44.7 / 45.0, 65536 x 128 24.5 / 24.7 / 22.2 / 22.0, 2000 x 768 (250 rows) 13.9 / 13.5 / 12.8 / 12.9;
+// GELU backward 8192 x 16384 (16 rows) 134.7 / 135.1 / 136.6 / 138.5.  With branches around the loads they
+// came one by one: 64.5.
+constexpr int kColsumCols = 16;
 template <class Pat, class PART>
 DISC_DEV void colsum_add_up(const typename Pat::Args& A) {
-  constexpr int NQ = Pat::NCOLSUM, CL = kColsumCols, PL = kColsumLanes;
-  __shared__ double red[NQ][PL][CL + 1];
-  const int cl = (int)threadIdx.x % CL, pl = (int)threadIdx.x / CL;
+  constexpr int NQ = Pat::NCOLSUM, CL = kColsumCols;
+  __shared__ double red[NQ][16][CL];
+  const int cl = (int)threadIdx.x % CL, pl = (int)threadIdx.x / CL, PL = (int)blockDim.x / CL;
   const i64 inner = A.inner, P = A.aux0;
   const PART* ws = reinterpret_cast<const PART*>(A.ws0);
   for (i64 c0 = (i64)blockIdx.x * CL; c0 < inner; c0 += (i64)gridDim.x * CL) {
     const i64 col = c0 + cl;
     constexpr int U = NQ >= 2 ? 4 : 8;            // partial rows in flight per lane and sum
-    double acc[NQ][U];
+    double acc[NQ];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
-#pragma unroll
-      for (int u = 0; u < U; ++u) acc[q][u] = 0.0;
+    for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
     if (col < inner) {
       const PART* src = ws + col;
       const i64 plane = P * inner;
       i64 p = pl;
-      for (; p + (U - 1) * PL < P; p += U * PL) {
-        PART x[NQ][U];
+      if (P > 2 * PL) {
+        for (; p < P; p += U * PL) {
+          PART x[NQ][U];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q)
+          for (int u = 0; u < U; ++u)
 #pragma unroll
-          for (int u = 0; u < U; ++u) x[q][u] = src[q * plane + (p + u * PL) * inner];
+            for (int q = 0; q < NQ; ++q) x[q][u] = src[q * plane + (p + u * PL < P ? p + u * PL : P - 1) * inner];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q)
+          for (int q = 0; q < NQ; ++q)
 #pragma unroll
-          for (int u = 0; u < U; ++u) acc[q][u] += x[q][u];
-      }
-      for (; p < P; p += PL) {
+            for (int u = 0; u < U; ++u) acc[q] += p + u * PL < P ? (double)x[q][u] : 0.0;
+        }
+      } else {                                    // one or two rows for every lane
+        for (; p < P; p += PL) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) acc[q][0] += src[q * plane + p * inner];
+          for (int q = 0; q < NQ; ++q) acc[q] += (double)src[q * plane + p * inner];
+        }
       }
     }
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      double t = 0.0;
-#pragma unroll
-      for (int u = 0; u < U; ++u) t += acc[q][u];
-      red[q][pl][cl] = t;
+    for (int q = 0; q < NQ; ++q) {                // the four lanes of a column in a wavefront, then the wavefronts
+      acc[q] += lane_xchg<16>(acc[q]);
+      acc[q] += lane_xchg<32>(acc[q]);
+      if (((int)threadIdx.x & 63) < CL) red[q][threadIdx.x >> 6][cl] = acc[q];
     }
     __syncthreads();
     if (pl == 0 && col < inner) {
@@ -1298,8 +1301,7 @@ DISC_DEV void colsum_add_up(const typename Pat::Args& A) {
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
         double t = 0.0;
-#pragma unroll
-        for (int k = 0; k < PL; ++k) t += red[q][k][cl];
+        for (int k = 0; k < PL / 4; ++k) t += red[q][k][cl];
         v[q] = (float)t;
       }
       Pat::colsum_store(A, col, v);
