@@ -626,7 +626,7 @@ struct Gen {
     os << "  template <int V, int NT = 0, class C, class SP> static DISC_DEV void " << name << "(const Args& A, const RowCtx& rc, C col, SP sp, Slot<V>& s) {\n";
     for (size_t i = 0; i < an.accesses.size(); ++i) {
       const Access& a = an.accesses[i];
-      if (a.is_output || !a.has_inner || !need[i] || late(a)) continue;
+      if (a.is_output || !a.has_inner || !need[i] || late(a) || (int)i == xpose()) continue;
       os << "    " << load_call(a, i, fmt("s.a%zu", i), a.kind == ACC_FULL ? "<(NT & 1) != 0>" : "",
                             a.kind == ACC_FULL ? ", rc.tail_ok" : "") << "\n";
     }
@@ -640,6 +640,14 @@ struct Gen {
       }
     }
     os << "    (void)A; (void)rc; (void)col; (void)sp; (void)s;\n  }\n";
+  }
+  int xpose() const { return opt ? opt->xpose_access : -1; }
+  // the operand that arrives transposed: its type, its address, its place in a slot
+  void emit_xpose() {
+    const Access& a = an.accesses[xpose()];
+    os << "  typedef " << dtype_ctype(a.dtype) << " XpT;\n"
+       << "  static DISC_DEV const XpT* xp_src(const Args& A) { return A.p" << a.slot << "; }\n"
+       << "  template <int V> static DISC_DEV disc::Vec<XpT, V>& xp_slot(Slot<V>& s) { return s.a" << xpose() << "; }\n";
   }
   void emit_store() {
     os << "  template <int V, int NT = 0, class C, class SP> static DISC_DEV void store(const Args& A, const RowCtx& rc, C col, SP sp, const OutSlot<V>& o) {\n";
@@ -1227,6 +1235,12 @@ struct Gen {
       k("k_loop_vec_i64", fmt("disc::kloop_body<Pat, %d, 1, true>(A);", V), nullptr);
       k("k_loop_scalar", "disc::kloop_body<Pat, 1, 4, false>(A);", nullptr);
       k("k_loop_scalar_i64", "disc::kloop_body<Pat, 1, 1, true>(A);", nullptr);
+    } else if (xpose() >= 0) {
+      max_threads = 1024;
+      for (const int nv : kXposeSlots)
+        for (const bool even : {false, true})
+          k(fmt("k_row_xpose_nv%d%s", nv, even ? "_e" : ""),
+            fmt("disc::row_xpose_body<Pat, %d, %d, disc::%s>(A, rp);", V, nv, even ? "EvenSpan" : "Span"), "RowPlan");
     } else if (an.tmpl == DISC_TEMPLATE_ROW_REDUCE) {
       // two slots per lane keep the register footprint near 100 VGPRs (4-5 waves per SIMD); longer
       // rows get more lanes (blocks of up to 1024 threads) rather than more slots per lane.  The
@@ -1330,6 +1344,7 @@ struct Gen {
       emit_slots(all, false, true);
       emit_row_begin();
       emit_load_store(all, false);
+      if (xpose() >= 0) emit_xpose();
       emit_acc_basic();
       if (row_tmpl()) {
         emit_stage_fns();
@@ -1416,6 +1431,26 @@ struct Gen {
 };
 
 }  // namespace
+
+// A row reduce without sums or reductions over the rows whose one per-element operand is this input, read in
+// full, one 16-byte access per slot.
+int xpose_access(const Analysis& an, int slot) {
+  if (an.tmpl != DISC_TEMPLATE_ROW_REDUCE || an.n_phases == 0 || an.n_col_sums > 0 || an.n_row_reds > 0) return -1;
+  int found = -1;
+  for (size_t i = 0; i < an.accesses.size(); ++i) {
+    const Access& a = an.accesses[i];
+    if (a.is_output) continue;
+    if (a.slot == slot) {
+      const int bytes = dtype_bytes(a.dtype);
+      if (found >= 0 || a.kind != ACC_FULL || a.src_value >= 0 || a.padded || a.prev || (bytes != 2 && bytes != 4) || an.vec_width * bytes != 16)
+        return -1;
+      found = (int)i;
+    } else if (a.kind == ACC_FULL || (a.has_inner && a.all_outer)) {
+      return -1;                                  // a second operand with an element per element
+    }
+  }
+  return found;
+}
 
 int generate(const Analysis& an, const std::string& prefix, Generated* out, std::string* err, const GenOptions* opt) {
   out->prefix = prefix;

@@ -1399,6 +1399,96 @@ DISC_DEV void ktranspose_body(const T* __restrict__ in, T* __restrict__ out, i64
   }
 }
 
+// A row reduce whose one full-size operand comes in transposed: instead of a transpose kernel, a buffer and
+// the row kernel, a block takes rpb rows of the result -- a strip of rpb columns of the operand
+// [batch][inner][A.aux0] -- and turns them on the way into its registers.  Slot j of all its lanes is a piece of G * V
+// operand rows: one 16-byte access per lane, all pieces at once, written to LDS by element and read back by row.
+// The row stays in registers as loaded through all phases and the epilogue, as in the streaming version (values
+// kept between the phases would take twice what is there).  The strips that share cache lines of the
+// operand are dealt to one XCD.
+// What bounds it: a strip of 16 or 32 bytes a row costs a cache line per access, and load, arithmetic and
+// stores of a block follow one another, so a CU needs several strips.  Two strips after one another in a block, the
+// second one loaded behind the first one's arithmetic, were no faster (8192 x 8192 99.9 us, 93.7 without).
+template <class Pat, int P, int V, int NV, class SP>
+DISC_DEV void row_xpose_phases(const typename Pat::Args& A, typename Pat::RowCtx& rc, typename Pat::template Slot<V> (&slot)[NV],
+                               int lane, int G, int inner) {
+  if constexpr (P < Pat::NPHASE) {
+    typename Pat::template Acc<P> acc;
+    Pat::template acc_init<P>(acc);
+    asm volatile("" : "+v"(lane));           // (columns are cheaper to compute again than to keep)
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const int col = (j * G + lane) * V;
+      typename Pat::template Keep<V> kp;
+      if (col < inner)
+        Pat::template phase<P, V, false>(A, acc, as_loaded<Pat, V>(slot[j]), kp, SP::upto(inner - col < V ? inner - col : V), col, rc);
+    }
+    group_allreduce<Pat, P>(acc, G);
+    Pat::template row_after<P>(A, rc, acc);
+    row_xpose_phases<Pat, P + 1, V, NV, SP>(A, rc, slot, lane, G, inner);
+  }
+}
+// A.aux0 = rows of a batch entry, A.aux1 = strips of one, A.aux2 = strips in all, A.aux3 = strips per XCD;
+// rp.flags = log2 of the 16-byte accesses of an operand row.  SP: EvenSpan where inner is a multiple of V.
+template <class Pat, int V, int NV, class SP>
+DISC_DEV void row_xpose_body(const typename Pat::Args& A, const RowPlan& rp) {
+  typedef typename Pat::XpT T;
+  static_assert(V * sizeof(T) == 16, "one 16-byte access per lane and piece");
+  constexpr int PAD = V;                                      // (rows of the tile on other banks, reads aligned)
+  __shared__ __attribute__((aligned(16))) T tile[2][1024 * V + 64 * PAD];
+  const int strip = (int)(blockIdx.x & 7) * (int)A.aux3 + (int)(blockIdx.x >> 3);      // (the grid is a multiple of 8)
+  if (strip >= (int)A.aux2) return;
+  const i64 Q = A.aux0;
+  const int P = (int)A.inner, G = rp.G, rpb = rp.rpb;
+  // (the last strip of a batch entry starts where it ends with the last row; the host sees to Q >= rpb)
+  const i64 batch = A.aux1 == A.aux2 ? 0 : (i64)((u32)strip / (u32)A.aux1);
+  const i64 q0 = (strip - batch * A.aux1) * rpb, first = q0 + rpb <= Q ? q0 : Q - rpb;
+  const int pitch = G * V + PAD;
+  const int tp = (int)threadIdx.x >> rp.flags, tq = ((int)threadIdx.x & ((1 << rp.flags) - 1)) * V;
+  const int lane = (int)threadIdx.x & (G - 1), grp = (int)threadIdx.x >> rp.log2G;
+  typename Pat::template Slot<V> slot[NV];                    // (first the pieces, then, from LDS, the slots)
+  {
+    const T* src = Pat::xp_src(A) + batch * P * Q + first;
+    const unsigned mine = (unsigned)tp * (unsigned)Q + (unsigned)tq;      // (fits in bytes: the host sees to it)
+#pragma unroll
+    for (int j = 0; j < NV; ++j)
+      if (j * G * V + tp < P)
+        Pat::template xp_slot<V>(slot[j]).v = *reinterpret_cast<const typename Vec<T, V>::unaligned_t*>(at(src + (i64)(j * G * V) * Q, mine));
+    asm volatile("" ::: "memory");                            // all loads before the first piece is turned
+  }
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    if (j * G * V < P) {
+      T* t = tile[j & 1];
+      Vec<T, V>& x = Pat::template xp_slot<V>(slot[j]);
+#pragma unroll
+      for (int e = 0; e < V; ++e) t[(tq + e) * pitch + tp] = x.get(e);
+      __syncthreads();
+      x.v = *reinterpret_cast<const typename Vec<T, V>::vec_t*>(t + grp * pitch + lane * V);
+    }
+  }
+  const bool active = first + grp >= q0;                      // (its first rows are the strip's before it)
+  const i64 row = batch * Q + first + grp;
+  typename Pat::RowCtx rc;
+  Pat::row_begin(A, row, rc);
+  rc.sl = nullptr;
+  row_xpose_phases<Pat, 0, V, NV, SP>(A, rc, slot, lane, G, P);
+  int l = lane;
+  asm volatile("" : "+v"(l));
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int col = (j * G + l) * V;
+    if (col < P) {
+      const SP sp = SP::upto(P - col < V ? P - col : V);
+      typename Pat::template OutSlot<V> o;
+      typename Pat::template Keep<V> kp;
+      Pat::template epilogue<V, false>(A, rc, as_loaded<Pat, V>(slot[j]), kp, col, sp, o);
+      if (active) Pat::template store<V>(A, rc, (unsigned)col, sp, o);
+    }
+  }
+  if (active && l == 0) Pat::row_store(A, row, rc);
+}
+
 // =======================================================================================
 // Input fusion with a column reduction as root (reduce over an outer axis).  Canonical
 // space [outer, mid, inner], `mid` reduced.  Three stages, no atomics, so results are

@@ -245,6 +245,7 @@ enum KernelId {
   K_COL_EPI2_VEC, K_COL_EPI2_VEC_NT, K_COL_EPI2_SCALAR,
   K_COMPACT_COUNT_VEC, K_COMPACT_COUNT_SCALAR, K_COMPACT_SCAN, K_COMPACT_SCATTER_VEC, K_COMPACT_SCATTER_SCALAR,
   K_COMPACT_SCATTER_VEC_NT, K_ROW_COLS_VEC, K_ROW_COLS_VEC_NT, K_COL_EPI2_VEC_NTS, K_ROW_STREAM_VECW,
+  K_ROW_XPOSE, K_ROW_XPOSE_LAST = K_ROW_XPOSE + 7,    // {4, 8, 12, 16 slots a lane} x {any row length, whole slots}
   K_ROW_BASE,
   K_COUNT = K_ROW_BASE + 96
 };
@@ -261,7 +262,12 @@ int kernel_id(const std::string& name);      // -1 when unknown (registration ti
 // Optional restriction of the generated module: only the named entry points (without prefix).
 struct GenOptions {
   std::vector<std::string> only_kernels;
+  int xpose_access = -1;     // row reduce: the input access that arrives transposed (row_xpose kernels only)
 };
+// Versions of a row reduce with a transposed operand: slots per lane
+constexpr int kXposeSlots[] = {4, 8, 12, 16};
+// The access of input `slot` when a row reduce can take it transposed, else -1 (codegen.cpp)
+int xpose_access(const Analysis& an, int slot);
 
 
 // checker.cpp: validate, close constraints, decide fusion, resolve contexts, collapse.

@@ -108,6 +108,9 @@ struct GraphGroup {
   // where each of those values lives at launch, resolved at registration: (kind, index) with kind
   // 0 = graph input, 1 = graph output, 2 = planned buffer
   std::vector<std::pair<int, int>> in_place, out_place;
+  // a row reduce that takes the result of the transpose pattern in front of it: the module whose kernels read
+  // the transpose's operand themselves (index into disc_ctx::fused, -1: none), and which input that is
+  int fused = -1, fused_input = -1;
 };
 struct GraphIntermediate {
   int value = -1;                // produced by group `first`, last read by group `last`
@@ -135,6 +138,7 @@ struct disc_ctx {
   int n_cus = 256;
   std::string err;
   std::vector<std::unique_ptr<Pattern>> patterns;
+  std::vector<std::unique_ptr<Pattern>> fused;   // row reduces of op graphs that take an operand transposed
   std::map<std::string, int> cache;
   disc_stats_t stats{};
   int force_variant = -1;
@@ -1058,6 +1062,48 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
   return DISC_OK;
 }
 
+// A row reduce with a transposed operand in one kernel: batch x per rows of `inner` elements.  false: two kernels.
+bool plan_xpose(const disc_ctx* c, int64_t per, int64_t batch, int64_t inner, int V, FullPlan* fp) {
+  // Strips of 8 rows (16 bytes of an operand row) in 512 threads; of 16 where that still leaves strips for the chip --
+  // fewer accesses to a cache line -- on 32 lanes a row, or 64 in 1024 threads for long rows; of 32 where there are
+  // thousands.  bf16 softmax, strips of 8 / 16 / 32, us: 1500 x 5000 (of the operand) 11.9 / 13.2 / 14.8, 2500 x 5000 17.6 /
+  // 18.6 / 22.1, 300 x 8192 6.2 / 5.7 / 5.6, 3000 x 8000 37.4 / 26.5 / -, 200 x 200000 76 / 45.5 / 38.1, 1000 x 60000 77 / 62 / 59.
+  // Against two kernels: 64 x 64 3.9 / 7.0, 1000 x 777 4.7 / 9.0, 2000 x 4000 11.5 / 17.3, 3000 x 8000 26.5 / 39.2, 4000 x 20000
+  // 86 / 119, 8192 x 8192 93.7 / 111.  Rows beyond 4096 elements leave one strip to a CU, whose load, arithmetic and stores
+  // follow one another: only with several strips for every CU (6000 x 4097 44.5 / 40.7, 8192 x 64 14.6 / 10.1, 5000 x 6200
+  // 45.2 / 49.2, 6000 x 7000 55.9 / 67.6).
+  const int64_t strips16 = (per + 15) / 16 * batch;
+  if (inner > 64 * V * 8 && strips16 < c->n_cus * 3 / 2) return false;
+  int G = 64, B = 512, nv = 0;
+  if (strips16 >= 8ll * c->n_cus && inner <= 16 * V * 12 && per >= 32) G = 16;
+  else if (strips16 >= c->n_cus * 7 / 4 || inner > 64 * V * 8) {
+    if (inner <= 32 * V * 12) G = 32;
+    else B = 1024;
+  }
+  for (int k : kXposeSlots)
+    if (nv == 0 && (int64_t)G * V * k >= inner) nv = k;
+  const int rpb = B / G;
+  if (nv == 0 || per < rpb || per > (1 << 18)) return false;
+  const int64_t strips = (per + rpb - 1) / rpb;
+  if (strips * batch > (1ll << 28)) return false;
+  LaunchRec& L = fp->launches[0];
+  L.kid = K_ROW_XPOSE + (nv / 4 - 1) * 2 + (inner % V == 0 ? 1 : 0);
+  L.block = (uint32_t)B;
+  L.plan_kind = 1;
+  L.rp.G = G;
+  L.rp.log2G = ilog2_ceil(G);
+  L.rp.nv = nv;
+  L.rp.flags = ilog2_ceil(rpb / V);
+  L.rp.rpb = rpb;
+  fp->aux[0] = per;
+  fp->aux[1] = strips;
+  fp->aux[2] = strips * batch;
+  fp->aux[3] = (strips * batch + 7) / 8;
+  L.grid[0] = (uint32_t)(fp->aux[3] * 8);
+  fp->pub.n_launches = 1;
+  return true;
+}
+
 int resident_blocks(const disc_ctx* c, const Pattern& p, int kid, uint32_t block, uint32_t dyn_lds) {
   const int estimate = std::max(1, 16 / (int)((block + 63) / 64));
   if (c->device < 0 || kid < 0 || kid >= K_COUNT || !p.fn[kid]) return estimate;
@@ -1258,6 +1304,8 @@ void disc_destroy(disc_ctx* ctx) {
   if (ctx->device >= 0) {
     for (auto& p : ctx->patterns)
       if (p->module) (void)hipModuleUnload(p->module);
+    for (auto& p : ctx->fused)
+      if (p->module) (void)hipModuleUnload(p->module);
     if (ctx->util_module) (void)hipModuleUnload(ctx->util_module);
   }
   delete ctx;
@@ -1322,6 +1370,28 @@ static std::string static_macros(const Pattern& p, const FullPlan& fp, const int
       << L.cp.chunk_rows << "LL; rp.outer = " << L.cp.outer << "LL; rp.epi_rows = " << L.cp.epi_rows << "LL;";
   a << "\n";
   return a.str();
+}
+
+// compiles the pattern's generated source and looks its kernels up
+static int load_module(disc_ctx* ctx, Pattern* p) {
+  std::vector<char> code;
+  const int rc = compile_source(ctx, p->gen.source, &code, &p->compile_ms);
+  p->compile_events = 1;
+  ctx->stats.compile_events++;
+  if (rc) return rc;
+  if (ctx->device >= 0) {
+    hipError_t e = hipModuleLoadData(&p->module, code.data());
+    if (e != hipSuccess) return hip_fail(ctx, e, "hipModuleLoadData");
+    for (const auto& name : p->gen.kernels) {
+      hipFunction_t f;
+      e = hipModuleGetFunction(&f, p->module, (p->gen.prefix + name).c_str());
+      if (e != hipSuccess) return hip_fail(ctx, e, ("hipModuleGetFunction " + name).c_str());
+      const int kid = kernel_id(name);
+      if (kid < 0) return set_err(ctx, DISC_ERR_COMPILE, "generated module holds an unnumbered kernel: " + name);
+      p->fn[kid] = f;
+    }
+  }
+  return DISC_OK;
 }
 
 static int register_impl(disc_ctx* ctx, const disc_op* ops, int n_ops, const disc_constraint* cs, int n_cs,
@@ -1440,23 +1510,8 @@ static int register_impl(disc_ctx* ctx, const disc_op* ops, int n_ops, const dis
     p->is_static = true;
     p->static_dims.assign(static_dims, static_dims + n_static_dims);
   }
-  std::vector<char> code;
-  rc = compile_source(ctx, p->gen.source, &code, &p->compile_ms);
-  p->compile_events = 1;
-  ctx->stats.compile_events++;
+  rc = load_module(ctx, p.get());
   if (rc) return rc;
-  if (ctx->device >= 0) {
-    hipError_t e = hipModuleLoadData(&p->module, code.data());
-    if (e != hipSuccess) return hip_fail(ctx, e, "hipModuleLoadData");
-    for (const auto& name : p->gen.kernels) {
-      hipFunction_t f;
-      e = hipModuleGetFunction(&f, p->module, (p->gen.prefix + name).c_str());
-      if (e != hipSuccess) return hip_fail(ctx, e, ("hipModuleGetFunction " + name).c_str());
-      const int kid = kernel_id(name);
-      if (kid < 0) return set_err(ctx, DISC_ERR_COMPILE, "generated module holds an unnumbered kernel: " + name);
-      p->fn[kid] = f;
-    }
-  }
   const int id = (int)ctx->patterns.size();
   ctx->cache[key] = id;
   ctx->patterns.push_back(std::move(p));
@@ -1555,6 +1610,33 @@ int disc_test_option(disc_ctx* ctx, int option, int value) {
 
 // own_need: the workspace has to hold what this launch uses (the static scratch array), not what
 // disc_workspace_bytes gives for operands of any alignment (a caller's workspace).
+// the planned launches of one call
+static int submit(disc_ctx* ctx, const Pattern* p, const FullPlan& fp, const int64_t* dims, const void* const* inputs,
+                  void* const* outputs, void* workspace, void* hip_stream) {
+  alignas(16) unsigned char buf[kArgBufBytes];
+  const int asz = p->gen.args.size;   // (fits: checked at registration)
+  fill_args(*p, fp, dims, inputs, outputs, workspace, buf);
+  for (int l = 0; l < fp.pub.n_launches; ++l) {
+    const LaunchRec& L = fp.launches[l];
+    const hipFunction_t fn = L.kid >= 0 && L.kid < K_COUNT ? p->fn[L.kid] : nullptr;
+    if (!fn) return set_err(ctx, DISC_ERR_HIP, std::string("kernel version missing: ") + kernel_name(L.kid));
+    size_t size = (size_t)asz;
+    if (L.plan_kind == 1) {
+      memcpy(buf + asz, &L.rp, sizeof L.rp);
+      size += sizeof L.rp;
+    } else if (L.plan_kind == 2) {
+      memcpy(buf + asz, &L.cp, sizeof L.cp);
+      size += sizeof L.cp;
+    }
+    void* extra[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, buf, HIP_LAUNCH_PARAM_BUFFER_SIZE, &size, HIP_LAUNCH_PARAM_END};
+    hipError_t e = hipModuleLaunchKernel(fn, L.grid[0], L.grid[1], L.grid[2], L.block, 1, 1, L.dyn_lds,
+                                         (hipStream_t)hip_stream, nullptr, extra);
+    if (e != hipSuccess) return hip_fail(ctx, e, "hipModuleLaunchKernel");
+    ctx->stats.device_launches++;
+  }
+  return DISC_OK;
+}
+
 static int launch_impl(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, const void* const* inputs, int n_in,
                        void* const* outputs, int n_out, void* workspace, size_t workspace_bytes, void* hip_stream, bool own_need) {
   const int64_t t0 = now_ns();
@@ -1587,27 +1669,8 @@ static int launch_impl(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dim
   if (need > 0 && (!workspace || workspace_bytes < need))
     return set_err(ctx, DISC_ERR_WORKSPACE, "workspace missing or too small");
 
-  alignas(16) unsigned char buf[kArgBufBytes];
-  const int asz = p->gen.args.size;   // (fits: checked at registration)
-  fill_args(*p, fp, dims, inputs, outputs, workspace, buf);
-  for (int l = 0; l < fp.pub.n_launches; ++l) {
-    const LaunchRec& L = fp.launches[l];
-    const hipFunction_t fn = L.kid >= 0 && L.kid < K_COUNT ? p->fn[L.kid] : nullptr;
-    if (!fn) return set_err(ctx, DISC_ERR_HIP, std::string("kernel version missing: ") + kernel_name(L.kid));
-    size_t size = (size_t)asz;
-    if (L.plan_kind == 1) {
-      memcpy(buf + asz, &L.rp, sizeof L.rp);
-      size += sizeof L.rp;
-    } else if (L.plan_kind == 2) {
-      memcpy(buf + asz, &L.cp, sizeof L.cp);
-      size += sizeof L.cp;
-    }
-    void* extra[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, buf, HIP_LAUNCH_PARAM_BUFFER_SIZE, &size, HIP_LAUNCH_PARAM_END};
-    hipError_t e = hipModuleLaunchKernel(fn, L.grid[0], L.grid[1], L.grid[2], L.block, 1, 1, L.dyn_lds,
-                                         (hipStream_t)hip_stream, nullptr, extra);
-    if (e != hipSuccess) return hip_fail(ctx, e, "hipModuleLaunchKernel");
-    ctx->stats.device_launches++;
-  }
+  rc = submit(ctx, p, fp, dims, inputs, outputs, workspace, hip_stream);
+  if (rc) return rc;
   ctx->stats.launch_calls++;
   if (fp.pub.variant >= 0 && fp.pub.variant < DISC_V_COUNT) ctx->stats.variant_count[fp.pub.variant]++;
   ctx->stats.host_launch_ns += now_ns() - t0;
@@ -1867,6 +1930,82 @@ int graph_layout(disc_ctx* ctx, const Graph& g, const int64_t* dims, int n_dims,
 }
 
 }  // namespace
+
+// Group gi is a transpose whose result only the row reduce behind it reads: a second module of that row
+// reduce, whose kernels read the transpose's operand.  Which route a call takes is decided per shape.
+static int register_fused(disc_ctx* ctx, Graph& g, size_t gi) {
+  const GraphGroup& t = g.groups[gi];
+  GraphGroup& r = g.groups[gi + 1];
+  if (ctx->patterns[t.pattern_id]->an.tmpl != DISC_TEMPLATE_TRANSPOSE || t.in_place.size() != 1 || t.out_values.size() != 1) return DISC_OK;
+  const int v = t.out_values[0];
+  const auto inter = g.inter_of_value.find(v);
+  if (inter == g.inter_of_value.end() || g.inter[inter->second].last != (int)gi + 1) return DISC_OK;
+  int input = -1;
+  for (size_t k = 0; k < r.in_values.size(); ++k)
+    if (r.in_values[k] == v) input = (int)k;
+  // (the operand is read while the results are written: it must not lie in a buffer that they reuse)
+  if (t.in_place[0].first == 2)
+    for (const auto& o : r.out_place)
+      if (o == t.in_place[0]) return DISC_OK;
+  const Pattern& base = *ctx->patterns[r.pattern_id];
+  const int access = input < 0 ? -1 : xpose_access(base.an, input);
+  if (access < 0) return DISC_OK;
+  std::unique_ptr<Pattern> p(new Pattern);
+  p->an = base.an;
+  p->eq_checks = base.eq_checks;
+  p->static_checks = base.static_checks;
+  p->class_of_dim = base.class_of_dim;
+  p->n_classes = base.n_classes;
+  p->io_numel = base.io_numel;
+  GenOptions opt;
+  opt.xpose_access = access;
+  std::string err;
+  int rc = generate(p->an, "disc_x" + std::to_string(ctx->fused.size()) + "_", &p->gen, &err, &opt);
+  if (rc) return set_err(ctx, rc, err);
+  p->gen.source = std::string(kDeviceHeader) + "\n" + p->gen.source;
+  rc = load_module(ctx, p.get());
+  if (rc) return rc;
+  r.fused = (int)ctx->fused.size();
+  r.fused_input = input;
+  ctx->fused.push_back(std::move(p));
+  return DISC_OK;
+}
+
+// The launch of group r with the transpose in front of it (group t) in the same kernel.  `taken`: false when
+// this call has to go through both patterns.
+static int launch_fused(disc_ctx* ctx, const GraphGroup& t, const GraphGroup& r, const int64_t* dims, const void* const* in,
+                        void* const* outp, void* hip_stream, bool* taken) {
+  *taken = false;
+  const int64_t t0 = now_ns();
+  if (ctx->device < 0 || ctx->force_variant >= 0) return DISC_OK;
+  const Pattern& tp = *ctx->patterns[t.pattern_id];
+  const Pattern& p = *ctx->fused[r.fused];
+  ShapeVals tv;
+  int rc = shape_calc(ctx, tp, dims, tp.an.n_sym, &tv);
+  if (rc) return rc;
+  FullPlan fp;
+  rc = shape_calc(ctx, p, dims, p.an.n_sym, &fp.sv);
+  if (rc) return rc;
+  const int ng = (int)tp.an.groups.size();
+  const int64_t per = tv.group[ng - 2], batch = ng == 3 ? tv.group[0] : 1;
+  const int V = p.an.vec_width;
+  if (fp.sv.rows == 0 || fp.sv.inner == 0 || fp.sv.rows != batch * per || fp.sv.inner != tv.group[ng - 1]) return DISC_OK;
+  if (!plan_xpose(ctx, per, batch, fp.sv.inner, V, &fp)) return DISC_OK;
+  const char* lo = static_cast<const char*>(in[r.fused_input]);
+  const char* hi = lo + fp.sv.rows * fp.sv.inner * dtype_bytes(tp.an.accesses[0].dtype);
+  for (const Access& a : p.an.accesses) {      // (through both patterns the operand was read before anything was written)
+    if (!a.is_output) continue;
+    const char* o = static_cast<const char*>(outp[a.slot]);
+    if (o < hi && lo < o + fp.sv.rows * (a.has_inner ? fp.sv.inner : 1) * dtype_bytes(a.dtype)) return DISC_OK;
+  }
+  ctx->stats.host_plan_ns += now_ns() - t0;
+  rc = submit(ctx, &p, fp, dims, in, outp, nullptr, hip_stream);
+  if (rc) return rc;
+  *taken = true;
+  ctx->stats.launch_calls++;
+  ctx->stats.host_launch_ns += now_ns() - t0;
+  return DISC_OK;
+}
 
 int disc_register_graph(disc_ctx* ctx, const disc_op* ops, int n_ops, const disc_constraint* cs, int n_cs,
                         int32_t* graph_id_out) {
@@ -2190,6 +2329,10 @@ int disc_register_graph(disc_ctx* ctx, const disc_op* ops, int n_ops, const disc
       return set_err(ctx, DISC_ERR_BAD_PATTERN, "too many operands in one pattern of the graph");
   }
   if (g->buffer_value.size() > (size_t)DISC_MAX_OPS) return set_err(ctx, DISC_ERR_BAD_PATTERN, "too many buffers");
+  for (size_t gi = 0; gi + 1 < g->groups.size(); ++gi) {
+    const int rc = register_fused(ctx, *g, gi);
+    if (rc) return rc;
+  }
   const int id = (int)ctx->graphs.size();
   ctx->graphs.push_back(std::move(g));
   *graph_id_out = id;
@@ -2247,7 +2390,28 @@ int disc_graph_launch(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims
   auto where = [&](const std::pair<int, int>& pl) -> void* {
     return pl.first == 0 ? const_cast<void*>(inputs[pl.second]) : pl.first == 1 ? outputs[pl.second] : ws + off[pl.second];
   };
-  for (const auto& gr : g->groups) {
+  for (size_t gi = 0; gi < g->groups.size(); ++gi) {
+    const GraphGroup& gr = g->groups[gi];
+    const GraphGroup* next = gi + 1 < g->groups.size() ? &g->groups[gi + 1] : nullptr;
+    if (next && next->fused >= 0) {
+      bool taken = true;
+      for (size_t k = 0; k < next->in_place.size(); ++k) {
+        in[k] = where(k == (size_t)next->fused_input ? gr.in_place[0] : next->in_place[k]);
+        taken = taken && in[k];
+      }
+      for (size_t k = 0; k < next->out_place.size(); ++k) {
+        outp[k] = where(next->out_place[k]);
+        taken = taken && outp[k];
+      }
+      if (taken) {
+        rc = launch_fused(ctx, gr, *next, dims, in, outp, hip_stream, &taken);
+        if (rc) return rc;
+        if (taken) {
+          ++gi;
+          continue;
+        }
+      }
+    }
     const int ni = (int)gr.in_place.size(), no = (int)gr.out_place.size();
     for (int k = 0; k < ni; ++k) {
       in[k] = where(gr.in_place[k]);
