@@ -1329,6 +1329,92 @@ DISC_DEV void colsum_finish_body(const typename Pat::Args& A) {
 // LDS write.  The LDS row pitch is an odd number of dwords, so the column-wise element reads of
 // the second half spread over the banks.
 // =======================================================================================
+// -> batch entry of tile t, and its first row and column in the result
+DISC_DEV i64 transpose_place(i64 t, i64 tiles_p, i64 tiles_q, int TP, int TQ, i64& p0, i64& q0) {
+  const i64 per_batch = tiles_p * tiles_q;
+  const i64 b = t / per_batch;
+  const i64 r = t - b * per_batch;
+  // consecutive blocks walk a diagonal of the tile grid: with a power-of-two row pitch the tiles
+  // of one tile row (or column) would otherwise queue up on the same memory channels
+  const i64 tq = r / tiles_p;
+  i64 tp = r - tq * tiles_p + tq;
+  if (tp >= tiles_p) tp %= tiles_p;
+  p0 = tp * TP;
+  q0 = tq * TQ;
+  return b;
+}
+// Two-byte elements: tiles of TP result rows x TQ result columns.  A lane loads the same eight elements of two operand
+// rows, packs those that will be neighbours into dwords and writes these, so that the other half reads whole
+// 16-byte pieces: ten LDS accesses per 16 elements in place of 32.  The dword of row pair r and column c lies at
+// r ^ (c / 8 << 2): the accesses that a wavefront makes side by side fall on all banks.
+// Bound by memory, and by how evenly the tiles spread over its channels; bf16, us, single elements through LDS / packed,
+// 128 x 128 / packed, 128 x 64: 1000 x 1000 7.0 / 6.9 / 4.6, 4000 x 4001 16.1 / 16.1 / 14.2, 30000 x 500 19.2 / 16.0 / 14.4, 6000 x
+// 4097 with a softmax behind it 40.7 / 40.2 / 39.3; 8192 x 8192 62 / 62 / 67.7, 5000 x 9000 52.7 / - / 62.7, 16384 x 8192 121 / -
+// / 144.  (64 x 128: 42.1 and 65.4, 64 x 64: 42.6 and 56.6 at 6000 x 4097 and 8192 x 8192.)
+template <int TP, int TQ, class T>
+DISC_DEV void ktranspose2_body(const T* __restrict__ in, T* __restrict__ out, i64 batch, i64 P, i64 Q) {
+  static_assert(sizeof(T) == 2 && TP == 128 && (TQ == 64 || TQ == 128), "two-byte elements");
+  constexpr int VP = TP / 8, VQ = TQ / 8, PQ = TQ / 2;
+  constexpr int NP = PQ * VP / 256, NR = TP * VQ / 256;      // pairs of 16-byte loads, and stores, of a lane
+  typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(16))) u32 tile[TP * PQ];
+  const i64 tiles_p = (P + TP - 1) / TP, tiles_q = (Q + TQ - 1) / TQ;
+  const i64 ntiles = batch * tiles_p * tiles_q;
+  const int v = (int)threadIdx.x % VP, g = (int)threadIdx.x / VP, vq = (int)threadIdx.x % VQ, c0 = (int)threadIdx.x / VQ;
+  for (i64 t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    i64 p0, q0;
+    const i64 b = transpose_place(t, tiles_p, tiles_q, TP, TQ, p0, q0);
+    const T* src = in + b * P * Q;
+    T* dst = out + b * P * Q;
+    Vec<T, 8> x[NP][2];
+#pragma unroll
+    for (int k = 0; k < NP; ++k)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {               // row q of the operand, elements p ...
+        const i64 q = q0 + 2 * (g + 256 / VP * k) + h, p = p0 + v * 8;
+        if (q < Q) {
+          if (p + 8 <= P) {
+            x[k][h].v = *reinterpret_cast<const typename Vec<T, 8>::unaligned_t*>(src + q * P + p);
+          } else {
+            x[k][h].clear();
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (p + e < P) x[k][h].set(e, src[q * P + p + e]);
+          }
+        }
+      }
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      const u32x4 lo = __builtin_bit_cast(u32x4, x[k][0].v), hi = __builtin_bit_cast(u32x4, x[k][1].v);
+      u32* at = tile + v * 8 * PQ + ((g + 256 / VP * k) ^ ((v << 2) & (PQ - 1)));
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        at[(2 * w) * PQ] = __builtin_amdgcn_perm(hi[w], lo[w], 0x05040100);
+        at[(2 * w + 1) * PQ] = __builtin_amdgcn_perm(hi[w], lo[w], 0x07060302);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {                // row p of the result, elements q ...
+      const int c = c0 + 256 / VQ * k;
+      const i64 p = p0 + c, q = q0 + vq * 8;
+      Vec<T, 8> o;
+      o.v = __builtin_bit_cast(typename Vec<T, 8>::vec_t,
+                               *reinterpret_cast<const u32x4*>(tile + c * PQ + ((vq << 2) ^ (((c >> 3) << 2) & (PQ - 1)))));
+      if (p < P) {
+        if (q + 8 <= Q) {
+          *reinterpret_cast<typename Vec<T, 8>::unaligned_t*>(dst + p * Q + q) = o.v;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (q + e < Q) dst[p * Q + q + e] = o.get(e);
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
 template <class T>
 DISC_DEV void ktranspose_body(const T* __restrict__ in, T* __restrict__ out, i64 batch, i64 P, i64 Q) {
   constexpr int VE = 16 / (int)sizeof(T);                    // elements per 16-byte access
@@ -1338,17 +1424,10 @@ DISC_DEV void ktranspose_body(const T* __restrict__ in, T* __restrict__ out, i64
   constexpr int NVEC = TS * VPR / 256;                       // pieces per lane and tile
   __shared__ __attribute__((aligned(16))) T tile[TS][TS + PAD];
   const i64 tiles_p = (P + TS - 1) / TS, tiles_q = (Q + TS - 1) / TS;
-  const i64 per_batch = tiles_p * tiles_q;
-  const i64 ntiles = batch * per_batch;
+  const i64 ntiles = batch * tiles_p * tiles_q;
   for (i64 t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const i64 b = t / per_batch;
-    const i64 r = t - b * per_batch;
-    // consecutive blocks walk a diagonal of the tile grid: with a power-of-two row pitch the tiles
-    // of one tile row (or column) would otherwise queue up on the same memory channels
-    const i64 tq = r / tiles_p;
-    i64 tp = r - tq * tiles_p + tq;
-    if (tp >= tiles_p) tp %= tiles_p;
-    const i64 p0 = tp * TS, q0 = tq * TS;
+    i64 p0, q0;
+    const i64 b = transpose_place(t, tiles_p, tiles_q, TS, TS, p0, q0);
     const T* src = in + b * P * Q;
     T* dst = out + b * P * Q;
     Vec<T, VE> piece[NVEC];

@@ -410,9 +410,12 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     const int64_t P = sv.group[ng - 2], Q = sv.group[ng - 1], batch = ng == 3 ? sv.group[0] : 1;
     // tiles of 256 bytes per row: 128 x 128 elements of one or two bytes, 64 x 64 wider ones
     const int64_t ts = dtype_bytes(an.accesses[0].dtype) <= 2 ? 128 : 64;
-    const int64_t ntiles = batch * ((P + ts - 1) / ts) * ((Q + ts - 1) / ts);
+    int64_t ntiles = batch * ((P + ts - 1) / ts) * ((Q + ts - 1) / ts);
+    // two-byte elements, tensors that the memory-side cache can hold: half tiles (see the kernel)
+    const bool half = dtype_bytes(an.accesses[0].dtype) == 2 && sv.alg_bytes < 2 * kNonTemporalMinBytes;
+    if (half) ntiles = batch * ((P + 127) / 128) * ((Q + 63) / 64);
     LaunchRec& L = fp->launches[0];
-    L.kid = K_TRANSPOSE_TILE;
+    L.kid = half ? K_TRANSPOSE_TILE_H : K_TRANSPOSE_TILE;
     L.block = 256;
     L.grid[0] = (uint32_t)std::min<int64_t>(ntiles, (int64_t)c->n_cus * 8);
     pub.variant = DISC_V_TRANSPOSE_TILE;

@@ -165,3 +165,33 @@ def test_tile_transpose_matches_oracle():
             assert_close(out.cpu(), want, f"transpose + softmax graph dims={dims}")
     finally:
         ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_packed_tiles_of_two_byte_elements(dtype):
+    """Edges of the 128 x 64 and 128 x 128 tiles, rows at any alignment, batches; a copy of all 65536 bit patterns."""
+    from paper_2103_05288_amd import Context
+    ctx = Context(0)
+    try:
+        for perm, shapes, kernel in (
+                ((1, 0), [[64, 128], [63, 127], [65, 129], [1, 1], [1, 300], [300, 1], [8, 8], [7, 1025], [129, 8], [255, 257],
+                          [66, 4099]], "k_transpose_tile_h"),
+                ((0, 2, 1), [[5, 65, 131], [300, 3, 5], [2, 1, 129]], "k_transpose_tile_h"),
+                ((1, 0), [[5801, 5795], [33, 1100003], [1100009, 31]], "k_transpose_tile"),
+                ((0, 2, 1), [[3, 3201, 3577]], "k_transpose_tile")):
+            h = ctx.register(pure_transpose(dtype, perm))
+            for dims in shapes:
+                assert h.plan(dims)["kernels"][0].endswith("_" + kernel), dims
+                n = 1
+                for d in dims:
+                    n *= d
+                x = (torch.arange(n, device="cuda") * 40503 % 65536).to(torch.uint16).view(TORCH_DTYPE[dtype]).reshape(dims)
+                want = x.permute(perm).contiguous()
+                out = torch.empty(n + 16, dtype=torch.int16, device="cuda").fill_(-21555)
+                h.launch(dims, [x], [out[8:n + 8].view(TORCH_DTYPE[dtype]).reshape(want.shape)])
+                torch.cuda.synchronize()
+                assert torch.equal(out[8:n + 8], want.view(torch.int16).reshape(-1)), (dtype, perm, dims)
+                assert bool((out[:8] == -21555).all()) and bool((out[n + 8:] == -21555).all()), (dtype, perm, dims)
+    finally:
+        ctx.close()
