@@ -1071,10 +1071,11 @@ bool plan_xpose(const disc_ctx* c, int64_t per, int64_t batch, int64_t inner, in
   // fewer accesses to a cache line -- on 32 lanes a row, or 64 in 1024 threads for long rows; of 32 where there are
   // thousands.  bf16 softmax, strips of 8 / 16 / 32, us: 1500 x 5000 (of the operand) 11.9 / 13.2 / 14.8, 2500 x 5000 17.6 /
   // 18.6 / 22.1, 300 x 8192 6.2 / 5.7 / 5.6, 3000 x 8000 37.4 / 26.5 / -, 200 x 200000 76 / 45.5 / 38.1, 1000 x 60000 77 / 62 / 59.
-  // Against two kernels: 64 x 64 3.9 / 7.0, 1000 x 777 4.7 / 9.0, 2000 x 4000 11.5 / 17.3, 3000 x 8000 26.5 / 39.2, 4000 x 20000
-  // 86 / 119, 8192 x 8192 93.7 / 111.  Rows beyond 4096 elements leave one strip to a CU, whose load, arithmetic and stores
-  // follow one another: only with several strips for every CU (6000 x 4097 44.5 / 40.7, 8192 x 64 14.6 / 10.1, 5000 x 6200
-  // 45.2 / 49.2, 6000 x 7000 55.9 / 67.6).
+  // Against two kernels: 2000 x 100 5.4 / 8.0, 1000 x 8000 9.5 / 15.1, 2000 x 4000 11.4 / 15.5, 3000 x 2001 11.5 / 15.5, 3500 x 5000
+  // 23.0 / 34.2, 8192 x 8192 93.2 / 110.4.  Rows beyond 4096 elements leave one strip to a CU, whose load, arithmetic and
+  // stores follow one another: only with several strips for every CU (6000 x 4097 44.5 / 39.4, 8192 x 64 14.6 / 10.1, 5000 x
+  // 6200 45.2 / 50.4, 6000 x 7000 55.9 / 67.9).  (4000 x 300 9.7 / 9.2 and 4000 x 800 12.0 / 11.0 are on the wrong side of the
+  // line; 4000 x 1200 12.5 / 12.7, 3200 x 500 8.5 / 9.7, 3600 x 1000 11.4 / 11.8.)
   const int64_t strips16 = (per + 15) / 16 * batch;
   if (inner > 64 * V * 8 && strips16 < c->n_cus * 3 / 2) return false;
   int G = 64, B = 512, nv = 0;
