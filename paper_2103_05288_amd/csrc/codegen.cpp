@@ -1271,7 +1271,6 @@ struct Gen {
         k("k_row_stream_vec", fmt("disc::row_stream_body<Pat, %d, %d>(A);", V, kStreamHeldSlots), nullptr);
       }
       max_threads = 256;
-      max_threads = 512;
       if (an.n_col_sums > 0) k("k_colsum_finish", "disc::colsum_finish_body<Pat>(A);", nullptr);
       max_threads = 1024;
       if (an.n_row_reds > 0) k("k_rowred_finish", "disc::rowred_finish_body<Pat>(A);", nullptr);

@@ -1245,48 +1245,56 @@ DISC_DEV void rowred_finish_body(const typename Pat::Args& A) {
 // Second launch of a row reduce with sums over the rows: adds up the P rows of partial sums of
 // every summed output, in a fixed order (the result does not depend on timing) and in fp64
 // (partial sums in fp32 each cover the rows of one block only).  A block takes 16 columns; its 256
-// or (from 128 partial rows on) 512 lanes are 16 columns x 16 or 32 lanes that each walk every 16th or 32nd partial
-// row of all sums together, eight loads in flight, the ones past the last row from that row instead (a tail
-// of single loads is a chain of trips to memory); the lanes of a column meet by lane exchanges, then in LDS.
-// Bound by those trips.  Whole calls, 256 lanes with such a tail / 256 / 512 / 1024: LayerNorm backward 32768 x 1024 (767 partial
-// rows, two sums) 47.0 us / 47.1 / 44.7 / 45.0, 65536 x 128 24.5 / 24.7 / 22.2 / 22.0, 2000 x 768 (250 rows) 13.9 / 13.5 / 12.8 / 12.9;
-// GELU backward 8192 x 16384 (16 rows) 134.7 / 135.1 / 136.6 / 138.5.  With branches around the loads they
-// came one by one: 64.5.
+// lanes are 16 columns x 16 lanes that each walk every 16th partial row of all sums together, sixteen
+// loads in flight, the ones past the last row from a lane's last row instead (a tail of single loads is a chain of trips
+// to memory); the lanes of a column meet by lane exchanges, then in LDS.
+// Bound by those trips.  Whole calls, us, four loads in flight a lane and sum and a tail of single ones / this: LayerNorm
+// backward (two sums) 32768 x 1024 (767 partial rows) 47.3 / 45.7, 65536 x 128 24.6 / 22.9, 2000 x 768 (250) 13.8 / 13.0, 100 x 1024
+// 8.6 / 8.2; GELU backward 3000 x 2048 11.4 / 11.4, 8192 x 16384 (16) 135.8 / 136.6.  512 lanes, 32 to a column, with eight loads: 44.8,
+// 22.2, 12.8, but 9.0 and 11.9 for the small ones.  All loads clamped, not the last batch alone: 100 x 1024 9.0, 3000 x 2048
+// 12.2.  With branches around the loads they came one by one: 64.5.
 constexpr int kColsumCols = 16;
 template <class Pat, class PART>
 DISC_DEV void colsum_add_up(const typename Pat::Args& A) {
   constexpr int NQ = Pat::NCOLSUM, CL = kColsumCols;
-  __shared__ double red[NQ][16][CL];
-  const int cl = (int)threadIdx.x % CL, pl = (int)threadIdx.x / CL, PL = (int)blockDim.x / CL;
+  __shared__ double red[NQ][4][CL];
+  const int cl = (int)threadIdx.x % CL, pl = (int)threadIdx.x / CL;
+  constexpr int PL = 256 / CL;
   const i64 inner = A.inner, P = A.aux0;
   const PART* ws = reinterpret_cast<const PART*>(A.ws0);
   for (i64 c0 = (i64)blockIdx.x * CL; c0 < inner; c0 += (i64)gridDim.x * CL) {
     const i64 col = c0 + cl;
-    constexpr int U = NQ >= 2 ? 4 : 8;            // partial rows in flight per lane and sum
+    constexpr int U = NQ >= 2 ? 8 : 16, UT = U / 2;    // partial rows in flight per lane and sum; ... behind the whole batches
     double acc[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
     if (col < inner) {
-      const PART* src = ws + col;
-      const i64 plane = P * inner;
-      i64 p = pl;
-      if (P > 2 * PL) {
-        for (; p < P; p += U * PL) {
-          PART x[NQ][U];
+      const i64 plane = P * inner, step = PL * inner;
+      const PART* src = ws + col + pl * inner;
+      int n = pl < P ? (int)((P - pl + PL - 1) / PL) : 0;   // this lane's partial rows
+      for (; n >= U; n -= U) {
+        PART x[NQ][U];
 #pragma unroll
-          for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u, src += step)
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) x[q][u] = src[q * plane + (p + u * PL < P ? p + u * PL : P - 1) * inner];
+          for (int q = 0; q < NQ; ++q) x[q][u] = src[q * plane];
 #pragma unroll
-          for (int q = 0; q < NQ; ++q)
+        for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int u = 0; u < U; ++u) acc[q] += p + u * PL < P ? (double)x[q][u] : 0.0;
+          for (int u = 0; u < U; ++u) acc[q] += (double)x[q][u];
+      }
+      for (; n > 0; n -= UT) {
+        PART x[NQ][UT];
+#pragma unroll
+        for (int u = 0; u < UT; ++u) {
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) x[q][u] = src[q * plane];
+          src += u + 1 < n ? step : 0;
         }
-      } else {                                    // one or two rows for every lane
-        for (; p < P; p += PL) {
 #pragma unroll
-          for (int q = 0; q < NQ; ++q) acc[q] += (double)src[q * plane + p * inner];
-        }
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+          for (int u = 0; u < UT; ++u) acc[q] += u < n ? (double)x[q][u] : 0.0;
       }
     }
 #pragma unroll
@@ -1301,7 +1309,8 @@ DISC_DEV void colsum_add_up(const typename Pat::Args& A) {
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
         double t = 0.0;
-        for (int k = 0; k < PL / 4; ++k) t += red[q][k][cl];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t += red[q][k][cl];
         v[q] = (float)t;
       }
       Pat::colsum_store(A, col, v);

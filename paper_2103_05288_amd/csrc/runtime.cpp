@@ -846,8 +846,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       fp->ws_off[0] = 0;
       LaunchRec& L1 = fp->launches[1];
       L1.kid = K_COLSUM_FINISH;
-      // (more lanes to a column where it has a few dozen rows of partial sums for each of them, see the kernel)
-      L1.block = fp->aux[0] >= 128 ? 512 : 256;
+      L1.block = 256;
       L1.grid[0] = (uint32_t)std::min<int64_t>((sv.inner + 15) / 16, max_grid * 4);   // 16 columns per block
       pub.n_launches = 2;
     }
