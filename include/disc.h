@@ -281,7 +281,8 @@ int disc_pattern_info(disc_ctx* ctx, int32_t id, disc_pattern_info_t* out);
 const char* disc_pattern_source(disc_ctx* ctx, int32_t id);
 
 /* Bytes of device workspace disc_launch needs at these dims, whatever the alignment of its operands
- * (0 for loop patterns and for row patterns without sums over the rows).  Buffer sizes are a result of the host-side shape
+ * (0 for loop patterns and for row patterns without sums over the rows; a column reduce of at most 2^20 elements also
+ * runs without it, in one launch where two would be faster).  Buffer sizes are a result of the host-side shape
  * calculation (Section 4.2.1) and the buffers come from the caller (Section 4.2.2: the framework's
  * allocator owns the memory). */
 int disc_workspace_bytes(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, size_t* out);
