@@ -1250,7 +1250,7 @@ DISC_DEV void rowred_finish_body(const typename Pat::Args& A) {
 // to memory); the lanes of a column meet by lane exchanges, then in LDS.
 // Bound by those trips.  Whole calls, us, four loads in flight a lane and sum and a tail of single ones / this: LayerNorm
 // backward (two sums) 32768 x 1024 (767 partial rows) 47.3 / 45.7, 65536 x 128 24.6 / 22.9, 2000 x 768 (250) 13.8 / 13.0, 100 x 1024
-// 8.6 / 8.2; GELU backward 3000 x 2048 11.4 / 11.4, 8192 x 16384 (16) 135.8 / 136.6.  512 lanes, 32 to a column, with eight loads: 44.8,
+// 8.6 / 8.2; GELU backward 3000 x 2048 11.5 / 11.5, 8192 x 16384 (16) 135.4 / 135.4, 136.6 in batches.  512 lanes, 32 to a column, with eight loads: 44.8,
 // 22.2, 12.8, but 9.0 and 11.9 for the small ones.  All loads clamped, not the last batch alone: 100 x 1024 9.0, 3000 x 2048
 // 12.2.  With branches around the loads they came one by one: 64.5.
 constexpr int kColsumCols = 16;
@@ -1282,6 +1282,11 @@ DISC_DEV void colsum_add_up(const typename Pat::Args& A) {
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
           for (int u = 0; u < U; ++u) acc[q] += (double)x[q][u];
+      }
+      if (P <= 2 * PL) {                          // one or two rows for every lane
+        for (; n > 0; --n, src += step)
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) acc[q] += (double)src[q * plane];
       }
       for (; n > 0; n -= UT) {
         PART x[NQ][UT];
