@@ -138,7 +138,8 @@ struct disc_ctx {
   int n_cus = 256;
   std::string err;
   std::vector<std::unique_ptr<Pattern>> patterns;
-  std::vector<std::unique_ptr<Pattern>> fused;   // row reduces of op graphs that take an operand transposed
+  std::vector<std::unique_ptr<Pattern>> fused;   // row reduces of op graphs that take an operand transposed ...
+  std::map<std::pair<int, int>, int> fused_of;   // ... by pattern and input: compiled once, shared by all graphs
   std::map<std::string, int> cache;
   disc_stats_t stats{};
   int force_variant = -1;
@@ -1953,6 +1954,12 @@ static int register_fused(disc_ctx* ctx, Graph& g, size_t gi) {
   const Pattern& base = *ctx->patterns[r.pattern_id];
   const int access = input < 0 ? -1 : xpose_access(base.an, input);
   if (access < 0) return DISC_OK;
+  const auto known = ctx->fused_of.find({r.pattern_id, input});
+  if (known != ctx->fused_of.end()) {
+    r.fused = known->second;
+    r.fused_input = input;
+    return DISC_OK;
+  }
   std::unique_ptr<Pattern> p(new Pattern);
   p->an = base.an;
   p->eq_checks = base.eq_checks;
@@ -1971,6 +1978,7 @@ static int register_fused(disc_ctx* ctx, Graph& g, size_t gi) {
   r.fused = (int)ctx->fused.size();
   r.fused_input = input;
   ctx->fused.push_back(std::move(p));
+  ctx->fused_of[{r.pattern_id, input}] = r.fused;
   return DISC_OK;
 }
 

@@ -56,6 +56,25 @@ def two_operands():
     return pb.build()
 
 
+def test_registered_again_compiles_nothing():
+    """The kernels of a row reduce over a transposed operand are compiled once in a context, whatever graphs use them."""
+    from paper_2103_05288_amd import Context
+    c = Context(-1)
+    try:
+        c.register_graph(softmax("bf16"))
+        before = c.stats()["compile_events"]
+        assert before == 3                         # transpose, row reduce, row reduce over the transposed operand
+        c.register_graph(softmax("bf16"))
+        assert c.stats()["compile_events"] == before
+        c.register_graph(softmax("f32"))           # another pattern
+        assert c.stats()["compile_events"] == before + 3
+        c.register_graph(softmax("f32"))
+        c.register_graph(softmax("bf16"))
+        assert c.stats()["compile_events"] == before + 3
+    finally:
+        c.close()
+
+
 @pytest.fixture(scope="module")
 def ctx():
     from paper_2103_05288_amd import Context
