@@ -139,7 +139,7 @@ struct disc_ctx {
   std::string err;
   std::vector<std::unique_ptr<Pattern>> patterns;
   std::vector<std::unique_ptr<Pattern>> fused;   // row reduces of op graphs that take an operand transposed ...
-  std::map<std::pair<int, int>, int> fused_of;   // ... by pattern and input: compiled once, shared by all graphs
+  std::map<std::pair<int, int>, int> fused_of;   // ... by pattern and input: compiled once, shared by all graphs (-1: it could not be)
   std::map<std::string, int> cache;
   disc_stats_t stats{};
   int force_variant = -1;
@@ -1935,31 +1935,8 @@ int graph_layout(disc_ctx* ctx, const Graph& g, const int64_t* dims, int n_dims,
 
 }  // namespace
 
-// Group gi is a transpose whose result only the row reduce behind it reads: a second module of that row
-// reduce, whose kernels read the transpose's operand.  Which route a call takes is decided per shape.
-static int register_fused(disc_ctx* ctx, Graph& g, size_t gi) {
-  const GraphGroup& t = g.groups[gi];
-  GraphGroup& r = g.groups[gi + 1];
-  if (ctx->patterns[t.pattern_id]->an.tmpl != DISC_TEMPLATE_TRANSPOSE || t.in_place.size() != 1 || t.out_values.size() != 1) return DISC_OK;
-  const int v = t.out_values[0];
-  const auto inter = g.inter_of_value.find(v);
-  if (inter == g.inter_of_value.end() || g.inter[inter->second].last != (int)gi + 1) return DISC_OK;
-  int input = -1;
-  for (size_t k = 0; k < r.in_values.size(); ++k)
-    if (r.in_values[k] == v) input = (int)k;
-  // (the operand is read while the results are written: it must not lie in a buffer that they reuse)
-  if (t.in_place[0].first == 2)
-    for (const auto& o : r.out_place)
-      if (o == t.in_place[0]) return DISC_OK;
-  const Pattern& base = *ctx->patterns[r.pattern_id];
-  const int access = input < 0 ? -1 : xpose_access(base.an, input);
-  if (access < 0) return DISC_OK;
-  const auto known = ctx->fused_of.find({r.pattern_id, input});
-  if (known != ctx->fused_of.end()) {
-    r.fused = known->second;
-    r.fused_input = input;
-    return DISC_OK;
-  }
+// The module of row reduce `base` with its input `access` transposed; null when it cannot be had.
+static std::unique_ptr<Pattern> fused_module(disc_ctx* ctx, const Pattern& base, int access) {
   std::unique_ptr<Pattern> p(new Pattern);
   p->an = base.an;
   p->eq_checks = base.eq_checks;
@@ -1970,16 +1947,46 @@ static int register_fused(disc_ctx* ctx, Graph& g, size_t gi) {
   GenOptions opt;
   opt.xpose_access = access;
   std::string err;
-  int rc = generate(p->an, "disc_x" + std::to_string(ctx->fused.size()) + "_", &p->gen, &err, &opt);
-  if (rc) return set_err(ctx, rc, err);
+  if (generate(p->an, "disc_x" + std::to_string(ctx->fused.size()) + "_", &p->gen, &err, &opt)) return nullptr;
   p->gen.source = std::string(kDeviceHeader) + "\n" + p->gen.source;
-  rc = load_module(ctx, p.get());
-  if (rc) return rc;
-  r.fused = (int)ctx->fused.size();
+  const std::string before = ctx->err;
+  if (load_module(ctx, p.get())) {
+    ctx->err = before;
+    if (p->module) (void)hipModuleUnload(p->module);
+    return nullptr;
+  }
+  return p;
+}
+
+// Group gi is a transpose whose result only the row reduce behind it reads: a second module of that row
+// reduce, whose kernels read the transpose's operand.  Which route a call takes is decided per shape; without
+// the module every call takes both patterns.
+static void register_fused(disc_ctx* ctx, Graph& g, size_t gi) {
+  const GraphGroup& t = g.groups[gi];
+  GraphGroup& r = g.groups[gi + 1];
+  if (ctx->patterns[t.pattern_id]->an.tmpl != DISC_TEMPLATE_TRANSPOSE || t.in_place.size() != 1 || t.out_values.size() != 1) return;
+  const int v = t.out_values[0];
+  const auto inter = g.inter_of_value.find(v);
+  if (inter == g.inter_of_value.end() || g.inter[inter->second].last != (int)gi + 1) return;
+  int input = -1;
+  for (size_t k = 0; k < r.in_values.size(); ++k)
+    if (r.in_values[k] == v) input = (int)k;
+  // (the operand is read while the results are written: it must not lie in a buffer that they reuse)
+  if (t.in_place[0].first == 2)
+    for (const auto& o : r.out_place)
+      if (o == t.in_place[0]) return;
+  const Pattern& base = *ctx->patterns[r.pattern_id];
+  const int access = input < 0 ? -1 : xpose_access(base.an, input);
+  if (access < 0) return;
+  const std::pair<int, int> key{r.pattern_id, input};
+  auto known = ctx->fused_of.find(key);
+  if (known == ctx->fused_of.end()) {
+    std::unique_ptr<Pattern> p = fused_module(ctx, base, access);
+    known = ctx->fused_of.emplace(key, p ? (int)ctx->fused.size() : -1).first;
+    if (p) ctx->fused.push_back(std::move(p));
+  }
+  r.fused = known->second;
   r.fused_input = input;
-  ctx->fused.push_back(std::move(p));
-  ctx->fused_of[{r.pattern_id, input}] = r.fused;
-  return DISC_OK;
 }
 
 // The launch of group r with the transpose in front of it (group t) in the same kernel.  `taken`: false when
@@ -2340,10 +2347,7 @@ int disc_register_graph(disc_ctx* ctx, const disc_op* ops, int n_ops, const disc
       return set_err(ctx, DISC_ERR_BAD_PATTERN, "too many operands in one pattern of the graph");
   }
   if (g->buffer_value.size() > (size_t)DISC_MAX_OPS) return set_err(ctx, DISC_ERR_BAD_PATTERN, "too many buffers");
-  for (size_t gi = 0; gi + 1 < g->groups.size(); ++gi) {
-    const int rc = register_fused(ctx, *g, gi);
-    if (rc) return rc;
-  }
+  for (size_t gi = 0; gi + 1 < g->groups.size(); ++gi) register_fused(ctx, *g, gi);
   const int id = (int)ctx->graphs.size();
   ctx->graphs.push_back(std::move(g));
   *graph_id_out = id;

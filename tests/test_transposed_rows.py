@@ -75,6 +75,25 @@ def test_registered_again_compiles_nothing():
         c.close()
 
 
+def test_a_failing_compile_of_the_one_kernel_leaves_two(tmp_path):
+    """The module of the fused kernel is an option: where it cannot be compiled the graph is registered all the same."""
+    import os
+    import struct
+    import subprocess
+    from paper_2103_05288_amd.binding import lib_path, marshal_pattern
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    exe, path = tmp_path / "optional_compile_fails", tmp_path / "graph"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(root, "include"),
+                    "-o", str(exe), os.path.join(root, "tests", "cpp", "optional_compile_fails.cpp"), lib_path(), "-L/opt/rocm/lib", "-lhiprtc",
+                    "-ldl", "-Wl,-rpath," + os.path.dirname(lib_path()), "-Wl,-rpath,/opt/rocm/lib"], check=True)
+    pat = softmax("bf16")
+    ops, n_ops, cs, n_cs = marshal_pattern(pat)
+    path.write_bytes(struct.pack("<iii", n_ops, n_cs, pat.n_dims) + bytes(ops) + (bytes(cs)[: n_cs * 20] if n_cs else b""))
+    r = subprocess.run([str(exe), str(path)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.returncode, r.stderr)
+    assert r.stdout.strip() == "compiles=3 failed=1 again=0"
+
+
 @pytest.fixture(scope="module")
 def ctx():
     from paper_2103_05288_amd import Context
