@@ -268,7 +268,8 @@ int disc_register_pattern(disc_ctx* ctx, const disc_op* ops, int n_ops, const di
                           int n_cs, int32_t* pattern_id_out);
 /* The same pattern compiled for ONE shape, the way a static-shape compiler would (Section 1 and
  * Section 5.3: the recompile-per-shape alternative, and the gap of the shape-generic kernels to
- * it).  `dims` (host, n_dims values, copied) are planned with the same host rules as any launch;
+ * it).  `dims` (host, n_dims values, copied) are planned with the same host rules as any launch
+ * (column reduces that run with and without a workspace: as one without);
  * the module then holds only the kernel versions that plan launches, with every extent, stride,
  * division constant and launch-plan member a compile-time constant.  The result is a pattern of
  * its own (one per shape, cached on op sequence + constraints + dims): disc_plan / disc_launch
@@ -281,8 +282,9 @@ int disc_pattern_info(disc_ctx* ctx, int32_t id, disc_pattern_info_t* out);
 const char* disc_pattern_source(disc_ctx* ctx, int32_t id);
 
 /* Bytes of device workspace disc_launch needs at these dims, whatever the alignment of its operands
- * (0 for loop patterns and for row patterns without sums over the rows; a column reduce of at most 2^20 elements also
- * runs without it, in one launch where two would be faster).  Buffer sizes are a result of the host-side shape
+ * (0 for loop patterns and for row patterns without sums over the rows; a column reduce of at most 2^20 elements that
+ * has an output along the reduced axis also runs with less or none, in one launch where two would be faster, and
+ * then adds its sums up in another order).  Buffer sizes are a result of the host-side shape
  * calculation (Section 4.2.1) and the buffers come from the caller (Section 4.2.2: the framework's
  * allocator owns the memory). */
 int disc_workspace_bytes(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, size_t* out);

@@ -897,8 +897,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     const bool million = !mul_ovf(outer * mid, inner, &total) && total <= (1ll << 20);
     const bool long_axis = p.gen.has_epilogue && mid > (held && million && total <= (1ll << 19) ? 2048 : 1024);
     const bool small = million && !long_axis;
-    const bool strip = want_strip >= 0 ? want_strip != 0 : small;
-    if (strip) {
+    auto plan_strip = [&]() {
       // strips of >= 32 bytes per row keep the accesses coalesced; narrower strips = more blocks
       int GC = 1;
       while (GC < 64 && (GC * (vec ? 16 : 4) < 32 || spr / (GC * 2) >= 64)) GC *= 2;
@@ -947,7 +946,8 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       pub.lds_bytes[0] = 0;
       snprintf(pub.kernel[0], sizeof pub.kernel[0], "%s%s", p.gen.prefix.c_str(), kernel_name(L0.kid));
       return DISC_OK;
-    }
+    };
+    if (want_strip >= 0 ? want_strip != 0 : small) return plan_strip();
     // Lanes along the columns per block: 16 lanes of one vector each (256 bytes of a row: two
     // whole cache lines) unless the rows are narrower; the other lanes of the block run down the
     // rows.  Narrow column tiles give the grid its width: with 64 lanes across, 1024 fp32 columns
@@ -986,9 +986,9 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     int64_t cells, red_bytes;
     if (mul_ovf(outer * nchunk, inner, &cells) || mul_ovf(cells, (int64_t)p.gen.n_acc_cells * 8, &red_bytes))
       return set_err(c, DISC_ERR_SHAPE, "workspace size overflows int64");
-    // (no workspace for a problem that fits one launch: one launch)
-    if (million && long_axis && force < 0 && !p.is_static && (uint64_t)red_bytes > ws_limit)
-      return make_plan(c, p, dims, n_dims, vec ? DISC_V_COL_STRIP_VEC : DISC_V_COL_STRIP_SCALAR, inputs, outputs, fp, ws_limit);
+    // (no workspace for a problem that fits one launch: one launch.  So do single-shape modules, which hold one
+    // plan for callers with and without a workspace.)
+    if (million && long_axis && force < 0 && (p.is_static || (uint64_t)red_bytes > ws_limit)) return plan_strip();
     fp->aux[0] = cells;                 // cells per accumulator-field plane
     fp->aux[1] = outer * inner * 8;     // bytes per reduce-result plane
     fp->ws_off[0] = 0;
@@ -1491,7 +1491,7 @@ static int register_impl(disc_ctx* ctx, const disc_op* ops, int n_ops, const dis
     // plan the one shape with the generic rules, then regenerate the module with only the kernel
     // versions that plan launches and with every extent and plan member as a constant
     FullPlan fp;
-    rc = make_plan(ctx, *p, static_dims, n_static_dims, -1, nullptr, nullptr, &fp);
+    rc = make_plan(ctx, *p, static_dims, n_static_dims, -1, nullptr, nullptr, &fp, p->an.tmpl == DISC_TEMPLATE_COL_REDUCE ? 0 : SIZE_MAX);
     if (rc) return rc;
     GenOptions opt;
     for (int l = 0; l < fp.pub.n_launches; ++l) {

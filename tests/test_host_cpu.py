@@ -512,6 +512,19 @@ def test_launch_path_makes_no_heap_allocation(tmp_path):
     assert "runtime error" not in r.stderr and "AddressSanitizer" not in r.stderr
 
 
+# ------------------------------------------------------------------ column reduces that also run without a workspace
+def test_single_shape_column_reduces_of_long_axes_need_no_workspace(ctx):
+    """A long reduced axis takes two launches where the caller has a workspace for them.  A single-shape module holds
+    one plan: the one launch that needs none."""
+    pat = CONFIGS["C3"].pattern()
+    for dims in ([5000, 100], [16384, 64], [4096, 256]):
+        assert ctx.register(pat).plan(dims)["n_launches"] == 2
+        h = ctx.register_static(pat, dims)
+        p = h.plan(dims)
+        assert p["n_launches"] == 1 and p["workspace_bytes"] == 0 and ctx.workspace_bytes(h.id, dims) == 0
+        assert h.info["n_variants"] == 1 and "k_col_strip" in p["kernels"][0] and p["kernels"][0].split("_k_")[1] in h.source
+
+
 # ------------------------------------------------------------------ outputs whose size depends on the data
 def test_compaction_patterns_checker_and_plan(ctx):
     pb = PatternBuilder()
