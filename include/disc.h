@@ -360,7 +360,8 @@ int disc_test_option(disc_ctx* ctx, int option, int value);
  * disc_graph_launch: `inputs` / `outputs` are host arrays of DEVICE pointers in the order of the
  * graph's PARAM / OUTPUT ops; `workspace` is DEVICE memory of at least disc_graph_workspace_bytes
  * (256-byte aligned), owned by the caller, free to reuse once the stream has passed the launch
- * (DISC_ERR_WORKSPACE when missing or too small).  The patterns run in order on `hip_stream`; the
+ * (DISC_ERR_WORKSPACE when missing or too small; what only patterns that also run without it would use may be
+ * missing, see disc_workspace_bytes).  The patterns run in order on `hip_stream`; the
  * call returns once they are enqueued.  A failure of one pattern's launch-time shape check returns
  * that status with the earlier patterns already enqueued. */
 enum { DISC_MAX_GRAPH_PATTERNS = 64 };

@@ -1065,6 +1065,10 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
   return DISC_OK;
 }
 
+// The workspace limit of a plan that does with as little as the pattern can (column reduces: none where the strip
+// version runs; what the others need does not depend on a limit that a caller's workspace sets).
+size_t least_limit(const Pattern& p) { return p.an.tmpl == DISC_TEMPLATE_COL_REDUCE ? 0 : SIZE_MAX; }
+
 // A row reduce with a transposed operand in one kernel: batch x per rows of `inner` elements.  false: two kernels.
 bool plan_xpose(const disc_ctx* c, int64_t per, int64_t batch, int64_t inner, int V, FullPlan* fp) {
   // Strips of 8 rows (16 bytes of an operand row) in 512 threads; of 16 where that still leaves strips for the chip --
@@ -1491,7 +1495,7 @@ static int register_impl(disc_ctx* ctx, const disc_op* ops, int n_ops, const dis
     // plan the one shape with the generic rules, then regenerate the module with only the kernel
     // versions that plan launches and with every extent and plan member as a constant
     FullPlan fp;
-    rc = make_plan(ctx, *p, static_dims, n_static_dims, -1, nullptr, nullptr, &fp, p->an.tmpl == DISC_TEMPLATE_COL_REDUCE ? 0 : SIZE_MAX);
+    rc = make_plan(ctx, *p, static_dims, n_static_dims, -1, nullptr, nullptr, &fp, least_limit(*p));
     if (rc) return rc;
     GenOptions opt;
     for (int l = 0; l < fp.pub.n_launches; ++l) {
@@ -1655,7 +1659,7 @@ static int launch_impl(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dim
   if ((n_in > 0 && !inputs) || !outputs) return set_err(ctx, DISC_ERR_INVALID_ARG, "null pointer array");
   FullPlan fp;
   // (a column reduce that could do without a workspace does, if there is none)
-  const size_t limit = own_need ? workspace_bytes : p->an.tmpl == DISC_TEMPLATE_COL_REDUCE ? (workspace ? workspace_bytes : 0) : SIZE_MAX;
+  const size_t limit = own_need ? workspace_bytes : workspace && least_limit(*p) == 0 ? workspace_bytes : least_limit(*p);
   int rc = make_plan(ctx, *p, dims, n_dims, ctx->force_variant, inputs, outputs, &fp, limit);
   const int64_t t1 = now_ns();
   ctx->stats.host_plan_ns += t1 - t0;
@@ -1907,7 +1911,8 @@ Graph* get_graph(disc_ctx* ctx, int32_t id) {
 
 // byte offset of every buffer and of the shared pattern-workspace region for one set of dims
 // buf_off: room for one offset per buffer (at most DISC_MAX_OPS)
-int graph_layout(disc_ctx* ctx, const Graph& g, const int64_t* dims, int n_dims, size_t* buf_off,
+// least: what the patterns cannot do without, instead of what they ask for
+int graph_layout(disc_ctx* ctx, const Graph& g, const int64_t* dims, int n_dims, bool least, size_t* buf_off,
                  size_t* pattern_ws_off, size_t* total) {
   if (!dims || n_dims != g.n_sym) return set_err(ctx, DISC_ERR_INVALID_ARG, "wrong number of dims for this graph");
   for (int i = 0; i < n_dims; ++i)
@@ -1923,11 +1928,11 @@ int graph_layout(disc_ctx* ctx, const Graph& g, const int64_t* dims, int n_dims,
   *pattern_ws_off = off;
   size_t need = 0;
   for (const auto& gr : g.groups) {
-    size_t w = 0;
-    const int ns = ctx->patterns[gr.pattern_id]->an.n_sym;
-    int rc = disc_workspace_bytes(ctx, gr.pattern_id, dims, ns, &w);
+    const Pattern& p = *ctx->patterns[gr.pattern_id];
+    FullPlan fp;
+    const int rc = make_plan(ctx, p, dims, p.an.n_sym, ctx->force_variant, nullptr, nullptr, &fp, least ? least_limit(p) : SIZE_MAX);
     if (rc) return rc;
-    need = std::max(need, w);
+    need = std::max(need, fp.pub.workspace_bytes);
   }
   *total = off + need;
   return DISC_OK;
@@ -2381,7 +2386,7 @@ int disc_graph_workspace_bytes(disc_ctx* ctx, int32_t id, const int64_t* dims, i
   if (!g || !out) return set_err(ctx, DISC_ERR_INVALID_ARG, "bad graph id or null output");
   size_t off[DISC_MAX_OPS];
   size_t pws = 0;
-  return graph_layout(ctx, *g, dims, n_dims, off, &pws, out);
+  return graph_layout(ctx, *g, dims, n_dims, false, off, &pws, out);
   DISC_CATCH(ctx)
 }
 
@@ -2396,9 +2401,16 @@ int disc_graph_launch(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims
   // the place of every operand was resolved at registration
   size_t off[DISC_MAX_OPS];
   size_t pws = 0, total = 0;
-  int rc = graph_layout(ctx, *g, dims, n_dims, off, &pws, &total);
+  int rc = graph_layout(ctx, *g, dims, n_dims, false, off, &pws, &total);
   if (rc) return rc;
-  if (total > 0 && (!workspace || workspace_bytes < total)) return set_err(ctx, DISC_ERR_WORKSPACE, "workspace missing or too small");
+  if (!workspace) workspace_bytes = 0;
+  if (workspace_bytes < total) {
+    size_t least = 0;
+    rc = graph_layout(ctx, *g, dims, n_dims, true, off, &pws, &least);
+    if (rc) return rc;
+    if (workspace_bytes < least) return set_err(ctx, DISC_ERR_WORKSPACE, "workspace missing or too small");
+    total = std::max(pws, workspace_bytes);      // (the patterns get what is left behind the buffers)
+  }
   char* ws = static_cast<char*>(workspace);
   const void* in[DISC_MAX_OPS];
   void* outp[DISC_MAX_OPS];

@@ -90,6 +90,50 @@ def test_cut_into_patterns(hctx):
     assert hctx.stats()["compile_events"] == before
 
 
+def test_graphs_of_long_column_reduces_run_without_a_workspace(hctx):
+    """A one-pattern graph whose pattern takes two launches with a workspace and one without: the launch gets as far as
+    the device (which a host-only context has not) with none, a small one and the one asked for.  A planned buffer
+    stays needed."""
+    from paper_2103_05288_amd import DiscError
+    def status(g, dims, nbytes):
+        with pytest.raises(DiscError) as e:
+            g.launch(dims, [4096] * g.info["n_inputs"], [4096] * g.info["n_outputs"], workspace=4096 if nbytes else None, workspace_bytes=nbytes, stream=0)
+        return e.value.status
+    g = hctx.register_graph(chain_graph(1))
+    assert g.info["n_patterns"] == 1 and g.info["n_buffers"] == 0
+    for dims in ([4096, 256], [16384, 64], [5000, 100]):
+        need = g.workspace_bytes(dims)
+        assert need > 0
+        assert [status(g, dims, n) for n in (0, 16, need - 1, need)] == ["INVALID_ARG"] * 4
+    g = hctx.register_graph(chain_graph(2))
+    assert g.info["n_buffers"] > 0
+    need = g.workspace_bytes([4096, 256])
+    assert [status(g, [4096, 256], n) for n in (0, 16)] == ["WORKSPACE"] * 2 and status(g, [4096, 256], need) == "INVALID_ARG"
+
+
+@pytest.mark.gpu
+def test_graph_of_a_long_column_reduce_with_and_without_workspace():
+    from oracle import run as oracle_run
+    from paper_2103_05288_amd import Context
+    from tests.util import assert_close, to_oracle_input
+    ctx = Context(0)
+    try:
+        pat = chain_graph(1)
+        g = ctx.register_graph(pat)
+        for dims in ([4096, 256], [5000, 100]):
+            x = torch.randn(dims, generator=torch.Generator().manual_seed(dims[0]))
+            want = oracle_run(pat, dims, [to_oracle_input(x)])[0][0]
+            need = g.workspace_bytes(dims)
+            for n, launches in ((0, 1), (need - 8, 1), (need, 2)):
+                out, before = torch.full(dims, float("nan"), device="cuda"), ctx.stats()["device_launches"]
+                g.launch(dims, [x.cuda()], [out], workspace=torch.empty(n, dtype=torch.uint8, device="cuda") if n else None)
+                torch.cuda.synchronize()
+                assert ctx.stats()["device_launches"] - before == launches
+                assert_close(out.cpu(), want, f"{dims} workspace {n}")
+    finally:
+        ctx.close()
+
+
 def test_buffers_are_shared_by_lifetime(hctx):
     # five stages: a row stage carries the column sum of the following column stage along, so four
     # patterns; every stage output is recomputed by the later stages from the graph input and the
