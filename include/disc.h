@@ -315,7 +315,8 @@ int disc_launch(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims,
  * allocates nothing and frees nothing, on the device or through any library.  A shape whose
  * partial results need more than the array holds is refused with DISC_ERR_WORKSPACE before
  * anything runs (use disc_launch with a workspace then).  Same kernels, same launch plan and same
- * results, bit for bit, as disc_launch.  Every call on one GPU shares that GPU's array: calls
+ * results, bit for bit, as disc_launch (a column reduce that also runs without a workspace leaves the array
+ * alone: as disc_launch without one).  Every call on one GPU shares that GPU's array: calls
  * that overlap in time on one GPU (two streams, two contexts, two threads) race on it -- keep
  * them on one stream, or give all but one of them a workspace through disc_launch.  Nothing in the
  * array has to be cleared between calls (each call writes every cell it later reads).

@@ -1658,8 +1658,10 @@ static int launch_impl(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dim
   }
   if ((n_in > 0 && !inputs) || !outputs) return set_err(ctx, DISC_ERR_INVALID_ARG, "null pointer array");
   FullPlan fp;
-  // (a column reduce that could do without a workspace does, if there is none)
-  const size_t limit = own_need ? workspace_bytes : workspace && least_limit(*p) == 0 ? workspace_bytes : least_limit(*p);
+  // (a column reduce that could do without a workspace does, if there is none; with the static array always, so
+  // that a call that can do without the shared array leaves it alone)
+  const bool without = least_limit(*p) == 0;
+  const size_t limit = own_need ? (without ? 0 : workspace_bytes) : workspace && without ? workspace_bytes : least_limit(*p);
   int rc = make_plan(ctx, *p, dims, n_dims, ctx->force_variant, inputs, outputs, &fp, limit);
   const int64_t t1 = now_ns();
   ctx->stats.host_plan_ns += t1 - t0;
@@ -1704,7 +1706,7 @@ int launch_need(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, cons
   const bool match = n_in == p->an.n_inputs && n_out == p->an.n_outputs;
   FullPlan fp;
   int rc = make_plan(ctx, *p, dims, n_dims, ctx->force_variant, match ? inputs : nullptr, match ? outputs : nullptr, &fp,
-                     DISC_STATIC_SCRATCH_BYTES);
+                     std::min<size_t>(least_limit(*p), DISC_STATIC_SCRATCH_BYTES));
   if (rc) return rc;
   *need = fp.ws_need > 0 ? fp.ws_need : fp.pub.workspace_bytes;
   return DISC_OK;

@@ -72,6 +72,28 @@ def test_static_scratch_matches_disc_launch_twice_second_smaller(ctx):
     _both_ways(ctx, h, pat, [37, 777], cfg.inputs([37, 777], seed=1), "C4")
 
 
+def test_column_reduces_that_run_without_scratch_leave_the_array_alone(ctx):
+    """A long reduced axis takes two launches with a caller's workspace.  Here it takes the one that needs none: calls
+    that used nothing shared may overlap on a GPU."""
+    cfg = CONFIGS["C3"]
+    pat = cfg.pattern()
+    h = ctx.register(pat)
+    for dims in ([5000, 100], [16384, 64], [4096, 256]):
+        assert h.plan(dims)["n_launches"] == 2
+        ins = cfg.inputs(dims, seed=dims[0])
+        dev = [t.cuda() for t in ins]
+        ref, outs = alloc_outputs(pat, dims, "cuda"), alloc_outputs(pat, dims, "cuda")
+        h.launch(dims, dev, ref, workspace=None)
+        before = ctx.stats()["device_launches"]
+        ctx.launch_static_scratch(h.id, dims, dev, outs)
+        torch.cuda.synchronize()
+        assert ctx.stats()["device_launches"] == before + 1
+        want = oracle_run(pat, dims, [to_oracle_input(t) for t in ins])[0]
+        for k, (a, b, w) in enumerate(zip(outs, ref, want)):
+            assert torch.equal(a, b), f"{dims} out{k}: differs from disc_launch without a workspace"
+            assert_close(a.cpu(), w, f"{dims} out{k}")
+
+
 def test_static_scratch_refuses_what_does_not_fit(ctx):
     from paper_2103_05288_amd import DiscError
     pat = extras.layernorm_backward_graph()
