@@ -1148,7 +1148,23 @@ struct Gen {
     os << "  };\n";
   }
 
-  bool col_held = false;     // column reduce: the epilogue reads no per-element operand that the reduction does not
+  bool col_held = false;     // column reduce: strips may stay in registers between the reduction and the epilogue
+  // A lane of a block of 1024 threads has 128 registers: kColHeldRows slots, and the accumulators of its columns six
+  // times over while the wavefronts' partial results meet.  Sum / maximum with position / sum and maximum of one fp32
+  // operand, maximum of one bf16 operand: 80 / 80 / 104 / 80 dwords by this count, two fp32 operands 112: 98 to 128
+  // registers, none or two spilled.  Sum of one bf16 operand 128: 10 spilled, no faster than in two passes (1062 x 24
+  // 7.6 us / 7.2); products of an fp32 and a bf16 operand 192: 46 x 3941 10.4 / 4.4; of three bf16 operands: 170
+  // spilled, 23 x 344 7.7 / 4.1, 21 x 34 x 476 21.0 / 6.1.
+  bool col_held_fits() const {
+    int slot = 0, acc = 0;
+    for (const Access& a : an.accesses)
+      if (!a.is_output && a.has_inner) slot += (std::max(4, an.vec_width * dtype_bytes(a.dtype)) + 3) / 4;
+    for (int id : an.reduces[0]) {
+      const std::string ct = acc_ctype(an.nodes[id]);
+      acc += (ct == "double" || ct == "disc::i64" ? 2 : 1) + (an.nodes[id].opcode == DISC_REDUCE_ARGMAX ? 1 : 0);
+    }
+    return kColHeldRows * slot + 6 * an.vec_width * acc <= 112;
+  }
   bool has_elem_outputs() const {
     for (const auto& out : an.outputs)
       if (elem_output(an.accesses[out.access])) return true;
@@ -1280,10 +1296,13 @@ struct Gen {
       k("k_col_partial_scalar", "disc::col_partial_body<Pat, 1>(A, rp);", "ColPlan");
       k("k_col_finish", "disc::col_finish_body<Pat>(A, rp);", "ColPlan");
       const char* epi = has_elem_outputs() ? "PatE" : "void";
-      if (col_held) max_threads = 1024;
-      k("k_col_strip_vec", fmt("disc::col_strip_body<Pat, %s, %d, %d>(A, rp);", epi, V, col_held ? kColHeldRows : 0), "ColPlan");
-      max_threads = 256;
-      k("k_col_strip_scalar", fmt("disc::col_strip_body<Pat, %s, 1, 0>(A, rp);", epi), "ColPlan");
+      if (col_held) {       // strips held in registers, and those that a block's lanes cannot hold
+        max_threads = 1024;
+        k("k_col_strip_vec", fmt("disc::col_strip_held_body<Pat, %s, %d, %d>(A, rp);", epi, V, kColHeldRows), "ColPlan");
+        max_threads = 256;
+      }
+      k(col_held ? "k_col_strip_vecl" : "k_col_strip_vec", fmt("disc::col_strip_body<Pat, %s, %d>(A, rp);", epi, V), "ColPlan");
+      k("k_col_strip_scalar", fmt("disc::col_strip_body<Pat, %s, 1>(A, rp);", epi), "ColPlan");
       if (has_elem_outputs()) {
         k("k_col_epi_vec", fmt("disc::kloop_body<PatE, %d, 4, false>(A);", V), nullptr);
         if (V > 1) k("k_col_epi_vec_nt", fmt("disc::kloop_body<PatE, %d, 4, false, 3>(A);", V), nullptr);
@@ -1390,8 +1409,8 @@ struct Gen {
         emit_load_store(need3, true);
         emit_epilogue(M_COL_EPI);
         emit_finish_elem();
-        // the epilogue's operands out of a slot of the reduction's, where it reads no others
-        col_held = true;
+        // the epilogue's operands out of a slot of the reduction's, where it reads no others and the registers do
+        col_held = col_held_fits();
         for (size_t i = 0; i < an.accesses.size(); ++i)
           if (!an.accesses[i].is_output && an.accesses[i].has_inner && need3[i] && !need1[i]) col_held = false;
         if (col_held) {

@@ -1775,7 +1775,7 @@ DISC_DEV void col_rows_epilogue(const typename Pat::Args& A, const typename PatE
 // merged and taken through the epilogue from there.  Bound by latency, one trip to memory, the merge and the
 // stores: 700 x 1024 fp32 7.2 us with two passes of four rows in flight, 6.0 like this, 4.0-4.7 for an empty call.
 template <class Pat, class PatE, int V, int NR>
-DISC_DEV void col_strip_held(const typename Pat::Args& A, const ColPlan& cp, typename Pat::template Acc<0>* lds, i64 o, i64 col,
+DISC_DEV void col_strip_hold(const typename Pat::Args& A, const ColPlan& cp, typename Pat::template Acc<0>* lds, i64 o, i64 col,
                              int nvalid, int tx, int ty, int TY) {
   typedef typename Pat::template Acc<0> AccT;
   const int mid = (int)A.mid;
@@ -1833,6 +1833,18 @@ DISC_DEV void col_strip_held(const typename Pat::Args& A, const ColPlan& cp, typ
   }
 }
 
+template <class Pat, class PatE, int V, int NR>
+DISC_DEV void col_strip_held_body(const typename Pat::Args& A, const ColPlan& cp) {
+  __shared__ typename Pat::template Acc<0> lds[256 * V];   // (blocks above 256 threads have at most 16 lanes along the columns)
+  const int tx = threadIdx.x & (cp.GC - 1);
+  const int ty = threadIdx.x >> cp.log2GC;
+  const i64 col = ((i64)blockIdx.x * cp.GC + tx) * V;
+  const i64 rem = A.inner - col;
+  const int nvalid = rem <= 0 ? 0 : (rem < (i64)V ? (int)rem : V);
+  for (i64 o = blockIdx.y; o < cp.outer; o += gridDim.y)
+    col_strip_hold<Pat, PatE, V, NR>(A, cp, lds, o, col, nvalid, tx, ty, (int)(blockDim.x >> cp.log2GC));
+}
+
 // Single-launch version for small problems, where every further launch costs more than the work
 // (a kernel that makes one round trip to memory takes 5-6 us on this part whatever it moves): a
 // block owns a strip of GC * V columns and ALL rows of it.  It reduces the strip, every lane ends up
@@ -1841,10 +1853,10 @@ DISC_DEV void col_strip_held(const typename Pat::Args& A, const ColPlan& cp, typ
 // the block walks its strip a second time for the epilogue, reading the tensor from cache.  Nothing
 // goes through memory between the two passes.  PatE = void: no epilogue; the reduce results go to
 // the workspace planes as in the three-launch version.
-template <class Pat, class PatE, int V, int NR>
+template <class Pat, class PatE, int V>
 DISC_DEV void col_strip_body(const typename Pat::Args& A, const ColPlan& cp) {
   typedef typename Pat::template Acc<0> AccT;
-  __shared__ AccT lds[256 * V];      // (blocks above 256 threads have at most 16 lanes along the columns)
+  __shared__ AccT lds[256 * V];
   const int tx = threadIdx.x & (cp.GC - 1);
   const int ty = threadIdx.x >> cp.log2GC;
   const int TY = blockDim.x >> cp.log2GC;
@@ -1852,12 +1864,6 @@ DISC_DEV void col_strip_body(const typename Pat::Args& A, const ColPlan& cp) {
   const i64 rem = A.inner - col;
   const int nvalid = rem <= 0 ? 0 : (rem < (i64)V ? (int)rem : V);
   for (i64 o = blockIdx.y; o < cp.outer; o += gridDim.y) {
-    if constexpr (NR > 0) {
-      if (A.mid <= NR * TY) {
-        col_strip_held<Pat, PatE, V, NR>(A, cp, lds, o, col, nvalid, tx, ty, TY);
-        continue;
-      }
-    }
     AccT acc[V];
     col_accumulate<Pat, V>(A, o, col, nvalid, 0, A.mid, ty, TY, acc);
     col_block_merge<Pat, V>(acc, lds, cp.GC, tx);

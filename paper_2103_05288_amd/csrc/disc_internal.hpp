@@ -244,7 +244,7 @@ enum KernelId {
   K_TRANSPOSE_TILE,
   K_COL_EPI2_VEC, K_COL_EPI2_VEC_NT, K_COL_EPI2_SCALAR,
   K_COMPACT_COUNT_VEC, K_COMPACT_COUNT_SCALAR, K_COMPACT_SCAN, K_COMPACT_SCATTER_VEC, K_COMPACT_SCATTER_SCALAR,
-  K_COMPACT_SCATTER_VEC_NT, K_ROW_COLS_VEC, K_ROW_COLS_VEC_NT, K_COL_EPI2_VEC_NTS, K_ROW_STREAM_VECW, K_TRANSPOSE_TILE_H,
+  K_COMPACT_SCATTER_VEC_NT, K_ROW_COLS_VEC, K_ROW_COLS_VEC_NT, K_COL_EPI2_VEC_NTS, K_ROW_STREAM_VECW, K_TRANSPOSE_TILE_H, K_COL_STRIP_VECL,
   K_ROW_XPOSE, K_ROW_XPOSE_LAST = K_ROW_XPOSE + 7,    // {4, 8, 12, 16 slots a lane} x {any row length, whole slots}
   K_ROW_BASE,
   K_COUNT = K_ROW_BASE + 96

@@ -907,6 +907,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // x 2000 6.4 / 7.5; 256 / 512 / 1024 threads: 300 x 1024 5.0 / 4.8 / 5.7, 700 x 1024 - / 6.0 / 6.4, 1000 x 1024
       // - / 7.6 / 7.3).  Before, in 256 threads that read the strip twice: 700 x 1024 7.2, 256 x 4096 7.7.
       uint32_t block = 256;
+      bool in_regs = false;
       if (held) {
         const int64_t strips = mid <= 256 ? 256 : 64;
         int g = 1;
@@ -918,6 +919,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         if (mid <= (int64_t)kColHeldRows * (b / g)) {
           GC = g;
           block = b;
+          in_regs = true;
         }
       }
       const int64_t col_tiles = (spr + GC - 1) / GC;
@@ -933,7 +935,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       pub.vec_width = v;
       pub.index_bits = 64;
       LaunchRec& L0 = fp->launches[0];
-      L0.kid = vec ? K_COL_STRIP_VEC : K_COL_STRIP_SCALAR;
+      L0.kid = !vec ? K_COL_STRIP_SCALAR : held && !in_regs ? K_COL_STRIP_VECL : K_COL_STRIP_VEC;
       L0.block = block;
       L0.grid[0] = (uint32_t)col_tiles;
       L0.grid[1] = (uint32_t)std::min<int64_t>(outer, 65535);

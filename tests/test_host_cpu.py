@@ -512,6 +512,43 @@ def test_launch_path_makes_no_heap_allocation(tmp_path):
     assert "runtime error" not in r.stderr and "AddressSanitizer" not in r.stderr
 
 
+# ------------------------------------------------------------------ strips of a column reduce held in registers
+def _centred(dtypes, op="sum"):
+    """Columns of the product of the operands, less their mean (or maximum)."""
+    pb = PatternBuilder()
+    t, c = pb.dims(2)
+    xs = [pb.param(d, [t, c]) for d in dtypes]
+    xs = [x if d == "f32" else pb.cast(x, "f32") for x, d in zip(xs, dtypes)]
+    v = xs[0]
+    for x in xs[1:]:
+        v = pb.op("mul", v, x)
+    m = pb.reduce(op, v, 0)
+    m = pb.op("div", m, pb.dim_size(t)) if op == "sum" else m
+    y = pb.op("sub", v, pb.broadcast(m, [t, c], [1]))
+    pb.output(y if dtypes[0] == "f32" else pb.cast(y, dtypes[0]))
+    return pb.build()
+
+
+@pytest.mark.parametrize("dtypes, op, held", [(["f32"], "sum", True), (["f32", "f32"], "sum", True), (["bf16"], "max", True), (["bf16"], "sum", False),
+                                              (["f32", "bf16"], "sum", False), (["bf16", "bf16", "bf16"], "sum", False)],
+                         ids=lambda v: "+".join(v) if isinstance(v, list) else str(v))
+def test_strips_are_held_where_the_registers_hold_them(ctx, tmp_path, dtypes, op, held):
+    """The strip kernel of a small column reduce keeps no register in memory, whatever the operands."""
+    import re
+    import subprocess
+    h = ctx.register(_centred(dtypes, op))
+    src, asm = tmp_path / "k.hip", tmp_path / "k.s"
+    src.write_text("#include <hip/hip_runtime.h>\n" + h.source)
+    subprocess.run(["/opt/rocm/bin/hipcc", "--offload-arch=gfx950", "--cuda-device-only", "-S", "-O3", "-std=c++17", "-Xclang", "-target-feature",
+                    "-Xclang", "-packed-fp32-ops", "-fno-slp-vectorize", "-fno-vectorize", "-Wno-unused-value", str(src), "-o", str(asm)], check=True)
+    spills = dict(re.findall(r"\.symbol: +\S+?_(k_col_strip\w+)\.kd.*?\.vgpr_spill_count: +(\d+)", asm.read_text(), re.S))
+    assert spills and all(int(n) == 0 for n in spills.values()), spills
+    assert ("_k_col_strip_vecl(" in h.source) == held
+    assert ctx.plan(h.id, [100, 512])["kernels"][0].endswith("_k_col_strip_vec")
+    if held:                                       # too many rows for the registers: the version in two passes
+        assert h.plan([70000, 1024], V["col_strip_vec"])["kernels"][0].endswith("_k_col_strip_vecl")
+
+
 # ------------------------------------------------------------------ column reduces that also run without a workspace
 def test_single_shape_column_reduces_of_long_axes_need_no_workspace(ctx):
     """A long reduced axis takes two launches where the caller has a workspace for them.  A single-shape module holds
