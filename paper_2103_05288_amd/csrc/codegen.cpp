@@ -708,6 +708,10 @@ struct Gen {
   }
 
   void emit_acc_basic() {
+    bool position = false;
+    for (int p = 0; p < an.n_phases; ++p)
+      for (int id : an.reduces[p]) position = position || an.nodes[id].opcode == DISC_REDUCE_ARGMAX;
+    os << "  static constexpr bool HAS_POSITION = " << (position ? "true" : "false") << ";\n";
     os << "  template <int P> static DISC_DEV void acc_init(Acc<P>& a) {\n";
     for (int p = 0; p < an.n_phases; ++p) {
       os << "    if constexpr (P == " << p << ") {\n";
@@ -1151,7 +1155,7 @@ struct Gen {
   bool col_held = false;     // column reduce: strips may stay in registers between the reduction and the epilogue
   // A lane of a block of 1024 threads has 128 registers: kColHeldRows slots, and the accumulators of its columns six
   // times over while the wavefronts' partial results meet.  Sum / maximum with position / sum and maximum of one fp32
-  // operand, maximum of one bf16 operand: 80 / 80 / 104 / 80 dwords by this count, two fp32 operands 112: 98 to 128
+  // operand, maximum of one bf16 operand: 80 / 80 / 104 / 80 dwords by this count, two fp32 operands 112: 88 to 128
   // registers, none or two spilled.  Sum of one bf16 operand 128: 10 spilled, no faster than in two passes (1062 x 24
   // 7.6 us / 7.2); products of an fp32 and a bf16 operand 192: 46 x 3941 10.4 / 4.4; of three bf16 operands: 170
   // spilled, 23 x 344 7.7 / 4.1, 21 x 34 x 476 21.0 / 6.1.

@@ -1675,7 +1675,8 @@ DISC_DEV void col_lane_step(typename Pat::template Acc<0> (&acc)[V]) {
 // then the wavefronts meet through one LDS cell per wavefront and column.  (One lane per column
 // walking all row-lanes' cells in LDS, as before, cost up to 2 us per block with 128 row-lanes.)
 // `lds` holds 4 * 64 * V accumulators; ends with a barrier, so the caller may reuse it at once.
-template <class Pat, int V>
+// IDENTITY: from the identity on, one merge more and a few registers less.
+template <class Pat, int V, bool IDENTITY = false>
 DISC_DEV void col_block_merge(typename Pat::template Acc<0> (&acc)[V], typename Pat::template Acc<0>* lds, int GC, int tx) {
   int g = GC;
   asm volatile("" : "+s"(g));
@@ -1692,21 +1693,33 @@ DISC_DEV void col_block_merge(typename Pat::template Acc<0> (&acc)[V], typename 
     for (int e = 0; e < V; ++e) lds[(wave * gw + lane) * V + e] = acc[e];
   }
   __syncthreads();
-#pragma unroll
-  for (int e = 0; e < V; ++e) Pat::template acc_init<0>(acc[e]);
   // (A multiple of four wavefronts, their cells read side by side: one dependent LDS read after the other, a
   // strip of 1024 threads took 7.4 us instead of 6.4 and every call of two launches 1 us more.)
-  for (int w = 0; w < nw; w += 4) {
-    typename Pat::template Acc<0> x[4][V];
+  // (Positions take registers that the waves in flight miss, and are read one by one: maximum with position, 2 x 13 x
+  // 48740, 19.8 / 16.4 us.)
+  constexpr int N = Pat::HAS_POSITION ? 1 : 4;
+  auto cells = [&](int w, auto first) {
+    typename Pat::template Acc<0> x[N][V];
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < N; ++k)
 #pragma unroll
       for (int e = 0; e < V; ++e) x[k][e] = lds[((w + k) * gw + tx) * V + e];
+    if constexpr (first.value) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+      for (int e = 0; e < V; ++e) acc[e] = x[0][e];
+    }
+#pragma unroll
+    for (int k = first.value; k < N; ++k)
 #pragma unroll
       for (int e = 0; e < V; ++e) Pat::template acc_merge<0>(acc[e], x[k][e]);
+  };
+  if constexpr (IDENTITY) {
+#pragma unroll
+    for (int e = 0; e < V; ++e) Pat::template acc_init<0>(acc[e]);
+  } else {
+    cells(0, IntC<1>{});
   }
+  for (int w = IDENTITY ? 0 : N; w < nw; w += N) cells(w, IntC<0>{});
   __syncthreads();
 }
 
@@ -1809,7 +1822,7 @@ DISC_DEV void col_strip_hold(const typename Pat::Args& A, const ColPlan& cp, typ
       }
     }
   }
-  col_block_merge<Pat, V>(acc, lds, cp.GC, tx);
+  col_block_merge<Pat, V, true>(acc, lds, cp.GC, tx);
   if (nvalid > 0) {
     typename PatE::template Slot<V> base;
     PatE::template clear_red<V>(base);
