@@ -1449,6 +1449,9 @@ struct Gen {
     out->row_held = row_held();
     out->stream_held = stream_held();
     out->col_held = col_held;
+    out->col_argmax = false;
+    if (col_tmpl())
+      for (int id : an.reduces[0]) out->col_argmax = out->col_argmax || an.nodes[id].opcode == DISC_REDUCE_ARGMAX;
     out->staged_elem_bytes.clear();
     for (int ai : staged_accesses()) out->staged_elem_bytes.push_back(dtype_bytes(an.accesses[ai].dtype));
     return DISC_OK;

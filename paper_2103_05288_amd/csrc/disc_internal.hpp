@@ -227,6 +227,7 @@ struct Generated {
   bool row_held = false;              // row reduce, nothing written per element or summed over the rows
   int stream_held = kStreamHeldSlots; // ... and in its blocks of up to 512 threads of row_held patterns
   bool col_held = false;              // column reduce: strips may stay in registers between the reduction and the epilogue
+  bool col_argmax = false;            // column reduce: some reduction keeps a position
   bool row_cols_ok = false;           // row reduce without reductions along the rows: the version by column tiles exists
   bool row_shift_ok = false;          // ... and their vector slots may be shifted to the 16-byte boundaries of the tensor
   bool row_narrow_late = false;       // row reduce: an operand of less than four bytes an element is the same for many rows, but not staged

@@ -887,41 +887,56 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     const int v = vec ? V : 1;
     const int64_t spr = (inner + v - 1) / v;
     // Small problems: one launch, a block per strip of columns (reduce, finish and epilogue in the
-    // same kernel), up to about a million elements.  A strip that the block can hold in registers is read once
-    // (col_held).  Long reduced axes leave too few strips and too many rows to a lane: two launches then, if
-    // the caller's workspace allows them.  fp32, one launch / two, us: 1000 x 1024 7.3 / 8.5, 500 x 2000 6.5 / 8.0, 2000 x
-    // 256 7.7 / 8.6, 2000 x 128 7.1 / 8.6; 2000 x 512 10.7 / 8.8, 3000 x 100 9.4 / 8.4, 4096 x 256 16.4 / 7.5, 5000 x 200 22.3 / 12.0, 16384
-    // x 64 46.4 / 9.2.  (1300 x 777 9.3 / 10.4 is on the wrong side of the line.)
+    // same kernel), up to about a million elements.
     int64_t total;
-    const bool held = vec && p.gen.col_held;
     const bool million = !mul_ovf(outer * mid, inner, &total) && total <= (1ll << 20);
-    const bool long_axis = p.gen.has_epilogue && mid > (held && million && total <= (1ll << 19) ? 2048 : 1024);
+    // strips of >= 32 bytes per row keep the accesses coalesced; narrower strips = more blocks
+    int strip_gc = 1;
+    while (strip_gc < 64 && (strip_gc * (vec ? 16 : 4) < 32 || spr / (strip_gc * 2) >= 64)) strip_gc *= 2;
+    strip_gc = std::min<int>(strip_gc, 1 << ilog2_ceil(std::min<int64_t>(spr, 64)));
+    const int64_t lane_rows = mid / (256 / strip_gc);       // rows that a lane walks, twice
+    // A strip that the block can hold in registers is read once (col_held): few rows leave room for more and narrower
+    // strips, one for every CU, many rows take more threads, four to eight rows to a lane (64 strips / 256: 256 x 4096 7.7 us
+    // / 5.4, 100 x 4096 5.3 / 4.8; 700 x 1024 6.0 / 6.8, 500 x 2000 6.4 / 7.5; 207 / 413: 159 x 3300 4.5 / 5.5; 256 / 512 /
+    // 1024 threads: 300 x 1024 5.0 / 4.8 / 5.7,
+    // 700 x 1024 - / 6.0 / 6.4, 1000 x 1024 - / 7.6 / 7.3).  With a batch there are strips enough, and rows fewer than half
+    // of a block's lanes down the rows leave these idle: 64 strips an entry and wider ones (maximum with position 10 x
+    // 34 x 1816 16.9 / 9.3, sum 7 x 4 x 10332 6.5 / 2.8).  Maxima with positions are too dear to merge over 16 wavefronts
+    // (2 x 1677 x 72 13.4 with 1024 threads, 10.9 in two passes, 9.2 with 512), and for a second round of blocks (held / two
+    // passes: 130 x 133 x 45, 780 blocks, 10.5 / 11.2; 175 x 133 x 45, 1050, 14.6 / 12.7; 10 x 34 x 1816, 1140, 9.3 / 8.2).
+    uint32_t strip_block = 256;
+    bool in_regs = false;
+    if (vec && p.gen.col_held) {
+      const bool narrow = mid <= 256 && outer < 4;
+      int g = 1;
+      auto strips = [&]() { return (spr + g - 1) / g; };
+      while (g < 64 && (g * 16 < 32 || (narrow ? strips() > 256 / outer : spr / (g * 2) >= 64) || (strips() * outer > c->n_cus && 256 / (g * 2) >= mid)))
+        g *= 2;
+      g = std::min<int>(g, 1 << ilog2_ceil(std::min<int64_t>(spr, 64)));
+      if (mid > (int64_t)kColHeldRows * (256 / g)) g = std::min(g, 16);     // (all that a block above 256 threads takes)
+      uint32_t b = 256;
+      if (g <= 16 && mid > 4 * (256 / g)) b = 512;
+      if (g <= 16 && mid > 6 * (512 / g) && !p.gen.col_argmax) b = 1024;
+      const bool resident = strips() * outer * b <= (int64_t)c->n_cus * 1024;
+      if (mid <= (int64_t)kColHeldRows * (b / g) && (resident || !p.gen.col_argmax)) {
+        strip_gc = g;
+        strip_block = b;
+        in_regs = true;
+      }
+    }
+    // Many rows to a lane: two launches then, if the caller's workspace allows them.  What counts is the rows that a
+    // lane of the two passes walks, whatever the length of the axis; one launch / two, us, single elements: 26 rows (6
+    // x 3300 x 2) 4.9 / 7.0, 43 (11000 x 1) 6.1 / 7.0, 49 (12623 x 1) 6.5 / 7.0, 47 (1500 x 5) 6.6 / 6.2, 64 (2040 x 5) 7.8 / 6.2, 344 (11000 x 5) 32.7 /
+    // 7.3; slots: 12 (1500 x 40) 8.7 / 9.9, 16 (4100 x 8) 8.6 / 9.5, 20 (2600 x 40) 10.4 / 10.0, 32 (4100 x 40) 15.1 / 10.8.
+    // Held strips: 10 (1300 x 777) 9.3 / 10.4, 16 (2040 x 20) 6.3 / 7.8, (6 x 2040 x 64) 8.7 / 9.0, but from 2 MB of operand on
+    // the pieces of a row meet in the caches of too few CUs (2040 x 512 10.6 / 8.4, 2600 x 256 11.3 / 7.8), unless a strip
+    // is whole rows (40 x 2600 x 8 6.9 / 8.5, 3300 x 8 6.7 / 7.7).
+    const bool few_bytes = sv.alg_bytes <= (4ll << 20);
+    const bool long_axis = p.gen.has_epilogue && mid > 1024 &&
+                           (in_regs ? spr > strip_gc && (lane_rows > 20 || (lane_rows > 12 && !few_bytes)) : lane_rows > (!vec ? 52 : p.gen.col_argmax ? 24 : 20));
     const bool small = million && !long_axis;
     auto plan_strip = [&]() {
-      // strips of >= 32 bytes per row keep the accesses coalesced; narrower strips = more blocks
-      int GC = 1;
-      while (GC < 64 && (GC * (vec ? 16 : 4) < 32 || spr / (GC * 2) >= 64)) GC *= 2;
-      GC = std::min<int>(GC, 1 << ilog2_ceil(std::min<int64_t>(spr, 64)));
-      // Held strips: few rows leave room for more and narrower strips, many rows take more threads, four to
-      // eight rows to a lane (64 strips / 256: 256 x 4096 7.7 us / 5.4, 100 x 4096 5.3 / 4.8; 700 x 1024 6.0 / 6.8, 500
-      // x 2000 6.4 / 7.5; 256 / 512 / 1024 threads: 300 x 1024 5.0 / 4.8 / 5.7, 700 x 1024 - / 6.0 / 6.4, 1000 x 1024
-      // - / 7.6 / 7.3).  Before, in 256 threads that read the strip twice: 700 x 1024 7.2, 256 x 4096 7.7.
-      uint32_t block = 256;
-      bool in_regs = false;
-      if (held) {
-        const int64_t strips = mid <= 256 ? 256 : 64;
-        int g = 1;
-        while (g < 16 && (g * 16 < 32 || spr / (g * 2) >= strips)) g *= 2;
-        g = std::min<int>(g, 1 << ilog2_ceil(std::min<int64_t>(spr, 16)));
-        uint32_t b = 256;
-        if (mid > 4 * (256 / g)) b = 512;
-        if (mid > 6 * (512 / g)) b = 1024;
-        if (mid <= (int64_t)kColHeldRows * (b / g)) {
-          GC = g;
-          block = b;
-          in_regs = true;
-        }
-      }
+      const int GC = strip_gc;
       const int64_t col_tiles = (spr + GC - 1) / GC;
       DeviceColPlan cp{GC, ilog2_ceil(GC), 1, 0, mid, outer, 0};
       fp->aux[0] = 0;
@@ -935,8 +950,8 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       pub.vec_width = v;
       pub.index_bits = 64;
       LaunchRec& L0 = fp->launches[0];
-      L0.kid = !vec ? K_COL_STRIP_SCALAR : held && !in_regs ? K_COL_STRIP_VECL : K_COL_STRIP_VEC;
-      L0.block = block;
+      L0.kid = !vec ? K_COL_STRIP_SCALAR : p.gen.col_held && !in_regs ? K_COL_STRIP_VECL : K_COL_STRIP_VEC;
+      L0.block = strip_block;
       L0.grid[0] = (uint32_t)col_tiles;
       L0.grid[1] = (uint32_t)std::min<int64_t>(outer, 65535);
       L0.plan_kind = 2;

@@ -213,6 +213,32 @@ def test_strips_held_in_registers(ctx, kind):
         assert_close(o.cpu(), w, f"strip without workspace {dims} out{k}")
 
 
+@pytest.mark.parametrize("op", ["sum", "max", "argmax"])
+def test_held_strips_of_any_width(ctx, op):
+    """Strips of 1 to 64 lanes across, rows from one to what the lanes hold, with a batch."""
+    pb = PatternBuilder()
+    a, t, c = pb.dims(3)
+    x = pb.param("f32", [a, t, c])
+    if op == "argmax":
+        pb.output(pb.reduce("argmax", x, 1))
+    m = pb.reduce("max" if op == "argmax" else op, x, 1)
+    pb.output(pb.op("sub", x, pb.broadcast(m, [a, t, c], [0, 2])))
+    pat = pb.build()
+    h = ctx.register(pat)
+    g = torch.Generator().manual_seed(8)
+    widths = set()
+    for dims in ([3, 1, 517], [2, 4, 20001], [1, 5, 32000], [1, 32, 16384], [1, 33, 16380], [5, 17, 1023], [2, 64, 516], [9, 31, 33], [3, 128, 8], [2, 129, 7],
+                 [1, 8192, 4], [2, 3300, 3], [1, 4096, 4], [1, 4097, 4], [2, 2049, 8]):
+        # (small whole numbers: sums of any order are exact)
+        x = torch.randint(-8, 8, dims, generator=g).float()
+        x[-1, -1, -1] = 9.0
+        compare(ctx, pat, dims, [x], "held " + op, handle=h)
+        p = h.plan(dims)
+        assert p["n_launches"] == (2 if op == "argmax" and dims[1] == 8192 else 1)
+        widths.add(p["lanes_per_row"])
+    assert widths >= {1, 2, 16, 32, 64}
+
+
 # ---------------------------------------------------------------- generic patterns
 def test_elementwise_op_zoo_fp32(ctx):
     pb = PatternBuilder()

@@ -549,6 +549,24 @@ def test_strips_are_held_where_the_registers_hold_them(ctx, tmp_path, dtypes, op
         assert h.plan([70000, 1024], V["col_strip_vec"])["kernels"][0].endswith("_k_col_strip_vecl")
 
 
+def test_strips_of_batches_and_of_narrow_long_axes(ctx):
+    """One launch or two is a matter of the rows that a lane walks, not of the reduced axis alone; and neither a batch nor
+    few rows make for narrow strips whose blocks have nothing to do."""
+    pb = PatternBuilder()
+    a, t, c = pb.dims(3)
+    x = pb.param("f32", [a, t, c])
+    m = pb.op("div", pb.reduce("sum", x, 1), pb.dim_size(t))
+    pb.output(pb.op("sub", x, pb.broadcast(m, [a, t, c], [0, 2])))
+    h = ctx.register(pb.build())
+    for dims in ([200, 1030, 4], [195, 1036, 1], [1, 4285, 1], [128, 2527, 2], [6, 2040, 20], [40, 2600, 8], [1, 1300, 777]):
+        assert h.plan(dims)["n_launches"] == 1, dims
+    for dims in ([1, 4096, 256], [1, 16384, 64], [1, 13150, 4], [1, 10341, 17], [6, 16000, 2], [6, 4100, 20]):
+        assert h.plan(dims)["n_launches"] == 2, dims
+    for dims, blocks in (([7, 4, 10332], 7 * 41), ([30, 11, 1040], 30 * 17), ([1, 9, 82304], 322), ([1, 256, 4096], 256)):
+        p = h.plan(dims)
+        assert p["n_launches"] == 1 and p["grid"][0][0] * p["grid"][0][1] == blocks, (dims, p["grid"])
+
+
 # ------------------------------------------------------------------ column reduces that also run without a workspace
 def test_single_shape_column_reduces_of_long_axes_need_no_workspace(ctx):
     """A long reduced axis takes two launches where the caller has a workspace for them.  A single-shape module holds
