@@ -709,9 +709,15 @@ struct Gen {
 
   void emit_acc_basic() {
     bool position = false;
+    unsigned sums = 0;       // phases that add up floating-point values
     for (int p = 0; p < an.n_phases; ++p)
-      for (int id : an.reduces[p]) position = position || an.nodes[id].opcode == DISC_REDUCE_ARGMAX;
+      for (int id : an.reduces[p]) {
+        const Node& n = an.nodes[id];
+        position = position || n.opcode == DISC_REDUCE_ARGMAX;
+        if (n.opcode == DISC_REDUCE_SUM && an.nodes[n.in[0]].rk == RK_F32) sums |= 1u << p;
+      }
     os << "  static constexpr bool HAS_POSITION = " << (position ? "true" : "false") << ";\n";
+    os << "  static constexpr unsigned SUM_PHASES = " << sums << "u;\n";
     os << "  template <int P> static DISC_DEV void acc_init(Acc<P>& a) {\n";
     for (int p = 0; p < an.n_phases; ++p) {
       os << "    if constexpr (P == " << p << ") {\n";

@@ -956,18 +956,22 @@ DISC_DEV void stream_row_reds(const typename Pat::Args& A, const float (&racc)[P
   }
 }
 
-template <class Pat, int P, int V, int NR>
+// S: held slots that a sum adds up in one chain; more of them meet as partial sums.
+template <class Pat, int P, int V, int NR, int S>
 DISC_DEV void row_stream_phases(const typename Pat::Args& A, typename Pat::RowCtx& rc, int whole,
                                 StreamRow<Pat, V, NR>& r, char* lds, int& parity) {
   if constexpr (P < Pat::NPHASE) {
     typedef typename Pat::template Acc<P> AccT;
-    AccT acc;
+    constexpr bool split = S < NR && (Pat::SUM_PHASES >> P & 1);
+    AccT acc, part;
     Pat::template acc_init<P>(acc);
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
       const int col = (int)(j * blockDim.x + threadIdx.x) * V;
       typename Pat::template Keep<V> kp;
-      if (col < whole) Pat::template phase<P, V, false>(A, acc, as_loaded<Pat, V>(r.held[j]), kp, TailSpan::upto(V), col, rc);
+      if (split && j % S == 0) Pat::template acc_init<P>(part);
+      if (col < whole) Pat::template phase<P, V, false>(A, split ? part : acc, as_loaded<Pat, V>(r.held[j]), kp, TailSpan::upto(V), col, rc);
+      if (split && (j % S == S - 1 || j == NR - 1)) Pat::template acc_merge<P>(acc, part);
     }
     for (int col = (int)(NR * blockDim.x + threadIdx.x) * V; col < whole; col += blockDim.x * V) {
       typename Pat::template Slot<V> slot;
@@ -989,7 +993,7 @@ DISC_DEV void row_stream_phases(const typename Pat::Args& A, typename Pat::RowCt
     acc = ex[(int)threadIdx.x & (nw - 1)];
     group_allreduce<Pat, P>(acc, nw);
     Pat::template row_after<P>(A, rc, acc);
-    row_stream_phases<Pat, P + 1, V, NR>(A, rc, whole, r, lds, parity);
+    row_stream_phases<Pat, P + 1, V, NR, S>(A, rc, whole, r, lds, parity);
   }
 }
 
@@ -1001,6 +1005,8 @@ DISC_DEV void row_stream_phases(const typename Pat::Args& A, typename Pat::RowCt
 // 16384 x 8000 54 / 48, 16384 x 4096 34 / 28.5.  Loading the next row while one is worked on took 44.4, 51.2, 50.4
 // and, in blocks of 1024, 61.8 us where four slots take 62 (2096 x 64000); 16 slots on half the threads 53 and
 // 51.6; 80 registers (28 of them spilled) 70 and 63.
+// Twice the slots on a lane would be a chain of fp32 additions twice as long (sums of squares of 16013 bf16 values: 5.3e-8
+// off, 4.0e-8 with four slots a lane): two slots to a chain, whose sums meet.
 template <class Pat, int V, int NR, int NT>
 DISC_DEV void row_held_run(const typename Pat::Args& A) {
   __shared__ __attribute__((aligned(16))) char lds[2 * 16 * Pat::MAX_ACC_BYTES];
@@ -1015,7 +1021,7 @@ DISC_DEV void row_held_run(const typename Pat::Args& A) {
     typename Pat::RowCtx rc;
     StreamRow<Pat, V, NR> r;
     stream_load<Pat, V, NR, NT>(A, row, inner, whole, rc, r);
-    row_stream_phases<Pat, 0, V, NR>(A, rc, whole, r, lds, parity);
+    row_stream_phases<Pat, 0, V, NR, 2>(A, rc, whole, r, lds, parity);
     if constexpr (Pat::NROWRED > 0) Pat::row_reds(A, rc, racc);   // (every lane holds the row's values)
     if (threadIdx.x == 0) Pat::row_store(A, row, rc);
   }
@@ -1044,7 +1050,7 @@ DISC_DEV void row_stream_body(const typename Pat::Args& A) {
     typename Pat::RowCtx rc;
     StreamRow<Pat, V, NR> r;
     stream_load<Pat, V, NR, 0>(A, row, inner, whole, rc, r);
-    row_stream_phases<Pat, 0, V, NR>(A, rc, whole, r, lds, parity);
+    row_stream_phases<Pat, 0, V, NR, NR>(A, rc, whole, r, lds, parity);
     if constexpr (Pat::NROWRED > 0) Pat::row_reds(A, rc, racc);   // (every lane holds the row's values)
     auto finish = [&](const auto& slot, auto width, int col) {
       constexpr int W = decltype(width)::value;

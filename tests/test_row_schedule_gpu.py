@@ -368,6 +368,35 @@ def test_held_rows(ctx, nt):
     assert seen == {("row_stream_vec", b) for b in (64, 128, 256, 512)} | {("row_stream_vecw", 1024)}
 
 
+@pytest.mark.parametrize("dims, lanes, slots", [((1903, 16013), 512, 4), ((4100, 32000), 1024, 4), ((9000, 4096), 256, 2)], ids=lambda v: str(v))
+def test_held_rows_add_up_in_chains_no_longer_than_the_other_versions(ctx, dims, lanes, slots):
+    """Sums of squares (of one sign: the error is that of the additions) against the same sum in fp32 as `lanes` lanes of
+    `slots` slots of eight elements take it, one chain of additions a lane, the lanes by halves: no further off."""
+    pb = PatternBuilder()
+    t, h = pb.dims(2)
+    x = pb.cast(pb.param("bf16", [t, h]), "f32")
+    pb.output(pb.reduce("sum", pb.op("mul", x, x), 1))
+    hd = ctx.register(pb.build())
+    assert hd.plan(list(dims))["variant_name"] == "row_stream_vec" and hd.plan(list(dims))["slots_per_lane"] > slots
+    T, H = dims
+    x = torch.randn(T, H, generator=torch.Generator().manual_seed(H)).to(torch.bfloat16).cuda()
+    out = torch.empty(T, device="cuda")
+    hd.launch(list(dims), [x], [out])
+    sq = torch.zeros(T, slots * lanes * 8, device="cuda")
+    sq[:, :H] = x.float() ** 2                      # (exact: eight significant bits squared)
+    sq = sq.view(T, slots, lanes, 8)
+    lane = torch.zeros(T, lanes, device="cuda")
+    for j in range(slots):
+        for e in range(8):
+            lane = lane + sq[:, j, :, e]
+    while lane.shape[1] > 1:
+        half = lane.shape[1] // 2
+        lane = lane[:, :half] + lane[:, half:]
+    want = (x.double() ** 2).sum(1)
+    off = lambda v: float((v.double() - want).norm() / want.norm())
+    assert off(out) <= 1.05 * off(lane[:, 0]), (off(out), off(lane[:, 0]))
+
+
 def test_ragged_rows_on_whole_lines():
     """Ragged rows with non-temporal accesses: vector slots on boundaries of 32, 64 or 128 elements of the tensor, up to
     127 + 7 single elements per row.  Odd and even lengths, a last slot that ends exactly at the row's end, the least
