@@ -927,25 +927,44 @@ DISC_DEV typename Pat::template Slot<V>& as_loaded(typename Pat::template Slot<V
   Pat::template opaque<V>(s);
   return s;
 }
+// The same as a copy, for the streaming version of four slots a lane, where the padding is a word or two: dot product of
+// bf16 rows 58 registers, 63 in place, maximum with position 63 / 71, residual + LayerNorm 93 / 106.
+template <class S>
+DISC_DEV S copied(const S& s) {
+  constexpr int W = (int)(sizeof(S) - sizeof(int)) / 4;      // (the last member is a placeholder)
+  u32 w[W > 0 ? W : 1];
+  __builtin_memcpy(w, &s, W * 4);
+#pragma unroll
+  for (int i = 0; i < W; ++i) asm volatile("" : "+v"(w[i]));
+  S r;
+  __builtin_memcpy(&r, w, W * 4);
+  return r;
+}
 template <class Pat, int V, int NR>
 struct StreamRow {
   typename Pat::template Slot<V> held[NR > 0 ? NR : 1];
   typename Pat::template Slot<1> end;
   int end_col;            // column of this lane's single element, -1: none
 };
-// Row `row` into the held slots, and the elements behind the last whole slot one each to the first lanes
-template <class Pat, int V, int NR, int NT>
-DISC_DEV void stream_load(const typename Pat::Args& A, i64 row, int inner, int whole, typename Pat::RowCtx& rc, StreamRow<Pat, V, NR>& r) {
-  Pat::row_begin(A, row, rc);
-  rc.sl = nullptr;
-#pragma unroll
-  for (int j = 0; j < NR; ++j) {
-    const int col = (int)(j * blockDim.x + threadIdx.x) * V;
-    if (col < whole) Pat::template load<V, NT>(A, rc, col, TailSpan::upto(V), r.held[j]);
-  }
-  r.end_col = whole + (int)threadIdx.x < inner ? whole + (int)threadIdx.x : -1;
-  if (r.end_col >= 0) Pat::template load<1>(A, rc, r.end_col, TailSpan::upto(1), r.end);
-  if constexpr (NR > 0) asm volatile("" ::: "memory");     // all of these loads before the first phase
+// The row of `rc` as held slots, and the elements behind the last whole slot one each to the first lanes.  A macro: filled
+// through a reference (stream_fill) the row takes 15 to 35 registers more, and so fewer wavefronts: log-sum-exp with eight
+// slots a lane 75, 63 like this; maximum with position 127 / 95 (4096 x 32000 62 us / 45), dot product of bf16 rows with four
+// 78 / 58 (270 x 20800 6.8 / 6.2), LayerNorm backward 128 with 12 spilled / 105 (3000 x 30000 381 / 365).
+#define DISC_STREAM_FILL(r, NT)                                                                               \
+  do {                                                                                                        \
+    _Pragma("unroll") for (int j = 0; j < NR; ++j) {                                                          \
+      const int col = (int)(j * blockDim.x + threadIdx.x) * V;                                                \
+      if (col < whole) Pat::template load<V, NT>(A, rc, col, TailSpan::upto(V), r.held[j]);                   \
+    }                                                                                                         \
+    r.end_col = whole + (int)threadIdx.x < inner ? whole + (int)threadIdx.x : -1;                             \
+    if (r.end_col >= 0) Pat::template load<1>(A, rc, r.end_col, TailSpan::upto(1), r.end);                    \
+    if constexpr (NR > 0) asm volatile("" ::: "memory");     /* all of these loads before the first phase */  \
+  } while (0)
+// Patterns that write an element per element and sum nothing over the rows are faster with the fewer wavefronts (5000 x
+// 26000: residual + LayerNorm 185 us, 190 through the macro; mixed chain 187 / 194; softmax the same).
+template <class Pat, int V, int NR>
+DISC_DEV void stream_fill(const typename Pat::Args& A, const typename Pat::RowCtx& rc, int inner, int whole, StreamRow<Pat, V, NR>& r) {
+  DISC_STREAM_FILL(r, 0);
 }
 // The block's partial results of reductions of per-row values over the rows
 template <class Pat>
@@ -970,7 +989,10 @@ DISC_DEV void row_stream_phases(const typename Pat::Args& A, typename Pat::RowCt
       const int col = (int)(j * blockDim.x + threadIdx.x) * V;
       typename Pat::template Keep<V> kp;
       if (split && j % S == 0) Pat::template acc_init<P>(part);
-      if (col < whole) Pat::template phase<P, V, false>(A, split ? part : acc, as_loaded<Pat, V>(r.held[j]), kp, TailSpan::upto(V), col, rc);
+      if (col < whole) {
+        if constexpr (S < NR) Pat::template phase<P, V, false>(A, split ? part : acc, as_loaded<Pat, V>(r.held[j]), kp, TailSpan::upto(V), col, rc);
+        else Pat::template phase<P, V, false>(A, acc, copied(r.held[j]), kp, TailSpan::upto(V), col, rc);
+      }
       if (split && (j % S == S - 1 || j == NR - 1)) Pat::template acc_merge<P>(acc, part);
     }
     for (int col = (int)(NR * blockDim.x + threadIdx.x) * V; col < whole; col += blockDim.x * V) {
@@ -1019,8 +1041,10 @@ DISC_DEV void row_held_run(const typename Pat::Args& A) {
   }
   for (i64 row = blockIdx.x; row < A.rows; row += gridDim.x) {
     typename Pat::RowCtx rc;
+    Pat::row_begin(A, row, rc);
+    rc.sl = nullptr;
     StreamRow<Pat, V, NR> r;
-    stream_load<Pat, V, NR, NT>(A, row, inner, whole, rc, r);
+    DISC_STREAM_FILL(r, NT);
     row_stream_phases<Pat, 0, V, NR, 2>(A, rc, whole, r, lds, parity);
     if constexpr (Pat::NROWRED > 0) Pat::row_reds(A, rc, racc);   // (every lane holds the row's values)
     if (threadIdx.x == 0) Pat::row_store(A, row, rc);
@@ -1048,11 +1072,14 @@ DISC_DEV void row_stream_body(const typename Pat::Args& A) {
   }
   for (i64 row = blockIdx.x; row < A.rows; row += gridDim.x) {
     typename Pat::RowCtx rc;
+    Pat::row_begin(A, row, rc);
+    rc.sl = nullptr;
     StreamRow<Pat, V, NR> r;
-    stream_load<Pat, V, NR, 0>(A, row, inner, whole, rc, r);
+    if constexpr (Pat::HAS_ELEM_OUT && Pat::NCOLSUM == 0) stream_fill<Pat, V, NR>(A, rc, inner, whole, r);
+    else DISC_STREAM_FILL(r, 0);
     row_stream_phases<Pat, 0, V, NR, NR>(A, rc, whole, r, lds, parity);
     if constexpr (Pat::NROWRED > 0) Pat::row_reds(A, rc, racc);   // (every lane holds the row's values)
-    auto finish = [&](const auto& slot, auto width, int col) {
+    auto finish = [&](auto slot, auto width, int col) {
       constexpr int W = decltype(width)::value;
       typename Pat::template OutSlot<W> o;
       typename Pat::template Keep<W> kp;
@@ -1081,7 +1108,7 @@ DISC_DEV void row_stream_body(const typename Pat::Args& A) {
 #pragma unroll
       for (int j = 0; j < NR; ++j) {
         const int col = (int)(j * blockDim.x + threadIdx.x) * V;
-        if (col < whole) finish(as_loaded<Pat, V>(r.held[j]), IntC<V>{}, col);
+        if (col < whole) finish(copied(r.held[j]), IntC<V>{}, col);
       }
       for (int col = (int)(NR * blockDim.x + threadIdx.x) * V; col < whole; col += blockDim.x * V) {
         typename Pat::template Slot<V> slot;
@@ -1095,6 +1122,8 @@ DISC_DEV void row_stream_body(const typename Pat::Args& A) {
   }
   if constexpr (Pat::NROWRED > 0) stream_row_reds<Pat>(A, racc);
 }
+
+#undef DISC_STREAM_FILL
 
 // An element-wise pattern with sums over the rows (no reduction along the rows: NPHASE = 0) does not need
 // a row in one block.  A block of 256 threads is TX = A.aux1 lanes along the columns (a power of two;

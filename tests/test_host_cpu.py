@@ -512,6 +512,32 @@ def test_launch_path_makes_no_heap_allocation(tmp_path):
     assert "runtime error" not in r.stderr and "AddressSanitizer" not in r.stderr
 
 
+# ------------------------------------------------------------------ registers of the generated kernels
+def _registers(source, tmp_path):
+    """kernel -> (vector registers, spilled), of the module's source compiled as at registration"""
+    import re
+    import subprocess
+    src, asm = tmp_path / "k.hip", tmp_path / "k.s"
+    src.write_text("#include <hip/hip_runtime.h>\n" + source)
+    subprocess.run(["/opt/rocm/bin/hipcc", "--offload-arch=gfx950", "--cuda-device-only", "-S", "-O3", "-std=c++17", "-Xclang", "-target-feature",
+                    "-Xclang", "-packed-fp32-ops", "-fno-slp-vectorize", "-fno-vectorize", "-Wno-unused-value", str(src), "-o", str(asm)], check=True)
+    found = re.findall(r"\.symbol: +\S+?_(k_\w+)\.kd.*?\.vgpr_count: +(\d+)\s+\.vgpr_spill_count: +(\d+)", asm.read_text(), re.S)
+    return {k: (int(n), int(spilled)) for k, n, spilled in found}
+
+
+def test_streaming_rows_keep_their_registers(ctx, tmp_path):
+    """The streaming version runs in blocks of up to 1024 threads: with 64 registers two of these fit a CU, and above 128
+    they spill."""
+    from workloads import extras
+    pb = PatternBuilder()
+    t, h = pb.dims(2)
+    x, y = (pb.cast(pb.param("bf16", [t, h]), "f32") for _ in range(2))
+    pb.output(pb.reduce("sum", pb.op("mul", x, y), 1))
+    for pat, most in ((pb.build(), 64), (extras.logsumexp_with_total_and_amax(), 64), (extras.layernorm_backward_graph(), 112)):
+        n, spilled = _registers(ctx.register(pat).source, tmp_path)["k_row_stream_vec"]
+        assert n <= most and spilled == 0, (pat.name, n, spilled)
+
+
 # ------------------------------------------------------------------ strips of a column reduce held in registers
 def _centred(dtypes, op="sum"):
     """Columns of the product of the operands, less their mean (or maximum)."""
@@ -534,15 +560,9 @@ def _centred(dtypes, op="sum"):
                          ids=lambda v: "+".join(v) if isinstance(v, list) else str(v))
 def test_strips_are_held_where_the_registers_hold_them(ctx, tmp_path, dtypes, op, held):
     """The strip kernel of a small column reduce keeps no register in memory, whatever the operands."""
-    import re
-    import subprocess
     h = ctx.register(_centred(dtypes, op))
-    src, asm = tmp_path / "k.hip", tmp_path / "k.s"
-    src.write_text("#include <hip/hip_runtime.h>\n" + h.source)
-    subprocess.run(["/opt/rocm/bin/hipcc", "--offload-arch=gfx950", "--cuda-device-only", "-S", "-O3", "-std=c++17", "-Xclang", "-target-feature",
-                    "-Xclang", "-packed-fp32-ops", "-fno-slp-vectorize", "-fno-vectorize", "-Wno-unused-value", str(src), "-o", str(asm)], check=True)
-    spills = dict(re.findall(r"\.symbol: +\S+?_(k_col_strip\w+)\.kd.*?\.vgpr_spill_count: +(\d+)", asm.read_text(), re.S))
-    assert spills and all(int(n) == 0 for n in spills.values()), spills
+    strips = {k: v for k, v in _registers(h.source, tmp_path).items() if k.startswith("k_col_strip")}
+    assert strips and all(spilled == 0 for _, spilled in strips.values()), strips
     assert ("_k_col_strip_vecl(" in h.source) == held
     assert ctx.plan(h.id, [100, 512])["kernels"][0].endswith("_k_col_strip_vec")
     if held:                                       # too many rows for the registers: the version in two passes
