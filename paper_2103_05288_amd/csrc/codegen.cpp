@@ -1183,7 +1183,14 @@ struct Gen {
 
   // Streaming row version of patterns that write nothing per element
   bool row_held() const { return row_tmpl() && !has_elem_outputs() && an.n_col_sums == 0; }
-  int stream_held() const { return row_held() && stream_slot_bytes() <= 16 ? 2 * kStreamHeldSlots : kStreamHeldSlots; }
+  // ... holds eight slots of one operand of 16 bytes a slot.  An operand that is read anew in every phase (a row vector)
+  // makes fewer and longer lanes slower: weighted bf16 sums, four slots / eight, us: 630 x 19472 7.6 / 8.4, 2409 x 14800 14.8 /
+  // 16.2, 16384 x 7000 51.0 / 53.0 (3000 x 32000 41.2 / 39.3).
+  int stream_held() const {
+    bool late_reads = false;
+    for (const Access& a : an.accesses) late_reads = late_reads || late(a);
+    return row_held() && !late_reads && stream_slot_bytes() <= 16 ? 2 * kStreamHeldSlots : kStreamHeldSlots;
+  }
   int stream_slot_bytes() const {   // registers of one slot, operands as they are loaded
     int bytes = 0;
     for (const Access& a : an.accesses)

@@ -505,18 +505,20 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // overlap with the next row's loads, and the streaming version keeps more rows on a CU.  bf16 log-sum-exp,
       // register-resident / streaming, 2^27 elements: 8192 columns 82.0 us / 48.8, 12288 61.4 / 55, 16000 99.1 / 45.
       // Rows of up to 768 slots (blocks of at most 256 threads in the register-resident versions): with enough of
-      // them and more than three slots for every lane of a wavefront, where they start on dword boundaries and one
-      // operand of 16 bytes a slot is all there is (two of them, or a row vector beside: 16384 rows of 2000, 22.6
-      // / 24.9; 2500, 27.3 / 34.6).
+      // them and more than three slots for every lane of a wavefront, where they start on dword boundaries and a lane
+      // holds eight slots (two operands: 16384 rows of 2000, 22.6 / 24.9; 2500, 27.3 / 34.6).
       // 16384 rows of 6000 columns 41.1 / 39.7, 4096 33.9 / 28.5, 3000 26.4 / 23.2, 2500 22.2 / 20.4, 2000 20.8 / 17.7;
       // but 1501 15.3 / 16.7, 1024 13.3 / 13.9; odd rows, whose slots the others shift: 4095 34.3 / 35.9, 2049 21.8 /
       // 21.8; 8192 rows of 2500 14.8 / 13.9, 6000 of 4096 17.4 / 14.8, 5000 of 3000 12.2 / 11.7, 4000 of 2500 10.1 / 10.4.
+      // Large launches that three slots a lane of 128 or 256 lanes fit are bound by the memory, and no faster: 30000 rows of
+      // 6080 66.0 / 69.6; fp32 sums, 40000 rows of 1240 31.8 / 33.3, of 1400 35.7 / 37.4 (but bf16, 30000 of 2800 41.4 / 34.7).
       if (p.gen.row_held) {
         bool dwords = true;
         for (const Access& a : an.accesses)
           if (a.kind == ACC_FULL && (sv.inner * dtype_bytes(a.dtype)) % 4 != 0) dwords = false;
-        const bool one = p.gen.stream_held > kStreamHeldSlots && p.gen.staged_elem_bytes.empty();
-        if (spr > 3 * 256 || (force < 0 && one && spr > 3 * 64 && dwords && sv.rows > 16ll * c->n_cus)) stream = true;
+        const bool one = p.gen.stream_held > kStreamHeldSlots;
+        const bool three = sv.alg_bytes >= (144ll << 20) && ((V <= 4 && spr > 256 && spr <= 384) || spr > 512);
+        if (spr > 3 * 256 || (force < 0 && one && spr > 3 * 64 && dwords && !three && sv.rows > 16ll * c->n_cus)) stream = true;
       }
       // Sums over the rows and three slots per lane do not fit the registers of a wide block
       // (LayerNorm backward of 24000 columns: 1007 us, 514 in the streaming version)
@@ -597,8 +599,11 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // the least block whose registers hold the row; rows up to twice of what the largest one holds
       // still run in it, longer ones (which are read again in every phase anyway) in blocks of 256
       const bool held = vec && p.gen.row_held;
-      // (a few rows per CU: more threads to a row instead, 1000 x 8000 bf16 9.4 us / 9.1)
-      const bool few = sv.rows <= 4ll * c->n_cus && spr <= 512 * kStreamHeldSlots;
+      // (a few rows per CU: more threads to a row, four slots a lane instead; us, four / eight: 1000 x 8000 bf16 9.1 / 9.4, fp32
+      // variances 272 x 4150 2.8 / 3.0; 769 to 1024 slots while the chip has work for a few rounds, log-sum-exp 1900 x 7200 11.2
+      // / 11.9, 4500 x 8160 17.3 / 19.0, 6000 x 8160 22.6 / 23.8; up to 2048, maximum with position 1200 x
+      // 16000 9.1 / 9.7; longer ones, maximum 3 x 31200 2.6 / 2.7, but with position 270 x 20800 6.8 / 5.3)
+      const bool few = sv.rows <= (spr <= 3 * 256 ? 4ll : spr <= 256 * kStreamHeldSlots ? 28 : spr <= 512 * kStreamHeldSlots ? 5 : 1) * c->n_cus;
       const int64_t per_lane = held && !few ? p.gen.stream_held : kStreamHeldSlots;
       if (vec && spr <= 2 * 1024 * kStreamHeldSlots) {
         if (held && per_lane > kStreamHeldSlots) L.block = 64;
@@ -606,7 +611,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         if (L.block * per_lane < spr) L.block = 1024;
       }
       if (held) {
-        if (L.block > 512) L.kid = K_ROW_STREAM_VECW;
+        if (L.block > 512 || few) L.kid = K_ROW_STREAM_VECW;
         // Held slots are read once.  (The line lies above that of the other non-temporal versions: nothing is
         // written, and inputs of up to 85 MB are still found in the memory-side cache when three of them take turns: 700 x
         // 50257 bf16, 70 MB, 21.1 us / 23.4 with the hint; 16384 x 2000 f32, 131 MB, 23.9 / 21.6; larger ones gain 3-10 %,
@@ -621,7 +626,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       fp->aux[0] = L.grid[0];   // rows of partial sums: one per block
       pub.lanes_per_row = (int)L.block;
       pub.slots_per_lane = (int)((spr + L.block - 1) / L.block);
-      pub.reg_slots = !vec ? 1 : (int)(L.kid == K_ROW_STREAM_VECW ? kStreamHeldSlots : per_lane);
+      pub.reg_slots = !vec ? 1 : (int)(held && L.kid == K_ROW_STREAM_VEC ? p.gen.stream_held : kStreamHeldSlots);
     } else {
       // Lanes per row G and slots per lane nv (<= 2): the pair with the least capacity G * nv that
       // holds the row, two slots per lane on a tie.  G is a power of two.  The kernels accept any

@@ -343,7 +343,8 @@ def test_streaming_rows_and_piped_wide_rows(ctx, cfg_name):
 @pytest.mark.parametrize("nt", [0, 1])
 def test_held_rows(ctx, nt):
     """Patterns that write nothing per element: the edges of what the blocks of the streaming version hold (8 slots of 8
-    elements a lane in 64 to 512 threads, 4 in 1024; longer rows are read again), ragged ends, plain and non-temporal."""
+    elements a lane in 64 to 512 threads, 4 in 1024 and where rows are few; longer rows are read again), ragged ends, plain
+    and non-temporal."""
     from workloads.extras import logsumexp_with_total_and_amax
     pat = logsumexp_with_total_and_amax()
     h = ctx.register(pat)
@@ -351,21 +352,24 @@ def test_held_rows(ctx, nt):
     ctx.test_option("non_temporal", nt)
     try:
         for i, (T, H) in enumerate([(4097, 1538), (4100, 4096), (4097, 4102), (1030, 6145), (1025, 8192), (1027, 8193), (1026, 16391),
-                                    (3, 6145), (2, 8193), (2, 16384), (3, 16391), (2, 32768), (3, 32769), (1, 65536), (2, 65537), (1, 70003)]):
+                                    (3, 6145), (2, 8193), (2, 16384), (3, 16391), (2, 32768), (3, 32769), (1, 65536), (2, 65537), (1, 70003),
+                                    (1300, 8193)]):
             x = (torch.randn(T, H, generator=torch.Generator().manual_seed(i)) * 2).to(torch.bfloat16)
             x[T - 1, H - 1] = 40.0 + i                      # the last single element decides the last row
             plan = h.plan([T, H])
             assert plan["variant_name"] == "row_stream_vec"
             seen.add((plan["kernels"][0].split("_k_")[1], plan["block"][0][0]))
+            assert plan["reg_slots"] == (4 if plan["kernels"][0].endswith("_vecw") else 8)
             got = run_gpu(h, pat, [T, H], [x])
             want = oracle_run(pat, [T, H], [to_oracle_input(x)])[0]
             for k, (g, w) in enumerate(zip(got, want)):
                 assert_close(g, w, f"held rows {T}x{H} out{k}")
     finally:
         ctx.test_option("non_temporal", -1)
-    for T, H, block in ((4097, 1538, 64), (1030, 6145, 128), (3, 6145, 256), (1026, 16391, 512), (3, 16391, 512), (3, 16384, 512), (1026, 32769, 1024)):
+    for T, H, block in ((4097, 1538, 64), (7180, 6145, 128), (1030, 6145, 256), (3, 6145, 256), (1026, 16391, 512), (3, 16391, 1024), (3, 16384, 512),
+                        (1026, 32769, 1024)):
         assert h.plan([T, H])["block"][0][0] == block
-    assert seen == {("row_stream_vec", b) for b in (64, 128, 256, 512)} | {("row_stream_vecw", 1024)}
+    assert seen == {("row_stream_vec", b) for b in (64, 128, 256, 512)} | {("row_stream_vecw", b) for b in (256, 512, 1024)}
 
 
 @pytest.mark.parametrize("dims, lanes, slots", [((1903, 16013), 512, 4), ((4100, 32000), 1024, 4), ((9000, 4096), 256, 2)], ids=lambda v: str(v))
