@@ -1534,6 +1534,8 @@ DISC_DEV void ktranspose_body(const T* __restrict__ in, T* __restrict__ out, i64
 // The row stays in registers as loaded through all phases and the epilogue, as in the streaming version (values
 // kept between the phases would take twice what is there).  The strips that share cache lines of the
 // operand are dealt to one XCD.
+// (A lane adds up to 16 slots where the row kernels have three: in one chain weighted sums of 1014 values a row were 1.5e-7
+// off, 1.0e-7 in two kernels.)
 // What bounds it: a strip of 16 or 32 bytes a row costs a cache line per access, and load, arithmetic and
 // stores of a block follow one another, so a CU needs several strips.  Two strips after one another in a block, the
 // second one loaded behind the first one's arithmetic, were no faster (8192 x 8192 99.9 us, 93.7 without).
@@ -1541,15 +1543,18 @@ template <class Pat, int P, int V, int NV, class SP>
 DISC_DEV void row_xpose_phases(const typename Pat::Args& A, typename Pat::RowCtx& rc, typename Pat::template Slot<V> (&slot)[NV],
                                int lane, int G, int inner) {
   if constexpr (P < Pat::NPHASE) {
-    typename Pat::template Acc<P> acc;
+    constexpr bool split = Pat::SUM_PHASES >> P & 1;        // two slots to a chain of additions, whose sums meet
+    typename Pat::template Acc<P> acc, part;
     Pat::template acc_init<P>(acc);
     asm volatile("" : "+v"(lane));           // (columns are cheaper to compute again than to keep)
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
       const int col = (j * G + lane) * V;
       typename Pat::template Keep<V> kp;
+      if (split && j % 2 == 0) Pat::template acc_init<P>(part);
       if (col < inner)
-        Pat::template phase<P, V, false>(A, acc, as_loaded<Pat, V>(slot[j]), kp, SP::upto(inner - col < V ? inner - col : V), col, rc);
+        Pat::template phase<P, V, false>(A, split ? part : acc, as_loaded<Pat, V>(slot[j]), kp, SP::upto(inner - col < V ? inner - col : V), col, rc);
+      if (split && j % 2 == 1) Pat::template acc_merge<P>(acc, part);
     }
     group_allreduce<Pat, P>(acc, G);
     Pat::template row_after<P>(A, rc, acc);

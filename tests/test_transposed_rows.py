@@ -177,6 +177,31 @@ def test_batches_row_vectors_and_what_stays_two_kernels(ctx):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("p, q", [(1014, 49800), (4096, 8000), (2400, 6000)])
+def test_sums_are_no_further_off_than_the_row_kernels(ctx, p, q):
+    """Sums of squares (of one sign) against the same sums of the transposed tensor through the row kernels."""
+    def build(transposed):
+        pb = PatternBuilder("squares")
+        P, Q = pb.dims(2)
+        x = pb.param("bf16", [P, Q] if transposed else [Q, P])
+        x = pb.cast(pb.transpose(x, (1, 0)) if transposed else x, "f32")
+        pb.output(pb.reduce("sum", pb.op("mul", x, x), 1))
+        return pb.build()
+    one, rows = build(True), build(False)
+    x = torch.randn(p, q, generator=torch.Generator().manual_seed(p)).bfloat16()
+    outs, n = run(ctx, ctx.register_graph(one), one, [p, q], [x])
+    assert n == 1
+    h = ctx.register(rows)
+    ref, dims = torch.empty(q, device="cuda"), [0, 0]
+    dims[rows.ops[rows.params[0]].dims[0]], dims[rows.ops[rows.params[0]].dims[1]] = q, p
+    h.launch(dims, [x.cuda().t().contiguous()], [ref])
+    torch.cuda.synchronize()
+    want = (x.cuda().double() ** 2).sum(0)
+    off = lambda v: float((v.double() - want).norm() / want.norm())
+    assert off(outs[0]) <= 1.05 * off(ref), (off(outs[0]), off(ref))
+
+
+@pytest.mark.gpu
 def test_result_over_its_operand_and_forced_versions(ctx):
     """Through two kernels the operand is read before anything is written; a call that relies on it still goes that way."""
     from oracle import run as oracle_run
