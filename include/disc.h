@@ -382,6 +382,10 @@ int disc_graph_info(disc_ctx* ctx, int32_t graph_id, disc_graph_info_t* out);
 /* Bytes of DEVICE workspace disc_graph_launch needs at these dims: the planned buffers plus the
  * largest workspace of any of its patterns. */
 int disc_graph_workspace_bytes(disc_ctx* ctx, int32_t graph_id, const int64_t* dims, int n_dims, size_t* out);
+/* Pure host: disc_plan for pattern `pattern` (0 .. n_patterns - 1) of the graph as disc_graph_launch runs it at these
+ * dims, for aligned operands that do not overlap.  A transpose and the row reduce behind it that run as one kernel:
+ * no launch for the first, that kernel for the second (variant -1). */
+int disc_graph_plan(disc_ctx* ctx, int32_t graph_id, int pattern, const int64_t* dims, int n_dims, disc_plan_t* out);
 /* Launches the patterns in order on `hip_stream`; same pointer conventions as disc_launch. */
 int disc_graph_launch(disc_ctx* ctx, int32_t graph_id, const int64_t* dims, int n_dims, const void* const* inputs,
                       int n_in, void* const* outputs, int n_out, void* workspace, size_t workspace_bytes,

@@ -168,6 +168,7 @@ def load_library():
     lib.disc_graph_workspace_bytes.argtypes = [vp, C.c_int32, i64p, C.c_int, C.POINTER(C.c_size_t)]
     lib.disc_graph_launch.argtypes = [vp, C.c_int32, i64p, C.c_int, C.POINTER(vp), C.c_int, C.POINTER(vp), C.c_int,
                                       vp, C.c_size_t, vp]
+    lib.disc_graph_plan.argtypes = [vp, C.c_int32, C.c_int, i64p, C.c_int, C.POINTER(disc_plan_t)]
     lib.disc_force_variant.argtypes = [vp, C.c_int]
     lib.disc_static_scratch_init.argtypes = [vp]
     lib.disc_launch_static_scratch.argtypes = [vp, C.c_int32, i64p, C.c_int, C.POINTER(vp), C.c_int, C.POINTER(vp), C.c_int, vp]
@@ -266,6 +267,13 @@ class GraphHandle:
         self.ctx._check(self.ctx.lib.disc_graph_workspace_bytes(self.ctx.h, self.id, arr, n, C.byref(out)))
         return int(out.value)
 
+    def plan(self, dims, pattern: int) -> dict:
+        """What the graph's pattern number `pattern` launches at these dims (disc_graph_plan)."""
+        arr, n = self.ctx._dims(dims)
+        p = disc_plan_t()
+        self.ctx._check(self.ctx.lib.disc_graph_plan(self.ctx.h, self.id, int(pattern), arr, n, C.byref(p)))
+        return self.ctx._plan_dict(p)
+
     def launch(self, dims, inputs: Sequence, outputs: Sequence, workspace=None, workspace_bytes: int = 0,
                stream: Optional[int] = None):
         ctx = self.ctx
@@ -359,6 +367,10 @@ class Context:
         ins = (C.c_void_p * max(1, len(inputs)))(*[_ptr(t) for t in inputs]) if inputs is not None else None
         outs = (C.c_void_p * max(1, len(outputs)))(*[_ptr(t) for t in outputs]) if outputs is not None else None
         self._check(self.lib.disc_plan(self.h, pid, arr, n, ins, outs, int(force_variant), C.byref(p)))
+        return self._plan_dict(p)
+
+    @staticmethod
+    def _plan_dict(p) -> dict:
         d = {k: getattr(p, k) for k, _ in p._fields_ if k not in ("grid", "block", "lds_bytes", "kernel")}
         d["kernels"] = [bytes(p.kernel[i]).split(b"\0")[0].decode() for i in range(p.n_launches)]
         d["grid"] = [list(g) for g in p.grid][: p.n_launches]

@@ -1114,8 +1114,16 @@ bool plan_xpose(const disc_ctx* c, int64_t per, int64_t batch, int64_t inner, in
     if (nv == 0 && (int64_t)G * V * k >= inner) nv = k;
   const int rpb = B / G;
   if (nv == 0 || per < rpb || per > (1 << 18)) return false;
-  const int64_t strips = (per + rpb - 1) / rpb;
-  if (strips * batch > (1ll << 28)) return false;
+  const int64_t strips = (per + rpb - 1) / rpb, blocks = (strips * batch + 7) / 8 * 8;
+  // (a launch has less than 2^32 threads)
+  if (blocks * B >= (1ll << 32)) return false;
+  // A strip costs what it costs however short its rows (softmax, 2.4 to 4 ns), and the two kernels write no more for
+  // short ones: rows of up to 16 elements only while the chip holds about all strips at once, of up to 31 while the
+  // launches are most of the time.  bf16 softmax, two kernels / one, us: 40000 columns of 3 5.4 / 5.7 (eager calls 7.0 / 5.7), 65537 of 5
+  // 6.5 / 7.2, 200000 of 3 8.1 / 19.0; batches 16 x 12 x 1500 7.1 / 6.9, 500 x 2 x 64 5.7 / 8.1, 4000 x 2 x 1500 104 / 515; 500 x
+  // 24 x 300 14.3 / 14.2, 500 x 24 x 1500 31.8 / 54.9; 500 x 50 x 300 22.0 / 18.0.
+  if (inner <= 16 && strips * batch > (batch > 1 ? 1250 + 25 * inner : 2100)) return false;
+  if (inner < 32 && strips * batch > 6000) return false;
   LaunchRec& L = fp->launches[0];
   L.kid = K_ROW_XPOSE + (nv / 4 - 1) * 2 + (inner % V == 0 ? 1 : 0);
   L.block = (uint32_t)B;
@@ -1128,8 +1136,8 @@ bool plan_xpose(const disc_ctx* c, int64_t per, int64_t batch, int64_t inner, in
   fp->aux[0] = per;
   fp->aux[1] = strips;
   fp->aux[2] = strips * batch;
-  fp->aux[3] = (strips * batch + 7) / 8;
-  L.grid[0] = (uint32_t)(fp->aux[3] * 8);
+  fp->aux[3] = blocks / 8;
+  L.grid[0] = (uint32_t)blocks;
   fp->pub.n_launches = 1;
   return true;
 }
@@ -2018,28 +2026,38 @@ static void register_fused(disc_ctx* ctx, Graph& g, size_t gi) {
   r.fused_input = input;
 }
 
-// The launch of group r with the transpose in front of it (group t) in the same kernel.  `taken`: false when
-// this call has to go through both patterns.
-static int launch_fused(disc_ctx* ctx, const GraphGroup& t, const GraphGroup& r, const int64_t* dims, const void* const* in,
-                        void* const* outp, void* hip_stream, bool* taken) {
+// The plan of group r with the transpose in front of it (group t) in the same kernel.  `taken`: false when such a
+// call goes through both patterns.
+static int plan_fused(disc_ctx* ctx, const GraphGroup& t, const GraphGroup& r, const int64_t* dims, FullPlan* fp, bool* taken) {
   *taken = false;
-  const int64_t t0 = now_ns();
-  if (ctx->device < 0 || ctx->force_variant >= 0) return DISC_OK;
+  if (ctx->force_variant >= 0) return DISC_OK;
   const Pattern& tp = *ctx->patterns[t.pattern_id];
   const Pattern& p = *ctx->fused[r.fused];
   ShapeVals tv;
   int rc = shape_calc(ctx, tp, dims, tp.an.n_sym, &tv);
   if (rc) return rc;
-  FullPlan fp;
-  rc = shape_calc(ctx, p, dims, p.an.n_sym, &fp.sv);
+  rc = shape_calc(ctx, p, dims, p.an.n_sym, &fp->sv);
   if (rc) return rc;
   const int ng = (int)tp.an.groups.size();
   const int64_t per = tv.group[ng - 2], batch = ng == 3 ? tv.group[0] : 1;
-  const int V = p.an.vec_width;
-  if (fp.sv.rows == 0 || fp.sv.inner == 0 || fp.sv.rows != batch * per || fp.sv.inner != tv.group[ng - 1]) return DISC_OK;
-  if (!plan_xpose(ctx, per, batch, fp.sv.inner, V, &fp)) return DISC_OK;
+  if (fp->sv.rows == 0 || fp->sv.inner == 0 || fp->sv.rows != batch * per || fp->sv.inner != tv.group[ng - 1]) return DISC_OK;
+  *taken = plan_xpose(ctx, per, batch, fp->sv.inner, p.an.vec_width, fp);
+  return DISC_OK;
+}
+
+// Its launch, unless the results lie over the operand.
+static int launch_fused(disc_ctx* ctx, const GraphGroup& t, const GraphGroup& r, const int64_t* dims, const void* const* in,
+                        void* const* outp, void* hip_stream, bool* taken) {
+  *taken = false;
+  const int64_t t0 = now_ns();
+  if (ctx->device < 0) return DISC_OK;
+  const Pattern& p = *ctx->fused[r.fused];
+  FullPlan fp;
+  bool one = false;
+  int rc = plan_fused(ctx, t, r, dims, &fp, &one);
+  if (rc || !one) return rc;
   const char* lo = static_cast<const char*>(in[r.fused_input]);
-  const char* hi = lo + fp.sv.rows * fp.sv.inner * dtype_bytes(tp.an.accesses[0].dtype);
+  const char* hi = lo + fp.sv.rows * fp.sv.inner * dtype_bytes(ctx->patterns[t.pattern_id]->an.accesses[0].dtype);
   for (const Access& a : p.an.accesses) {      // (through both patterns the operand was read before anything was written)
     if (!a.is_output) continue;
     const char* o = static_cast<const char*>(outp[a.slot]);
@@ -2411,6 +2429,45 @@ int disc_graph_workspace_bytes(disc_ctx* ctx, int32_t id, const int64_t* dims, i
   size_t off[DISC_MAX_OPS];
   size_t pws = 0;
   return graph_layout(ctx, *g, dims, n_dims, false, off, &pws, out);
+  DISC_CATCH(ctx)
+}
+
+int disc_graph_plan(disc_ctx* ctx, int32_t id, int pattern, const int64_t* dims, int n_dims, disc_plan_t* out) {
+  DISC_TRY
+  Graph* g = get_graph(ctx, id);
+  if (!g || !out || pattern < 0 || pattern >= (int)g->groups.size())
+    return set_err(ctx, DISC_ERR_INVALID_ARG, "bad graph id, pattern index or null output");
+  if (!dims || n_dims != g->n_sym) return set_err(ctx, DISC_ERR_INVALID_ARG, "wrong number of dims for this graph");
+  const size_t gi = (size_t)pattern;
+  FullPlan fp;
+  for (const bool second : {true, false}) {     // the row reduce of a fused pair, the transpose of one
+    if (second ? gi == 0 : gi + 1 >= g->groups.size()) continue;
+    const GraphGroup &t = g->groups[second ? gi - 1 : gi], &r = g->groups[second ? gi : gi + 1];
+    if (r.fused < 0) continue;
+    bool taken = false;
+    const int rc = plan_fused(ctx, t, r, dims, &fp, &taken);
+    if (rc) return rc;
+    if (!taken) continue;
+    memset(out, 0, sizeof *out);
+    out->variant = -1;
+    if (!second) return DISC_OK;
+    const LaunchRec& L = fp.launches[0];
+    out->rows = fp.sv.rows;
+    out->inner = fp.sv.inner;
+    out->algorithmic_bytes = fp.sv.alg_bytes;
+    out->n_launches = 1;
+    out->vec_width = ctx->fused[r.fused]->an.vec_width;
+    out->index_bits = 64;
+    out->lanes_per_row = L.rp.G;
+    out->slots_per_lane = out->reg_slots = L.rp.nv;
+    for (int k = 0; k < 3; ++k) out->grid[0][k] = L.grid[k];
+    out->block[0][0] = L.block;
+    out->block[0][1] = out->block[0][2] = 1;
+    snprintf(out->kernel[0], sizeof out->kernel[0], "%s%s", ctx->fused[r.fused]->gen.prefix.c_str(), kernel_name(L.kid));
+    return DISC_OK;
+  }
+  const Pattern& p = *ctx->patterns[g->groups[gi].pattern_id];
+  return disc_plan(ctx, g->groups[gi].pattern_id, dims, p.an.n_sym, nullptr, nullptr, ctx->force_variant, out);
   DISC_CATCH(ctx)
 }
 

@@ -75,6 +75,35 @@ def test_registered_again_compiles_nothing():
         c.close()
 
 
+def test_which_calls_take_one_kernel():
+    """By the plan: all eight versions are reached; very short rows in great number, and launches of 2^32 threads and more
+    (which the device refuses), take two kernels."""
+    from paper_2103_05288_amd import Context
+    c = Context(-1)
+    try:
+        g = c.register_graph(softmax("bf16"))
+        seen = set()
+        for dims in ([8, 15], [64 * 8 * 4, 8], [64 * 8 * 4 + 1, 13], [64 * 8 * 8, 16], [32 * 8 * 12, 7201], [32 * 8 * 12 - 1, 7201],
+                     [64 * 8 * 12 + 8, 6145], [64 * 8 * 12 + 3, 6145], [40, 200000], [5, 65537], [3, 40000]):
+            first, second = g.plan(dims, 0), g.plan(dims, 1)
+            assert first["n_launches"] == 0 and second["n_launches"] == 1, dims
+            assert second["grid"][0][0] * second["block"][0][0] < 1 << 32
+            seen.add(second["kernels"][0].split("_k_row_xpose_")[1])
+        assert seen == {"nv%d%s" % (n, e) for n in (4, 8, 12, 16) for e in ("", "_e")}
+        for dims in ([3, 200000], [1, 154872], [8, 200000], [7, 7], [64 * 8 * 8 + 1, 16]):
+            first, second = g.plan(dims, 0), g.plan(dims, 1)
+            assert first["n_launches"] == 1 and "k_transpose_tile" in first["kernels"][0] and second["n_launches"] == 1, dims
+            assert "k_row_xpose" not in second["kernels"][0]
+        g = c.register_graph(softmax("bf16", rank3=True))
+        for dims in ([500, 2, 64], [4000, 2, 1500], [8252, 2, 908], [500, 24, 1500], [1 << 20, 33, 256]):
+            assert g.plan(dims, 0)["n_launches"] == 1 and "k_row_xpose" not in g.plan(dims, 1)["kernels"][0], dims
+        for dims in ([500, 50, 300], [16, 12, 1500], [1 << 20, 33, 224]):
+            p = g.plan(dims, 1)
+            assert g.plan(dims, 0)["n_launches"] == 0 and p["grid"][0][0] * p["block"][0][0] < 1 << 32, dims
+    finally:
+        c.close()
+
+
 def test_a_failing_compile_of_the_one_kernel_leaves_two(tmp_path):
     """The module of the fused kernel is an option: where it cannot be compiled the graph is registered all the same."""
     import os
