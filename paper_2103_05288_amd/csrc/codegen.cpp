@@ -1458,7 +1458,6 @@ struct Gen {
     for (const Access& a : an.accesses)
       if (late(a) && a.kind != ACC_ROWVEC && dtype_bytes(a.dtype) < 4) out->row_narrow_late = true;
     out->row_cols_ok = row_cols_ok();
-    out->row_elem_out = row_tmpl() && has_elem_outputs();
     out->row_held = row_held();
     out->stream_held = stream_held();
     out->col_held = col_held;

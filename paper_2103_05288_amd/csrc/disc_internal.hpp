@@ -223,7 +223,6 @@ struct Generated {
   int n_row_reds = 0;                 // row reduce: per-row values reduced over the rows to one number (last launch)
   std::vector<int> staged_elem_bytes; // row reduce: element size of each row vector that can be staged in LDS
   bool row_tail_ok = false;           // row reduce: there are versions that take a ragged end of a row as single elements (_t)
-  bool row_elem_out = false;          // row reduce: some output has an element per element of the iteration space
   bool row_held = false;              // row reduce, nothing written per element or summed over the rows
   int stream_held = kStreamHeldSlots; // ... and in its blocks of up to 512 threads of row_held patterns
   bool col_held = false;              // column reduce: strips may stay in registers between the reduction and the epilogue
@@ -269,7 +268,6 @@ struct GenOptions {
 constexpr int kXposeSlots[] = {4, 8, 12, 16};
 // The access of input `slot` when a row reduce can take it transposed, else -1 (codegen.cpp)
 int xpose_access(const Analysis& an, int slot);
-
 
 // checker.cpp: validate, close constraints, decide fusion, resolve contexts, collapse.
 // number of operands (`in[]` entries that mean something) of an opcode

@@ -1650,8 +1650,6 @@ int disc_test_option(disc_ctx* ctx, int option, int value) {
   DISC_CATCH(ctx)
 }
 
-// own_need: the workspace has to hold what this launch uses (the static scratch array), not what
-// disc_workspace_bytes gives for operands of any alignment (a caller's workspace).
 // the planned launches of one call
 static int submit(disc_ctx* ctx, const Pattern* p, const FullPlan& fp, const int64_t* dims, const void* const* inputs,
                   void* const* outputs, void* workspace, void* hip_stream) {
@@ -1679,6 +1677,8 @@ static int submit(disc_ctx* ctx, const Pattern* p, const FullPlan& fp, const int
   return DISC_OK;
 }
 
+// own_need: the workspace has to hold what this launch uses (the static scratch array), not what
+// disc_workspace_bytes gives for operands of any alignment (a caller's workspace).
 static int launch_impl(disc_ctx* ctx, int32_t id, const int64_t* dims, int n_dims, const void* const* inputs, int n_in,
                        void* const* outputs, int n_out, void* workspace, size_t workspace_bytes, void* hip_stream, bool own_need) {
   const int64_t t0 = now_ns();
