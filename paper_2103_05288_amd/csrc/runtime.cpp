@@ -413,11 +413,13 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     const int64_t ts = dtype_bytes(an.accesses[0].dtype) <= 2 ? 128 : 64;
     int64_t ntiles = batch * ((P + ts - 1) / ts) * ((Q + ts - 1) / ts);
     // two-byte elements: half tiles (64 result columns, see the kernel) for operand and result of up to 84 MiB together, where
-    // more tiles in flight count (us, whole / half tiles: 4000 x 4001, 61 MiB, 16.4 / 14.4; 4 x 9488 x 564, 82 MiB, 23.8 / 24.4;
-    // 1586 x 15009, 91 MiB, 28.3 / 32.2; 37 x 107 x 7877, 119 MiB, 36.1 / 44.8), and where a whole tile would be half empty: up
-    // to 64 result columns (64 x 500000 29.4 / 26.1, 30 x 2000000 90.6 / 83.3) or 128 result rows (510230 x 102 106.8 / 88.8,
-    // 600000 x 80 52.7 / 41.0; but 102 x 510230 59 / 84)
-    const bool half = dtype_bytes(an.accesses[0].dtype) == 2 && (sv.alg_bytes < (84ll << 20) || P <= 128 || Q <= 64);
+    // more tiles in flight count (us, whole / half tiles: 4000 x 4001, 61 MiB, 16.4 / 14.4), and up to 128 MiB where the result's
+    // rows start on 32-byte boundaries (8000 x 3700 31.2 / 27.7, 14400 x 2001 28.5 / 24.8, 6000 x 4097 25.1 / 24.8; elsewhere a
+    // half tile's row ends inside a sector of memory twice as often: 1586 x 15009 28.3 / 32.2, 4264 x 5864 29.1 / 31.4; 37 x
+    // 112 x 7877 34.7 / 40.9); and where a whole tile would be half empty: up to 64 result columns (64 x 500000 29.4 / 26.1, 30
+    // x 2000000 90.6 / 83.3) or 128 result rows (510230 x 102 106.8 / 88.8, 600000 x 80 52.7 / 41.0; but 102 x 510230 59 / 84)
+    const bool half = dtype_bytes(an.accesses[0].dtype) == 2 &&
+                      (sv.alg_bytes < (84ll << 20) || (sv.alg_bytes < 2 * kNonTemporalMinBytes && Q % 16 == 0 && Q > 128) || P <= 128 || Q <= 64);
     if (half) ntiles = batch * ((P + 127) / 128) * ((Q + 63) / 64);
     LaunchRec& L = fp->launches[0];
     L.kid = half ? K_TRANSPOSE_TILE_H : K_TRANSPOSE_TILE;

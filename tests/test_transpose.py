@@ -176,7 +176,7 @@ def test_packed_tiles_of_two_byte_elements(dtype):
     try:
         for perm, shapes, kernel in (
                 ((1, 0), [[64, 128], [63, 127], [65, 129], [1, 1], [1, 300], [300, 1], [8, 8], [7, 1025], [129, 8], [255, 257],
-                          [66, 4099], [33, 1100003], [1100009, 31]], "k_transpose_tile_h"),
+                          [66, 4099], [33, 1100003], [1100009, 31], [6000, 4097]], "k_transpose_tile_h"),
                 ((0, 2, 1), [[5, 65, 131], [300, 3, 5], [2, 1, 129]], "k_transpose_tile_h"),
                 ((1, 0), [[5801, 5795], [101, 430007], [170009, 131], [4097, 6000]], "k_transpose_tile"),
                 ((0, 2, 1), [[3, 3201, 3577], [37, 107, 7877]], "k_transpose_tile")):
