@@ -516,14 +516,15 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // 16384 rows of 6000 columns 41.1 / 39.7, 4096 33.9 / 28.5, 3000 26.4 / 23.2, 2500 22.2 / 20.4, 2000 20.8 / 17.7;
       // but 1501 15.3 / 16.7, 1024 13.3 / 13.9; odd rows, whose slots the others shift: 4095 34.3 / 35.9, 2049 21.8 /
       // 21.8; 8192 rows of 2500 14.8 / 13.9, 6000 of 4096 17.4 / 14.8, 5000 of 3000 12.2 / 11.7, 4000 of 2500 10.1 / 10.4.
-      // Large launches that three slots a lane of 128 or 256 lanes fit are bound by the memory, and no faster: 30000 rows of
-      // 6080 66.0 / 69.6; fp32 sums, 40000 rows of 1240 31.8 / 33.3, of 1400 35.7 / 37.4 (but bf16, 30000 of 2800 41.4 / 34.7).
+      // Launches beyond the memory-side cache that three slots a lane of 256 lanes fit are bound by the memory, and no faster: 30000
+      // rows of 6080 66.0 / 69.6, of 5120 59.9 / 60.9 (16000 rows of 5000 39.1 / 33.6); and of 128 lanes, four-byte elements, from
+      // 144 MiB: fp32 sums, 40000 rows of 1240 31.8 / 33.3, of 1400 35.7 / 37.4.
       if (p.gen.row_held) {
         bool dwords = true;
         for (const Access& a : an.accesses)
           if (a.kind == ACC_FULL && (sv.inner * dtype_bytes(a.dtype)) % 4 != 0) dwords = false;
         const bool one = p.gen.stream_held > kStreamHeldSlots;
-        const bool three = sv.alg_bytes >= (144ll << 20) && ((V <= 4 && spr > 256 && spr <= 384) || spr > 512);
+        const bool three = V <= 4 && spr > 256 && spr <= 384 ? sv.alg_bytes >= (144ll << 20) : spr > 512 && sv.alg_bytes >= (256ll << 20);
         if (spr > 3 * 256 || (force < 0 && one && spr > 3 * 64 && dwords && !three && sv.rows > 16ll * c->n_cus)) stream = true;
       }
       // Sums over the rows and three slots per lane do not fit the registers of a wide block
