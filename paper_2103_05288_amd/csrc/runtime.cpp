@@ -1124,6 +1124,10 @@ bool plan_xpose(const disc_ctx* c, int64_t per, int64_t batch, int64_t inner, in
   const int64_t strips = (per + rpb - 1) / rpb, blocks = (strips * batch + 7) / 8 * 8;
   // (a launch has less than 2^32 threads)
   if (blocks * B >= (1ll << 32)) return false;
+  // Operand rows of an odd number of two-byte elements: every access is off dword boundaries, which shows where a few strips walk
+  // many rows (before the fused kernel / two kernels / one, 2900 x 65 9.4 / 7.1 / 10.4, 3527 x 65 10.3 / 8.1 / 11.9, 4096 x 65 9.0 / 6.8 /
+  // 12.4; even ones: 4096 x 16 8.0 / 6.2 / 6.8, 3527 x 300 12.3 / 9.5 / 8.9; 3000 x 2001 15.5 / - / 11.5).
+  if (V == 8 && per % 2 != 0 && inner > 64 * V * 5 && per * batch < 512) return false;
   // A strip costs what it costs however short its rows (softmax, 2.4 to 4 ns), and the two kernels write no more for
   // short ones: rows of up to 16 elements only while the chip holds about all strips at once, of up to 31 while the
   // launches are most of the time.  bf16 softmax, two kernels / one, us: 40000 columns of 3 5.4 / 5.7 (eager calls 7.0 / 5.7), 65537 of 5

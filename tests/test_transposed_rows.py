@@ -90,7 +90,7 @@ def test_which_calls_take_one_kernel():
             assert second["grid"][0][0] * second["block"][0][0] < 1 << 32
             seen.add(second["kernels"][0].split("_k_row_xpose_")[1])
         assert seen == {"nv%d%s" % (n, e) for n in (4, 8, 12, 16) for e in ("", "_e")}
-        for dims in ([3, 200000], [1, 154872], [8, 200000], [7, 7], [64 * 8 * 8 + 1, 16]):
+        for dims in ([3, 200000], [1, 154872], [8, 200000], [7, 7], [64 * 8 * 8 + 1, 16], [3527, 65]):
             first, second = g.plan(dims, 0), g.plan(dims, 1)
             assert first["n_launches"] == 1 and "k_transpose_tile" in first["kernels"][0] and second["n_launches"] == 1, dims
             assert "k_row_xpose" not in second["kernels"][0]
@@ -169,8 +169,9 @@ def test_strips_and_row_lengths(ctx, dtype):
     pat = softmax(dtype)
     g = ctx.register_graph(pat)
     V = 4 if dtype == "f32" else 8
+    odd = 1 if dtype == "f32" else 2               # few long rows off dword boundaries
     for i, (p, q, n) in enumerate([(1, 8, 1), (3, 9, 1), (7, 7, 2), (8, 1, 2), (8, 15, 1), (9, 17, 1), (64 * V, 31, 1), (64 * V + 1, 33, 1),
-                                   (64 * V * 4, 8, 1), (64 * V * 4 + 1, 13, 1), (64 * V * 8 - 1, 21, 1), (64 * V * 8, 16, 1),
+                                   (64 * V * 4, 8, 1), (64 * V * 4 + 1, 13, 1), (64 * V * 8 - 1, 22, 1), (64 * V * 8 - 1, 21, odd), (64 * V * 8, 16, 1), (64 * V * 5 + 3, 513, 1),
                                    (64 * V * 8 + 1, 16, 2), (64 * V * 16 + 1, 40, 2), (37, 7168, 1), (16 * V + 5, 32801, 1), (5, 65537, 1),
                                    (16 * V * 12, 32800, 1), (16 * V * 12 + 1, 32800, 1), (32 * V * 12, 7201, 1), (32 * V * 12 + 3, 7169, 1),
                                    (64 * V * 8 + 3, 6145, 1), (64 * V * 12 + 8, 6145, 1), (64 * V * 12, 6144 - 16, 2)]):
@@ -192,7 +193,7 @@ def test_batches_row_vectors_and_what_stays_two_kernels(ctx):
     for dtype in ("bf16", "f16"):
         pat = weighted_sums(dtype)
         g = ctx.register_graph(pat)
-        for i, (p, q) in enumerate([(8, 8), (63, 100), (2050, 31), (4096, 9), (515, 7300)]):
+        for i, (p, q) in enumerate([(8, 8), (63, 100), (2050, 31), (4096, 10), (515, 7300)]):
             check(ctx, g, pat, [p, q], 1, 40 + i, positive=True)
     pat = distance_to_max_i32()
     g = ctx.register_graph(pat)
