@@ -609,8 +609,9 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // (a few rows per CU: more threads to a row, four slots a lane instead; us, four / eight: 1000 x 8000 bf16 9.1 / 9.4, fp32
       // variances 272 x 4150 2.8 / 3.0; 769 to 1024 slots while the chip has work for a few rounds, log-sum-exp 1900 x 7200 11.2
       // / 11.9, 4500 x 8160 17.3 / 19.0, 6000 x 8160 22.6 / 23.8; up to 2048, maximum with position 1200 x
-      // 16000 9.1 / 9.7; longer ones, maximum 3 x 31200 2.6 / 2.7, but with position 270 x 20800 6.8 / 5.3)
-      const bool few = sv.rows <= (spr <= 3 * 256 ? 4ll : spr <= 256 * kStreamHeldSlots ? 28 : spr <= 512 * kStreamHeldSlots ? 5 : 1) * c->n_cus;
+      // 16000 9.1 / 9.7; not longer ones, maximum with position 270 x 20800
+      // 6.8 / 5.3, though 3 x 31200 of a maximum alone 2.6 / 2.7)
+      const bool few = sv.rows <= (spr <= 3 * 256 ? 4ll : spr <= 256 * kStreamHeldSlots ? 28 : spr <= 512 * kStreamHeldSlots ? 5 : 0) * c->n_cus;
       const int64_t per_lane = held && !few ? p.gen.stream_held : kStreamHeldSlots;
       if (vec && spr <= 2 * 1024 * kStreamHeldSlots) {
         if (held && per_lane > kStreamHeldSlots) L.block = 64;

@@ -366,7 +366,7 @@ def test_held_rows(ctx, nt):
                 assert_close(g, w, f"held rows {T}x{H} out{k}")
     finally:
         ctx.test_option("non_temporal", -1)
-    for T, H, block in ((4097, 1538, 64), (7180, 6145, 128), (1030, 6145, 256), (3, 6145, 256), (1026, 16391, 512), (3, 16391, 1024), (3, 16384, 512),
+    for T, H, block in ((4097, 1538, 64), (7180, 6145, 128), (1030, 6145, 256), (3, 6145, 256), (1026, 16391, 512), (3, 16391, 512), (3, 16384, 512),
                         (1026, 32769, 1024)):
         assert h.plan([T, H])["block"][0][0] == block
     assert seen == {("row_stream_vec", b) for b in (64, 128, 256, 512)} | {("row_stream_vecw", b) for b in (256, 512, 1024)}
