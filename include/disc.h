@@ -338,8 +338,11 @@ typedef enum {
   DISC_OPT_STAGE_ROW_VECTORS = 1, /* 1 host rule (default), 0 row vectors are never staged in LDS     */
   DISC_OPT_ROW_ROUNDS = 2,        /* 0 host rule (default), n > 0: row-kernel grid = n rounds of the
                                      blocks the chip holds at once                                    */
-  DISC_OPT_ALIGN_ROW_SLOTS = 3    /* 1 host rule (default), 0: the vector slots of ragged rows are never
+  DISC_OPT_ALIGN_ROW_SLOTS = 3,   /* 1 host rule (default), 0: the vector slots of ragged rows are never
                                      shifted to the 16-byte boundaries of the tensor                  */
+  DISC_OPT_COMPACT_LOOKS = 4      /* -1 host rule (default), n >= 0: compactions of two launches take the
+                                     one-pass version, which looks n times for another block's count
+                                     before it counts that block's elements itself                    */
 } disc_test_option_id;
 int disc_test_option(disc_ctx* ctx, int option, int value);
 

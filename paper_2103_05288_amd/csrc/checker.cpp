@@ -295,7 +295,7 @@ struct KernelNames {
         "k_col_epi_vec", "k_col_epi_vec_i64", "k_col_epi_scalar", "k_col_epi_scalar_i64", "k_col_epi_vec_nt",
         "k_transpose_tile", "k_col_epi2_vec", "k_col_epi2_vec_nt", "k_col_epi2_scalar",
         "k_compact_count_vec", "k_compact_count_scalar", "k_compact_scan", "k_compact_scatter_vec", "k_compact_scatter_scalar",
-        "k_compact_scatter_vec_nt", "k_row_cols_vec", "k_row_cols_vec_nt", "k_col_epi2_vec_nts", "k_row_stream_vecw", "k_transpose_tile_h", "k_col_strip_vecl",
+        "k_compact_scatter_vec_nt", "k_compact_clear", "k_compact_chain_vec", "k_row_cols_vec", "k_row_cols_vec_nt", "k_col_epi2_vec_nts", "k_row_stream_vecw", "k_transpose_tile_h", "k_col_strip_vecl",
         "k_row_xpose_nv4", "k_row_xpose_nv4_e", "k_row_xpose_nv8", "k_row_xpose_nv8_e", "k_row_xpose_nv12", "k_row_xpose_nv12_e",
         "k_row_xpose_nv16", "k_row_xpose_nv16_e"};
     for (int i = 0; i < K_ROW_BASE; ++i) name[i] = fixed[i];

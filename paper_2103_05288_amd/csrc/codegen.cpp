@@ -457,9 +457,22 @@ struct Gen {
     return false;
   }
   int window_arg(int w) const { return (int)(an.products.size() + an.offsets.size()) + 2 * w; }
+  // the same input read where it is, of one read an element earlier: -1 if there is none
+  int twin(size_t i) const {
+    const Access& a = an.accesses[i];
+    for (size_t k = 0; k < an.accesses.size(); ++k) {
+      const Access& b = an.accesses[k];
+      if (!b.is_output && !b.prev && b.slot == a.slot && b.kind == ACC_FULL && a.kind == ACC_FULL && !b.padded && b.src_value < 0 && a.src_value < 0 &&
+          b.has_inner && !late(b))
+        return (int)k;
+    }
+    return -1;
+  }
   // load of a slot of an operand; a padded one takes the padding value wherever the operand is not
   std::string load_call(const Access& a, size_t i, const std::string& dst, const std::string& ld_tmpl, const std::string& extra) {
     const std::string ptr = elem_ptr(a, fmt("A.p%d", a.slot));
+    if (a.prev && twin(i) >= 0)
+      return "disc::ld_prev_first(" + dst + ", " + ptr + ", " + elem_base(a, i) + ", sp, rc.sb + (disc::i64)" + elem_base(a, i) + " > 0);";
     if (a.prev) return "disc::ld_prev(" + dst + ", " + ptr + ", " + elem_base(a, i) + ", sp, rc.sb + (disc::i64)" + elem_base(a, i) + " > 0);";
     if (!a.padded) return "disc::ld" + ld_tmpl + "(" + dst + ", " + ptr + ", " + elem_base(a, i) + ", sp" + extra + ");";
     std::string lo = "0", hi = "0x7fffffffffffffffLL";
@@ -1119,19 +1132,46 @@ struct Gen {
     os << "    (void)A; (void)o; (void)c; (void)acc; (void)s; (void)e; (void)write;\n  }\n";
   }
 
+  // compaction: bytes of the kept values of an element, all outputs
+  int compact_held_bytes() const {
+    int bytes = 0;
+    for (const auto& out : an.outputs)
+      if (an.accesses[out.access].compact) bytes += dtype_bytes(an.accesses[out.access].dtype);
+    return bytes;
+  }
   // compaction pattern: where the kept values, the slots and the count go
   void emit_compact_fns() {
-    // the kept values of one slot of a wavefront, one output after the other through the same LDS
+    os << "  template <int V> static DISC_DEV void compact_prev(Slot<V>& s) {\n";
+    for (size_t i = 0; i < an.accesses.size(); ++i)
+      if (an.accesses[i].prev && twin(i) >= 0) os << fmt("    disc::prev_from(s.a%zu, s.a%d);\n", i, twin(i));
+    os << "    (void)s;\n  }\n";
+    // the kept values of a wavefront's part of a tile, one output after the other through the same LDS
     int bytes = 0;
-    os << "  template <int V, bool NT> static DISC_DEV void compact_put(const Args& A, const OutSlot<V>& o, disc::u32 kb, int before, int kept, disc::i64 pos, char* stage) {\n";
+    os << "  template <int V, bool NT, int U> static DISC_DEV void compact_put(const Args& A, const OutSlot<V> (&o)[U], const disc::u32 (&kb)[U], const int (&before)[U], int kept, disc::i64 pos, char* stage) {\n";
     for (const auto& out : an.outputs) {
       const Access& a = an.accesses[out.access];
       if (!a.compact) continue;
       bytes = std::max(bytes, dtype_bytes(a.dtype));
-      os << "    disc::compact_put_elems<V, NT>(A.o" << a.slot << ", pos, kb, before, kept, stage, [&](int e) { return o.o" << a.slot << ".get(e); });\n";
+      os << "    disc::compact_put_elems<V, NT, U>(A.o" << a.slot << ", pos, kb, before, kept, stage, [&](int u, int e) { return o[u].o" << a.slot << ".get(e); });\n";
     }
     os << "    (void)A; (void)o; (void)kb; (void)before; (void)kept; (void)pos; (void)stage;\n  }\n";
-    os << "  static constexpr int COMPACT_BYTES = " << bytes << ", COMPACT_SLOTS = " << kCompactLaneSlots << ";\n";
+    // ... and in two halves, every output in LDS of its own
+    const int held = compact_held_bytes();
+    for (const bool flush : {false, true}) {
+      os << (flush ? "  template <bool NT> static DISC_DEV void compact_flush(const Args& A, int kept, disc::i64 pos, const char* stage) {\n"
+                   : "  template <int V, int U> static DISC_DEV void compact_hold(const OutSlot<V> (&o)[U], const disc::u32 (&kb)[U], const int (&before)[U], char* stage) {\n");
+      int at = 0;
+      for (const auto& out : an.outputs) {
+        const Access& a = an.accesses[out.access];
+        if (!a.compact) continue;
+        const std::string where = fmt("stage + %d * 64 * %d * %d", at, an.vec_width, kCompactLaneSlots);
+        if (flush) os << "    disc::compact_flush_elems<NT>(A.o" << a.slot << ", pos, kept, " << where << ");\n";
+        else os << "    disc::compact_hold_elems<V, U, " << dtype_ctype(a.dtype) << ">(kb, before, " << where << ", [&](int u, int e) { return o[u].o" << a.slot << ".get(e); });\n";
+        at += dtype_bytes(a.dtype);
+      }
+      os << (flush ? "    (void)A; (void)kept; (void)pos; (void)stage;\n  }\n" : "    (void)o; (void)kb; (void)before; (void)stage;\n  }\n");
+    }
+    os << "  static constexpr int COMPACT_BYTES = " << bytes << ", COMPACT_ALL_BYTES = " << held << ", COMPACT_SLOTS = " << kCompactLaneSlots << ";\n";
     // the slots of the V elements of one slot of the tile, stored as one vector
     os << "  template <int V, bool NT, class SP> static DISC_DEV void rank_store(const Args& A, disc::i64 base, unsigned col, const disc::i64 (&rank)[V], SP sp) {\n";
     for (const auto& out : an.outputs) {
@@ -1259,6 +1299,10 @@ struct Gen {
       k("k_compact_scatter_vec", fmt("disc::compact_scatter_body<Pat, %d>(A);", V), nullptr);
       k("k_compact_scatter_vec_nt", fmt("disc::compact_scatter_body<Pat, %d, true>(A);", V), nullptr);
       k("k_compact_scatter_scalar", "disc::compact_scatter_body<Pat, 1>(A);", nullptr);
+      // (kept values of two tiles wait in LDS: 32 KB for one output of the narrowest type, four blocks to a CU)
+      out->compact_chain = V > 1 && compact_held_bytes() * V <= 16;
+      k("k_compact_clear", "disc::compact_clear_body<Pat>(A);", nullptr);
+      if (out->compact_chain) k("k_compact_chain_vec", fmt("disc::compact_chain_body<Pat, %d>(A);", V), nullptr);
       max_threads = 1024;
       k("k_compact_scan", "disc::compact_scan_body<Pat>(A);", nullptr);
       max_threads = 256;

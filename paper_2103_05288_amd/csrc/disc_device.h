@@ -264,6 +264,24 @@ DISC_DEV void ld_prev(Vec<T, N>& d, const T* __restrict__ p, I off, SP sp, bool 
   }
 }
 
+// The same where the operand itself is in the slot too: d[0] is all that is loaded, and the others are copied from there
+// when the slot is used (prev_from; carried along with the slot they would take registers twice).
+template <class T, int N, class I, class SP>
+DISC_DEV void ld_prev_first(Vec<T, N>& d, const T* __restrict__ p, I off, SP, bool has_prev) {
+  d.clear();
+  T first = T(0);
+  if (__is_same(SP, InnerSpan) || has_prev) first = at(p - 1, off)[0];
+  d.set(0, first);
+}
+template <class T, int N>
+DISC_DEV void prev_from(Vec<T, N>& d, const Vec<T, N>& same) {
+  const T first = d.get(0);
+  d.clear();
+  d.set(0, first);
+#pragma unroll
+  for (int e = 1; e < N; ++e) d.set(e, same.get(e - 1));
+}
+
 // storage <-> register conversions (float values live in fp32 registers; one rounding,
 // to nearest even, at the store)
 DISC_DEV float to_f32(float x) { return x; }
@@ -2042,17 +2060,16 @@ DISC_DEV void col_epi2_body(const typename Pat::Args& A, const ColPlan& cp) {
 // contiguous stretch per wavefront.  Kept elements are counted and ranked with lane masks (ballot,
 // mbcnt, popcount: two or three instructions per element, no scan over the lanes) and meet in LDS,
 // slot by slot, so that they leave as contiguous stores whatever the share that is kept.
-// No atomics, nothing read back by the host, no block waits for another:
-//   1. compact_count:   a block owns a chunk of consecutive tiles, evaluates the fused chain and
-//                       counts what is kept; one count per chunk to the workspace.
-//   2. compact_scan:    (short inputs only: chunks of one tile) one block turns the counts into
+// The output order is the input order; nothing is read back by the host:
+//   1. compact_count:   evaluates the fused chain and counts what is kept; the counts go to the workspace.
+//   2. compact_scan:    (short inputs only: a tile to a block) one block turns the counts into
 //                       exclusive offsets, in a fixed order, and stores the total -- the
 //                       data-dependent size -- in the COMPACT_COUNT outputs.
-//   3. compact_scatter: the blocks evaluate their chunks again (the inputs are read twice; nothing
-//                       but the counts is kept between the launches) and store the kept values and
-//                       the ranks.  Without the scan launch every block adds up the counts in
-//                       front of its own (at most a couple of thousand), and the last one stores
-//                       the total.
+//   3. compact_scatter: evaluates the chain again (the inputs are read twice; nothing but the counts is kept between the
+//                       launches) and stores the kept values and the ranks.  Without the scan launch every
+//                       block adds up the counts in front of its own (four for each of at most 1024 blocks), and
+//                       the last one stores the total.
+//   Large inputs: compact_clear and compact_chain, which reads them once.
 // =======================================================================================
 constexpr int kCompactWaves = 4;          // wavefronts per block
 // (slots per lane: Pat::COMPACT_SLOTS)
@@ -2064,18 +2081,16 @@ DISC_DEV int opaque_lane() {
   return lane;
 }
 
-// Evaluates the calling lane's slots of a wavefront's part of a tile: values, and one word of kept
-// flags per slot (bit e = element e).  `w0` = first element of the part (a scalar: the lanes add
-// 32-bit offsets).  Returns what the WAVEFRONT keeps.  WHOLE: the part lies inside the tensor, so
-// no slot is ragged and every load is one wide access; only slot 0 can be the tensor's first one.
+// The calling lane's slots of a wavefront's part of a tile.  `w0` = first element of the part (a scalar: the lanes add
+// 32-bit offsets).  WHOLE: the part lies inside the tensor, so no slot is ragged and every load is one wide access; only
+// slot 0 can be the tensor's first one.
 template <bool WHOLE, class Pat, int V, int U>
-DISC_DEV int compact_eval(const typename Pat::Args& A, i64 w0, typename Pat::template OutSlot<V> (&o)[U], u32 (&kb)[U]) {
+DISC_DEV void compact_load(const typename Pat::Args& A, i64 w0, typename Pat::template Slot<V> (&slot)[U]) {
   const int lane = opaque_lane();
   typename Pat::RowCtx rc;
   Pat::row_begin3(A, 0, 0, w0, rc);
-  typename Pat::template Slot<V> slot[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) {             // all loads first
+  for (int u = 0; u < U; ++u) {
     const unsigned at = (unsigned)((u * 64 + lane) * V);
     if constexpr (WHOLE) {
       if (u == 0) Pat::template load<V>(A, rc, at, EvenSpan::upto(V), slot[u]);
@@ -2085,7 +2100,14 @@ DISC_DEV int compact_eval(const typename Pat::Args& A, i64 w0, typename Pat::tem
       if (rem > 0) Pat::template load<V>(A, rc, at, Span::upto(rem < (i64)V ? (int)rem : V), slot[u]);
     }
   }
-  int cnt = 0;
+}
+// Their values, and one word of kept flags per slot (bit e = element e).
+template <bool WHOLE, class Pat, int V, int U>
+DISC_DEV void compact_eval(const typename Pat::Args& A, i64 w0, const typename Pat::template Slot<V> (&slot)[U],
+                           typename Pat::template OutSlot<V> (&o)[U], u32 (&kb)[U]) {
+  const int lane = opaque_lane();
+  typename Pat::RowCtx rc;
+  Pat::row_begin3(A, 0, 0, w0, rc);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const i64 col = w0 + (u * 64 + lane) * V, rem = A.inner - col;
@@ -2093,42 +2115,69 @@ DISC_DEV int compact_eval(const typename Pat::Args& A, i64 w0, typename Pat::tem
     u32 bits = 0;
     if (n > 0) {
       typename Pat::template Keep<V> kp;
-      if constexpr (!WHOLE) Pat::template epilogue<V, false>(A, rc, slot[u], kp, col, Span::upto(n), o[u]);
-      else if (u == 0) Pat::template epilogue<V, false>(A, rc, slot[u], kp, col, EvenSpan::upto(n), o[u]);
-      else Pat::template epilogue<V, false>(A, rc, slot[u], kp, col, InnerSpan::upto(n), o[u]);
+      typename Pat::template Slot<V> x = slot[u];
+      Pat::template compact_prev<V>(x);
+      if constexpr (!WHOLE) Pat::template epilogue<V, false>(A, rc, x, kp, col, Span::upto(n), o[u]);
+      else if (u == 0) Pat::template epilogue<V, false>(A, rc, x, kp, col, EvenSpan::upto(n), o[u]);
+      else Pat::template epilogue<V, false>(A, rc, x, kp, col, InnerSpan::upto(n), o[u]);
 #pragma unroll
       for (int e = 0; e < V; ++e) bits |= (e < n && o[u].keep[e]) ? 1u << e : 0u;
     }
-    // one register of flags per slot from here on: as lane masks, U * V of them would not fit the
-    // scalar registers
-    asm volatile("" : "+v"(bits));
     kb[u] = bits;
-#pragma unroll
-    for (int e = 0; e < V; ++e) cnt += __builtin_popcountll(__builtin_amdgcn_ballot_w64((bits >> e) & 1));
   }
-  return cnt;
+}
+// Inclusive sum over the lanes of a wavefront, all of them active: four steps within rows of 16 lanes, then the last
+// lane of a row to the row behind it and of a half to the other.
+DISC_DEV u32 wave_scan(u32 x) {
+  x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);   // row_shr:1
+  x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+  x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+  x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+  x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);   // row_bcast:15, rows 1 and 3
+  x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);   // row_bcast:31, rows 2 and 3
+  return x;
 }
 
-// Stores the kept values and the ranks of a wavefront's part of a tile; `pos` = number of elements
-// kept in front of it.  `stage`: 64 * V * COMPACT_BYTES bytes of LDS of the wavefront's own.
-template <bool WHOLE, bool NT, class Pat, int V, int U>
-DISC_DEV void compact_emit(const typename Pat::Args& A, i64 w0, const typename Pat::template OutSlot<V> (&o)[U],
-                           const u32 (&kb)[U], i64 pos, char* stage) {
-  const int lane = opaque_lane();
+// Where the kept elements of a part go: what the lanes in front keep of the same slot, two slots to a word, and what
+// the wavefront keeps of each.
+template <int U>
+struct CompactRanks {
+  u32 front[U / 2], all[U / 2];
+  DISC_DEV int count(const u32 (&kb)[U]) {
+    int kept = 0;
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    int before = 0, kept = 0;               // kept in front of the lane / by the wavefront, in this slot
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-      const u64 m = __builtin_amdgcn_ballot_w64((kb[u] >> e) & 1);
-      before = (int)__builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, (u32)before));
-      kept += __builtin_popcountll(m);
+    for (int h = 0; h < U / 2; ++h) {
+      const u32 own = (u32)__builtin_popcount(kb[2 * h]) | (u32)__builtin_popcount(kb[2 * h + 1]) << 16;
+      const u32 upto = wave_scan(own);
+      front[h] = upto - own;
+      all[h] = (u32)__builtin_amdgcn_readlane((int)upto, 63);
+      kept += (int)(all[h] & 0xffff) + (int)(all[h] >> 16);
     }
-    Pat::template compact_put<V, NT>(A, o[u], kb[u], before, kept, pos, stage);
-    if constexpr (Pat::HAS_RANK) {
+    return kept;
+  }
+  // kept in front of the lane's slots, in this part; returns what the part keeps
+  DISC_DEV int before(int (&b)[U]) const {
+    static_assert(U % 2 == 0, "two slots to a word");
+    int kept = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      b[u] = kept + (int)(u % 2 ? front[u / 2] >> 16 : front[u / 2] & 0xffff);
+      kept += (int)(u % 2 ? all[u / 2] >> 16 : all[u / 2] & 0xffff);
+    }
+    return kept;
+  }
+};
+
+// Stores the ranks of a wavefront's part of a tile; `pos` = number of elements kept in front of it.
+template <bool WHOLE, bool NT, class Pat, int V, int U>
+DISC_DEV void compact_store_ranks(const typename Pat::Args& A, i64 w0, const u32 (&kb)[U], const int (&before)[U], i64 pos) {
+  if constexpr (Pat::HAS_RANK) {
+    const int lane = opaque_lane();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
       const unsigned at = (unsigned)((u * 64 + lane) * V);
       i64 rank[V];
-      int r = before - 1;
+      int r = before[u] - 1;
 #pragma unroll
       for (int e = 0; e < V; ++e) {
         r += (int)((kb[u] >> e) & 1);
@@ -2138,26 +2187,45 @@ DISC_DEV void compact_emit(const typename Pat::Args& A, i64 w0, const typename P
       if constexpr (WHOLE) Pat::template rank_store<V, NT>(A, w0, at, rank, EvenSpan::upto(V));
       else if (rem > 0) Pat::template rank_store<V, NT>(A, w0, at, rank, Span::upto(rem < (i64)V ? (int)rem : V));
     }
-    pos += kept;
   }
 }
+// The kept values too; returns `pos` with the part's own added.  `stage`: (64 * V * U + 64) * COMPACT_BYTES bytes of
+// LDS of the wavefront's own.
+template <bool WHOLE, bool NT, class Pat, int V, int U>
+DISC_DEV i64 compact_emit(const typename Pat::Args& A, i64 w0, const typename Pat::template OutSlot<V> (&o)[U],
+                          const u32 (&kb)[U], const CompactRanks<U>& ranks, i64 pos, char* stage) {
+  int before[U];
+  const int kept = ranks.before(before);
+  compact_store_ranks<WHOLE, NT, Pat, V, U>(A, w0, kb, before, pos);
+  Pat::template compact_put<V, NT, U>(A, o, kb, before, kept, pos, stage);
+  return pos + kept;
+}
 
-// A wavefront's part of a tile, first the count and later the stores.
+// A tile's part of a wavefront, first the count and later the stores (short inputs).
 template <bool NT, class Pat, int V, int U>
 struct CompactPart {
   typename Pat::template OutSlot<V> o[U];
   u32 kb[U];
+  CompactRanks<U> ranks;
   i64 w0;
   bool whole;
   DISC_DEV int count(const typename Pat::Args& A, i64 tile) {
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     w0 = (tile * kCompactWaves + wave) * (64 * U * V);
     whole = w0 + 64 * U * V <= A.inner;
-    return whole ? compact_eval<true, Pat, V, U>(A, w0, o, kb) : compact_eval<false, Pat, V, U>(A, w0, o, kb);
+    typename Pat::template Slot<V> slot[U];
+    if (whole) {
+      compact_load<true, Pat, V, U>(A, w0, slot);
+      compact_eval<true, Pat, V, U>(A, w0, slot, o, kb);
+    } else {
+      compact_load<false, Pat, V, U>(A, w0, slot);
+      compact_eval<false, Pat, V, U>(A, w0, slot, o, kb);
+    }
+    return ranks.count(kb);
   }
   DISC_DEV void store(const typename Pat::Args& A, i64 pos, char* stage) {
-    if (whole) compact_emit<true, NT, Pat, V, U>(A, w0, o, kb, pos, stage);
-    else compact_emit<false, NT, Pat, V, U>(A, w0, o, kb, pos, stage);
+    if (whole) compact_emit<true, NT, Pat, V, U>(A, w0, o, kb, ranks, pos, stage);
+    else compact_emit<false, NT, Pat, V, U>(A, w0, o, kb, ranks, pos, stage);
   }
 };
 DISC_DEV i64 wave_scalar(i64 x) {
@@ -2171,37 +2239,129 @@ DISC_DEV void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// The kept elements of one slot of a wavefront (at most 64 * V), collected in LDS and stored as one
-// contiguous stretch at dst + pos.  (Stored straight from the lanes, a kept element here and there,
-// every store instruction covers the same few cache lines once more.)
-template <int V, bool NT, class T, class GET>
-DISC_DEV void compact_put_elems(T* __restrict__ dst, i64 pos, u32 kb, int before, int kept, char* stage, GET get) {
+// The kept elements of a wavefront's part, collected in LDS and stored as one contiguous stretch at dst + pos, by
+// pieces of 64 elements that start where dst does: one piece per part is written by two parts, not one per slot.
+// (Stored straight from the lanes, a kept element here and there, every store instruction covers the same few cache
+// lines once more.)
+template <int V, bool NT, int U, class T, class GET>
+DISC_DEV void compact_put_elems(T* __restrict__ dst, i64 pos, const u32 (&kb)[U], const int (&before)[U], int kept, char* stage, GET get) {
   T* q = reinterpret_cast<T*>(stage);
   const int lane = (int)threadIdx.x & 63;
+  const int h = (int)pos & 63;
   wave_lds_sync();
-  int r = before;
 #pragma unroll
-  for (int e = 0; e < V; ++e) {
-    if ((kb >> e) & 1) q[r++] = get(e);
+  for (int u = 0; u < U; ++u) {
+    int r = h + before[u];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      if ((kb[u] >> e) & 1) q[r++] = get(u, e);
+    }
   }
   wave_lds_sync();
-  for (int i = lane; i < kept; i += 64) {
-    if constexpr (NT) __builtin_nontemporal_store(q[i], dst + pos + i);
-    else dst[pos + i] = q[i];
+  T* to = dst + (pos - h);
+  for (int i = lane; i < h + kept; i += 64) {
+    if (i >= h) {
+      if constexpr (NT) __builtin_nontemporal_store(q[i], to + i);
+      else to[i] = q[i];
+    }
   }
 }
 
-// A.aux0 = number of chunks, A.aux1 = tiles per chunk
+// The two halves of it, for values that wait in LDS until their place is known.
+template <int V, int U, class T, class GET>
+DISC_DEV void compact_hold_elems(const u32 (&kb)[U], const int (&before)[U], char* stage, GET get) {
+  T* q = reinterpret_cast<T*>(stage);
+  wave_lds_sync();
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    int r = before[u];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      if ((kb[u] >> e) & 1) q[r++] = get(u, e);
+    }
+  }
+}
+template <bool NT, class T>
+DISC_DEV void compact_flush_elems(T* __restrict__ dst, i64 pos, int kept, const char* stage) {
+  const T* q = reinterpret_cast<const T*>(stage);
+  const int lane = (int)threadIdx.x & 63;
+  const int h = (int)pos & 63;
+  wave_lds_sync();
+  T* to = dst + pos;
+  for (int i = lane - h; i < kept; i += 64) {
+    if (i >= 0) {
+      if constexpr (NT) __builtin_nontemporal_store(q[i], to + i);
+      else to[i] = q[i];
+    }
+  }
+}
+
+// Longer inputs: the parts of a launch dealt out to its wavefronts in contiguous runs of A.aux1 or, the first A.aux3
+// of them, one more; f(part, its slots) for the whole ones, the next one loaded before the current one is used.  Returns
+// the part behind the run's whole ones.  (Contiguous, because the kept values of neighbouring parts share a line: dealt out
+// one by one, sorted i32 keys, 10^7 25.4 us against 24.1, 2^21 10.5 / 8.7.)
+template <class Pat, int V, int U, class F>
+DISC_DEV i64 compact_run(const typename Pat::Args& A, i64 p, i64 end, typename Pat::template Slot<V> (&slot)[U], F f) {
+  for (; p < end; ++p) {
+    typename Pat::template Slot<V> next[U];
+    if (p + 1 < end) compact_load<true, Pat, V, U>(A, (p + 1) * (64 * U * V), next);
+    asm volatile("" ::: "memory");          // these loads before what is done with the current part
+    f(p, slot);
+#pragma unroll
+    for (int u = 0; u < U; ++u) slot[u] = next[u];
+  }
+  return p;
+}
+struct CompactRange {
+  i64 first, last;                          // the wavefront's whole parts
+  bool ragged;                              // the last part of the tensor is not whole, and the wavefront's
+};
+template <class Pat, int V, int U>
+DISC_DEV CompactRange compact_range(const typename Pat::Args& A) {
+  const i64 w = (i64)blockIdx.x * kCompactWaves + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const i64 whole = A.inner / (64 * U * V);
+  CompactRange r;
+  r.first = w * A.aux1 + (w < A.aux3 ? w : A.aux3);
+  const i64 end = r.first + A.aux1 + (w < A.aux3 ? 1 : 0);
+  r.ragged = whole >= r.first && whole < end && whole * (64 * U * V) < A.inner;
+  r.last = end < whole ? end : whole;
+  return r;
+}
+
+// A.aux2 = 0: A.aux0 tiles, one to a block, whose counts go to the workspace as 8 bytes each; otherwise A.aux0
+// blocks, a run of parts and four bytes to a wavefront.
 template <class Pat, int V>
 DISC_DEV void compact_count_body(const typename Pat::Args& A) {
-  __shared__ i64 wsum[kCompactWaves];
+  constexpr int U = Pat::COMPACT_SLOTS;
   const int wave = (int)threadIdx.x >> 6;
-  for (i64 c = blockIdx.x; c < A.aux0; c += gridDim.x) {
-    i64 cnt = 0;
-    for (i64 t = c * A.aux1; t < (c + 1) * A.aux1; ++t) {
-      CompactPart<false, Pat, V, Pat::COMPACT_SLOTS> part;
-      cnt += part.count(A, t);
+  if (A.aux2) {
+    const CompactRange r = compact_range<Pat, V, U>(A);
+    typename Pat::template Slot<V> slot[U];
+    int cnt = 0;
+    if (r.first < r.last) compact_load<true, Pat, V, U>(A, r.first * (64 * U * V), slot);
+    compact_run<Pat, V, U>(A, r.first, r.last, slot, [&](i64 p, const typename Pat::template Slot<V> (&s)[U]) {
+      typename Pat::template OutSlot<V> o[U];
+      u32 kb[U];
+      compact_eval<true, Pat, V, U>(A, p * (64 * U * V), s, o, kb);
+      CompactRanks<U> ranks;
+      cnt += ranks.count(kb);
+    });
+    if (r.ragged) {
+      const i64 w0 = A.inner / (64 * U * V) * (64 * U * V);
+      typename Pat::template OutSlot<V> o[U];
+      u32 kb[U];
+      compact_load<false, Pat, V, U>(A, w0, slot);
+      compact_eval<false, Pat, V, U>(A, w0, slot, o, kb);
+      CompactRanks<U> ranks;
+      cnt += ranks.count(kb);
     }
+    if (((int)threadIdx.x & 63) == 0) reinterpret_cast<int*>(A.ws0)[(i64)blockIdx.x * kCompactWaves + wave] = cnt;
+    return;
+  }
+  __shared__ i64 wsum[kCompactWaves];
+  for (i64 c = blockIdx.x; c < A.aux0; c += gridDim.x) {
+    CompactPart<false, Pat, V, U> part;
+    const int cnt = part.count(A, c);
     if (((int)threadIdx.x & 63) == 0) wsum[wave] = cnt;
     __syncthreads();
     if (threadIdx.x == 0) reinterpret_cast<i64*>(A.ws0)[c] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
@@ -2252,49 +2412,232 @@ DISC_DEV i64 compact_block_sum(i64 x, i64 (&cell)[kCompactWaves]) {
   return x;
 }
 
-// A.aux2: the workspace holds counts (no scan launch), not offsets.  NT: non-temporal stores, for
-// launches whose results do not fit the memory-side cache anyway.  With plain stores the results of
-// one call sit there dirty, and the count launch of the next call, which only reads, first has to
-// push them out to memory: 2^25 i32 keys, a quarter of them distinct: count 44 us (3.0 TB/s), scatter
-// 60 us with plain stores, 27 us (5.0 TB/s) and 54 us (5.6 TB/s, all traffic) with these.  What is
-// left is the second read of the inputs.  (With slots that lie next to each other in a lane, one
-// kept element per store and a scan launch of its own it was 48 + 12 + 89 us.  A single pass that
-// chains the tiles' counts by look-back was built as well: 72 us + 5 us to clear its status words;
-// its tile counter alone costs 25 us at 4096 tiles, 12 ns an increment.)
+// A.aux2: see compact_count_body.  NT: non-temporal stores, for launches whose results do not fit the memory-side cache
+// anyway.  With plain stores the results of one call sit there dirty, and the count launch of the next call, which only
+// reads, first has to push them out to memory.  Bound by latency up to some 10^6 elements and by memory above; sorted i32
+// keys, a quarter distinct, a slot's kept values at a time, blocks of whole tiles and a second wide load for the element in
+// front / as it is: 300007 8.4 us / 8.0, 2 x 10^6 9.2 / 8.6, 6 x 10^6 15.7 / 13.2, 20007 (three launches) 11.8 / 11.3.
 template <class Pat, int V, bool NT = false>
 DISC_DEV void compact_scatter_body(const typename Pat::Args& A) {
+  constexpr int U = Pat::COMPACT_SLOTS;
   __shared__ i64 cell[kCompactWaves];
-  __shared__ int wsum[2][kCompactWaves];
-  __shared__ __attribute__((aligned(16))) char stage[kCompactWaves][64 * V * Pat::COMPACT_BYTES + 16];
-  const int wave = (int)threadIdx.x >> 6;
-  const i64* counts = reinterpret_cast<const i64*>(A.ws0);
-  for (i64 c = blockIdx.x; c < A.aux0; c += gridDim.x) {
-    i64 pos;
-    if (A.aux2) {
-      i64 x = 0;
-      for (i64 i = threadIdx.x; i < c; i += 256) x += counts[i];
-      pos = wave_scalar(compact_block_sum(x, cell));
-    } else {
-      pos = wave_scalar(counts[c]);
-    }
-    int buf = 0;
-    for (i64 t = c * A.aux1; t < (c + 1) * A.aux1; ++t, buf ^= 1) {
-      CompactPart<NT, Pat, V, Pat::COMPACT_SLOTS> part;
-      const int cnt = part.count(A, t);
-      if (((int)threadIdx.x & 63) == 0) wsum[buf][wave] = cnt;
-      __syncthreads();
-      int before = 0, all = 0;
+  __shared__ int wsum[kCompactWaves];
+  __shared__ __attribute__((aligned(16))) char stage[kCompactWaves][(64 * V * U + 64) * Pat::COMPACT_BYTES + 16];
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (A.aux2) {
+    const CompactRange r = compact_range<Pat, V, U>(A);
+    typename Pat::template Slot<V> slot[U];
+    if (r.first < r.last) compact_load<true, Pat, V, U>(A, r.first * (64 * U * V), slot);
+    typedef int int4v __attribute__((ext_vector_type(4)));
+    const int4v* counts = reinterpret_cast<const int4v*>(A.ws0);
+    i64 x = 0;
+    for (int i = (int)threadIdx.x; i < (int)blockIdx.x; i += 256) x += (i64)counts[i][0] + counts[i][1] + counts[i][2] + counts[i][3];
+    const int4v own = counts[blockIdx.x];
+    i64 pos = compact_block_sum(x, cell);
 #pragma unroll
-      for (int w = 0; w < kCompactWaves; ++w) {
-        before += w < wave ? wsum[buf][w] : 0;
-        all += wsum[buf][w];
-      }
-      part.store(A, pos + __builtin_amdgcn_readfirstlane(before), stage[wave]);
-      pos += __builtin_amdgcn_readfirstlane(all);
+    for (int w = 0; w < kCompactWaves; ++w) pos += w < wave ? own[w] : 0;
+    pos = wave_scalar(pos);
+    compact_run<Pat, V, U>(A, r.first, r.last, slot, [&](i64 p, const typename Pat::template Slot<V> (&s)[U]) {
+      typename Pat::template OutSlot<V> o[U];
+      u32 kb[U];
+      compact_eval<true, Pat, V, U>(A, p * (64 * U * V), s, o, kb);
+      CompactRanks<U> ranks;
+      ranks.count(kb);
+      pos = compact_emit<true, NT, Pat, V, U>(A, p * (64 * U * V), o, kb, ranks, pos, stage[wave]);
+    });
+    if (r.ragged) {
+      const i64 w0 = A.inner / (64 * U * V) * (64 * U * V);
+      typename Pat::template OutSlot<V> o[U];
+      u32 kb[U];
+      compact_load<false, Pat, V, U>(A, w0, slot);
+      compact_eval<false, Pat, V, U>(A, w0, slot, o, kb);
+      CompactRanks<U> ranks;
+      ranks.count(kb);
+      pos = compact_emit<false, NT, Pat, V, U>(A, w0, o, kb, ranks, pos, stage[wave]);
     }
-    if (A.aux2 && c == A.aux0 - 1 && threadIdx.x == 0) Pat::count_store(A, pos);
+    if (blockIdx.x == gridDim.x - 1 && (int)threadIdx.x == 64 * (kCompactWaves - 1)) Pat::count_store(A, pos);
+    return;
+  }
+  const i64* offsets = reinterpret_cast<const i64*>(A.ws0);
+  for (i64 c = blockIdx.x; c < A.aux0; c += gridDim.x) {
+    const i64 pos = wave_scalar(offsets[c]);
+    CompactPart<NT, Pat, V, U> part;
+    const int cnt = part.count(A, c);
+    if (((int)threadIdx.x & 63) == 0) wsum[wave] = cnt;
+    __syncthreads();
+    int before = 0;
+#pragma unroll
+    for (int w = 0; w < kCompactWaves; ++w) before += w < wave ? wsum[w] : 0;
+    part.store(A, pos + __builtin_amdgcn_readfirstlane(before), stage[wave]);
     __syncthreads();
   }
+}
+
+// Large inputs in one pass: A.aux0 tiles dealt out to the blocks one by one (gridDim.x <= 1024, all resident), a part of a
+// tile to a wavefront.  A block publishes what a tile keeps, plus one, in a cell of the workspace (zero before the launch) two
+// iterations before it stores that tile, and the place of a tile is that of the block's tile before it plus the cells
+// in between, one per block: no chain of look-backs, one exchange per iteration, with a whole iteration and more
+// between publishing and use.  Until then the tile's flags are a word per lane and its kept values wait in LDS.
+// The result does not depend on a wait: a cell that has not come after A.aux2 looks -- its block may not be resident -- is
+// counted by the wavefront that misses it, from the inputs, and published for the others.  A cell is one
+// 4-byte word, written and read whole at device scope; nothing else passes between blocks.
+// Bound by memory: 2^25 sorted i32 keys, a quarter distinct, 302 MB in 56 us (5.4 TB/s; a plain copy of as much moves
+// 5.7) + 4.4 to clear the cells; two launches that read them twice 78.7 us.  2^25 i64 121 / 92, 1.2 x 10^7 i32 29.9 / 21.1.
+// Published one iteration ahead, the looks ended up behind the stores of the iteration before: 67.5.  (Two blocks a CU
+// 75, three 60.9, four 60.4; numbers in between load the CUs unevenly and the fuller ones set the pace, 3.5 to a
+// CU 79; non-temporal loads 61.0.)
+// A.aux3: the kept values non-temporal too (the ranks are in any case): from some 150 MiB of operands and results on (i32, plain / so:
+// 12 x 10^6 21.1 / 23.0, 16 x 10^6 25.3 / 28.0, 22 x 10^6 38.9 / 37.9; i64 12 x 10^6 37.1 / 34.5); ranks plain as well 28.4 at 12 x 10^6.
+template <class Pat, int V, int U>
+DISC_DEV int compact_recount(const typename Pat::Args& A, i64 tile) {
+  int cnt = 0;
+#pragma unroll 1
+  for (int k = 0; k < kCompactWaves * U; ++k) {               // (a slot at a time: few registers beside those in use)
+    const i64 w0 = (tile * (kCompactWaves * U) + k) * (64 * V);
+    typename Pat::template Slot<V> s[1];
+    typename Pat::template OutSlot<V> o[1];
+    u32 kb[1];
+    compact_load<false, Pat, V, 1>(A, w0, s);
+    compact_eval<false, Pat, V, 1>(A, w0, s, o, kb);
+    cnt += __builtin_amdgcn_readlane((int)wave_scan((u32)__builtin_popcount(kb[0])), 63);
+  }
+  return cnt;
+}
+template <class Pat, int V>
+DISC_DEV void compact_chain_body(const typename Pat::Args& A) {
+  constexpr int U = Pat::COMPACT_SLOTS, E = 64 * U * V, C = 4;       // C cells of a window to a lane
+  static_assert(U * V <= 32, "the kept flags of a part in one word");
+  __shared__ __attribute__((aligned(16))) char stage[2][kCompactWaves][E * Pat::COMPACT_ALL_BYTES + 16];
+  __shared__ int kept[2][kCompactWaves], gap[2][kCompactWaves];
+  __shared__ u32 arrived[2];
+  u32* cells = reinterpret_cast<u32*>(A.ws0);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+  if (threadIdx.x < 2) arrived[threadIdx.x] = 0;
+  __syncthreads();
+  auto first = [&](i64 t) { return (t * kCompactWaves + wave) * (i64)E; };
+  // a part of the block's tile t whose place is not known yet
+  struct Waiting {
+    u32 flags;
+    CompactRanks<U> ranks;
+    int before;                             // what the wavefronts in front keep of the tile
+  };
+  Waiting now, next, eval;                  // of tiles t, t + grid, t + 2 grid
+  typename Pat::template Slot<V> slot[U];
+  u32 win[C];
+  // the window of a tile: cells [lo, lo + n)
+  i64 lo = 0;
+  int n = 0;
+  auto look = [&](int c) {
+    return c * 256 + (int)threadIdx.x < n ? __hip_atomic_load(cells + lo + c * 256 + (int)threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 1u;
+  };
+  const i64 G = gridDim.x;
+  i64 t = blockIdx.x - 2 * G, run = 0;      // (negative: no tile yet)
+  if (first(blockIdx.x) + E <= A.inner) compact_load<true, Pat, V, U>(A, first(blockIdx.x), slot);
+  for (int buf = 0;; buf ^= 1, t += G) {
+    // two tiles ahead: count, publish, load the one behind it
+    const i64 t2 = t + 2 * G, w2 = first(t2);
+    typename Pat::template OutSlot<V> o[U];
+    u32 kb[U];
+    if (t2 < A.aux0) {
+      if (w2 + E <= A.inner) {
+        compact_eval<true, Pat, V, U>(A, w2, slot, o, kb);
+      } else {
+        compact_load<false, Pat, V, U>(A, w2, slot);
+        compact_eval<false, Pat, V, U>(A, w2, slot, o, kb);
+      }
+      const int cnt = eval.ranks.count(kb);
+      if (lane == 0) {
+        kept[buf][wave] = cnt;
+        // (a tile has less than 2^24 elements: its count and the wavefronts that have added theirs in one word)
+        const u32 before = __hip_atomic_fetch_add(&arrived[buf], (1u << 24) + (u32)cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (before >> 24 == kCompactWaves - 1) {
+          __hip_atomic_store(cells + t2, (before & 0xffffff) + (u32)cnt + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          arrived[buf] = 0;
+        }
+      }
+      eval.flags = 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) eval.flags |= kb[u] << (u * V);
+      if (first(t2 + G) + E <= A.inner) compact_load<true, Pat, V, U>(A, first(t2 + G), slot);
+    }
+    // this tile's window
+    if (t >= 0) {
+      for (i64 looks = 0;; ++looks) {
+        bool missing = false;
+#pragma unroll
+        for (int c = 0; c < C; ++c) missing = missing || win[c] == 0;
+        if (wave_all(!missing)) break;
+        if (looks < A.aux2) {
+          __builtin_amdgcn_s_sleep(2);
+#pragma unroll
+          for (int c = 0; c < C; ++c)
+            if (win[c] == 0) win[c] = look(c);
+        } else {
+          int at = -1;                      // the first missing cell of the wavefront's share
+#pragma unroll
+          for (int c = C - 1; c >= 0; --c) {
+            const u64 m = __builtin_amdgcn_ballot_w64(win[c] == 0);
+            if (m != 0) at = c * 64 + (int)__builtin_ctzll(m);
+          }
+          const i64 tile = lo + (at >> 6) * 256 + wave * 64 + (at & 63);
+          const u32 got = (u32)compact_recount<Pat, V, U>(A, tile) + 1;
+          if (lane == (at & 63)) __hip_atomic_store(cells + tile, got, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+          for (int c = 0; c < C; ++c)
+            if (c == at >> 6 && lane == (at & 63)) win[c] = got;
+        }
+      }
+      u32 sum = 0;
+#pragma unroll
+      for (int c = 0; c < C; ++c) sum += win[c] - 1;
+      sum = wave_scan(sum);
+      if (lane == 63) gap[buf][wave] = (int)sum;
+    }
+    __syncthreads();
+    if (t2 < A.aux0) {
+      int ahead = 0;
+#pragma unroll
+      for (int w = 0; w < kCompactWaves; ++w) ahead += w < wave ? kept[buf][w] : 0;
+      eval.before = __builtin_amdgcn_readfirstlane(ahead);
+    }
+    if (t + G >= 0 && t + G < A.aux0) {
+      lo = t >= 0 ? t : 0;
+      n = t >= 0 ? (int)G : (int)blockIdx.x;
+#pragma unroll
+      for (int c = 0; c < C; ++c) win[c] = look(c);
+      asm volatile("" ::: "memory");        // (looked at in the next iteration: before the stores)
+    }
+    if (t >= 0) {
+      int all = 0;
+#pragma unroll
+      for (int w = 0; w < kCompactWaves; ++w) all += gap[buf][w];
+      run += __builtin_amdgcn_readfirstlane(all);
+      const i64 at = wave_scalar(run + now.before), w0 = first(t);
+      int before[U];
+      const int cnt = now.ranks.before(before);
+      u32 kb0[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) kb0[u] = (now.flags >> (u * V)) & ((1u << V) - 1);
+      if (w0 + E <= A.inner) compact_store_ranks<true, true, Pat, V, U>(A, w0, kb0, before, at);
+      else compact_store_ranks<false, true, Pat, V, U>(A, w0, kb0, before, at);
+      if (A.aux3) Pat::template compact_flush<true>(A, cnt, at, stage[buf][wave]);
+      else Pat::template compact_flush<false>(A, cnt, at, stage[buf][wave]);
+      if (t == A.aux0 - 1 && wave == kCompactWaves - 1 && lane == 0) Pat::count_store(A, at + cnt);
+      if (t + G >= A.aux0) break;
+    }
+    if (t2 < A.aux0) {
+      int before[U];
+      eval.ranks.before(before);
+      Pat::template compact_hold<V, U>(o, kb, before, stage[buf][wave]);
+    }
+    now = next;
+    next = eval;
+  }
+}
+template <class Pat>
+DISC_DEV void compact_clear_body(const typename Pat::Args& A) {
+  const i64 i = (i64)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < A.aux0) reinterpret_cast<u32*>(A.ws0)[i] = 0;
 }
 
 }  // namespace disc

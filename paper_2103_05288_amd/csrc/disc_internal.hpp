@@ -227,6 +227,7 @@ struct Generated {
   int stream_held = kStreamHeldSlots; // ... and in its blocks of up to 512 threads of row_held patterns
   bool col_held = false;              // column reduce: strips may stay in registers between the reduction and the epilogue
   bool col_argmax = false;            // column reduce: some reduction keeps a position
+  bool compact_chain = false;         // compaction: the one-pass version exists
   bool row_cols_ok = false;           // row reduce without reductions along the rows: the version by column tiles exists
   bool row_shift_ok = false;          // ... and their vector slots may be shifted to the 16-byte boundaries of the tensor
   bool row_narrow_late = false;       // row reduce: an operand of less than four bytes an element is the same for many rows, but not staged
@@ -244,7 +245,7 @@ enum KernelId {
   K_TRANSPOSE_TILE,
   K_COL_EPI2_VEC, K_COL_EPI2_VEC_NT, K_COL_EPI2_SCALAR,
   K_COMPACT_COUNT_VEC, K_COMPACT_COUNT_SCALAR, K_COMPACT_SCAN, K_COMPACT_SCATTER_VEC, K_COMPACT_SCATTER_SCALAR,
-  K_COMPACT_SCATTER_VEC_NT, K_ROW_COLS_VEC, K_ROW_COLS_VEC_NT, K_COL_EPI2_VEC_NTS, K_ROW_STREAM_VECW, K_TRANSPOSE_TILE_H, K_COL_STRIP_VECL,
+  K_COMPACT_SCATTER_VEC_NT, K_COMPACT_CLEAR, K_COMPACT_CHAIN_VEC, K_ROW_COLS_VEC, K_ROW_COLS_VEC_NT, K_COL_EPI2_VEC_NTS, K_ROW_STREAM_VECW, K_TRANSPOSE_TILE_H, K_COL_STRIP_VECL,
   K_ROW_XPOSE, K_ROW_XPOSE_LAST = K_ROW_XPOSE + 7,    // {4, 8, 12, 16 slots a lane} x {any row length, whole slots}
   K_ROW_BASE,
   K_COUNT = K_ROW_BASE + 96

@@ -150,6 +150,7 @@ struct disc_ctx {
   int row_nt = -1;           // non-temporal versions: -1 = host rule, 0 = never, 1 = wherever the version exists
   int row_rounds = 0;        // row kernels: grid = this many rounds of resident blocks (0: host rule)
   int row_stage = 1;         // 0: row vectors are never staged in LDS
+  int compact_looks = -1;    // compaction in one pass: looks for a count (-1: host rule)
   int row_shift = 1;         // 0: vector slots of ragged rows are never shifted to the tensor's 16-byte boundaries
 };
 constexpr int kGridMult = 8;     // loop / column kernels: grid capped at this many blocks per CU
@@ -320,10 +321,13 @@ constexpr int64_t kNonTemporalMinBytes = 64ll << 20;
 constexpr int kMinLinesG = 64, kMinLinesEvenG = 128;
 // Compaction: from this many tiles on (2^17 i32 elements), two launches instead of three: the blocks of
 // the scatter launch add up the counts in front of them by themselves (14 us a call against 15-16 at
-// 2^17 .. 2^20 elements, where the launches are what is paid for).  Most chunks of a launch: 1024 / 2048 / 4096
-// take 76.8 / 78.5 / 75.0 us at 2^25 i32 elements and 120.7 / 120.8 / 119.2 at 2^25 i64; every block reads up to that
-// many counts.
-constexpr int64_t kCompactTwoLaunchTiles = 32, kCompactMaxChunks = 2048;
+// 2^17 .. 2^20 elements, where the launches are what is paid for), in at most kCompactBlocksPerCu blocks to a CU.
+// From kCompactOnePassMinBytes on -- the line of the non-temporal versions, which its stores are -- one pass (the kernel's comment
+// has both sides; 8 x 10^6 i32 20.5 / 17.1, 4 x 10^6 12.6 / 9.6, 6 x 10^6 and 3 x 10^6 i64 the same); from kCompactStreamMinBytes on
+// the kept values are non-temporal too.  A look at a missing count takes 2 us: the limit is a millisecond, far beyond the time
+// between two blocks that are both resident.
+constexpr int64_t kCompactTwoLaunchTiles = 32, kCompactBlocksPerCu = 4;
+constexpr int64_t kCompactOnePassMinBytes = kNonTemporalMinBytes, kCompactStreamMinBytes = 150ll << 20, kCompactLooks = 500;
 
 // nt_name: the non-temporal sibling of names[0] (vector width, 32-bit index), taken for large
 // launches (`big`) whose rows start on 16-byte boundaries (`aligned`: the full-size operands are;
@@ -437,23 +441,40 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     const int v = vec ? V : 1;
     const int64_t tile = 256ll * kCompactLaneSlots * v;
     const int64_t nb = (sv.inner + tile - 1) / tile;
-    // From kCompactTwoLaunchTiles tiles on, chunks of consecutive tiles whose counts every block of
-    // the scatter launch adds up by itself, and no scan launch; below, a chunk is a tile.
     const bool two = nb >= kCompactTwoLaunchTiles;
-    const int64_t per_chunk = two ? (nb + kCompactMaxChunks - 1) / kCompactMaxChunks : 1;
-    const int64_t chunks = (nb + per_chunk - 1) / per_chunk;
+    const bool nt = vec && two && c->row_nt != 0 && (c->row_nt > 0 || sv.alg_bytes >= kNonTemporalMinBytes);
+    const bool one_pass = vec && two && p.gen.compact_chain && (c->compact_looks >= 0 || (nt && sv.alg_bytes >= kCompactOnePassMinBytes));
+    // three launches: a tile to a block, 8 bytes each; two: runs of parts (a wavefront's share of a tile) as even as can be,
+    // four bytes for each wavefront; one pass: four bytes for each tile
+    const int64_t parts = (sv.inner + tile / 4 - 1) / (tile / 4);
+    const int64_t chunks = one_pass || !two ? nb : std::min<int64_t>(nb, (int64_t)c->n_cus * kCompactBlocksPerCu);
     fp->aux[0] = chunks;
-    fp->aux[1] = per_chunk;
-    fp->aux[2] = two;
+    if (one_pass) {
+      fp->aux[1] = 0;
+      fp->aux[2] = c->compact_looks >= 0 ? c->compact_looks : kCompactLooks;
+      fp->aux[3] = sv.alg_bytes >= kCompactStreamMinBytes;
+    } else {
+      fp->aux[1] = two ? parts / (4 * chunks) : 1;
+      fp->aux[2] = two;
+      fp->aux[3] = two ? parts % (4 * chunks) : 0;
+    }
     fp->ws_off[0] = 0;
-    pub.workspace_bytes = (size_t)std::max<int64_t>(nb, 1) * 8;
+    pub.workspace_bytes = one_pass ? (size_t)nb * 4 : two ? (size_t)chunks * 16 : (size_t)std::max<int64_t>(nb, 1) * 8;
     pub.variant = vec ? DISC_V_COMPACT_VEC : DISC_V_COMPACT_SCALAR;
     pub.vec_width = v;
     pub.index_bits = 64;
     pub.slots_per_lane = kCompactLaneSlots;
     const uint32_t grid = (uint32_t)std::min<int64_t>(chunks, max_grid * 4);
     int l = 0;
-    if (nb > 0) {
+    if (one_pass) {
+      // as many blocks as are resident, the same number on every CU
+      const int64_t per_cu = std::min<int64_t>(kCompactBlocksPerCu, resident_blocks(c, p, K_COMPACT_CHAIN_VEC, 256, 0));
+      fp->launches[0].kid = K_COMPACT_CLEAR;
+      fp->launches[0].grid[0] = (uint32_t)((nb + 255) / 256);
+      fp->launches[1].kid = K_COMPACT_CHAIN_VEC;
+      fp->launches[1].grid[0] = (uint32_t)std::min<int64_t>(nb, std::min<int64_t>((int64_t)c->n_cus * per_cu, 1024));
+      l = 2;
+    } else if (nb > 0) {
       fp->launches[l].kid = vec ? K_COMPACT_COUNT_VEC : K_COMPACT_COUNT_SCALAR;
       fp->launches[l].grid[0] = grid;
       ++l;
@@ -464,8 +485,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       fp->launches[l].grid[0] = 1;
       ++l;
     }
-    if (nb > 0) {
-      const bool nt = vec && two && c->row_nt != 0 && (c->row_nt > 0 || sv.alg_bytes >= kNonTemporalMinBytes);
+    if (nb > 0 && !one_pass) {
       fp->launches[l].kid = nt ? K_COMPACT_SCATTER_VEC_NT : vec ? K_COMPACT_SCATTER_VEC : K_COMPACT_SCATTER_SCALAR;
       fp->launches[l].grid[0] = grid;
       ++l;
@@ -1653,6 +1673,7 @@ int disc_test_option(disc_ctx* ctx, int option, int value) {
     case DISC_OPT_STAGE_ROW_VECTORS: ctx->row_stage = value != 0; return DISC_OK;
     case DISC_OPT_ROW_ROUNDS: ctx->row_rounds = std::max(0, value); return DISC_OK;
     case DISC_OPT_ALIGN_ROW_SLOTS: ctx->row_shift = value != 0; return DISC_OK;
+    case DISC_OPT_COMPACT_LOOKS: ctx->compact_looks = std::max(-1, value); return DISC_OK;
     default: return set_err(ctx, DISC_ERR_INVALID_ARG, "unknown option");
   }
   DISC_CATCH(ctx)
