@@ -439,7 +439,9 @@ struct Gen {
       if (need_nl2e.count((int)i)) o << "    float n" << i << ";\n";
     }
     if (col_tmpl()) o << "    disc::i64 ob;\n";   // offset of this row's outer slice in the reduce-result planes
-    o << "    const char* sl;\n";                 // staged row vectors in LDS (row reduce), or null
+    // staged row vectors in LDS (row reduce), or null, and where the lane group's copies begin
+    o << "    const char* sl;\n";
+    if (row_tmpl()) o << "    Staged so;\n";
     o << "    int unused_;\n";
     return o.str();
   }
@@ -783,14 +785,8 @@ struct Gen {
   }
 
   // May the vector slots of a row start at any column (the _t versions shift them to the 16-byte
-  // boundaries of the tensor)?  The copies of row vectors in LDS are then read with element
-  // alignment, which is only as fast as an aligned read for elements of 4 bytes and more.
-  bool row_shift_ok() const {
-    if (!row_tmpl() || an.n_col_sums > 0) return false;
-    for (int ai : staged_accesses())
-      if (dtype_bytes(an.accesses[ai].dtype) < 4) return false;
-    return true;
-  }
+  // boundaries of the tensor)?
+  bool row_shift_ok() const { return row_tmpl() && an.n_col_sums == 0; }
   // row-vector operands of a row reduce that can be staged in LDS, in access order
   std::vector<int> staged_accesses() const {
     std::vector<int> r;
@@ -805,27 +801,36 @@ struct Gen {
       if (st[k] == access) return (int)k;
     return -1;
   }
-  // byte offset of staged operand k: operands are laid out one after the other, each
-  // (inner + vector width) elements long (zero padding behind), rounded up to 16 bytes.  The
+  // Staged operands are laid out one after the other, a copy of each (or several, see StagePlan) of
+  // (inner + 2 * vector width) elements (zero padding behind), rounded up to 16 bytes.  The
   // padding is that of the pattern's vector width whatever the width of the slot that reads the
   // copy (the single elements at the end of a row read it too).
+  void emit_staged_struct() {
+    os << "  struct Staged {\n";
+    for (size_t k = 0; k < staged_accesses().size(); ++k) os << "    int b" << k << ";\n";
+    os << "    int unused_;\n  };\n";
+  }
   void emit_stage_fns() {
     std::vector<int> st = staged_accesses();
     const int pad = an.vec_width;
-    os << "  static constexpr int N_STAGED = " << st.size() << ";\n";
-    os << "  static DISC_DEV int stage_offset(const Args& A, int k) {\n    int off = 0;\n";
-    for (size_t k = 0; k < st.size(); ++k)
-      os << "    if (k > " << k << ") off += (((int)A.inner + " << pad << ") * " << dtype_bytes(an.accesses[st[k]].dtype) << " + 15) & ~15;\n";
-    os << "    (void)A; (void)k;\n    return off;\n  }\n";
-    os << "  template <int V> static DISC_DEV void stage(const Args& A, char* lds, int tid, int nthreads) {\n";
-    for (size_t k = 0; k < st.size(); ++k) {
-      const Access& a = an.accesses[st[k]];
-      os << "    {\n      " << dtype_ctype(a.dtype) << "* dst = reinterpret_cast<" << dtype_ctype(a.dtype)
-         << "*>(lds + stage_offset(A, " << k << "));\n";
-      os << "      const int n = (int)A.inner;\n";
-      os << "      disc::stage_copy<" << pad << ">(dst, A.p" << a.slot << ", n, tid, nthreads);\n    }\n";
+    auto bytes = [&](size_t k) { return fmt("(((int)A.inner + %d) * %d + 15 & ~15)", 2 * pad, dtype_bytes(an.accesses[st[k]].dtype)); };
+    auto next = [&](size_t k) {
+      return fmt("    at += sp.copies(disc::stage_align<%d, %s>()) * bytes%zu;\n", pad, dtype_ctype(an.accesses[st[k]].dtype), k);
+    };
+    for (const bool copy : {true, false}) {
+      os << (copy ? "  static DISC_DEV void stage(const Args& A, char* lds, int tid, int nthreads, const disc::StagePlan& sp) {\n    int at = 0;\n"
+                  : "  static DISC_DEV void stage_at(const Args& A, const disc::StagePlan& sp, int grp, Staged& st) {\n    int at = 0;\n");
+      for (size_t k = 0; k < st.size(); ++k) {
+        const Access& a = an.accesses[st[k]];
+        os << "    const int bytes" << k << " = " << bytes(k) << ";\n";
+        if (copy)
+          os << "    disc::stage_copy<" << pad << ">(reinterpret_cast<" << dtype_ctype(a.dtype) << "*>(lds + at), A.p" << a.slot << ", (int)A.inner, bytes" << k << ", sp, tid, nthreads);\n";
+        else
+          os << "    st.b" << k << " = disc::stage_place<" << pad << ", " << dtype_ctype(a.dtype) << ">(at, bytes" << k << ", sp, grp);\n";
+        os << next(k);
+      }
+      os << (copy ? "    (void)A; (void)lds; (void)tid; (void)nthreads; (void)sp; (void)at;\n  }\n" : "    (void)A; (void)sp; (void)grp; (void)st; (void)at;\n  }\n");
     }
-    os << "    (void)A; (void)lds; (void)tid; (void)nthreads;\n  }\n";
   }
 
   // version by column tiles: a lane's columns are the same in every row, so the operands that do not
@@ -850,7 +855,7 @@ struct Gen {
       if (st >= 0) {
         // a compile-time choice: behind a run-time branch the wait for the operand would cover both
         // the LDS and the global counter, and so also the row loads that are in flight for later
-        o << ind << "if constexpr (STAGED) disc::ld_lds<SP::kAnyColumn && " << (row_shift_ok() ? "true" : "false") << ">(l" << ai << ", rc.sl, stage_offset(A, " << st << "), (int)col);\n";
+        o << ind << "if constexpr (STAGED) disc::ld_lds(l" << ai << ", rc.sl, rc.so.b" << st << ", (int)col);\n";
         o << ind << "else " << load_call(a, ai, fmt("l%d", ai), "", "") << "\n";
       } else {
         o << ind << load_call(a, ai, fmt("l%d", ai), "", "") << "\n";
@@ -1421,6 +1426,7 @@ struct Gen {
     os << "  static constexpr int MAX_ACC_BYTES = " << acc_bytes << ";\n";
     os << "  template <int P> using Acc = typename PatAccSel<P>::type;\n";
     emit_args();
+    if (row_tmpl()) emit_staged_struct();
     os << "  struct RowCtx {\n" << row_fields() << "  };\n";
     if (!col_tmpl()) {
       emit_slots(all, false, true);

@@ -92,7 +92,6 @@ struct Vec<T, N, true> {
 // slot alive across the phases was measured slower -- they do not fit the scalar registers next
 // to the kernel arguments and were spilled to vector-register lanes on every path.
 struct Span {
-  static constexpr bool kAnyColumn = false;
   int n;
   static DISC_DEV Span upto(int n) {
     Span s;
@@ -108,7 +107,6 @@ struct Span {
 // knows -- every ragged-tail path (predicated bodies, piecewise loads and stores, the wave-wide
 // "all full?" vote) drops out of the kernel versions built on it.
 struct EvenSpan {
-  static constexpr bool kAnyColumn = false;
   int n;
   static DISC_DEV EvenSpan upto(int n) {
     EvenSpan s;
@@ -481,10 +479,8 @@ DISC_DEV void kloop_body(const typename Pat::Args& A) {
 // =======================================================================================
 // The span of a slot in the kernel versions that take the ragged ends of a row as single elements:
 // whole like EvenSpan, but the slot may start at ANY column (the vector slots of a row may be
-// shifted to 16-byte boundaries of memory, and single elements sit anywhere), so copies of row
-// vectors in LDS are read with element alignment only.
+// shifted to 16-byte boundaries of memory, and single elements sit anywhere).
 struct TailSpan : EvenSpan {
-  static constexpr bool kAnyColumn = true;
   static DISC_DEV TailSpan upto(int n) {
     TailSpan s;
     s.n = n;
@@ -511,24 +507,83 @@ struct RowPlan {
 // no per-slot trip through the vector memory pipeline and no ragged-tail path for them.
 extern __shared__ __attribute__((aligned(16))) char disc_stage_lds[];
 
-// cooperative copy of n elements (+ pad zero elements) into LDS: 16-byte pieces, then the tail
+// Slots that start at a boundary of the tensor and not of the row (TAIL versions, below) start at a column
+// head + k * V; every lane group of the block has a head of its own, and keeps it.  An LDS access
+// of 8 or 16 bytes off its own alignment is served one lane a cycle (64 cycles, 6 aligned), and as single dwords
+// the slots of a wavefront's lanes meet on the same banks (40), so the copies are shifted instead: element i of a row
+// vector lies at i + shift, which makes every slot start on 16 bytes (E elements; less where V elements are less).
+// A copy for every lane group, or for every shift where these are fewer.  Mixed chain of bf16, us, single dwords /
+// shifted copies: 46773 x 5739 253.5 / 243.5, 180000 x 1501 253.8 / 246.9, 4000 x 8191 35.4 / 32.2.
+struct StagePlan {
+  int groups;   // lane groups of the block, 0: unshifted slots
+  i64 row0;     // row of the first one
+  i64 rows;
+  int inner, al;
+  DISC_DEV int head(int grp) const {
+    const i64 r = row0 + grp < rows ? row0 + grp : rows - 1;
+    const int e0 = ((int)(r & (al - 1)) * (inner & (al - 1))) & (al - 1);   // (row * inner) mod al
+    return (al - e0) & (al - 1);
+  }
+  DISC_DEV int copies(int E) const { return groups == 0 ? 1 : groups < E ? groups : E; }
+  DISC_DEV int shift(int E, int copy) const { return groups == 0 ? 0 : groups <= E ? -head(copy) & (E - 1) : copy; }
+  DISC_DEV int copy_of(int E, int grp) const { return groups == 0 ? 0 : groups <= E ? grp : -head(grp) & (E - 1); }
+};
+// elements of a slot's access that have to start on its alignment
+template <int V, class T>
+constexpr int stage_align() { return V * (int)sizeof(T) < 16 ? V : 16 / (int)sizeof(T); }
+// cooperative copy of n elements (+ PAD zero elements) into LDS: 16-byte pieces, then the tail; or several shifted ones
+// of `bytes` each, in 16-byte pieces that lie on 16 bytes there, four of a lane's loads in flight at once
 template <int PAD, class T>
-DISC_DEV void stage_copy(T* dst, const T* __restrict__ src, int n, int tid, int nthreads) {
-  constexpr int E = 16 / (int)sizeof(T);
-  const int nvec = n / E;
-  for (int i = tid; i < nvec; i += nthreads)
-    reinterpret_cast<typename Vec<T, E>::vec_t*>(dst)[i] =
-        *reinterpret_cast<const typename Vec<T, E>::unaligned_t*>(src + (i64)i * E);
-  for (int i = nvec * E + tid; i < n + PAD; i += nthreads) dst[i] = i < n ? src[i] : T(0);
+DISC_DEV void stage_copy(T* dst, const T* __restrict__ src, int n, int bytes, const StagePlan& sp, int tid, int nthreads) {
+  constexpr int N = 16 / (int)sizeof(T), E = stage_align<PAD, T>();
+  if (sp.groups == 0) {
+    const int nvec = n / N;
+    for (int i = tid; i < nvec; i += nthreads)
+      reinterpret_cast<typename Vec<T, N>::vec_t*>(dst)[i] =
+          *reinterpret_cast<const typename Vec<T, N>::unaligned_t*>(src + (i64)i * N);
+    for (int i = nvec * N + tid; i < n + PAD; i += nthreads) dst[i] = i < n ? src[i] : T(0);
+    return;
+  }
+  const int copies = sp.copies(E), log2 = 31 - __builtin_clz(copies);
+  const int pieces = (n + PAD + N - 1) / N * copies;
+  for (int w0 = tid; w0 < pieces; w0 += 4 * nthreads) {
+    Vec<T, N> x[4];
+    int from[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int w = w0 + u * nthreads;
+      from[u] = (w >> log2) * N - sp.shift(E, w & (copies - 1));
+      if (w < pieces && from[u] >= 0 && from[u] + N <= n)
+        x[u].v = *reinterpret_cast<const typename Vec<T, N>::unaligned_t*>(src + from[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int w = w0 + u * nthreads;
+      if (w < pieces) {
+        if (from[u] < 0 || from[u] + N > n) {      // the ends of a copy
+          x[u].clear();
+#pragma unroll
+          for (int e = 0; e < N; ++e)
+            if (from[u] + e >= 0 && from[u] + e < n) x[u].set(e, src[from[u] + e]);
+        }
+        *reinterpret_cast<typename Vec<T, N>::vec_t*>(reinterpret_cast<char*>(dst) + (w & (copies - 1)) * bytes + (w >> log2) * 16) = x[u].v;
+      }
+    }
+  }
+}
+// where a lane group's copy of a row vector begins: its byte `at`, copies of `bytes`
+template <int V, class T>
+DISC_DEV int stage_place(int at, int bytes, const StagePlan& sp, int grp) {
+  constexpr int E = stage_align<V, T>();
+  if (sp.groups == 0) return at;
+  return at + sp.copy_of(E, grp) * bytes + (-sp.head(grp) & (E - 1)) * (int)sizeof(T);
 }
 
-// each staged operand is stored as [inner elements | zeros]; col is a multiple of N, or (ANY) any
-// column, read with element alignment
-template <bool ANY = false, class T, int N>
+// slot at column `col` of the copy that begins at byte_off
+template <class T, int N>
 DISC_DEV void ld_lds(Vec<T, N>& d, const char* base, int byte_off, int col) {
-  const char* q = base + byte_off + col * (int)sizeof(T);
-  if constexpr (ANY) d.v = *reinterpret_cast<const typename Vec<T, N>::unaligned_t*>(q);
-  else d.v = *reinterpret_cast<const typename Vec<T, N>::vec_t*>(q);
+  typedef typename Vec<T, N>::vec_t aligned_t __attribute__((aligned(sizeof(T) * N < 16 ? sizeof(T) * N : 16)));
+  d.v = *reinterpret_cast<const aligned_t*>(base + byte_off + col * (int)sizeof(T));
 }
 
 // Sums over the rows carried along by a row reduce (Pat::NCOLSUM of them): every lane adds the
@@ -632,8 +687,11 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
   const int inner = (int)A.inner;
   int parity = 0;
   const char* staged = nullptr;
+  typename Pat::Staged placed{};
   if constexpr (Pat::STAGED) {
-    Pat::template stage<V>(A, disc_stage_lds, threadIdx.x, blockDim.x);
+    const StagePlan sp{TAIL && (rp.flags & 4) ? rpb : 0, (i64)blockIdx.x * rpb, rows, inner, TAIL ? rp.flags >> 8 : 0};
+    Pat::stage(A, disc_stage_lds, threadIdx.x, blockDim.x, sp);
+    Pat::stage_at(A, sp, grp, placed);
     __syncthreads();
     staged = disc_stage_lds;
   }
@@ -666,12 +724,7 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
   // an alignment matter only: any value 0 .. al-1 addresses the row correctly.
   int head = 0;
   if constexpr (TAIL) {
-    if (rp.flags & 4) {
-      const i64 r = rw + dgrp < rows ? rw + dgrp : rows - 1;
-      const int al = rp.flags >> 8;
-      const int e0 = ((int)(r & (al - 1)) * (inner & (al - 1))) & (al - 1);   // (row * inner) mod al
-      head = (al - e0) & (al - 1);
-    }
+    if (rp.flags & 4) head = StagePlan{rpb, (i64)blockIdx.x * rpb, rows, inner, rp.flags >> 8}.head(grp);
   }
   int col0 = lane * V;
   int nvalid[NV];
@@ -730,6 +783,7 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
   auto load_row = [&]() {
     begin_row(rw, sbw, rc);
     rc.sl = staged;
+    rc.so = placed;
 #pragma unroll
     for (int j = 0; j < NV; ++j)
       if (nvalid[j] > 0) Pat::template load<V, NT>(A, rc, (unsigned)(col0 + j * rp.G * V), SP::upto(nvalid[j]), slot[j]);
@@ -761,6 +815,7 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
         }
         begin_row(rw + rstep, sbw + sbstep, rcn);
         rcn.sl = staged;
+        rcn.so = placed;
 #pragma unroll
         for (int j = 0; j < NV; ++j)
           if (nvalidn[j] > 0) {

@@ -319,6 +319,7 @@ struct FullPlan {
 constexpr int64_t kNonTemporalMinBytes = 64ll << 20;
 // Ragged rows with the non-temporal hint: fewest lanes per row, rows off dword boundaries / others.
 constexpr int kMinLinesG = 64, kMinLinesEvenG = 128;
+constexpr int64_t kMaxShiftedStageBytes = 64 * 1024;
 // Compaction: from this many tiles on (2^17 i32 elements), two launches instead of three: the blocks of
 // the scatter launch add up the counts in front of them by themselves (14 us a call against 15-16 at
 // 2^17 .. 2^20 elements, where the launches are what is paid for), in at most kCompactBlocksPerCu blocks to a CU.
@@ -769,9 +770,31 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       L.rp.rpb = block / G;
       // stage row vectors in LDS when they fit a modest budget (keeps >= 3 blocks per CU resident)
       {
-        int64_t bytes = 0;
-        for (int eb : p.gen.staged_elem_bytes) bytes += ((sv.inner + v) * eb + 15) & ~15ll;
-        const bool stage = vec && V > 1 && c->row_stage && bytes > 0 && bytes <= 48 * 1024;
+        // Shifted slots read copies shifted alike: one for every lane group, or for every shift (4 to 16 bytes of
+        // elements), and every block writes them.  That pays for one copy a block, and for four of fp32 vectors in
+        // large launches; smaller ones are not shifted (mixed chain, us, shifted with four copies / not: 3000 x 1023 6.6 / 5.6,
+        // 30000 x 321 12.9 (single dwords) / 12.1; large, single dwords / four copies, 180000 x 1501 253.8 / 246.9).  Vectors of
+        // two-byte elements: large launches of one copy (LayerNorm, not shifted / one copy, 10000 x 5739 85.5 / 77.7, 8000 x
+        // 5001 58.2 / 52.4, 8000 x 7801 77.8 / 72.2; with four copies 60000 x 1023 79.6 / 85.5, with two 30000 x 2047 78.8 / 80.7).
+        bool narrow = false;
+        auto stage_bytes = [&](bool shifted) {
+          int64_t bytes = 0;
+          for (int eb : p.gen.staged_elem_bytes) {
+            const int64_t copies = shifted ? std::min(block / G, std::min(V, 16 / eb)) : 1;
+            bytes += copies * (((sv.inner + 2 * V) * eb + 15) & ~15ll);
+            narrow = narrow || eb < 4;
+          }
+          return bytes;
+        };
+        int64_t bytes = stage_bytes(shift);
+        const bool large = c->row_nt > 0 || sv.alg_bytes >= kNonTemporalMinBytes;
+        if (shift && bytes > 0 && c->row_stage &&
+            (bytes > kMaxShiftedStageBytes || (block > G && !large) || (narrow && (block > G || !lines))))
+          shift = lines = false;
+        if (!shift) bytes = stage_bytes(false);
+        const bool stage = vec && V > 1 && c->row_stage && bytes > 0 && bytes <= (shift ? kMaxShiftedStageBytes : 48 * 1024);
+        // (from memory a shifted slot of a row vector of two-byte elements is off dword boundaries)
+        if (shift && narrow && !stage) shift = lines = false;
         L.rp.flags = (stage ? 1 : 0) | (n_col_sums == 0 ? 0 : 2);
         L.dyn_lds = stage ? (uint32_t)bytes : 0;
         const bool wide_version = block > 256;
