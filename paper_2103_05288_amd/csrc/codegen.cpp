@@ -1404,7 +1404,7 @@ struct Gen {
         out->kernels.push_back(name);
       };
       const bool two = dtype_bytes(an.accesses[0].dtype) == 2;
-      auto tiles = [&](const char* body) { return fmt("disc::%s(A.p0, A.o0, %s, A.gs%d, A.gs%d);", body, batch.c_str(), ng - 2, ng - 1); };
+      auto tiles = [&](const char* body) { return fmt("disc::%s(A.p0, A.o0, %s, A.gs%d, A.gs%d, A.aux0 != 0);", body, batch.c_str(), ng - 2, ng - 1); };
       k("k_transpose_tile", tiles(two ? "ktranspose2_body<128, 128>" : "ktranspose_body"));
       if (two) k("k_transpose_tile_h", tiles("ktranspose2_body<128, 64>"));
       out->source = os.str();

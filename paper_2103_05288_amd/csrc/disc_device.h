@@ -1451,16 +1451,46 @@ DISC_DEV void colsum_finish_body(const typename Pat::Args& A) {
 // LDS write.  The LDS row pitch is an odd number of dwords, so the column-wise element reads of
 // the second half spread over the banks.
 // =======================================================================================
-// -> batch entry of tile t, and its first row and column in the result
-DISC_DEV i64 transpose_place(i64 t, i64 tiles_p, i64 tiles_q, int TP, int TQ, i64& p0, i64& q0) {
+// Which tile is the t-th: its batch entry, and its first row and column in the result.  Where tiles of one result row
+// end inside cache lines, the two parts of a line should meet in one L2: `lists` gives every XCD (block t runs
+// on t mod 8) a contiguous eighth of the tiles, result columns first over kTransposeNear tile rows at a time, whose operand rows lie
+// side by side.  Otherwise consecutive blocks walk a diagonal of the tile grid: with a power-of-two row pitch
+// the tiles of one tile row (or column) would otherwise queue up on the same memory channels.
+// us, diagonal / lists, a tile to a block: bf16 6000 x 4097 24.4 / 22.4, 9000 x 9000 95.0 / 76.5, 3001 x 5000 16.9 / 12.2, 701 x 30000
+// 23.4 / 17.8; f32 12001 x 8003 243 / 187.  (1 / 3 / 8 tile rows at a time: 6000 x 7000 41.7 / - / 41.7, 41.0 with 4; 30000
+// x 500 15.1 / 15.0 / 13.3, 13.3 with 4.)
+constexpr u32 kTransposeNear = 4;
+DISC_DEV i64 transpose_place(i64 t, i64 batch, i64 tiles_p, i64 tiles_q, int TP, int TQ, bool lists, i64& p0, i64& q0) {
   const i64 per_batch = tiles_p * tiles_q;
-  const i64 b = t / per_batch;
-  const i64 r = t - b * per_batch;
-  // consecutive blocks walk a diagonal of the tile grid: with a power-of-two row pitch the tiles
-  // of one tile row (or column) would otherwise queue up on the same memory channels
-  const i64 tq = r / tiles_p;
-  i64 tp = r - tq * tiles_p + tq;
-  if (tp >= tiles_p) tp %= tiles_p;
+  i64 b, tq, tp;
+  if (batch * per_batch < (1LL << 31)) {         // (64-bit divisions take 0.3 us each in front of the first load)
+    const u32 pb = (u32)per_batch, Tp = (u32)tiles_p, Tq = (u32)tiles_q;
+    u32 k = (u32)t, n, p, q;
+    if (lists) {
+      const u32 all = (u32)batch * pb, x = k & 7, extra = all & 7;
+      k = x * (all >> 3) + (x < extra ? x : extra) + (k >> 3);
+    }
+    n = batch > 1 ? k / pb : 0;
+    k -= n * pb;
+    if (lists) {
+      const u32 g = k / (kTransposeNear * Tq), in = k - g * (kTransposeNear * Tq), left = Tp - g * kTransposeNear;
+      q = left >= kTransposeNear ? in / kTransposeNear : in / left;
+      p = g * kTransposeNear + in - q * (left >= kTransposeNear ? kTransposeNear : left);
+    } else {
+      q = k / Tp;
+      p = k - q * Tp + q;
+      if (p >= Tp) p %= Tp;
+    }
+    b = __builtin_amdgcn_readfirstlane((int)n);
+    tq = __builtin_amdgcn_readfirstlane((int)q);
+    tp = __builtin_amdgcn_readfirstlane((int)p);
+  } else {
+    b = t / per_batch;
+    const i64 r = t - b * per_batch;
+    tq = r / tiles_p;
+    tp = r - tq * tiles_p + tq;
+    if (tp >= tiles_p) tp %= tiles_p;
+  }
   p0 = tp * TP;
   q0 = tq * TQ;
   return b;
@@ -1474,7 +1504,7 @@ DISC_DEV i64 transpose_place(i64 t, i64 tiles_p, i64 tiles_q, int TP, int TQ, i6
 // 4097 with a softmax behind it 40.7 / 40.2 / 39.3; 8192 x 8192 62 / 62 / 67.7, 5000 x 9000 52.7 / - / 62.7, 16384 x 8192 121 / -
 // / 144.  (64 x 128: 42.1 and 65.4, 64 x 64: 42.6 and 56.6 at 6000 x 4097 and 8192 x 8192.)
 template <int TP, int TQ, class T>
-DISC_DEV void ktranspose2_body(const T* __restrict__ in, T* __restrict__ out, i64 batch, i64 P, i64 Q) {
+DISC_DEV void ktranspose2_body(const T* __restrict__ in, T* __restrict__ out, i64 batch, i64 P, i64 Q, bool lists) {
   static_assert(sizeof(T) == 2 && TP == 128 && (TQ == 64 || TQ == 128), "two-byte elements");
   constexpr int VP = TP / 8, VQ = TQ / 8, PQ = TQ / 2;
   constexpr int NP = PQ * VP / 256, NR = TP * VQ / 256;      // pairs of 16-byte loads, and stores, of a lane
@@ -1485,7 +1515,7 @@ DISC_DEV void ktranspose2_body(const T* __restrict__ in, T* __restrict__ out, i6
   const int v = (int)threadIdx.x % VP, g = (int)threadIdx.x / VP, vq = (int)threadIdx.x % VQ, c0 = (int)threadIdx.x / VQ;
   for (i64 t = blockIdx.x; t < ntiles; t += gridDim.x) {
     i64 p0, q0;
-    const i64 b = transpose_place(t, tiles_p, tiles_q, TP, TQ, p0, q0);
+    const i64 b = transpose_place(t, batch, tiles_p, tiles_q, TP, TQ, lists, p0, q0);
     const T* src = in + b * P * Q;
     T* dst = out + b * P * Q;
     Vec<T, 8> x[NP][2];
@@ -1538,7 +1568,7 @@ DISC_DEV void ktranspose2_body(const T* __restrict__ in, T* __restrict__ out, i6
 }
 
 template <class T>
-DISC_DEV void ktranspose_body(const T* __restrict__ in, T* __restrict__ out, i64 batch, i64 P, i64 Q) {
+DISC_DEV void ktranspose_body(const T* __restrict__ in, T* __restrict__ out, i64 batch, i64 P, i64 Q, bool lists) {
   constexpr int VE = 16 / (int)sizeof(T);                    // elements per 16-byte access
   constexpr int TS = sizeof(T) <= 2 ? 128 : 64;
   constexpr int PAD = sizeof(T) >= 4 ? 1 : 4 / (int)sizeof(T);
@@ -1549,7 +1579,7 @@ DISC_DEV void ktranspose_body(const T* __restrict__ in, T* __restrict__ out, i64
   const i64 ntiles = batch * tiles_p * tiles_q;
   for (i64 t = blockIdx.x; t < ntiles; t += gridDim.x) {
     i64 p0, q0;
-    const i64 b = transpose_place(t, tiles_p, tiles_q, TS, TS, p0, q0);
+    const i64 b = transpose_place(t, batch, tiles_p, tiles_q, TS, TS, lists, p0, q0);
     const T* src = in + b * P * Q;
     T* dst = out + b * P * Q;
     Vec<T, VE> piece[NVEC];

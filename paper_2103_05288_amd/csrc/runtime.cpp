@@ -429,7 +429,14 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     LaunchRec& L = fp->launches[0];
     L.kid = half ? K_TRANSPOSE_TILE_H : K_TRANSPOSE_TILE;
     L.block = 256;
-    L.grid[0] = (uint32_t)std::min<int64_t>(ntiles, (int64_t)c->n_cus * 8);
+    // A tile to a block (before / after, 8 blocks a CU that walked the tiles: 16384 x 8192 117 / 109, 8192 x 4096 f32 59.1 / 53.1,
+    // 9000 x 9000 with lists 87 / 76.4), as many as a launch may have.
+    L.grid[0] = (uint32_t)std::min<int64_t>(ntiles, 1 << 23);
+    // The order of the tiles: lists where the lines of the operand are shared by tiles that are not of one row either, and
+    // for large operands whose rows are whole lines (us, diagonal / lists: 16384 x 8192 109 / 100, 2001 x 28800 63.4 / 54.4, 8192 x
+    // 8192 57.2 / 55.7, 14400 x 14400 169 / 167; but 2001 x 14400 27.6 / 30.7, 6400 x 6400 33.6 / 35.5, 4000 x 4000 f32 26.0 / 27.4).
+    const bool whole_lines = P * dtype_bytes(an.accesses[0].dtype) % 128 == 0;
+    fp->aux[0] = ntiles < (1ll << 31) && (!whole_lines || sv.alg_bytes >= (192ll << 20));
     pub.variant = DISC_V_TRANSPOSE_TILE;
     pub.n_launches = 1;
     pub.vec_width = 1;
