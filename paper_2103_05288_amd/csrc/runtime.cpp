@@ -1156,12 +1156,13 @@ bool plan_xpose(const disc_ctx* c, int64_t per, int64_t batch, int64_t inner, in
   // thousands.  bf16 softmax, strips of 8 / 16 / 32, us: 1500 x 5000 (of the operand) 11.9 / 13.2 / 14.8, 2500 x 5000 17.6 /
   // 18.6 / 22.1, 300 x 8192 6.2 / 5.7 / 5.6, 3000 x 8000 37.4 / 26.5 / -, 200 x 200000 76 / 45.5 / 38.1, 1000 x 60000 77 / 62 / 59.
   // Against two kernels: 2000 x 100 5.4 / 8.0, 1000 x 8000 9.5 / 15.1, 2000 x 4000 11.4 / 15.5, 3000 x 2001 11.5 / 15.5, 3500 x 5000
-  // 23.0 / 34.2, 8192 x 8192 93.2 / 110.4.  Rows beyond 4096 elements leave one strip to a CU, whose load, arithmetic and
-  // stores follow one another: only with several strips for every CU (6000 x 4097 44.5 / 39.4, 8192 x 64 14.6 / 10.1, 5000 x
-  // 6200 45.2 / 50.4, 6000 x 7000 55.9 / 67.9).  (4000 x 300 9.7 / 9.2 and 4000 x 800 12.0 / 11.0 are on the wrong side of the
-  // line; 4000 x 1200 12.5 / 12.7, 3200 x 500 8.5 / 9.7, 3600 x 1000 11.4 / 11.8.)
+  // 23.0 / 28.9, 8192 x 8192 95.4 / 107.  Rows beyond 4096 elements leave one strip to a CU, whose load, arithmetic and
+  // stores follow one another, 20 us however many there are: with several strips for every CU, or one for most of
+  // them (6000 x 2200 24.3 / 20.5, 4500 x 2600 21.0 / 20.0, 6000 x 3000 24.7 / 28.1, 4500 x 4000 20.9 / 29.3, 8192 x 4000 38.8 / 50.4, 6000 x
+  // 4097, a second round for one strip, 45.4 / 38.0; 8192 x 64 14.6 / 10.1, 5000 x 6200 45.3 / 47.5, 6000 x 7000 55.8 / 65.1).  (4000 x 300
+  // 9.7 / 9.2 and 4000 x 800 12.0 / 11.0 are on the wrong side of the line; 3200 x 500 8.5 / 9.7, 3600 x 1000 11.4 / 11.8.)
   const int64_t strips16 = (per + 15) / 16 * batch;
-  if (inner > 64 * V * 8 && strips16 < c->n_cus * 3 / 2) return false;
+  if (inner > 64 * V * 8 && strips16 < c->n_cus * 3 / 2 && !(strips16 > c->n_cus * 2 / 3 && strips16 < c->n_cus)) return false;
   int G = 64, B = 512, nv = 0;
   if (strips16 >= 8ll * c->n_cus && inner <= 16 * V * 12 && per >= 32) G = 16;
   else if (strips16 >= c->n_cus * 7 / 4 || inner > 64 * V * 8) {

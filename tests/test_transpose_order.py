@@ -54,3 +54,28 @@ def test_copies(dtype):
             assert bool((out[:16] == 5).all()) and bool((out[n + 16:] == 5).all()), (dtype, dims)
     finally:
         ctx.close()
+
+
+def _softmax_graph(ctx):
+    from tests.test_transposed_rows import softmax
+    return ctx.register_graph(softmax("bf16"))
+
+
+def test_one_strip_of_long_rows_for_most_cus():
+    """Rows beyond 4096 elements: one kernel where strips of 16 give between two thirds of the CUs and all of them one."""
+    from paper_2103_05288_amd import Context
+    ctx = Context(-1)
+    g = _softmax_graph(ctx)
+    for cols, one in ((16 * 170, False), (16 * 171, True), (3000, True), (16 * 255, True), (16 * 255 + 1, False), (4097, False)):
+        assert ("k_row_xpose" in g.plan([6000, cols], 1)["kernels"][0]) == one, cols
+    ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims", [[4097, 2737], [6000, 3001], [8192, 4080]])
+def test_one_strip_of_long_rows_matches_oracle(dims):
+    from paper_2103_05288_amd import Context
+    from tests.test_transposed_rows import check, softmax
+    ctx = Context(0)
+    check(ctx, _softmax_graph(ctx), softmax("bf16"), dims, 1, 7)
+    ctx.close()
