@@ -1788,7 +1788,7 @@ struct ColPlan {
   int GC;          // lanes along inner per block, power of two <= 64
   int log2GC;
   int nchunk;      // chunks of the reduced axis
-  int pad;
+  int lists;       // order of the blocks, see col_place
   i64 chunk_rows;  // rows per chunk
   i64 outer;
   i64 epi_rows;    // two-launch version: rows of the reduced axis per block of the second launch
@@ -1911,17 +1911,39 @@ DISC_DEV void col_block_merge(typename Pat::template Acc<0> (&acc)[V], typename 
   __syncthreads();
 }
 
+// Column tile and row range (chunk, in the first launch) of a block.  `lists`: every XCD (blocks i mod 8) takes a contiguous
+// eighth of the tiles, all tiles of a row range before the next one: where the pieces of a row do not end on cache
+// lines, their neighbours have the other part of a line, and meet in one L2 (dealt out one by one to the XCDs, a
+// line was fetched and written in two).  fp32 centring, us, one by one / lists: 65536 x 700 187 / 140, 65536 x 333 114.6 / 68.2,
+// 30000 x 1000 78.5 / 68.1, 10000 x 301 19.7 / 14.2; pieces of whole lines, 20000 x 1024 40.2 / 44.6.
+// In the second launch (BACK) an XCD takes the same rows as in the first one, the last ones first: what it read last is the
+// likeliest to be still in its L2, or in the memory-side cache (ranges from the end,
+// XCDs the other way round: 4000 x 1000 15.7 us, 14.2 like this, 4000 x 300 10.5 / 9.5, 65536 x 333 72.3 / 70.5).
+template <bool BACK>
+DISC_DEV void col_place(bool lists, i64& tile, i64& range) {
+  tile = blockIdx.x;
+  range = BACK ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
+  if (lists) {                                  // (the host sees to fewer than 2^31 blocks)
+    const u32 at = blockIdx.y * gridDim.x + blockIdx.x, n = gridDim.x * gridDim.y, x = at & 7, extra = n & 7;
+    const u32 first = x * (n >> 3) + (x < extra ? x : extra), last = first + (n >> 3) - (x < extra ? 0 : 1);
+    const u32 k = BACK ? last - (at >> 3) : first + (at >> 3), q = k / gridDim.x;
+    range = __builtin_amdgcn_readfirstlane((int)q);
+    tile = __builtin_amdgcn_readfirstlane((int)(k - q * gridDim.x));
+  }
+}
+
 template <class Pat, int V>
 DISC_DEV void col_partial_body(const typename Pat::Args& A, const ColPlan& cp) {
   typedef typename Pat::template Acc<0> AccT;
   __shared__ AccT lds[256 * V];
+  i64 tile, chunk;
+  col_place<false>(cp.lists != 0, tile, chunk);
   const int tx = threadIdx.x & (cp.GC - 1);
   const int ty = threadIdx.x >> cp.log2GC;
   const int TY = blockDim.x >> cp.log2GC;
-  const i64 col = ((i64)blockIdx.x * cp.GC + tx) * V;
+  const i64 col = (tile * cp.GC + tx) * V;
   const i64 rem = A.inner - col;
   const int nvalid = rem <= 0 ? 0 : (rem < (i64)V ? (int)rem : V);
-  const i64 chunk = blockIdx.y;
   const i64 m0 = chunk * cp.chunk_rows;
   const i64 m1 = m0 + cp.chunk_rows < A.mid ? m0 + cp.chunk_rows : A.mid;
   for (i64 o = blockIdx.z; o < cp.outer; o += gridDim.z) {
@@ -2146,13 +2168,14 @@ template <class Pat, class PatE, int V, int NT>
 DISC_DEV void col_epi2_body(const typename Pat::Args& A, const ColPlan& cp) {
   typedef typename Pat::template Acc<0> AccT;
   __shared__ AccT lds[256 * V];
+  i64 tile, rb;
+  col_place<true>(cp.lists != 0, tile, rb);
   const int tx = threadIdx.x & (cp.GC - 1);
   const int ty = threadIdx.x >> cp.log2GC;
   const int TY = blockDim.x >> cp.log2GC;
-  const i64 col = ((i64)blockIdx.x * cp.GC + tx) * V;
+  const i64 col = (tile * cp.GC + tx) * V;
   const i64 rem = A.inner - col;
   const int nvalid = rem <= 0 ? 0 : (rem < (i64)V ? (int)rem : V);
-  const i64 rb = (i64)gridDim.y - 1 - blockIdx.y;
   const i64 m0 = rb * cp.epi_rows;
   const i64 m1 = m0 + cp.epi_rows < A.mid ? m0 + cp.epi_rows : A.mid;
   for (i64 o = blockIdx.z; o < cp.outer; o += gridDim.z) {

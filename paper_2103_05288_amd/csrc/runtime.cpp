@@ -29,7 +29,7 @@ struct DeviceRowPlan {   // mirrors disc::RowPlan of the device header
   int32_t G, log2G, nv, flags, rpb;
 };
 struct DeviceColPlan {   // mirrors disc::ColPlan of the device header
-  int32_t GC, log2GC, nchunk, pad;
+  int32_t GC, log2GC, nchunk, lists;
   int64_t chunk_rows, outer, epi_rows;
 };
 constexpr int kLdsStep = 512, kLdsSteps = 48 * 1024 / kLdsStep + 2;
@@ -1075,7 +1075,17 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     else nchunk = std::min<int64_t>(std::max<int64_t>(1, std::min<int64_t>(((int64_t)c->n_cus * 4 + tiles - 1) / tiles, max_chunks)), 1024);
     const int64_t chunk_rows = (mid + nchunk - 1) / nchunk;
     nchunk = (mid + chunk_rows - 1) / chunk_rows;
-    DeviceColPlan cp{GC, ilog2_ceil(GC), (int32_t)nchunk, 0, chunk_rows, outer, 0};
+    // pieces of a row that a block takes: whole 128-byte lines?
+    bool lines = true;
+    int64_t row_bytes = 0;
+    for (const Access& a : an.accesses) {
+      if (a.kind != ACC_FULL || a.is_output) continue;
+      if (inner * dtype_bytes(a.dtype) % 128 != 0 || (int64_t)GC * v * dtype_bytes(a.dtype) < 128) lines = false;
+      row_bytes = std::max(row_bytes, inner * dtype_bytes(a.dtype));
+    }
+    // (fewer than 2^31 blocks in either launch)
+    const bool lists = !lines && col_tiles < (1 << 15);
+    DeviceColPlan cp{GC, ilog2_ceil(GC), (int32_t)nchunk, lists, chunk_rows, outer, 0};
     int64_t cells, red_bytes;
     if (mul_ovf(outer * nchunk, inner, &cells) || mul_ovf(cells, (int64_t)p.gen.n_acc_cells * 8, &red_bytes))
       return set_err(c, DISC_ERR_SHAPE, "workspace size overflows int64");
@@ -1114,11 +1124,13 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // a block are whole 128-byte lines, i.e. nobody else wants the rest of a line (fp32, stores only / both: 60000 x
       // 512 66.3 / 61.0 us, 40000 x 768 73.6 / 65.4, 20000 x 2016 88.9 / 77.8, 65536 x 1024 130.9 / 128.9); with
       // pieces of 64 bytes, or rows that end inside a line, it loses (60000 x 256 52.8 / 62.5, 90000 x 384 116 / 130;
-      // 30000 x 1000 80.8 / 91.6, 7857 x 3628 84.3 / 93.2, 276620 x 248 306 / 373).
-      bool lines = true;
-      for (const Access& a : an.accesses)
-        if (a.kind == ACC_FULL && !a.is_output && (inner * dtype_bytes(a.dtype) % 128 != 0 || (int64_t)GC * v * dtype_bytes(a.dtype) < 128)) lines = false;
-      L1.kid = !vec ? K_COL_EPI2_SCALAR : !nt ? K_COL_EPI2_VEC : lines || c->row_nt > 0 ? K_COL_EPI2_VEC_NT : K_COL_EPI2_VEC_NTS;
+      // 30000 x 1000 80.8 / 91.6, 7857 x 3628 84.3 / 93.2, 276620 x 248 306 / 373, all without lists).
+      // Without whole lines the blocks come in lists, whose neighbours write the parts of a line shortly after
+      // one another: up to 224 MiB, for rows of 3840 bytes and more and for rows of whole lines in smaller pieces the hint on the stores still gains, beyond it the plain
+      // store does (stores with the hint / plain: 30000 x 700 56.8 / 60.8, 40000 x 700 78.9 / 80.9, 50000 x 700 113.6 / 102.2, 65536 x
+      // 500 98.5 / 86.5, 65536 x 900 184 / 177, 65536 x 1000 149 / 177, 40000 x 1500 158 / 171, 20000 x 3000 133 / 159).
+      const bool nts = nt && (sv.alg_bytes < (224ll << 20) || row_bytes >= 3840 || row_bytes % 128 == 0);
+      L1.kid = !vec ? K_COL_EPI2_SCALAR : nt && (lines || c->row_nt > 0) ? K_COL_EPI2_VEC_NT : nts ? K_COL_EPI2_VEC_NTS : K_COL_EPI2_VEC;
       L1.grid[0] = (uint32_t)col_tiles;
       L1.grid[1] = (uint32_t)row_blocks;
       L1.grid[2] = (uint32_t)std::min<int64_t>(outer, 65535);
