@@ -467,7 +467,9 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       fp->aux[3] = two ? parts % (4 * chunks) : 0;
     }
     fp->ws_off[0] = 0;
-    pub.workspace_bytes = one_pass ? (size_t)nb * 4 : two ? (size_t)chunks * 16 : (size_t)std::max<int64_t>(nb, 1) * 8;
+    // (one pass: no less than shorter inputs need, so that a workspace asked for at the most elements serves them all)
+    fp->ws_need = one_pass ? (size_t)nb * 4 : two ? (size_t)chunks * 16 : (size_t)std::max<int64_t>(nb, 1) * 8;
+    pub.workspace_bytes = one_pass ? std::max(fp->ws_need, (size_t)c->n_cus * kCompactBlocksPerCu * 16) : fp->ws_need;
     pub.variant = vec ? DISC_V_COMPACT_VEC : DISC_V_COMPACT_SCALAR;
     pub.vec_width = v;
     pub.index_bits = 64;

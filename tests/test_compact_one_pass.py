@@ -21,7 +21,7 @@ def test_which_calls_take_one_pass():
     p = h.plan([line + 8])
     assert _kernels(p) == ["clear", "chain_vec"] and p["n_launches"] == 2
     tiles = -(-(line + 8) // 4096)
-    assert p["workspace_bytes"] == 4 * tiles and p["grid"][1][0] == 1024 and p["grid"][0][0] == -(-tiles // 256)
+    assert p["workspace_bytes"] == max(4 * tiles, 1024 * 16) and p["grid"][1][0] == 1024 and p["grid"][0][0] == -(-tiles // 256)
     assert _kernels(h.plan([1 << 25], VARIANTS.index("compact_scalar"))) == ["count_scalar", "scatter_scalar"]
     ctx.test_option("non_temporal", 0)                        # its stores are: without them two launches
     assert _kernels(h.plan([1 << 25])) == ["count_vec", "scatter_vec"]
@@ -43,6 +43,16 @@ def _one_output(dtype):
     pb.output(pb.compact(x, keep))
     pb.output(pb.compact_count(keep, "i32"))
     return pb.build()
+
+
+@pytest.mark.parametrize("dtype", ["i32", "i64"])
+def test_the_workspace_of_the_most_elements_serves_fewer(dtype):
+    from paper_2103_05288_amd import Context
+    ctx = Context(-1)
+    h = ctx.register(unique_sorted(dtype))
+    sizes = [h.plan([int(2 ** (k / 8))])["workspace_bytes"] for k in range(80, 208)]
+    assert sizes == sorted(sizes)
+    ctx.close()
 
 
 @pytest.mark.gpu
