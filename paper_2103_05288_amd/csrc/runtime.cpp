@@ -720,10 +720,15 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // every other CU has a row group at most (us, three / two: LayerNorm backward 3000 x 130 12.5 / 10.8, 300 x 140 11.8 / 10.5, 500
       // x 700 11.8 / 10.6, 64 x 150 11.5 / 9.9; with 312 groups 5000 x 350 15.5 / 16.1, 10000 x 150 14.9 / 15.6; 2000 x 1400 14.7
       // / 16.6), and blocks of 512 threads for rows that fill two thirds of their lanes (300 x 5500 20.0 / 17.5, 10000 x 6140 95.9
-      // / 93.5; 2000 x 5000 28.0 / 29.9).
+      // / 93.5; 2000 x 5000 28.0 / 29.9).  A row group has a row of partial sums: more rows ask for as many as the fewer ones on
+      // twice the lanes do, so that a workspace asked for at the most rows serves them all.
+      int64_t fewer_rows_blocks = 0;
+      bool count_even = false;
       if (n_col_sums > 0 && nv == 3) {
         const int64_t groups = (sv.rows + 256 / G - 1) / (256 / G);
-        if ((G <= 32 && 2 * groups <= c->n_cus) || (G == 256 && 3 * spr > 2 * 1024)) {
+        if (G <= 32 && 2 * groups > c->n_cus) fewer_rows_blocks = c->n_cus;
+        count_even = G == 256 && 3 * spr > 2 * 1024;
+        if ((G <= 32 && 2 * groups <= c->n_cus) || count_even) {
           G *= 2;
           nv = 2;
           block = std::max(block, G);
@@ -877,7 +882,8 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       auto odd = [&](int64_t g) { return g > 2 && g % 2 == 0 && g < ngroups ? g - 1 : g; };
       int64_t grid = blocks_of(L.kid);
       for (const int kid : {kid_aligned, kid_any})
-        if (n_col_sums + n_row_reds > 0) most_blocks = std::max(most_blocks, may_shift ? blocks_of(kid) : odd(blocks_of(kid)));
+        if (n_col_sums + n_row_reds > 0) most_blocks = std::max(most_blocks, may_shift || count_even ? blocks_of(kid) : odd(blocks_of(kid)));
+      most_blocks = std::max(most_blocks, fewer_rows_blocks);
       // An odd grid: with an even one a block of one row per iteration would only ever see even or
       // only odd rows, and when the row length is odd every other row starts two bytes off a
       // dword -- half of the blocks would run ~20 % slower all the time and set the kernel's time

@@ -19,6 +19,20 @@ def test_two_slots_in_place_of_three():
     ctx.close()
 
 
+def test_the_workspace_of_the_most_rows_serves_fewer():
+    """Up to the row of partial sums by which grids are made odd, where it was so before those schedules."""
+    from paper_2103_05288_amd import Context
+    ctx = Context(-1)
+    h = ctx.register(layernorm_backward_graph())
+    for H in (130, 300, 700, 5500, 6140):
+        most = 0
+        for k in range(8 * 16):
+            need = h.plan([int(2 ** (k / 8)), H])["workspace_bytes"]
+            assert need >= most - (2 * 4 * H if H < 5464 else 0), (k, H)
+            most = max(most, need)
+    ctx.close()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dims", DIMS, ids=lambda d: f"{d[0]}x{d[1]}")
 def test_results(dims):
