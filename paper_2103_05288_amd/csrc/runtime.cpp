@@ -32,7 +32,7 @@ struct DeviceColPlan {   // mirrors disc::ColPlan of the device header
   int32_t GC, log2GC, nchunk, lists;
   int64_t chunk_rows, outer, epi_rows;
 };
-constexpr int kLdsStep = 512, kLdsSteps = 48 * 1024 / kLdsStep + 2;
+constexpr int kLdsStep = 512, kLdsSteps = 64 * 1024 / kLdsStep + 2;
 constexpr int kArgBufBytes = 4096;    // kernel-argument block + launch-plan struct
 constexpr int kMaxShapeValues = 64;   // strides + base offsets + padding windows of one pattern
 struct FastDivHost {
