@@ -717,18 +717,18 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         tail = true;
       }
       // Sums over the rows, three slots a lane: 200 registers, two blocks on a CU.  Two slots on twice the lanes while
-      // every other CU has a row group at most (us, three / two: LayerNorm backward 3000 x 130 12.5 / 10.8, 300 x 140 11.8 / 10.5, 500
-      // x 700 11.8 / 10.6, 64 x 150 11.5 / 9.9; with 312 groups 5000 x 350 15.5 / 16.1, 10000 x 150 14.9 / 15.6; 2000 x 1400 14.7
-      // / 16.6), and blocks of 512 threads for rows that fill two thirds of their lanes (300 x 5500 20.0 / 17.5, 10000 x 6140 95.9
+      // every other CU has a row group at most (us, three / two: LayerNorm backward 3000 x 130 12.5 / 10.8, 300 x 140 11.8 / 10.5,
+      // 64 x 150 11.5 / 9.9; longer rows, 500 x 700 11.8 / 10.6, would double a workspace that is no longer small;
+      // with 312 groups 5000 x 350 15.5 / 16.1, 10000 x 150 14.9 / 15.6; 2000 x 1400 14.7 / 16.6), and blocks of 512 threads for rows that fill two thirds of their lanes (300 x 5500 20.0 / 17.5, 10000 x 6140 95.9
       // / 93.5; 2000 x 5000 28.0 / 29.9).  A row group has a row of partial sums: more rows ask for as many as the fewer ones on
       // twice the lanes do, so that a workspace asked for at the most rows serves them all.
       int64_t fewer_rows_blocks = 0;
       bool count_even = false;
       if (n_col_sums > 0 && nv == 3) {
         const int64_t groups = (sv.rows + 256 / G - 1) / (256 / G);
-        if (G <= 32 && 2 * groups > c->n_cus) fewer_rows_blocks = c->n_cus;
+        if (G <= 16 && 2 * groups > c->n_cus) fewer_rows_blocks = c->n_cus;
         count_even = G == 256 && 3 * spr > 2 * 1024;
-        if ((G <= 32 && 2 * groups <= c->n_cus) || count_even) {
+        if ((G <= 16 && 2 * groups <= c->n_cus) || count_even) {
           G *= 2;
           nv = 2;
           block = std::max(block, G);

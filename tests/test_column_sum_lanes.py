@@ -12,7 +12,7 @@ def test_two_slots_in_place_of_three():
     from paper_2103_05288_amd import Context
     ctx = Context(-1)
     h = ctx.register(layernorm_backward_graph())
-    for dims, lanes, slots in (([2048, 140], 16, 2), ([4096, 140], 16, 2), ([4097, 140], 8, 3), ([1024, 700], 64, 2), ([1025, 700], 32, 3),
+    for dims, lanes, slots in (([2048, 140], 16, 2), ([4096, 140], 16, 2), ([4097, 140], 8, 3), ([2048, 380], 32, 2), ([2049, 380], 16, 3), ([1024, 700], 32, 3),
                                ([300, 1400], 64, 3), ([300, 5464], 512, 2), ([300, 5456], 256, 3), ([9000, 6144], 512, 2)):
         p = h.plan(dims)
         assert (p["lanes_per_row"], p["slots_per_lane"]) == (lanes, slots), dims
