@@ -703,16 +703,17 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         choose(spr);
         tail = tail_ok && tail_fits(sv.inner / v);   // (the whole slots alone would have fitted fewer lanes than a slot has elements)
       }
-      // Ragged rows of 10 to 12 slots would run on four lanes, with a ragged last slot in every group: with
+      // Ragged rows of 9 to 12 slots would run on four lanes, with a ragged last slot in every group: with
       // enough of them, eight lanes that take the ragged ends as single elements are faster although a
       // third of them is idle.  300007 rows of 73 / 77 / 85 / 93 / 95 in us, on four and on eight lanes: mixed chain
       // 33.2 / 36.6 / 39.9 / 42.7 / 44.5 and 34.1 / 35.3 / 36.9 / 38.6 / 39.0; softmax 24.7 / 26.2 / 30.3 / 32.7 / 34.3
       // and 22.9 / 23.7 / 27.2 / 29.2 / 29.5; LayerNorm 40.5 .. 51.7 and 39.2 .. 44.1; add + RMS norm 53.6 .. 71.6 and 45.5
-      // .. 54.0; log-sum-exp and row amax 19.2 .. 20.1, 12.3 .. 13.9 and 19.0 .. 19.7, 10.1 .. 11.4.  The line does not lie
-      // where eight lanes stop gaining: rows of eight whole slots (65 .. 71) would gain more (mixed chain 29.8
-      // / 24.2, softmax 17.4 / 14.3, LayerNorm 35.9 / 30.7) and have kept the one schedule that they have at any
-      // number of rows.  (3000 or 1200 rows take the time of a launch either way, 4.7 .. 5.0.)
-      if (tail_ok && !tail && G == 4 && v == 8 && sv.inner / v > 8 && sv.rows >= 4ll * c->n_cus) {
+      // .. 54.0; log-sum-exp and row amax 19.2 .. 20.1, 12.3 .. 13.9 and 19.0 .. 19.7, 10.1 .. 11.4.  Rows of eight
+      // whole slots, one to a lane, gain most: 300007 rows of 65 .. 71, mixed chain 29.8 / 24.2, softmax 17.4 / 14.3, LayerNorm 35.9 /
+      // 30.7; attention softmax 128 x 16 x 69 x 69 13.4 / 9.4, 16 x 16 x 71 x 71 5.1 / 4.7.  (Rows of 65, which would gain as
+      // much, keep the one schedule that they are held to at any number of rows.  3000 or 1200 rows take the time
+      // of a launch either way, 4.7 .. 5.0.)
+      if (tail_ok && !tail && G == 4 && v == 8 && sv.inner > 8 * v + 1 && sv.rows >= 4ll * c->n_cus) {
         G = 8;
         tail = true;
       }

@@ -450,6 +450,20 @@ def test_short_ragged_rows_on_eight_lanes(ctx):
         assert check(ctx, "C1", [4, 4, S], seed=S, handle=h1)["lanes_per_row"] == 8
 
 
+def test_ragged_rows_of_nine_slots_on_eight_lanes(ctx):
+    """The same for rows of eight whole slots and two to seven elements."""
+    h = ctx.register(CONFIGS["C4"].pattern())
+    for H in (66, 68, 71):
+        few, many = h.plan([1023, H]), h.plan([1024, H])
+        assert few["lanes_per_row"] == 4 and not few["kernels"][0].endswith("_t")
+        assert many["lanes_per_row"] == 8 and many["kernels"][0].endswith("_t")
+        check(ctx, "C4", [1031, H], seed=H, handle=h)
+    h1 = ctx.register(CONFIGS["C1"].pattern())
+    for S in (66, 71):
+        assert check(ctx, "C1", [4, 4, S], seed=S, handle=h1)["lanes_per_row"] == 8
+
+
+
 def test_single_shape_module_with_operands_off_a_line():
     """Ragged rows on whole lines in a module for one shape: operands on a line, on 16 bytes and off them."""
     from paper_2103_05288_amd import Context
