@@ -71,12 +71,23 @@ struct Gen {
   std::set<int> need_nl2e;     // per-row values r for which -r*log2(e) is precomputed (exp(x - r))
   const GenOptions* opt = nullptr;
   std::set<int> read_on;       // ops whose value something other than an OUTPUT reads
+  std::set<int> decides;       // compaction: nodes that the predicate is computed from
   explicit Gen(const Analysis& a) : an(a) {
+    if (compact_tmpl()) add_decisive(an.compact_keep);
     for (const auto& op : an.ops)
       if (op.opcode != DISC_OUTPUT)
         for (int k = 0; k < operand_count(op.opcode); ++k) read_on.insert(op.in[k]);
   }
 
+  // An element is counted in one place and stored in another (another kernel, or another wavefront in the one-pass
+  // version), which have to agree about it to the last bit.  Which product a sum takes into a fused multiply-add is the
+  // compiler's choice, in each copy of the code anew (with the values not stored, it was another one in the
+  // counting kernel), so the sums that the predicate is computed from take none.
+  void add_decisive(int id) {
+    if (id < 0 || !decides.insert(id).second) return;
+    for (int k = 0; k < an.nodes[id].n_in; ++k) add_decisive(an.nodes[id].in[k]);
+  }
+  bool decisive(const Node& n) const { return decides.count((int)(&n - an.nodes.data())) != 0; }
   // no reduction along the rows, sums over the rows only: a row need not stay in one block (one outer
   // group at most, so that an operand that does not span it is the same in every row)
   bool row_cols_ok() const {
@@ -304,8 +315,12 @@ struct Gen {
         case DISC_SIGMOID: return f ? "disc::fast_sigmoid(" + a(0) + ")" : "(1.0f / (1.0f + expf(-" + a(0) + ")))";
         case DISC_ERF: return "erff(" + a(0) + ")";
         // integers wrap (two's complement of the declared width): computed on the unsigned type
-        case DISC_ADD: return k == RK_F32 ? a(0) + " + " + a(1) : wrap_arith(k, a(0), "+", a(1));
-        case DISC_SUB: return k == RK_F32 ? a(0) + " - " + a(1) : wrap_arith(k, a(0), "-", a(1));
+        case DISC_ADD:
+          if (k == RK_F32 && g.decisive(n)) return "disc::add_apart(" + a(0) + ", " + a(1) + ")";
+          return k == RK_F32 ? a(0) + " + " + a(1) : wrap_arith(k, a(0), "+", a(1));
+        case DISC_SUB:
+          if (k == RK_F32 && g.decisive(n)) return "disc::add_apart(" + a(0) + ", -(" + a(1) + "))";
+          return k == RK_F32 ? a(0) + " - " + a(1) : wrap_arith(k, a(0), "-", a(1));
         case DISC_MUL: return k == RK_F32 ? a(0) + " * " + a(1) : wrap_arith(k, a(0), "*", a(1));
         case DISC_DIV: {
           if (k == RK_F32 && mode == M_ROWLOCAL) {

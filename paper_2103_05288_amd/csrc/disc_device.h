@@ -323,6 +323,11 @@ DISC_DEV float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 DISC_DEV float fast_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896341f); }
 DISC_DEV float fast_log(float x) { return __builtin_amdgcn_logf(x) * 0.693147180559945309f; }
 DISC_DEV float fast_sigmoid(float x) { return fast_rcp(1.0f + fast_exp(-x)); }
+// a sum whose operands are rounded first, whatever they are (never part of a fused multiply-add)
+DISC_DEV float add_apart(float x, float y) {
+#pragma clang fp contract(off)
+  return x + y;
+}
 // tanh(x) = 1 - 2 / (exp(2x) + 1): exact limits at +-inf, absolute error ~1e-7 everywhere
 DISC_DEV float fast_tanh(float x) { return 1.0f - 2.0f * fast_rcp(fast_exp(2.0f * x) + 1.0f); }
 

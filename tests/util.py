@@ -1,4 +1,9 @@
 """Helpers shared by the tests: comparator bars and the GPU / oracle drivers."""
+import ctypes
+import os
+import re
+import subprocess
+
 import numpy as np
 import torch
 
@@ -82,3 +87,23 @@ def assert_close(got: torch.Tensor, want: np.ndarray, what: str = ""):
         raise AssertionError(f"{what}: {int(bad.sum())} of {g.size} elements outside the {got.dtype} bar; "
                              f"worst at {tuple(int(i) for i in idx)}: gpu={g[idx]!r} oracle={w[idx]!r} "
                              f"err={err[idx]:.3e} limit={lim[idx]:.3e}")
+
+
+def device_code(source: str, path) -> dict:
+    """Kernel name (without the pattern's prefix) -> its instructions, as the library's own compiler call builds them."""
+    rtc = ctypes.CDLL("libhiprtc.so")
+    flags = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-value",
+             "-fno-slp-vectorize", "-fno-vectorize"]
+    prog, size = ctypes.c_void_p(), ctypes.c_size_t()
+    assert rtc.hiprtcCreateProgram(ctypes.byref(prog), source.encode(), b"pattern.hip", 0, None, None) == 0
+    assert rtc.hiprtcCompileProgram(prog, len(flags), (ctypes.c_char_p * len(flags))(*[f.encode() for f in flags])) == 0
+    assert rtc.hiprtcGetCodeSize(prog, ctypes.byref(size)) == 0
+    code = ctypes.create_string_buffer(size.value)
+    assert rtc.hiprtcGetCode(prog, code) == 0
+    rtc.hiprtcDestroyProgram(ctypes.byref(prog))
+    path = str(path)
+    with open(path, "wb") as f:
+        f.write(code.raw)
+    text = subprocess.run([os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump"), "-d", path], check=True,
+                          capture_output=True, text=True).stdout
+    return {m[1]: m[2] for m in re.finditer(r"^[0-9a-f]+ <\w+?_k_(\w+)>:\n(.*?)(?=^[0-9a-f]+ <|\Z)", text, re.M | re.S)}
