@@ -1508,7 +1508,7 @@ DISC_DEV void colsum_finish_body(const typename Pat::Args& A) {
 // the tiles of one tile row (or column) would otherwise queue up on the same memory channels.
 // us, diagonal / lists, a tile to a block: bf16 6000 x 4097 24.4 / 22.4, 9000 x 9000 95.0 / 76.5, 3001 x 5000 16.9 / 12.2, 701 x 30000
 // 23.4 / 17.8; f32 12001 x 8003 243 / 187.  (1 / 3 / 8 tile rows at a time: 6000 x 7000 41.7 / - / 41.7, 41.0 with 4; 30000
-// x 500 15.1 / 15.0 / 13.3, 13.3 with 4.)
+// x 500 15.1 / 15.0 / 13.3, 13.3 with 4.)  The host asks for lists below 2^29 tiles: kTransposeNear rows of them fit 32 bits.
 constexpr u32 kTransposeNear = 4;
 DISC_DEV i64 transpose_place(i64 t, i64 batch, i64 tiles_p, i64 tiles_q, int TP, int TQ, bool lists, i64& p0, i64& q0) {
   const i64 per_batch = tiles_p * tiles_q;

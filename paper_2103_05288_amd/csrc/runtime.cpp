@@ -320,6 +320,8 @@ constexpr int64_t kNonTemporalMinBytes = 64ll << 20;
 // Ragged rows with the non-temporal hint: fewest lanes per row, rows off dword boundaries / others.
 constexpr int kMinLinesG = 64, kMinLinesEvenG = 128;
 constexpr int64_t kMaxShiftedStageBytes = 64 * 1024;
+// Tile transposes: from this many tiles on no lists, whose four tile rows of as many tiles, in one row of tiles, would not be counted in 32 bits.
+constexpr int64_t kTransposeListTiles = 1ll << 29;
 // Compaction: from this many tiles on (2^17 i32 elements), two launches instead of three: the blocks of
 // the scatter launch add up the counts in front of them by themselves (14 us a call against 15-16 at
 // 2^17 .. 2^20 elements, where the launches are what is paid for), in at most kCompactBlocksPerCu blocks to a CU.
@@ -436,7 +438,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
     // for large operands whose rows are whole lines (us, diagonal / lists: 16384 x 8192 109 / 100, 2001 x 28800 63.4 / 54.4, 8192 x
     // 8192 57.2 / 55.7, 14400 x 14400 169 / 167; but 2001 x 14400 27.6 / 30.7, 6400 x 6400 33.6 / 35.5, 4000 x 4000 f32 26.0 / 27.4).
     const bool whole_lines = P * dtype_bytes(an.accesses[0].dtype) % 128 == 0;
-    fp->aux[0] = ntiles < (1ll << 31) && (!whole_lines || sv.alg_bytes >= (192ll << 20));
+    fp->aux[0] = ntiles < kTransposeListTiles && (!whole_lines || sv.alg_bytes >= (192ll << 20));
     pub.variant = DISC_V_TRANSPOSE_TILE;
     pub.n_launches = 1;
     pub.vec_width = 1;

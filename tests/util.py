@@ -107,3 +107,25 @@ def device_code(source: str, path) -> dict:
     text = subprocess.run([os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump"), "-d", path], check=True,
                           capture_output=True, text=True).stdout
     return {m[1]: m[2] for m in re.finditer(r"^[0-9a-f]+ <\w+?_k_(\w+)>:\n(.*?)(?=^[0-9a-f]+ <|\Z)", text, re.M | re.S)}
+
+
+def host_build(body: str, path):
+    """A shared library, for the CPU, of index arithmetic cut out of the device header."""
+    head = """typedef long long i64; typedef unsigned u32; typedef unsigned long long u64;
+#define DISC_DEV static inline
+#define __builtin_amdgcn_readfirstlane(x) (x)
+static struct { unsigned x, y, z; } blockIdx, gridDim;
+"""
+    src, lib = str(path) + ".cpp", str(path) + ".so"
+    with open(src, "w") as f:
+        f.write(head + body)
+    subprocess.run([os.environ.get("CXX", "g++"), "-O1", "-std=c++17", "-shared", "-fPIC", "-o", lib, src], check=True)
+    return ctypes.CDLL(lib)
+
+
+def device_header(first: str, last: str) -> str:
+    """The text of the device header from the line that starts with `first` to the closing brace of the function `last`."""
+    import paper_2103_05288_amd
+    with open(os.path.join(os.path.dirname(paper_2103_05288_amd.__file__), "csrc", "disc_device.h")) as f:
+        text = f.read()
+    return re.search("^" + re.escape(first) + r".*?\b" + last + r"\(.*?^}$", text, re.M | re.S)[0]
