@@ -1,22 +1,49 @@
 """Column reduces in two and three launches whose blocks come in lists of neighbouring tiles (rows that do not end on cache
 lines, or pieces of a row shorter than one) or one by one."""
+import ctypes
+
 import pytest
 
 from oracle import run as oracle_run
-from tests.util import assert_close, run_gpu, to_oracle_input
+from tests.util import assert_close, device_header, host_build, run_gpu, to_oracle_input
 from workloads import PatternBuilder
 from workloads.configs import CONFIGS
 
 
-def _place(at, tiles, ranges):
-    n, x = tiles * ranges, at % 8
-    k = x * (n // 8) + min(x, n % 8) + at // 8
-    return k % tiles, k // tiles
+@pytest.fixture(scope="module")
+def place(tmp_path_factory):
+    """col_place of the device header, built for the CPU: the (tile, row range) of every block, in the order of the blocks"""
+    lib = host_build(device_header("template <bool BACK>", "col_place") + """
+extern "C" void place(int back, int lists, unsigned tiles, unsigned ranges, i64* out) {
+  gridDim.x = tiles;
+  gridDim.y = ranges;
+  for (blockIdx.y = 0; blockIdx.y < ranges; ++blockIdx.y)
+    for (blockIdx.x = 0; blockIdx.x < tiles; ++blockIdx.x, out += 2)
+      if (back) col_place<true>(lists != 0, out[0], out[1]);
+      else col_place<false>(lists != 0, out[0], out[1]);
+}
+""", tmp_path_factory.mktemp("place") / "columns")
+
+    def call(back, lists, tiles, ranges):
+        out = (ctypes.c_int64 * (2 * tiles * ranges))()
+        lib.place(back, lists, tiles, ranges, out)
+        return list(zip(out[0::2], out[1::2]))
+    return call
 
 
-def test_lists_hold_every_block_once():
-    for tiles, ranges in [(1, 1), (1, 9), (3, 5), (11, 32), (64, 8), (7, 1), (5, 13)]:
-        assert {_place(i, tiles, ranges) for i in range(tiles * ranges)} == {(t, r) for t in range(tiles) for r in range(ranges)}
+@pytest.mark.parametrize("lists", [0, 1])
+def test_every_block_once(place, lists):
+    for tiles, ranges in [(1, 1), (1, 9), (3, 5), (11, 32), (64, 8), (7, 1), (5, 13), (1000, 33)]:
+        forward, back = place(0, lists, tiles, ranges), place(1, lists, tiles, ranges)
+        every = [(t, r) for t in range(tiles) for r in range(ranges)]
+        assert sorted(forward) == every and sorted(back) == every
+        if lists:                 # an XCD (blocks i mod 8): neighbours one after the other, and the same ones backwards in the second launch
+            for x in range(8):
+                at = [r * tiles + t for t, r in forward[x::8]]
+                assert at == list(range(at[0], at[0] + len(at))) if at else True
+                assert back[x::8] == forward[x::8][::-1]
+        else:
+            assert back == [(t, ranges - 1 - r) for t, r in forward]
 
 
 @pytest.mark.gpu
