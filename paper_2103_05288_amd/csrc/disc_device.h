@@ -517,8 +517,8 @@ extern __shared__ __attribute__((aligned(16))) char disc_stage_lds[];
 // of 8 or 16 bytes off its own alignment is served one lane a cycle (64 cycles, 6 aligned), and as single dwords
 // the slots of a wavefront's lanes meet on the same banks (40), so the copies are shifted instead: element i of a row
 // vector lies at i + shift, which makes every slot start on 16 bytes (E elements; less where V elements are less).
-// A copy for every lane group, or for every shift where these are fewer.  Mixed chain of bf16, us, single dwords /
-// shifted copies: 46773 x 5739 253.5 / 243.5, 180000 x 1501 253.8 / 246.9, 4000 x 8191 35.4 / 32.2.
+// A copy for every lane group, or for every shift where these are fewer (which of them pay is the host's rule).  Mixed
+// chain of bf16, us, single dwords / shifted copies: 46773 x 5739 253.5 / 243.5, 4000 x 8191 35.4 / 32.2.
 struct StagePlan {
   int groups;   // lane groups of the block, 0: unshifted slots
   i64 row0;     // row of the first one
@@ -778,7 +778,7 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
   int col0 = lane * V;
   int nvalid[NV];
   int tcol = -1;                        // column of this lane's single element (TAIL versions), -1: none
-  auto place = [&](int r, int& c0, int (&n)[NV], int& tc) {
+  auto place = [&](int r, int head, int& c0, int (&n)[NV], int& tc) {
     int l = lane + r;
     if (l >= rp.G) l -= rp.G;
     if constexpr (TAIL) {
@@ -800,12 +800,19 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
       }
     }
   };
-  place(rot, col0, nvalid, tcol);
+  place(rot, head, col0, nvalid, tcol);
+  const int head_w = __builtin_amdgcn_readfirstlane(head);     // (of all lanes where a row has several wavefronts)
   // Software pipeline over the rows of a block: the loads of the next row are issued as soon as
   // the first reduction phase has consumed the current row's slots (every load issued so far
   // has landed by then, so no wait in the rest of the iteration touches the new loads); they
   // complete behind the lane reductions, the later phases, the epilogue and the stores.
+  // (Where the row vectors are is set here, for this row and the next one alike, and not where a row is loaded: merged
+  // with a context that was not filled in, the pointer is no longer known to be one to LDS, and every read through it
+  // is a flat load, which waits for the row loads in flight too.  us, flat / LDS reads: LayerNorm of fp32 rows with one
+  // vector 21592 x 777 51.1 / 37.4, bf16 43184 x 777 49.2 / 41.2.)
   typename Pat::RowCtx rc{};
+  rc.sl = staged;
+  rc.so = placed;
   typename Pat::template Slot<V> slot[NV];
   typedef typename TailSel<Pat, TAIL>::type TS;
   TS ts, tsn;
@@ -831,8 +838,6 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
   };
   auto load_row = [&]() {
     begin_row(rw, sbw, rc);
-    rc.sl = staged;
-    rc.so = placed;
 #pragma unroll
     for (int j = 0; j < NV; ++j)
       if (nvalid[j] > 0) Pat::template load<V, NT>(A, rc, (unsigned)(col0 + j * rp.G * V), SP::upto(nvalid[j]), slot[j]);
@@ -851,6 +856,8 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
     const i64 row = rw + dgrp;
     const bool active = row < rows;
     typename Pat::RowCtx rcn{};
+    rcn.sl = staged;
+    rcn.so = placed;
     typename Pat::template Slot<V> nxt[NV];
     int col0n = col0, tcoln = tcol;
     int nvalidn[NV];
@@ -860,11 +867,9 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
       if (PIPE && rw + rstep - grp_w < rows) {
         if (wpr > 1) {
           rot = rot + 64 < rp.G ? rot + 64 : 0;
-          place(rot, col0n, nvalidn, tcoln);
+          place(rot, head_w, col0n, nvalidn, tcoln);
         }
         begin_row(rw + rstep, sbw + sbstep, rcn);
-        rcn.sl = staged;
-        rcn.so = placed;
 #pragma unroll
         for (int j = 0; j < NV; ++j)
           if (nvalidn[j] > 0) {
@@ -929,7 +934,7 @@ DISC_DEV void row_reg_body(const typename Pat::Args& A, const RowPlan& rp) {
       }
     } else if (wpr > 1) {
       rot = rot + 64 < rp.G ? rot + 64 : 0;
-      place(rot, col0, nvalid, tcol);
+      place(rot, head_w, col0, nvalid, tcol);
     }
   }
   if constexpr (Pat::NCOLSUM > 0) {

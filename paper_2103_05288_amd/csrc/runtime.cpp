@@ -876,7 +876,12 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
           two_rounds = false;
       }
       auto blocks_of = [&](int kid) {
-        const int64_t held = (int64_t)c->n_cus * resident_blocks(c, p, kid, L.block, L.dyn_lds);
+        int64_t per_cu = resident_blocks(c, p, kid, L.block, L.dyn_lds);
+        // Ragged rows with staged vectors: at most 28 wavefronts on a CU (whole blocks: seven of 256 threads, three of 512, one of
+        // 1024).  With all 32 the memory delivers less (us, 28 / 32: fp32 LayerNorm of one vector 21592 x 777 37.0 / 43.4, 40427 x
+        // 415 40.9 / 44.7, 4095 x 4097 35.9 / 38.0; fp32 rows and bf16 rows scaled by their norm 65280 x 257 28.9 / 29.2, 4793 x 3500 12.3 / 13.4).
+        if (tail && L.dyn_lds > 0) per_cu = std::min<int64_t>(per_cu, std::max<int64_t>(1, 28 * 64 / L.block));
+        const int64_t held = (int64_t)c->n_cus * per_cu;
         // (with sums over the rows every block writes a row of partial sums: one round, or two)
         const int rounds = c->row_rounds > 0 ? c->row_rounds
                            : (L.block > 256 || n_col_sums > 0 ? (two_rounds ? 2 : 1) : (int)std::max<int64_t>(1, std::min<int64_t>(3, ngroups / (held * 4))));

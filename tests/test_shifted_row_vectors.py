@@ -3,7 +3,7 @@ copy of its own."""
 import pytest
 
 from oracle import run as oracle_run
-from tests.util import assert_close, run_gpu, to_oracle_input
+from tests.util import assert_close, device_code, run_gpu, to_oracle_input
 from workloads.configs import CONFIGS
 
 
@@ -38,4 +38,14 @@ def test_results(name, H):
         want = oracle_run(cfg.pattern(), [T, H], [to_oracle_input(t) for t in ins])[0]
         for k, (g, w) in enumerate(zip(run_gpu(h, cfg.pattern(), [T, H], ins), want)):
             assert_close(g, w, f"{name} {[T, H]} out{k}")
+    c.close()
+
+
+def test_reads_of_the_copies_are_lds_reads(tmp_path):
+    """A pointer that is LDS on one path and null on another makes flat loads, which the row loads in flight wait with."""
+    c = _context(-1)
+    code = device_code(c.register(CONFIGS["C4"].pattern()).source, tmp_path / "pattern.co")
+    staged = [k for k in code if k.startswith("row_vec_nv") and "_s" in k]
+    assert len(staged) >= 9
+    assert not [k for k in staged if "flat_load" in code[k] or "ds_read" not in code[k]]
     c.close()
