@@ -319,7 +319,9 @@ struct FullPlan {
 constexpr int64_t kNonTemporalMinBytes = 64ll << 20;
 // Ragged rows with the non-temporal hint: fewest lanes per row, rows off dword boundaries / others.
 constexpr int kMinLinesG = 64, kMinLinesEvenG = 128;
-constexpr int64_t kMaxShiftedStageBytes = 64 * 1024;
+constexpr int64_t kNarrowShiftMinBytes = kNonTemporalMinBytes * 5 / 4;
+// LDS for row vectors, and for their copies that shifted slots read in wide blocks of large launches.
+constexpr int64_t kMaxStageBytes = 48 * 1024, kMaxShiftedStageBytes = 64 * 1024;
 // Tile transposes: from this many tiles on no lists, whose four tile rows of as many tiles, in one row of tiles, would not be counted in 32 bits.
 constexpr int64_t kTransposeListTiles = 1ll << 29;
 // Compaction: from this many tiles on (2^17 i32 elements), two launches instead of three: the blocks of
@@ -742,8 +744,53 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // the next row.  The three-slot version (which has one) runs the same rows, from eight of them per
       // CU on (2^27 elements in rows of 16000: mixed chain 190 us / 151 with it, LayerNorm 172 / 149;
       // 13000: 209 / 172 and 192 / 164).  Not where the two-slot version takes the ragged ends as
-      // single elements with shifted slots (12289: mixed chain 162 / 184; LayerNorm, unshifted, 224 / 200).
-      const bool piped_wide = vec && block == 1024 && n_col_sums == 0 && sv.rows >= 8ll * c->n_cus && !(tail && p.gen.row_shift_ok);
+      // single elements with shifted slots (12289: mixed chain 162 / 184; LayerNorm, unshifted, 224 / 200): that is, not where fp32 row
+      // vectors are read, but where the copies of two-byte ones do not fit.
+      //
+      // Row vectors that can be staged in LDS: bytes of one copy of each, or of a copy for every lane group or
+      // shift, whichever are fewer; and bytes of a row of the full-size operands and results.
+      bool narrow = false, off_dword = false;
+      bool slot_bases = true, line_bases = true;   // full-size operands on boundaries of slots, and of 128 bytes
+      int64_t row_bytes = 0, stage_pad = 0;      // (the slot of padding that only shifted copies need)
+      for (int eb : p.gen.staged_elem_bytes) {
+        narrow = narrow || eb < 4;
+        stage_pad += V * eb;
+      }
+      for (const Access& a : an.accesses) {
+        if (a.kind != ACC_FULL) continue;
+        row_bytes += sv.inner * dtype_bytes(a.dtype);
+        if (a.src_value >= 0) continue;
+        const void* ptr = a.is_output ? (outputs ? outputs[a.slot] : nullptr) : (inputs ? inputs[a.slot] : nullptr);
+        if (reinterpret_cast<uintptr_t>(ptr) % (uintptr_t)(v * dtype_bytes(a.dtype)) != 0) slot_bases = false;
+        if (reinterpret_cast<uintptr_t>(ptr) % 128 != 0) line_bases = false;
+        if (dtype_bytes(a.dtype) >= 2 && (sv.inner * dtype_bytes(a.dtype)) % 4 != 0) off_dword = true;
+      }
+      auto stage_bytes = [&](int64_t groups) {
+        int64_t bytes = 0;
+        for (int eb : p.gen.staged_elem_bytes)
+          bytes += std::min<int64_t>(groups, std::min(V, 16 / eb)) * (((sv.inner + 2 * V) * eb + 15) & ~15ll);
+        return bytes;
+      };
+      const int64_t copies = stage_bytes(block / G), one = stage_bytes(1);
+      const bool large = c->row_nt > 0 || sv.alg_bytes >= kNonTemporalMinBytes;
+      // LDS for the row vectors of shifted rows: wide blocks of large launches take 64 KiB (bf16 rows, two fp32 vectors, 9585 x
+      // 7001, 56 KB, from memory / staged 87.3 / 69.7 us); where three blocks share a CU, or a block has few rows, from memory
+      // (three vectors 13419 x 5001, 60 KB, 99.4 / 124; 599 x 7001 6.3 / 7.4).  (Right at the limit, LayerNorm of three two-byte
+      // vectors, from memory / staged: 8206 x 8178 89.4 / 77.7, 256 x 8177 5.6 / 7.1.)
+      auto fits = [&](int64_t bytes, bool shifted) {
+        return bytes <= (shifted && block > 256 && large ? kMaxShiftedStageBytes : kMaxStageBytes + (large ? stage_pad : 0));
+      };
+      // Two-byte row vectors, whose rows have plain accesses where they are not shifted: launches beyond what the memory-side
+      // cache holds of a few of them in turn (rows scaled by their norm and one vector, 64 MiB, 2396 x 7001, unshifted / shifted,
+      // 13.3 / 15.8 us), blocks with one lane group, so that one copy serves it, and rows off dword boundaries (LayerNorm
+      // with three, 9585 x 7001 84.2 / 79.1); rows on them where the vectors are a small part of what a row takes anyway (2^26 elements
+      // of 4098, one / two / three vectors, 78.7 / 82.7 / 83.6 and 73.7 / 85.7 / 90.1; of 7002, one / two, 77.9 / 77.0 and 72.2 / 70.8).
+      auto narrow_copies = [&]() {
+        return block == G && c->row_nt != 0 && (c->row_nt > 0 || sv.alg_bytes >= kNarrowShiftMinBytes) && c->row_stage && fits(one, true) &&
+               (off_dword || (block <= 256 ? 2 * one <= row_bytes : block <= 512 && 10 * one <= 7 * row_bytes));
+      };
+      const bool shift_stays = !narrow || narrow_copies();
+      const bool piped_wide = vec && block == 1024 && n_col_sums == 0 && sv.rows >= 8ll * c->n_cus && !(tail && p.gen.row_shift_ok && shift_stays);
       if (piped_wide) tail = false;
       if (tail) spr = sv.inner / v;
       nv = (int)((spr + G - 1) / G);
@@ -766,29 +813,35 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // elements of other patterns: bf16 softmax 2047 203 / 180, 4100 204 / 177, 777 205 / 202; fp32 softmax 1501 405 / 378,
       // 8191 403 / 366, 601 405 / 407; log-sum-exp (no element outputs) 1501 99.5 / 91.1, 4095 109 / 108; add + RMS norm 4100
       // 425 / 387; row amax 3001 94.0 / 90.9, 1023 90.1 / 91.9.
-      bool shift = tail && p.gen.row_shift_ok && G >= 2 * v - 2 && c->row_shift != 0;
-      const bool may_shift = shift;         // with operands of the right alignment
-      int align = v;                        // elements
-      bool lines = shift && G >= kMinLinesG && c->row_nt != 0 && (c->row_nt > 0 || sv.alg_bytes >= kNonTemporalMinBytes);
-      if (shift) {
-        bool off_dword = false;
-        for (const Access& a : an.accesses) {
-          if (a.kind != ACC_FULL || a.src_value >= 0) continue;
-          const void* ptr = a.is_output ? (outputs ? outputs[a.slot] : nullptr) : (inputs ? inputs[a.slot] : nullptr);
-          if (reinterpret_cast<uintptr_t>(ptr) % (uintptr_t)(v * dtype_bytes(a.dtype)) != 0) shift = false;
-          // (a base on a slot but off a line still gains from 128 lanes on, 16 bytes past a line without / with: bf16
-          // softmax 2047 76.6 us / 72.2, 5739 77.3 / 71.0, add + RMS norm 4095 159 / 151; with 64 add + RMS norm 777 159 / 168)
-          if (reinterpret_cast<uintptr_t>(ptr) % 128 != 0 && G < kMinLinesEvenG) lines = false;
-          if (dtype_bytes(a.dtype) >= 2 && (sv.inner * dtype_bytes(a.dtype)) % 4 != 0) off_dword = true;
-        }
+      const bool may_shift = tail && p.gen.row_shift_ok && G >= 2 * v - 2 && c->row_shift != 0;   // with operands of the right alignment
+      struct Shift { bool shift, lines; };
+      auto shifted = [&](bool slots, bool whole_lines) {
+        if (!may_shift || !slots) return Shift{false, false};
+        bool lines = G >= kMinLinesG && c->row_nt != 0 && (c->row_nt > 0 || sv.alg_bytes >= kNonTemporalMinBytes);
+        // (a base on a slot but off a line still gains from 128 lanes on, 16 bytes past a line without / with: bf16
+        // softmax 2047 76.6 us / 72.2, 5739 77.3 / 71.0, add + RMS norm 4095 159 / 151; with 64 add + RMS norm 777 159 / 168)
+        if (!whole_lines && G < kMinLinesEvenG) lines = false;
         // An operand like the mask [B, 1, 1, S] of a softmax has its own boundaries, which shifted slots miss: then
         // only where two slots per lane are nearly full, and in wide blocks (f16, without / with lines: S = 777 170 us /
         // 177, 1501 177 / 180, 1700 159 / 164, 3001 157 / 166, 5742 116 / 123; 2047 143 / 137, 4098 105 / 103, 8191 206 / 194).
         if (p.gen.row_narrow_late && block <= 256 && !(G >= 128 && nv == 2 && 8 * spr >= 7 * 2 * G)) lines = false;
-        lines = lines && shift && (off_dword || G >= kMinLinesEvenG);
-        shift = shift && (off_dword || lines);
-        if (lines) align = std::min(128, G / 2);
-      }
+        lines = lines && (off_dword || G >= kMinLinesEvenG);
+        bool shift = off_dword || lines;
+        // Row vectors.  Shifted slots read copies shifted alike, one for every lane group or shift, and every block writes them.
+        // That pays in large launches while they are no more than 3.5 times a row (unshifted / shifted, us: one fp32 vector of bf16 rows in
+        // four copies, LayerNorm 44709 x 1501 78.0 / 75.0, mixed chain 44709 x 1501 69.8 / 65.8; two of fp32 rows in two 44709 x 1501 150 / 137;
+        // but two of bf16 rows in four copies 32800 x 1023 41.2 / 45.0, three 41.7 / 48.2).  Beyond, and in smaller launches, rows are not
+        // shifted (mixed chain 3000 x 1023 5.6 / 6.6).  One copy a block always pays; where it does not fit, fp32 vectors are read
+        // from memory (three vectors 11693 x 5739, unshifted / shifted and from memory, 108 / 95.2; two 8207 x 8177 94.4 / 79.0).
+        if (shift && one > 0) {
+          if (narrow) shift = lines && narrow_copies();   // (from memory their slots are off dword boundaries)
+          else if (c->row_stage && block > G && fits(one, false)) shift = large && fits(copies, true) && 2 * copies <= 7 * row_bytes;
+        }
+        return Shift{shift, lines && shift};
+      };
+      auto [shift, lines] = shifted(slot_bases, line_bases);
+      const bool aligned_shift = shifted(true, true).shift;
+      const int align = lines ? std::min(128, G / 2) : v;    // elements
       int inst = piped_wide ? 3 : std::max(nv, 2);   // instantiated slots per lane: 2 or 3
       int kid_aligned = 0, kid_any = 0;     // kernel for aligned operands, and for others
       pub.variant = vec ? DISC_V_ROW_REG_VEC : DISC_V_ROW_REG_SCALAR;
@@ -798,35 +851,13 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       L.rp.log2G = ilog2_ceil(G);
       L.rp.nv = nv;
       L.rp.rpb = block / G;
-      // stage row vectors in LDS when they fit a modest budget (keeps >= 3 blocks per CU resident)
+      uint32_t lds_unshifted = 0;           // LDS of the same launch with operands off the boundaries of slots
       {
-        // Shifted slots read copies shifted alike: one for every lane group, or for every shift (4 to 16 bytes of
-        // elements), and every block writes them.  That pays for one copy a block, and for four of fp32 vectors in
-        // large launches; smaller ones are not shifted (mixed chain, us, shifted with four copies / not: 3000 x 1023 6.6 / 5.6,
-        // 30000 x 321 12.9 (single dwords) / 12.1; large, single dwords / four copies, 180000 x 1501 253.8 / 246.9).  Vectors of
-        // two-byte elements: large launches of one copy (LayerNorm, not shifted / one copy, 10000 x 5739 85.5 / 77.7, 8000 x
-        // 5001 58.2 / 52.4, 8000 x 7801 77.8 / 72.2; with four copies 60000 x 1023 79.6 / 85.5, with two 30000 x 2047 78.8 / 80.7).
-        bool narrow = false;
-        auto stage_bytes = [&](bool shifted) {
-          int64_t bytes = 0;
-          for (int eb : p.gen.staged_elem_bytes) {
-            const int64_t copies = shifted ? std::min(block / G, std::min(V, 16 / eb)) : 1;
-            bytes += copies * (((sv.inner + 2 * V) * eb + 15) & ~15ll);
-            narrow = narrow || eb < 4;
-          }
-          return bytes;
-        };
-        int64_t bytes = stage_bytes(shift);
-        const bool large = c->row_nt > 0 || sv.alg_bytes >= kNonTemporalMinBytes;
-        if (shift && bytes > 0 && c->row_stage &&
-            (bytes > kMaxShiftedStageBytes || (block > G && !large) || (narrow && (block > G || !lines))))
-          shift = lines = false;
-        if (!shift) bytes = stage_bytes(false);
-        const bool stage = vec && V > 1 && c->row_stage && bytes > 0 && bytes <= (shift ? kMaxShiftedStageBytes : 48 * 1024);
-        // (from memory a shifted slot of a row vector of two-byte elements is off dword boundaries)
-        if (shift && narrow && !stage) shift = lines = false;
+        // Staged or not, whatever the alignment of the operands: a single-shape module has one kernel for all of them.
+        const bool stage = vec && V > 1 && c->row_stage && one > 0 && fits(aligned_shift ? copies : one, aligned_shift);
         L.rp.flags = (stage ? 1 : 0) | (n_col_sums == 0 ? 0 : 2);
-        L.dyn_lds = stage ? (uint32_t)bytes : 0;
+        L.dyn_lds = !stage ? 0 : (uint32_t)(shift ? copies : one);
+        lds_unshifted = stage ? (uint32_t)one : 0;
         const bool wide_version = block > 256;
         // Non-temporal version (blocks of 256 threads, vector width only).  Host rule, measured on
         // softmax and LayerNorm sweeps: the hint gains 5-15 % when every row starts and ends on a
@@ -875,22 +906,25 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
             (uint64_t)bytes + 8ull * (uint64_t)n_row_reds * (uint64_t)c->n_cus + 256 > ws_limit)
           two_rounds = false;
       }
-      auto blocks_of = [&](int kid) {
-        int64_t per_cu = resident_blocks(c, p, kid, L.block, L.dyn_lds);
+      auto blocks_with = [&](int kid, uint32_t lds) {
+        int64_t per_cu = resident_blocks(c, p, kid, L.block, lds);
         // Ragged rows with staged vectors: at most 28 wavefronts on a CU (whole blocks: seven of 256 threads, three of 512, one of
         // 1024).  With all 32 the memory delivers less (us, 28 / 32: fp32 LayerNorm of one vector 21592 x 777 37.0 / 43.4, 40427 x
         // 415 40.9 / 44.7, 4095 x 4097 35.9 / 38.0; fp32 rows and bf16 rows scaled by their norm 65280 x 257 28.9 / 29.2, 4793 x 3500 12.3 / 13.4).
-        if (tail && L.dyn_lds > 0) per_cu = std::min<int64_t>(per_cu, std::max<int64_t>(1, 28 * 64 / L.block));
+        if (tail && lds > 0) per_cu = std::min<int64_t>(per_cu, std::max<int64_t>(1, 28 * 64 / L.block));
         const int64_t held = (int64_t)c->n_cus * per_cu;
         // (with sums over the rows every block writes a row of partial sums: one round, or two)
         const int rounds = c->row_rounds > 0 ? c->row_rounds
                            : (L.block > 256 || n_col_sums > 0 ? (two_rounds ? 2 : 1) : (int)std::max<int64_t>(1, std::min<int64_t>(3, ngroups / (held * 4))));
         return std::min<int64_t>(ngroups, held * rounds);
       };
+      auto blocks_of = [&](int kid) { return blocks_with(kid, L.dyn_lds); };
       auto odd = [&](int64_t g) { return g > 2 && g % 2 == 0 && g < ngroups ? g - 1 : g; };
       int64_t grid = blocks_of(L.kid);
       for (const int kid : {kid_aligned, kid_any})
         if (n_col_sums + n_row_reds > 0) most_blocks = std::max(most_blocks, may_shift || count_even ? blocks_of(kid) : odd(blocks_of(kid)));
+      // (a caller that asked with aligned operands, or with none, launches with others: unshifted, less LDS)
+      if (may_shift && n_row_reds > 0) most_blocks = std::max(most_blocks, blocks_with(kid_any, lds_unshifted));
       most_blocks = std::max(most_blocks, fewer_rows_blocks);
       // An odd grid: with an even one a block of one row per iteration would only ever see even or
       // only odd rows, and when the row length is odd every other row starts two bytes off a
