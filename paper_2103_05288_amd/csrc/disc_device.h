@@ -2642,7 +2642,8 @@ DISC_DEV void compact_scatter_body(const typename Pat::Args& A) {
 // in between, one per block: no chain of look-backs, one exchange per iteration, with a whole iteration and more
 // between publishing and use.  Until then the tile's flags are a word per lane and its kept values wait in LDS.
 // The result does not depend on a wait: a cell that has not come after A.aux2 looks -- its block may not be resident -- is
-// counted by the wavefront that misses it, from the inputs, and published for the others.  A cell is one
+// counted by the wavefront that misses it, from the inputs, and published for the others: one at a time, each wavefront
+// another one, and all are looked at again after it.  A cell is one
 // 4-byte word, written and read whole at device scope; nothing else passes between blocks.
 // Bound by memory: 2^25 sorted i32 keys, a quarter distinct, 302 MB in 56 us (5.4 TB/s; a plain copy of as much moves
 // 5.7) + 4.4 to clear the cells; two launches that read them twice 78.7 us.  2^25 i64 121 / 92, 1.2 x 10^7 i32 29.9 / 21.1.
@@ -2695,6 +2696,7 @@ DISC_DEV void compact_chain_body(const typename Pat::Args& A) {
   };
   const i64 G = gridDim.x;
   i64 t = blockIdx.x - 2 * G, run = 0;      // (negative: no tile yet)
+  i64 patience = A.aux2;                    // looks at a window before a cell is counted here; few after one that came to that
   if (first(blockIdx.x) + E <= A.inner) compact_load<true, Pat, V, U>(A, first(blockIdx.x), slot);
   for (int buf = 0;; buf ^= 1, t += G) {
     // two tiles ahead: count, publish, load the one behind it
@@ -2725,31 +2727,40 @@ DISC_DEV void compact_chain_body(const typename Pat::Args& A) {
     }
     // this tile's window
     if (t >= 0) {
+      bool counted = false;
       for (i64 looks = 0;; ++looks) {
-        bool missing = false;
+        u64 gone[C], any = 0;
 #pragma unroll
-        for (int c = 0; c < C; ++c) missing = missing || win[c] == 0;
-        if (wave_all(!missing)) break;
-        if (looks < A.aux2) {
+        for (int c = 0; c < C; ++c) any |= gone[c] = __builtin_amdgcn_ballot_w64(win[c] == 0);
+        if (any == 0) break;
+        if (looks < patience) {
           __builtin_amdgcn_s_sleep(2);
-#pragma unroll
-          for (int c = 0; c < C; ++c)
-            if (win[c] == 0) win[c] = look(c);
         } else {
-          int at = -1;                      // the first missing cell of the wavefront's share
+          // one of the wavefront's missing cells, another one in every block, which then finds those that the others have counted
+          counted = true;
+          const int turn = (int)(blockIdx.x * 2654435761u >> 26);
+          int cell = -1;
 #pragma unroll
-          for (int c = C - 1; c >= 0; --c) {
-            const u64 m = __builtin_amdgcn_ballot_w64(win[c] == 0);
-            if (m != 0) at = c * 64 + (int)__builtin_ctzll(m);
+          for (int k = C - 1; k >= 0; --k) {
+            const int c = (k + (int)blockIdx.x) & (C - 1);
+            u64 m = gone[0];
+#pragma unroll
+            for (int i = 1; i < C; ++i) m = c == i ? gone[i] : m;
+            m = m >> turn | m << (-turn & 63);
+            if (m != 0) cell = c * 64 + (((int)__builtin_ctzll(m) + turn) & 63);
           }
-          const i64 tile = lo + (at >> 6) * 256 + wave * 64 + (at & 63);
+          const i64 tile = lo + (cell >> 6) * 256 + wave * 64 + (cell & 63);
           const u32 got = (u32)compact_recount<Pat, V, U>(A, tile) + 1;
-          if (lane == (at & 63)) __hip_atomic_store(cells + tile, got, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (lane == (cell & 63)) __hip_atomic_store(cells + tile, got, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
           for (int c = 0; c < C; ++c)
-            if (c == at >> 6 && lane == (at & 63)) win[c] = got;
+            if (c == cell >> 6 && lane == (cell & 63)) win[c] = got;
         }
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+          if (win[c] == 0) win[c] = look(c);
       }
+      patience = !counted ? A.aux2 : A.aux2 < 8 ? A.aux2 : 8;
       u32 sum = 0;
 #pragma unroll
       for (int c = 0; c < C; ++c) sum += win[c] - 1;
