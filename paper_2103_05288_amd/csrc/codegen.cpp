@@ -1159,6 +1159,14 @@ struct Gen {
       if (an.accesses[out.access].compact) bytes += dtype_bytes(an.accesses[out.access].dtype);
     return bytes;
   }
+  // ... and slots of a lane whose kept values of one output leave together: 8 KB of them to a wavefront at most
+  int compact_stretch() const {
+    int bytes = 1, s = kCompactLaneSlots;
+    for (const auto& out : an.outputs)
+      if (an.accesses[out.access].compact) bytes = std::max(bytes, dtype_bytes(an.accesses[out.access].dtype));
+    while (s > 1 && 64 * an.vec_width * bytes * s > 8192) s /= 2;
+    return s;
+  }
   // compaction pattern: where the kept values, the slots and the count go
   void emit_compact_fns() {
     os << "  template <int V> static DISC_DEV void compact_prev(Slot<V>& s) {\n";
@@ -1167,14 +1175,14 @@ struct Gen {
     os << "    (void)s;\n  }\n";
     // the kept values of a wavefront's part of a tile, one output after the other through the same LDS
     int bytes = 0;
-    os << "  template <int V, bool NT, int U> static DISC_DEV void compact_put(const Args& A, const OutSlot<V> (&o)[U], const disc::u32 (&kb)[U], const int (&before)[U], int kept, disc::i64 pos, char* stage) {\n";
+    os << "  template <int V, bool NT, int U> static DISC_DEV void compact_put(const Args& A, const OutSlot<V> (&o)[U], const disc::u32 (&kb)[U], const disc::CompactRanks<U>& ranks, const int (&before)[U], disc::i64 pos, char* stage) {\n";
     for (const auto& out : an.outputs) {
       const Access& a = an.accesses[out.access];
       if (!a.compact) continue;
       bytes = std::max(bytes, dtype_bytes(a.dtype));
-      os << "    disc::compact_put_elems<V, NT, U>(A.o" << a.slot << ", pos, kb, before, kept, stage, [&](int u, int e) { return o[u].o" << a.slot << ".get(e); });\n";
+      os << "    disc::compact_put_elems<V, NT, U, COMPACT_STRETCH>(A.o" << a.slot << ", pos, kb, ranks, before, stage, [&](int u, int e) { return o[u].o" << a.slot << ".get(e); });\n";
     }
-    os << "    (void)A; (void)o; (void)kb; (void)before; (void)kept; (void)pos; (void)stage;\n  }\n";
+    os << "    (void)A; (void)o; (void)kb; (void)ranks; (void)before; (void)pos; (void)stage;\n  }\n";
     // ... and in two halves, every output in LDS of its own
     const int held = compact_held_bytes();
     for (const bool flush : {false, true}) {
@@ -1191,7 +1199,7 @@ struct Gen {
       }
       os << (flush ? "    (void)A; (void)kept; (void)pos; (void)stage;\n  }\n" : "    (void)o; (void)kb; (void)before; (void)stage;\n  }\n");
     }
-    os << "  static constexpr int COMPACT_BYTES = " << bytes << ", COMPACT_ALL_BYTES = " << held << ", COMPACT_SLOTS = " << kCompactLaneSlots << ";\n";
+    os << "  static constexpr int COMPACT_BYTES = " << bytes << ", COMPACT_ALL_BYTES = " << held << ", COMPACT_SLOTS = " << kCompactLaneSlots << ", COMPACT_STRETCH = " << compact_stretch() << ";\n";
     // the slots of the V elements of one slot of the tile, stored as one vector
     os << "  template <int V, bool NT, class SP> static DISC_DEV void rank_store(const Args& A, disc::i64 base, unsigned col, const disc::i64 (&rank)[V], SP sp) {\n";
     for (const auto& out : an.outputs) {

@@ -2318,6 +2318,13 @@ struct CompactRanks {
     }
     return kept;
   }
+  // kept by the wavefront in slots up to u
+  DISC_DEV int upto(int u) const {
+    int kept = 0;
+#pragma unroll
+    for (int k = 0; k < U; ++k) kept += k < u ? (int)(k % 2 ? all[k / 2] >> 16 : all[k / 2] & 0xffff) : 0;
+    return kept;
+  }
   // kept in front of the lane's slots, in this part; returns what the part keeps
   DISC_DEV int before(int (&b)[U]) const {
     static_assert(U % 2 == 0, "two slots to a word");
@@ -2352,15 +2359,15 @@ DISC_DEV void compact_store_ranks(const typename Pat::Args& A, i64 w0, const u32
     }
   }
 }
-// The kept values too; returns `pos` with the part's own added.  `stage`: (64 * V * U + 64) * COMPACT_BYTES bytes of
-// LDS of the wavefront's own.
+// The kept values too; returns `pos` with the part's own added.  `stage`: (64 * V * COMPACT_STRETCH + 64) * COMPACT_BYTES
+// bytes of LDS of the wavefront's own.
 template <bool WHOLE, bool NT, class Pat, int V, int U>
 DISC_DEV i64 compact_emit(const typename Pat::Args& A, i64 w0, const typename Pat::template OutSlot<V> (&o)[U],
                           const u32 (&kb)[U], const CompactRanks<U>& ranks, i64 pos, char* stage) {
   int before[U];
   const int kept = ranks.before(before);
   compact_store_ranks<WHOLE, NT, Pat, V, U>(A, w0, kb, before, pos);
-  Pat::template compact_put<V, NT, U>(A, o, kb, before, kept, pos, stage);
+  Pat::template compact_put<V, NT, U>(A, o, kb, ranks, before, pos, stage);
   return pos + kept;
 }
 
@@ -2405,27 +2412,32 @@ DISC_DEV void wave_lds_sync() {
 // The kept elements of a wavefront's part, collected in LDS and stored as one contiguous stretch at dst + pos, by
 // pieces of 64 elements that start where dst does: one piece per part is written by two parts, not one per slot.
 // (Stored straight from the lanes, a kept element here and there, every store instruction covers the same few cache
-// lines once more.)
-template <int V, bool NT, int U, class T, class GET>
-DISC_DEV void compact_put_elems(T* __restrict__ dst, i64 pos, const u32 (&kb)[U], const int (&before)[U], int kept, char* stage, GET get) {
+// lines once more.)  S slots at a time: all four, or as many as 8 KB of a wavefront hold (8-byte values of two-byte operands took 68 KB of
+// a block; the registers leave two blocks on a CU either way, 33555445 of them 80.7 us / 80.8, 300007 8.7 / 8.5).
+template <int V, bool NT, int U, int S, class T, class GET>
+DISC_DEV void compact_put_elems(T* __restrict__ dst, i64 pos, const u32 (&kb)[U], const CompactRanks<U>& ranks, const int (&before)[U], char* stage, GET get) {
   T* q = reinterpret_cast<T*>(stage);
   const int lane = (int)threadIdx.x & 63;
-  const int h = (int)pos & 63;
-  wave_lds_sync();
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    int r = h + before[u];
+  for (int s = 0; s < U; s += S) {
+    const int first = ranks.upto(s), kept = ranks.upto(s + S) - first;
+    const int h = (int)(pos + first) & 63;
+    wave_lds_sync();
 #pragma unroll
-    for (int e = 0; e < V; ++e) {
-      if ((kb[u] >> e) & 1) q[r++] = get(u, e);
+    for (int u = s; u < s + S; ++u) {
+      int r = h + before[u] - first;
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        if ((kb[u] >> e) & 1) q[r++] = get(u, e);
+      }
     }
-  }
-  wave_lds_sync();
-  T* to = dst + (pos - h);
-  for (int i = lane; i < h + kept; i += 64) {
-    if (i >= h) {
-      if constexpr (NT) __builtin_nontemporal_store(q[i], to + i);
-      else to[i] = q[i];
+    wave_lds_sync();
+    T* to = dst + (pos + first - h);
+    for (int i = lane; i < h + kept; i += 64) {
+      if (i >= h) {
+        if constexpr (NT) __builtin_nontemporal_store(q[i], to + i);
+        else to[i] = q[i];
+      }
     }
   }
 }
@@ -2585,7 +2597,7 @@ DISC_DEV void compact_scatter_body(const typename Pat::Args& A) {
   constexpr int U = Pat::COMPACT_SLOTS;
   __shared__ i64 cell[kCompactWaves];
   __shared__ int wsum[kCompactWaves];
-  __shared__ __attribute__((aligned(16))) char stage[kCompactWaves][(64 * V * U + 64) * Pat::COMPACT_BYTES + 16];
+  __shared__ __attribute__((aligned(16))) char stage[kCompactWaves][(64 * V * Pat::COMPACT_STRETCH + 64) * Pat::COMPACT_BYTES + 16];
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   if (A.aux2) {
     const CompactRange r = compact_range<Pat, V, U>(A);

@@ -122,6 +122,47 @@ def test_captured_and_replayed():
     ctx.close()
 
 
+def _wide_values(pred, value, outputs=1):
+    """keep = x > thr for a narrow x; kept: operands of a wider type"""
+    pb = PatternBuilder("wide_values")
+    n = pb.dim()
+    x = pb.param(pred, [n])
+    values = [pb.param(value, [n]) for _ in range(outputs)]
+    keep = pb.op("gt", pb.cast(x, "f32"), pb.param("f32", []), dims=[n])
+    for v in values:
+        pb.output(pb.compact(v, keep))
+    pb.output(pb.compact_rank(keep, "i32"))
+    pb.output(pb.compact_count(keep, "i32"))
+    return pb.build()
+
+
+def test_kept_values_take_8_kb_of_a_wavefront():
+    """All four slots of a lane leave together, or as many as that holds."""
+    from paper_2103_05288_amd import Context
+    ctx = Context(-1)
+    for pat, slots in ((unique_sorted("i32"), 4), (unique_sorted("i64"), 4), (filtered(), 4), (_wide_values("bf16", "i64"), 2)):
+        assert f"COMPACT_STRETCH = {slots};" in ctx.register(pat).source
+    ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("outputs", [1, 2])
+def test_wide_values_of_narrow_operands(outputs):
+    """A wavefront's kept values in two stretches: tiles of 8192 elements, whole ones and one element more or less, one slot and
+    one stretch of a last part; none, some and all kept.  Copied values: exact."""
+    from paper_2103_05288_amd import Context
+    ctx = Context(0)
+    pat = _wide_values("bf16", "i64", outputs)
+    g = torch.Generator().manual_seed(23)
+    for n in (1, 511, 513, 1025, 8191, 8193, 32 * 8192 - 1, 33 * 8192 + 1025, 260 * 8192 + 1537):
+        x = torch.round(torch.randn(n, generator=g) * 4).to(torch.bfloat16)
+        values = [torch.randint(-2 ** 62, 2 ** 62, (n,), generator=g) for _ in range(outputs)]
+        for thr in (-1e9, 1e9, 2.0):
+            print(f"[wide values] n={n} thr={thr}", flush=True)
+            check(ctx, pat, [n], [x, *values, torch.tensor(thr)], f"n={n} thr={thr}")
+    ctx.close()
+
+
 @pytest.mark.gpu
 def test_counting_for_others_is_shared():
     """Every cell that is not there at once counted by who misses it, as if its block were never resident: wavefronts take different
