@@ -1178,7 +1178,10 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // Without whole lines the blocks come in lists, whose neighbours write the parts of a line shortly after
       // one another: up to 224 MiB, for rows of 3840 bytes and more and for rows of whole lines in smaller pieces the hint on the stores still gains, beyond it the plain
       // store does (stores with the hint / plain: 30000 x 700 56.8 / 60.8, 40000 x 700 78.9 / 80.9, 50000 x 700 113.6 / 102.2, 65536 x
-      // 500 98.5 / 86.5, 65536 x 900 184 / 177, 65536 x 1000 149 / 177, 40000 x 1500 158 / 171, 20000 x 3000 133 / 159).
+      // 500 98.5 / 86.5, 65536 x 900 184 / 177, 65536 x 1000 149 / 177, 40000 x 1500 158 / 171, 20000 x 3000 133 / 159).  With one
+      // operand rows of 3840 bytes are where a block's pieces become 256 bytes wide; batches have such pieces of shorter rows, and keep the plain
+      // store (3 x 20000 x 500 71.0 / 61.6, 8 x 6000 x 700 77.9 / 70.4; but 40 x 2000 x 700 133 / 141), as two operands of 2 and 4 bytes have narrower ones
+      // of longer rows, and the hint (30000 x 1000 86.5 / 92.0, 65536 x 1000 233 / 227).
       const bool nts = nt && (sv.alg_bytes < (224ll << 20) || row_bytes >= 3840 || row_bytes % 128 == 0);
       L1.kid = !vec ? K_COL_EPI2_SCALAR : nt && (lines || c->row_nt > 0) ? K_COL_EPI2_VEC_NT : nts ? K_COL_EPI2_VEC_NTS : K_COL_EPI2_VEC;
       L1.grid[0] = (uint32_t)col_tiles;
@@ -1232,12 +1235,12 @@ bool plan_xpose(const disc_ctx* c, int64_t per, int64_t batch, int64_t inner, in
   // 18.6 / 22.1, 300 x 8192 6.2 / 5.7 / 5.6, 3000 x 8000 37.4 / 26.5 / -, 200 x 200000 76 / 45.5 / 38.1, 1000 x 60000 77 / 62 / 59.
   // Against two kernels: 2000 x 100 5.4 / 8.0, 1000 x 8000 9.5 / 15.1, 2000 x 4000 11.4 / 15.5, 3000 x 2001 11.5 / 15.5, 3500 x 5000
   // 23.0 / 28.9, 8192 x 8192 95.4 / 107.  Rows beyond 4096 elements leave one strip to a CU, whose load, arithmetic and
-  // stores follow one another, 20 us however many there are: with several strips for every CU, or one for most of
+  // stores follow one another, 20 us however many there are: with several strips for every CU, or one for most or all of
   // them (6000 x 2200 24.3 / 20.5, 4500 x 2600 21.0 / 20.0, 6000 x 3000 24.7 / 28.1, 4500 x 4000 20.9 / 29.3, 8192 x 4000 38.8 / 50.4, 6000 x
-  // 4097, a second round for one strip, 45.4 / 38.0; 8192 x 64 14.6 / 10.1, 5000 x 6200 45.3 / 47.5, 6000 x 7000 55.8 / 65.1).  (4000 x 300
+  // 4090 26.0 / 38.9, 6000 x 4096 29.6 / 38.6, 8192 x 4096 38.8 / 43.9, 6000 x 4097, a second round for one strip, 45.4 / 38.0; 8192 x 64 14.6 / 10.1, 5000 x 6200 45.3 / 47.5, 6000 x 7000 55.8 / 65.1).  (4000 x 300
   // 9.7 / 9.2 and 4000 x 800 12.0 / 11.0 are on the wrong side of the line; 3200 x 500 8.5 / 9.7, 3600 x 1000 11.4 / 11.8.)
   const int64_t strips16 = (per + 15) / 16 * batch;
-  if (inner > 64 * V * 8 && strips16 < c->n_cus * 3 / 2 && !(strips16 > c->n_cus * 2 / 3 && strips16 < c->n_cus)) return false;
+  if (inner > 64 * V * 8 && strips16 < c->n_cus * 3 / 2 && !(strips16 > c->n_cus * 2 / 3 && strips16 <= c->n_cus)) return false;
   int G = 64, B = 512, nv = 0;
   if (strips16 >= 8ll * c->n_cus && inner <= 16 * V * 12 && per >= 32) G = 16;
   else if (strips16 >= c->n_cus * 7 / 4 || inner > 64 * V * 8) {

@@ -113,13 +113,13 @@ def test_one_strip_of_long_rows_for_most_cus():
     from paper_2103_05288_amd import Context
     ctx = Context(-1)
     g = _softmax_graph(ctx)
-    for cols, one in ((16 * 170, False), (16 * 171, True), (3000, True), (16 * 255, True), (16 * 255 + 1, False), (4097, False)):
+    for cols, one in ((16 * 170, False), (16 * 171, True), (3000, True), (16 * 255, True), (16 * 255 + 1, True), (4096, True), (4097, False)):
         assert ("k_row_xpose" in g.plan([6000, cols], 1)["kernels"][0]) == one, cols
     ctx.close()
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("dims", [[4097, 2737], [6000, 3001], [8192, 4080]])
+@pytest.mark.parametrize("dims", [[4097, 2737], [6000, 3001], [8192, 4080], [4500, 4096]])
 def test_one_strip_of_long_rows_matches_oracle(dims):
     from paper_2103_05288_amd import Context
     from tests.test_transposed_rows import check, softmax
