@@ -180,8 +180,10 @@ typedef enum {
                                    predicate computed in the same pattern (DISC_COMPACT and
                                    friends): per-block counts, a fixed-order scan of the counts (short
                                    inputs; the blocks of the scatter add up the counts themselves
-                                   otherwise), a scatter -- two or three launches, no atomics, the
-                                   element count written to device memory                         */
+                                   otherwise), a scatter, in two or three launches; or, large inputs,
+                                   a launch that clears four bytes a tile and one pass whose blocks
+                                   pass their counts on through them.  The element count is written
+                                   to device memory                                               */
 } disc_template;
 
 typedef struct {

@@ -2223,9 +2223,9 @@ DISC_DEV void col_epi2_body(const typename Pat::Args& A, const ColPlan& cp) {
 // of a sorted tensor is the case keep[i] = x[i] != x[i-1]).  Rank-1 values of length N = A.inner.
 // A tile is 4 wavefronts x COMPACT_SLOTS slots x 64 lanes x V elements; a wavefront's part of it is
 // contiguous and its slots are striped over the lanes, so every load and every rank store is one
-// contiguous stretch per wavefront.  Kept elements are counted and ranked with lane masks (ballot,
-// mbcnt, popcount: two or three instructions per element, no scan over the lanes) and meet in LDS,
-// slot by slot, so that they leave as contiguous stores whatever the share that is kept.
+// contiguous stretch per wavefront.  A slot's kept elements are one word of flags; what the lanes in
+// front keep comes from one scan over the wavefront for two slots, and what a part keeps meets in LDS,
+// so that it leaves as contiguous stores whatever the share that is kept.
 // The output order is the input order; nothing is read back by the host:
 //   1. compact_count:   evaluates the fused chain and counts what is kept; the counts go to the workspace.
 //   2. compact_scan:    (short inputs only: a tile to a block) one block turns the counts into

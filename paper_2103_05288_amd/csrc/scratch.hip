@@ -85,8 +85,8 @@ extern "C" int disc_launch_static_scratch(disc_ctx* ctx, int32_t id, const int64
     if (rc != DISC_OK) return rc;
   }
   // The kernels take `ptr` as their workspace argument.  Nothing in the array has to start at zero:
-  // every cell a kernel reads was written earlier in the same call (no atomics, no counters), so
-  // what an earlier call left behind is never seen.
+  // every cell a kernel reads was written earlier in the same call (or cleared, by a launch of its own),
+  // so what an earlier call left behind is never seen.
   return disc::launch_scratch(ctx, id, dims, n_dims, inputs, n_in, outputs, n_out, ptr,
                               need > 0 ? (size_t)DISC_STATIC_SCRATCH_BYTES : 0, hip_stream);
 }
