@@ -776,9 +776,12 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       // LDS for the row vectors of shifted rows: wide blocks of large launches take 64 KiB (bf16 rows, two fp32 vectors, 9585 x
       // 7001, 56 KB, from memory / staged 87.3 / 69.7 us); where three blocks share a CU, or a block has few rows, from memory
       // (three vectors 13419 x 5001, 60 KB, 99.4 / 124; 599 x 7001 6.3 / 7.4).  (Right at the limit, LayerNorm of three two-byte
-      // vectors, from memory / staged: 8206 x 8178 89.4 / 77.7, 256 x 8177 5.6 / 7.1.)
+      // vectors, from memory / staged: 8206 x 8178 89.4 / 77.7, 256 x 8177 5.6 / 7.1.)  fp32 vectors of blocks of 1024 threads, one to a CU,
+      // pay for it from six rows a block on (mixed chain 1100 / 1366 / 1700 / 2400 x 12289, from memory 22.0 / 25.7 / 29.9 / 40.9, staged 22.0
+      // / 25.6 / 29.4 / 39.7; two of fp32 rows, 7001, from memory 23.3 / 28.1 / 32.6 / 44.6, staged 24.2 / 28.4 / 32.5 / 43.1).
+      const bool wide_copies = block > 256 && large && (narrow || block < 1024 || sv.rows >= 6ll * c->n_cus);
       auto fits = [&](int64_t bytes, bool shifted) {
-        return bytes <= (shifted && block > 256 && large ? kMaxShiftedStageBytes : kMaxStageBytes + (large ? stage_pad : 0));
+        return bytes <= (shifted && wide_copies ? kMaxShiftedStageBytes : kMaxStageBytes + (large ? stage_pad : 0));
       };
       // Two-byte row vectors, whose rows have plain accesses where they are not shifted: launches beyond what the memory-side
       // cache holds of a few of them in turn (rows scaled by their norm and one vector, 64 MiB, 2396 x 7001, unshifted / shifted,

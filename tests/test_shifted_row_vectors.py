@@ -151,3 +151,14 @@ def test_rows_off_the_limits(vectors, dtype, H):
                 assert_close(o.cpu(), w, f"{vectors} {dtype} {H} off={off} out{k} single={handle is single}")
                 o.fill_(float("nan"))
     c.close()
+
+
+def test_blocks_of_1024_threads_stage_from_six_rows_on():
+    """One vector of 48 to 64 KiB; the launches are beyond 64 MiB on either side of the line."""
+    from paper_2103_05288_amd import Context
+    c = Context(-1)
+    h = c.register(CONFIGS["C4"].pattern())
+    line = 6 * 256                            # a block to a CU
+    for H in (12289, 16001):
+        assert [h.plan([T, H])["kernels"][0].endswith("_s_t") for T in (50, line - 1, line, 4 * line)] == [False, False, True, True], H
+    c.close()
