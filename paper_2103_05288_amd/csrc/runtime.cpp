@@ -855,6 +855,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       L.rp.nv = nv;
       L.rp.rpb = block / G;
       uint32_t lds_unshifted = 0;           // LDS of the same launch with operands off the boundaries of slots
+      int kid_unstaged = -1;                // kernel of fewer rows, where they read the row vectors from memory
       {
         // Staged or not, whatever the alignment of the operands: a single-shape module has one kernel for all of them.
         const bool stage = vec && V > 1 && c->row_stage && one > 0 && fits(aligned_shift ? copies : one, aligned_shift);
@@ -889,6 +890,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         kid_aligned = version(nt);
         L.kid = nt && c->row_nt < 0 && !full_aligned() ? version(false) : kid_aligned;
         kid_any = nt && c->row_nt < 0 ? version(false) : kid_aligned;
+        if (stage && tail && one > kMaxStageBytes) kid_unstaged = K_ROW_BASE + row_kernel_index(!vec, inst, wide_version, false, 3);
       }
       // grid-stride over row groups: a small whole number of rounds of the blocks the chip holds
       // at once.  Measured: with plenty of rows, blocks of one wavefront-quad do best with three
@@ -928,6 +930,7 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
         if (n_col_sums + n_row_reds > 0) most_blocks = std::max(most_blocks, may_shift || count_even ? blocks_of(kid) : odd(blocks_of(kid)));
       // (a caller that asked with aligned operands, or with none, launches with others: unshifted, less LDS)
       if (may_shift && n_row_reds > 0) most_blocks = std::max(most_blocks, blocks_with(kid_any, lds_unshifted));
+      if (kid_unstaged >= 0 && n_row_reds > 0) most_blocks = std::max(most_blocks, blocks_with(kid_unstaged, 0));
       most_blocks = std::max(most_blocks, fewer_rows_blocks);
       // An odd grid: with an even one a block of one row per iteration would only ever see even or
       // only odd rows, and when the row length is odd every other row starts two bytes off a

@@ -162,3 +162,15 @@ def test_blocks_of_1024_threads_stage_from_six_rows_on():
     for H in (12289, 16001):
         assert [h.plan([T, H])["kernels"][0].endswith("_s_t") for T in (50, line - 1, line, 4 * line)] == [False, False, True, True], H
     c.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("vectors,dtype,H", [(1, "f32", 12289), (2, "bf16", 15001), (2, "f32", 7001)])
+def test_workspace_of_the_most_rows_serves_fewer(vectors, dtype, H):
+    """Fewer rows that do not stage have more blocks on a CU, and a partial result for each (plans only)."""
+    from paper_2103_05288_amd import Context
+    c = Context(0)
+    h = c.register(_norm(vectors, dtype, loss=True))
+    need = [c.workspace_bytes(h.id, [T, H]) for T in (100, 300, 512, 900, 1100, 1366, 1535, 1536, 2047, 2048, 3000, 9000, 60000)]
+    assert need == sorted(need), need
+    c.close()
