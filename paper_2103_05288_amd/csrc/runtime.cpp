@@ -913,10 +913,12 @@ int make_plan(disc_ctx* c, const Pattern& p, const int64_t* dims, int n_dims, in
       }
       auto blocks_with = [&](int kid, uint32_t lds) {
         int64_t per_cu = resident_blocks(c, p, kid, L.block, lds);
-        // Ragged rows with staged vectors: at most 28 wavefronts on a CU (whole blocks: seven of 256 threads, three of 512, one of
-        // 1024).  With all 32 the memory delivers less (us, 28 / 32: fp32 LayerNorm of one vector 21592 x 777 37.0 / 43.4, 40427 x
-        // 415 40.9 / 44.7, 4095 x 4097 35.9 / 38.0; fp32 rows and bf16 rows scaled by their norm 65280 x 257 28.9 / 29.2, 4793 x 3500 12.3 / 13.4).
-        if (tail && lds > 0) per_cu = std::min<int64_t>(per_cu, std::max<int64_t>(1, 28 * 64 / L.block));
+        // Ragged rows with staged vectors: at most 24 wavefronts on a CU (whole blocks: six of 256 threads, three of 512, one of
+        // 1024).  With more the memory delivers less in launches of one round (us, 32 / 28 / 24: fp32 LayerNorm of one vector 21592 x 777
+        // 43.4 / 37.1 / 36.9, 40427 x 415 44.7 / 40.8 / 39.5; 28 / 24, of two 21592 x 777 46.6 / 38.4, 65280 x 257 49.9 / 43.6, 8196 x 2047
+        // 44.3 / 39.4); several rounds take it either way (of two 86369 x 777 142.7 / 139.2, 130308 x 515 152.9 / 156.2; fp32 rows
+        // scaled by their norm 65154 x 515 52.8 / 54.5).
+        if (tail && lds > 0) per_cu = std::min<int64_t>(per_cu, std::max<int64_t>(1, 24 * 64 / L.block));
         const int64_t held = (int64_t)c->n_cus * per_cu;
         // (with sums over the rows every block writes a row of partial sums: one round, or two)
         const int rounds = c->row_rounds > 0 ? c->row_rounds
